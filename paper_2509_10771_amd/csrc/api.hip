@@ -346,6 +346,7 @@ struct PpoPlan {
   void* perm_ws = nullptr;
   TrainBufs actor, critic, pred;
   NetBufs targ;
+  WeightPack targ_pack;
   float* stage_a = nullptr;          // staged (padded, mirrored) network inputs, when worth it (see staged_width)
   float* stage_c = nullptr;
   int dp_a = 0, dp_c = 0;            // their row widths, 0 = not staged
@@ -385,6 +386,7 @@ void ppo_plan(Carver& c, const rslx_mlp* actor, const rslx_mlp* critic, const rs
     carve_train(c, *rnd->predictor, p.mb, 1, p.pred);
     p.pred.sumsq = c.take<double>((size_t)p.pred.n_sumsq + 1);
     carve_net(c, *rnd->target, p.mb, false, p.targ);
+    p.targ_pack.base = c.take<uint16_t>(WeightPack::offset(*rnd->target, rnd->target->n_layers));
     const int K = rnd->target->dims[rnd->target->n_layers];
     p.mse_partials = c.take<double>(mse_num_blocks((int64_t)p.mb * K));
   }
@@ -513,12 +515,6 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
     return x;
   };
 
-  {   // transposed weights once per call; every Adam launch below keeps them current
-    const XView none;
-    BwdJob tj[2] = {BwdJob{actor, none, p.rows, &p.actor.act, p.actor.d_out, p.actor.wt, p.actor.partials, &p.actor.plan},
-                    BwdJob{critic, none, p.rows, &p.critic.act, p.critic.d_out, p.critic.wt, p.critic.partials, &p.critic.plan}};
-    if (cfg->epochs > 0) RSLX_TRY(transpose_weights(tj, 2, s, false));
-  }
   for (int e = 0; e < cfg->epochs; ++e) {
     for (int m = 0; m < cfg->minibatches; ++m) {
       const int32_t* idx = p.perms + (size_t)e * p.B + (size_t)m * p.mb;
@@ -528,7 +524,14 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
                                 sym ? sym->sign_obs_a : nullptr, idx);
       const XView xc = obs_view(ro->obs_critic, ro->Dc, p.stage_c, p.dp_c, sym ? sym->perm_obs_c : nullptr,
                                 sym ? sym->sign_obs_c : nullptr, idx);
-      NetJob fj[2] = {NetJob{actor, xa, p.rows, &p.actor.act}, NetJob{critic, xc, p.rows, &p.critic.act}};
+      {
+        PackBatch pb;
+        pb.count = 0;
+        pack_add_net(pb, *actor, p.actor.pack, 1);
+        pack_add_net(pb, *critic, p.critic.pack, 1);
+        RSLX_HIP(launch_pack_weights(pb, s));
+      }
+      NetJob fj[2] = {NetJob{actor, xa, p.rows, &p.actor.act, &p.actor.pack}, NetJob{critic, xc, p.rows, &p.critic.act, &p.critic.pack}};
       RSLX_TRY(forward_nets(fj, 2, s, p.fused_head));
 
       PpoLossArgs la;
@@ -559,9 +562,9 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
       } else {
         RSLX_HIP(launch_ppo_loss(la, s));
       }
-      BwdJob bj[2] = {BwdJob{actor, xa, p.rows, &p.actor.act, p.actor.d_out, p.actor.wt, p.actor.partials, &p.actor.plan},
-                      BwdJob{critic, xc, p.rows, &p.critic.act, p.critic.d_out, p.critic.wt, p.critic.partials, &p.critic.plan}};
-      RSLX_TRY(backward_nets(bj, 2, s, p.fused_head, true));
+      BwdJob bj[2] = {BwdJob{actor, xa, p.rows, &p.actor.act, p.actor.d_out, p.actor.partials, &p.actor.plan, nullptr, &p.actor.pack},
+                      BwdJob{critic, xc, p.rows, &p.critic.act, p.critic.d_out, p.critic.partials, &p.critic.plan, nullptr, &p.critic.pack}};
+      RSLX_TRY(backward_nets(bj, 2, s, p.fused_head));
       {   // one launch: both networks' split sums and the loss head's sums
         ReduceArgs ra;
         memset(&ra, 0, sizeof ra);
@@ -583,8 +586,6 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
       aa.seg[0] = AdamSegment{actor->params, actor->grads, actor->adam_m, actor->adam_v, param_count(*actor)};
       aa.seg[1] = AdamSegment{critic->params, critic->grads, critic->adam_m, critic->adam_v, param_count(*critic)};
       aa.n_seg = 2;
-      adam_keeps_transposed(aa.seg[0], *actor, p.actor.wt);
-      adam_keeps_transposed(aa.seg[1], *critic, p.critic.wt);
       aa.sumsq_blocks = p.sumsq_all; aa.n_sumsq = p.actor.n_sumsq + p.critic.n_sumsq + 1;
       aa.max_grad_norm = cfg->max_grad_norm;
       aa.lr = cfg->lr; aa.beta1 = cfg->beta1; aa.beta2 = cfg->beta2; aa.eps = cfg->adam_eps;
@@ -600,13 +601,18 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
         XView xr;
         xr.base = ro->obs_actor; xr.ld = ro->Da; xr.row_idx = idx; xr.src_rows = p.B;
         if (rnd->subset_idx) { xr.col_map = rnd->subset_idx; xr.map_from = 0; }
-        NetJob rj[2] = {NetJob{&pr, xr, p.mb, &p.pred.act}, NetJob{rnd->target, xr, p.mb, &p.targ}};
+        PackBatch pb;
+        pb.count = 0;
+        pack_add_net(pb, pr, p.pred.pack, 1);
+        if (e == 0 && m == 0) pack_add_net(pb, *rnd->target, p.targ_pack, rnd->target->n_layers);
+        RSLX_HIP(launch_pack_weights(pb, s));
+        NetJob rj[2] = {NetJob{&pr, xr, p.mb, &p.pred.act, &p.pred.pack}, NetJob{rnd->target, xr, p.mb, &p.targ, &p.targ_pack}};
         RSLX_TRY(forward_nets(rj, 2, s));
         const int nbm = mse_num_blocks((int64_t)p.mb * K);
         RSLX_HIP(launch_mse(p.pred.act.out[pr.n_layers - 1], p.targ.out[pr.n_layers - 1], nullptr, p.mb, K,
                             p.pred.d_out, p.mse_partials, s));
         RSLX_HIP(launch_mse_finish(p.mse_partials, nbm, (int64_t)p.mb * K, stats_row + RSLX_STAT_RND_LOSS, s));
-        BwdJob rb{&pr, xr, p.mb, &p.pred.act, p.pred.d_out, p.pred.wt, p.pred.partials, &p.pred.plan};
+        BwdJob rb{&pr, xr, p.mb, &p.pred.act, p.pred.d_out, p.pred.partials, &p.pred.plan, nullptr, &p.pred.pack};
         RSLX_TRY(backward_nets(&rb, 1, s));
         RSLX_TRY(reduce_net(pr, p.pred, s));
         const int64_t tr = *rnd_step + 1;
@@ -737,30 +743,29 @@ int32_t bc_update_impl(rslx_mlp* student, const rslx_mlp* teacher, const float* 
   }
   const int nbm = mse_num_blocks((int64_t)p.mb * A);
   if (cfg->epochs > 0) {
-    // once per call: the statistics rows start at zero (each step then writes its loss and gradient norm), and the
-    // transposed weights are formed; every Adam launch below keeps them current
+    // once per call: the statistics rows start at zero (each step then writes its loss and gradient norm)
     RSLX_HIP(launch_fill(stats, (int64_t)cfg->epochs * cfg->minibatches * RSLX_NSTATS, 0.f, s));
-    const XView none;
-    BwdJob tj{student, none, p.mb, &p.student.act, p.student.d_out, p.student.wt, p.student.partials, &p.student.plan};
-    RSLX_TRY(transpose_weights(&tj, 1, s, false));
   }
   for (int e = 0; e < cfg->epochs; ++e) {
     for (int m = 0; m < cfg->minibatches; ++m) {
       const int32_t* idx = p.perms + (size_t)e * B + (size_t)m * p.mb;
       float* stats_row = stats + ((size_t)e * cfg->minibatches + m) * RSLX_NSTATS;
       XView xs; xs.base = obs_student; xs.ld = student->dims[0]; xs.row_idx = idx; xs.src_rows = B;
-      NetJob fj{student, xs, p.mb, &p.student.act};
+      PackBatch pb;
+      pb.count = 0;
+      pack_add_net(pb, *student, p.student.pack, 1);
+      RSLX_HIP(launch_pack_weights(pb, s));
+      NetJob fj{student, xs, p.mb, &p.student.act, &p.student.pack};
       RSLX_TRY(forward_nets(&fj, 1, s));
       RSLX_HIP(launch_mse(p.student.act.out[Ls - 1], targets, idx, p.mb, A, p.student.d_out, p.mse_partials, s));
       RSLX_HIP(launch_mse_finish(p.mse_partials, nbm, (int64_t)p.mb * A, stats_row, s));
-      BwdJob bj{student, xs, p.mb, &p.student.act, p.student.d_out, p.student.wt, p.student.partials, &p.student.plan};
-      RSLX_TRY(backward_nets(&bj, 1, s, false, true));
+      BwdJob bj{student, xs, p.mb, &p.student.act, p.student.d_out, p.student.partials, &p.student.plan, nullptr, &p.student.pack};
+      RSLX_TRY(backward_nets(&bj, 1, s));
       RSLX_TRY(reduce_net(*student, p.student, s));
       const int64_t t = *adam_step + 1;
       AdamArgs aa;
       memset(&aa, 0, sizeof aa);
       aa.seg[0] = AdamSegment{student->params, student->grads, student->adam_m, student->adam_v, weight_count(*student)};
-      adam_keeps_transposed(aa.seg[0], *student, p.student.wt);
       aa.n_seg = 1;
       aa.sumsq_blocks = p.student.sumsq; aa.n_sumsq = p.student.n_sumsq;
       aa.max_grad_norm = cfg->max_grad_norm;

@@ -457,7 +457,14 @@ int32_t ppo_update_recurrent_impl(rslx_memory* gru_actor, rslx_mlp* actor, rslx_
 
       // ---- MLPs on the hidden states, loss head, MLP backward down to the hidden states ----
       XView xa = plain_view(p.ma.hs, gru_actor->hidden), xc = plain_view(p.mc.hs, gru_critic->hidden);
-      NetJob fj[2] = {NetJob{actor, xa, rows, &p.actor.act}, NetJob{critic, xc, rows, &p.critic.act}};
+      {
+        PackBatch pb;
+        pb.count = 0;
+        pack_add_net(pb, *actor, p.actor.pack, 0);
+        pack_add_net(pb, *critic, p.critic.pack, 0);
+        RSLX_HIP(launch_pack_weights(pb, s));
+      }
+      NetJob fj[2] = {NetJob{actor, xa, rows, &p.actor.act, &p.actor.pack}, NetJob{critic, xc, rows, &p.critic.act, &p.critic.pack}};
       RSLX_TRY(forward_nets(fj, 2, s, p.fused_head));
       PpoLossArgs la;
       memset(&la, 0, sizeof la);
@@ -484,8 +491,8 @@ int32_t ppo_update_recurrent_impl(rslx_memory* gru_actor, rslx_mlp* actor, rslx_
       } else {
         RSLX_HIP(launch_ppo_loss(la, s));
       }
-      BwdJob bj[2] = {BwdJob{actor, xa, rows, &p.actor.act, p.actor.d_out, p.actor.wt, p.actor.partials, &p.actor.plan, p.ma.dh},
-                      BwdJob{critic, xc, rows, &p.critic.act, p.critic.d_out, p.critic.wt, p.critic.partials, &p.critic.plan, p.mc.dh}};
+      BwdJob bj[2] = {BwdJob{actor, xa, rows, &p.actor.act, p.actor.d_out, p.actor.partials, &p.actor.plan, p.ma.dh, &p.actor.pack},
+                      BwdJob{critic, xc, rows, &p.critic.act, p.critic.d_out, p.critic.partials, &p.critic.plan, p.mc.dh, &p.critic.pack}};
       RSLX_TRY(backward_nets(bj, 2, s, p.fused_head));
 
       RSLX_TRY(memories_backward(mem, mb, 2, obs, ridx, dones, T, nb, p.N, s));
@@ -673,11 +680,15 @@ int32_t rslx_bc_update_recurrent(rslx_memory* gru, rslx_mlp* student, const floa
       RSLX_HIP(launch_fill(stats_row, RSLX_NSTATS, 0.f, s));
       RSLX_TRY(memories_forward(mem, mb, 1, obs, h0s, envs, ridx, dones, T, nb, N, s));
       XView xs = plain_view(p.mem.hs, gru->hidden);
-      NetJob fj{student, xs, rows, &p.student.act};
+      PackBatch pb;
+      pb.count = 0;
+      pack_add_net(pb, *student, p.student.pack, 0);
+      RSLX_HIP(launch_pack_weights(pb, s));
+      NetJob fj{student, xs, rows, &p.student.act, &p.student.pack};
       RSLX_TRY(forward_nets(&fj, 1, s));
       RSLX_HIP(launch_mse(p.student.act.out[Ls - 1], targets, ridx, rows, A, p.student.d_out, p.mse_partials, s));
       RSLX_HIP(launch_mse_finish(p.mse_partials, nbm, (int64_t)rows * A, stats_row, s));
-      BwdJob bj{student, xs, rows, &p.student.act, p.student.d_out, p.student.wt, p.student.partials, &p.student.plan, p.mem.dh};
+      BwdJob bj{student, xs, rows, &p.student.act, p.student.d_out, p.student.partials, &p.student.plan, p.mem.dh, &p.student.pack};
       RSLX_TRY(backward_nets(&bj, 1, s));
       RSLX_TRY(memories_backward(mem, mb, 1, obs, ridx, dones, T, nb, N, s));
       {

@@ -1,26 +1,38 @@
-// fp32 matrix-core contraction for gfx950 (v_mfma_f32_32x32x2_f32), used by every dense layer of the
-// actor, critic, student, teacher and RND networks: forward, input gradient and weight gradient.
+// Contraction kernel for gfx950, used by every dense layer of the actor, critic, student, teacher and RND networks:
+// forward, input gradient and weight gradient.  Operands, sums and results are fp32; the products run on the bf16
+// matrix cores (v_mfma_f32_32x32x16_bf16), sixteen times the rate of the fp32 ones, on operands split in three:
 //
-// Tiling: one workgroup = 4 wavefronts (256 lanes) computes a BM x BN block of C.  Operand tiles of
-// BK (16) contraction steps are staged through LDS in contraction-major order (As[k][m], Bs[k][n]),
-// so that the 32 lanes of an MFMA operand row read 32 consecutive words (bank-conflict free), and are
-// double-buffered: global loads of tile k+1 are in flight while tile k feeds the matrix cores.
+//   a = a0 + a1 + a2,   a0 = bf16(a), a1 = bf16(a - a0), a2 = bf16(a - a0 - a1)      (exact: 3 x 8 significant bits)
+//   a b ~ a0 b0 + (a0 b1 + a1 b0) + (a1 b1 + a0 b2 + a2 b0)
 //
-// MFMA 32x32x2 fp32 register layout (wave64, lane l, g = l / 32, j = l % 32):
-//   A operand: A[row = j][k = g]      B operand: B[k = g][col = j]
+// What is left out (a1 b2, a2 b1, a2 b2) is below 2^-25 of the product, less than half the rounding of an fp32 product,
+// and bf16 has the exponent range of fp32, so no scaling is needed.  Six products at sixteen times the rate are 2.7
+// times the fp32 peak.  Operands that have no such split (infinite, or rounded to infinity) make their outputs
+// non-finite; a tile that finds a non-finite sum repeats its contraction on the fp32 matrix cores (fp32_contract), so
+// the results of such inputs are those of fp32 arithmetic.
+//
+// Tiling: one workgroup = 4 wavefronts (256 lanes) computes a BM x BN block of C in steps of 16 contraction indices.
+// The operand tile of step k + 1 is split in registers and written to LDS, and the fp32 values of step k + 2 are
+// requested, while step k feeds the matrix cores (LDS double buffer).  An LDS plane holds one of the three parts of
+// eight consecutive contraction indices of all tile rows, 16 bytes a row: a lane's matrix operand is one 16-byte
+// read, and 32 lanes read 512 contiguous bytes.
+//
+// MFMA 32x32x16 bf16 register layout (wave64, lane l, g = l / 32, j = l % 32):
+//   A operand: A[row = j][k = 8 g .. 8 g + 7]      B operand: B[k = 8 g .. 8 g + 7][col = j]
 //   D/C, 16 accumulators r = 0..15:   D[row = 8 * (r / 4) + 4 * g + r % 4][col = j]
 #include <cstdio>
 #include <cstring>
 #include <type_traits>
 
 #include "kernels.h"
+#include "split_bf16.h"
 
 namespace rslx {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int PAD = 4;    // LDS row padding (floats); keeps rows 16-byte aligned
 constexpr int NT = 256;   // lanes per workgroup
+constexpr int BK = 16;    // contraction indices per step
 
 __device__ __forceinline__ int wrap_row(const GemmProblem& P, int r) { return r >= P.idx_mod ? r - P.idx_mod : r; }
 
@@ -30,244 +42,259 @@ __device__ __forceinline__ int src_row(const GemmProblem& P, int r) {
   return r >= P.idx_mod ? v + P.wrap_add : v;
 }
 
+// The bf16 matrix instructions round their sums down a little more often than up: by about 1.2e-11 of the sum's size
+// per instruction (mean error of 256 x 128 sums of 4096 random terms -2.1e-7 of their rms, at a total error of 1.0e-6; no
+// such offset on the fp32 matrix cores).  One result does not notice, but sums over many results do, and gradients over
+// whole minibatches are such sums: the offset has the same sign in every row and on every optimiser step.  So a part of
+// every contraction is summed with its sign reversed, and the offsets cancel: the weight gradient negates its terms in
+// every other split; weights that are split once per optimiser step are stored negated from step sign_flip_step on, and
+// the accumulators change sign there, at six tenths of the way: the offset follows the size of the sum, for random signs
+// the root of the index reached, and has done about half of its work by then (the mean over a minibatch falls to a tenth).
+__host__ __device__ __forceinline__ int sign_flip_step(int steps) { return steps < 2 ? steps : (steps * 59 + 50) / 100; }
+
+// LDS image of one operand tile of R rows: plane (part s, k-group kg) at (2 s + kg) * pitch, 16 bytes per row.  The 64
+// bytes between planes put the two k-groups of a row in different banks when they are written together.
+template <int R> constexpr int plane_pitch() { return R * 16 + 64; }
+template <int R> constexpr int tile_bytes() { return 6 * plane_pitch<R>(); }
+
+// The parts of four values of consecutive contraction indices 4 q .. 4 q + 3 of one tile row, and their LDS writes.
+struct Quad {
+  uint2 part[3];
+  __device__ __forceinline__ void split_lo(const float* v) { split_pair(v[0], v[1], part[0].x, part[1].x, part[2].x); }
+  __device__ __forceinline__ void split_hi(const float* v) { split_pair(v[2], v[3], part[0].y, part[1].y, part[2].y); }
+  template <int R>
+  __device__ __forceinline__ void put(char* tile, int row, int q) const {
+    char* d = tile + (q >> 1) * plane_pitch<R>() + row * 16 + (q & 1) * 8;
+#pragma unroll
+    for (int s = 0; s < 3; ++s) *reinterpret_cast<uint2*>(d + 2 * s * plane_pitch<R>()) = part[s];
+  }
+};
+
+// How an operand is read.  FORM_FAST: 16-byte loads of rows that are contiguous along the contraction; plain rows where
+// the M / N index is contiguous.  FORM_GATHER (weight gradient): its contraction rows are gathered.  FORM_GENERAL: any
+// alignment, gather and column map.
+enum Form { FORM_FAST, FORM_GATHER, FORM_GENERAL };
+
 // ---- operand with the contraction index contiguous in memory (tile rows = M or N index) ---------------------
-// Everything that does not change along the contraction (row pointers with the gather applied, validity,
-// whether the row uses the column map) is set up once per tile; a k-tile fetch is then loads only.
-// Element (row, k) lands at lds[k][row].
-template <int R, int BK, bool IS_X, bool VEC>
+// Lane -> row tid / 4 (+ 64 per pass), contraction indices 4 (tid % 4) .. + 3: four lanes read the 64 bytes of a row's
+// step.  Everything that does not change along the contraction (row offsets with the gather applied) is set up once
+// per tile.  Rows past the end repeat the last one; the outputs they feed are dropped.
+template <int R, bool IS_X, int FORM>
 struct KContig {
-  static constexpr int NREG = R * BK / NT;
-  static constexpr int LK = BK / 4;                 // vector path: lanes along k (one float4 each)
-  static constexpr int RPV = NT / LK;               // vector path: rows per pass
-  static constexpr int RPS = NT / BK;               // scalar path: rows per pass
-  static constexpr int NPTR = VEC ? R / RPV : R / RPS;
-  static constexpr bool vec = VEC;
-  const float* ptr[VEC ? 1 : NPTR];                 // scalar path: row pointers, gather applied
-  uint32_t off[VEC ? NPTR : 1];                     // vector path: element offsets of the rows from `base`; rows past the
-                                                    // end point at the last row, so every offset can be loaded from
+  static constexpr int NP = R >= 64 ? R / 64 : 1;
+  static constexpr int NREG = 4 * NP;
+  static constexpr bool VEC = FORM == FORM_FAST;
   const float* base;
-  uint32_t mapped;                                  // scalar path, bit p: row of pass p reads through col_map / col_sign
-  uint32_t valid;                                   // vector path, bit p: the row of pass p exists
+  const float* ptr[VEC ? 1 : NP];
+  uint32_t off[VEC ? NP : 1];   // bytes from `base`
+  uint32_t mapped;              // bit p: the row of pass p reads through col_map / col_sign (never with VEC)
+  int q;
 
   __device__ __forceinline__ void setup(const GemmProblem& P, const float* b, int ld, int row0, int row_end) {
-    const int tid = threadIdx.x;
-    mapped = 0;
-    valid = 0;
     base = b;
-    if constexpr (VEC) {
+    q = threadIdx.x & 3;
+    mapped = 0;
 #pragma unroll
-      for (int p = 0; p < R / RPV; ++p) {
-        const int row = row0 + p * RPV + tid / LK;
-        if (row < row_end) valid |= 1u << p;
-        const int rc = min(row, row_end - 1);
-        off[p] = (uint32_t)(IS_X ? src_row(P, rc) : rc) * (uint32_t)ld + 4u * (tid % LK);
-      }
-    } else {
-#pragma unroll
-      for (int p = 0; p < R / RPS; ++p) {
-        const int row = row0 + p * RPS + tid / BK;
-        ptr[p] = nullptr;
-        if (row < row_end) {
-          ptr[p] = base + (long)(IS_X ? src_row(P, row) : row) * ld;
-          if (IS_X && P.col_map != nullptr && row >= P.map_from) mapped |= 1u << p;
-        }
+    for (int p = 0; p < NP; ++p) {
+      const int row = min(row0 + p * 64 + (int)(threadIdx.x >> 2), row_end - 1);
+      const int sr = IS_X ? src_row(P, row) : row;
+      if constexpr (VEC) {
+        off[p] = 4u * ((uint32_t)sr * (uint32_t)ld);
+      } else {
+        ptr[p] = b + (long)sr * ld;
+        if (IS_X && P.col_map != nullptr && row >= P.map_from) mapped |= 1u << p;
       }
     }
   }
-
-  __device__ __forceinline__ void fetch(const GemmProblem& P, int k0, int k_end, float (&reg)[NREG]) const {
-    const int tid = threadIdx.x;
+  // One pass of the fetch of step k0.  Past k_end the last values are read again: in bounds, and nullified by a zero in
+  // one of the two operands.
+  __device__ __forceinline__ void fetch(const GemmProblem& P, int k0, int k_end, float (&reg)[NREG], int p) {
     if constexpr (VEC) {
-      const float* bk = base + k0;                 // uniform; the per-lane part is the 32-bit offset
-      const bool kok = k0 + 4 * (tid % LK) < k_end;
-#pragma unroll
-      for (int p = 0; p < R / RPV; ++p) {
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (kok && ((valid >> p) & 1u)) v = *reinterpret_cast<const float4*>(bk + off[p]);
-        reg[4 * p + 0] = v.x; reg[4 * p + 1] = v.y; reg[4 * p + 2] = v.z; reg[4 * p + 3] = v.w;
-      }
+      const uint32_t kb = 4u * (uint32_t)min(k0 + 4 * q, k_end - 4);
+      const float4 v = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(base) + (off[p] + kb));
+      reg[4 * p + 0] = v.x; reg[4 * p + 1] = v.y; reg[4 * p + 2] = v.z; reg[4 * p + 3] = v.w;
     } else {
-      const int c = k0 + tid % BK;
-      const bool kok = c < k_end;
-      int cm = c;
-      float sg = 1.0f;
-      if (IS_X && kok && P.col_map != nullptr) {
-        cm = P.col_map[c];
-        if (P.col_sign != nullptr) sg = P.col_sign[c];
-      }
 #pragma unroll
-      for (int p = 0; p < R / RPS; ++p) {
-        float v = 0.f;
-        if (kok && ptr[p] != nullptr) v = ((mapped >> p) & 1u) ? sg * ptr[p][cm] : ptr[p][c];
-        reg[p] = v;
+      for (int c = 0; c < 4; ++c) {
+        const int col = min(k0 + 4 * q + c, k_end - 1);
+        float v;
+        if (IS_X && ((mapped >> p) & 1u)) v = (P.col_sign != nullptr ? P.col_sign[col] : 1.0f) * ptr[p][P.col_map[col]];
+        else v = ptr[p][col];
+        reg[4 * p + c] = v;
       }
     }
   }
-
-  // One 16-byte load / its LDS writes at a time, without bounds checks (whole BK-tiles of the contraction only; rows
-  // past the end repeat the last row and feed output rows that are dropped): the contraction loop places them
-  // between its matrix-core instructions.
-  static constexpr int NPIECE = VEC ? R / RPV : 0;
-  __device__ __forceinline__ void fetch_piece(int k0, float (&reg)[NREG], int p) const {
-    const float4 v = *reinterpret_cast<const float4*>(base + k0 + off[VEC ? p : 0]);
-    reg[4 * p + 0] = v.x; reg[4 * p + 1] = v.y; reg[4 * p + 2] = v.z; reg[4 * p + 3] = v.w;
-  }
-  template <int S>
-  __device__ __forceinline__ void stash_piece(float (*lds)[S], const float (&reg)[NREG], int p) const {
-    const int tid = threadIdx.x;
-    const int row = p * RPV + tid / LK;
-    const int kq = 4 * (tid % LK);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) lds[kq + c][row] = reg[4 * p + c];
-  }
-
-  template <int S>
-  __device__ __forceinline__ void stash(float (*lds)[S], const float (&reg)[NREG]) const {
-    const int tid = threadIdx.x;
-    if constexpr (VEC) {
-#pragma unroll
-      for (int p = 0; p < R / RPV; ++p) {
-        const int row = p * RPV + tid / LK;
-        const int kq = 4 * (tid % LK);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) lds[kq + c][row] = reg[4 * p + c];
-      }
-    } else {
-#pragma unroll
-      for (int p = 0; p < R / RPS; ++p) lds[tid % BK][p * RPS + tid / BK] = reg[p];
-    }
+  __device__ __forceinline__ bool valid(int k0, int k_end, int c) const { return k0 + 4 * q + c < k_end; }
+  __device__ __forceinline__ void put(char* tile, const Quad& quad, int p) const {
+    const int row = p * 64 + (int)(threadIdx.x >> 2);
+    if (R >= 64 || row < R) quad.template put<R>(tile, row, q);
   }
 };
 
-// ---- operand with the M / N index contiguous in memory (tile rows = contraction index) ----------------------
-// The column (and its mapped twin for mirrored rows) is fixed per lane; the contraction row changes per k-tile.
-template <int Cw, int BK, bool IS_X, bool VEC>
+// ---- operand with the M / N index contiguous in memory (contraction index = memory row) ---------------------
+// Wavefront w takes the contraction indices 4 w .. 4 w + 3 of a step, its lanes 64 consecutive columns (+ 64 per pass):
+// the memory rows are uniform, every load is a scalar row address plus the lane's column, of any alignment, and a
+// lane ends up with consecutive contraction indices of one column, which is what the split parts are packed along.
+template <int Cw, int FORM>
 struct Direct {
-  static constexpr int NREG = Cw * BK / NT;
-  static constexpr int V = Cw / 4;                  // vector path: float4 per tile row
-  static constexpr int RPV = NT / V;                // vector path: tile rows per pass
-  static constexpr int RPS = NT / Cw;               // scalar path: tile rows per pass
+  static constexpr int NP = Cw >= 64 ? Cw / 64 : 1;
+  static constexpr int NREG = 4 * NP;
+  static constexpr bool MAPPED = FORM == FORM_GENERAL;
   const float* base;
-  int ld, col, cm;
-  int colc;                                         // vector path: col, or the last whole 16-byte column group of the matrix
-  float sg;
-  bool col_ok, has_map;
-  uint32_t off[VEC ? (BK / RPV > 0 ? BK / RPV : 1) : 1];   // vector path, rows not gathered: offsets from row k0
-  int next_row[(VEC && IS_X) ? (BK / RPV > 0 ? BK / RPV : 1) : 1];   // vector path, gathered rows: source rows of the next fetch
-  static constexpr bool vec = VEC;
+  int ld, w;
+  uint32_t col[NP], cm[MAPPED ? NP : 1];        // byte offsets of the lane's columns in a row
+  float sg[MAPPED ? NP : 1];
+  const int32_t* row_idx;
+  int idx_mod, wrap_add, map_from;
+  int next_row;                                 // lane c % 4: source row c of the next fetch, looked up one step ahead of it
 
   __device__ __forceinline__ void setup(const GemmProblem& P, const float* b, int ld_, int col0, int col_end) {
-    const int tid = threadIdx.x;
     base = b; ld = ld_;
-    col = vec ? col0 + 4 * (tid % V) : col0 + tid % Cw;
-    col_ok = col < col_end;
-    has_map = false; cm = col; sg = 1.0f;
-    colc = col_ok ? col : max(col_end - 4, 0);
-    if constexpr (VEC) {
+    w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    row_idx = P.row_idx; idx_mod = P.idx_mod; wrap_add = P.wrap_add; map_from = P.map_from;
 #pragma unroll
-      for (int p = 0; p < BK / RPV; ++p) off[p] = (uint32_t)(p * RPV + tid / V) * (uint32_t)ld + (uint32_t)colc;
-    }
-    if (IS_X && !vec && col_ok && P.col_map != nullptr) {
-      has_map = true;
-      cm = P.col_map[col];
-      if (P.col_sign != nullptr) sg = P.col_sign[col];
-    }
-  }
-
-  // Gathered rows (vector path): the source rows of a tile are looked up while the previous tile is fetched, so
-  // that no fetch waits for its own index loads.  `prime` looks up the rows of the first tile; every fetch then
-  // looks up the rows of the tile BK further on (fetches walk the contraction range in steps of BK).
-  __device__ __forceinline__ void prime(const GemmProblem& P, int k0, int k_end) {
-    if constexpr (VEC && IS_X) {
-      const int tid = threadIdx.x;
-#pragma unroll
-      for (int p = 0; p < BK / RPV; ++p) next_row[p] = src_row(P, min(k0 + p * RPV + tid / V, k_end - 1));
-    }
-  }
-
-  __device__ __forceinline__ void fetch(const GemmProblem& P, int k0, int k_end, float (&reg)[NREG]) {
-    const int tid = threadIdx.x;
-    if constexpr (VEC) {
-      const float* bk = base + (long)k0 * ld;      // uniform
-#pragma unroll
-      for (int p = 0; p < BK / RPV; ++p) {
-        const int kk = k0 + p * RPV + tid / V;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (col_ok && kk < k_end) {
-          if constexpr (IS_X) v = *reinterpret_cast<const float4*>(base + (long)next_row[p] * ld + col);
-          else v = *reinterpret_cast<const float4*>(bk + off[p]);
+    for (int p = 0; p < NP; ++p) {
+      const int c = min(col0 + p * 64 + (int)(threadIdx.x & 63), col_end - 1);   // columns past the end repeat the last one
+      col[p] = 4u * (uint32_t)c;
+      if constexpr (MAPPED) {
+        cm[p] = col[p]; sg[p] = 1.0f;
+        if (P.col_map != nullptr) {
+          cm[p] = 4u * (uint32_t)P.col_map[c];
+          if (P.col_sign != nullptr) sg[p] = P.col_sign[c];
         }
-        reg[4 * p + 0] = v.x; reg[4 * p + 1] = v.y; reg[4 * p + 2] = v.z; reg[4 * p + 3] = v.w;
-      }
-      if constexpr (IS_X) {
-#pragma unroll
-        for (int p = 0; p < BK / RPV; ++p) next_row[p] = src_row(P, min(k0 + BK + p * RPV + tid / V, k_end - 1));
-      }
-    } else {
-#pragma unroll
-      for (int p = 0; p < BK / RPS; ++p) {
-        const int kk = k0 + p * RPS + tid / Cw;
-        float v = 0.f;
-        if (col_ok && kk < k_end) {
-          const float* rowp = base + (long)(IS_X ? src_row(P, kk) : kk) * ld;
-          v = (has_map && kk >= P.map_from) ? sg * rowp[cm] : rowp[col];
-        }
-        reg[p] = v;
       }
     }
   }
-
-  // Piecewise variants without bounds checks (whole BK-tiles of the contraction; matrix widths that are multiples of
-  // four): columns past the end repeat the last column group and feed outputs that are dropped.  The first form is
-  // for contraction rows that are not gathered (row kk is row kk), the second walks the gathered rows like `fetch`.
-  static constexpr int NPIECE = VEC ? BK / RPV : 0;
-  __device__ __forceinline__ void fetch_piece(int k0, float (&reg)[NREG], int p) const {
-    const float4 v = *reinterpret_cast<const float4*>(base + (long)k0 * ld + off[VEC ? p : 0]);
-    reg[4 * p + 0] = v.x; reg[4 * p + 1] = v.y; reg[4 * p + 2] = v.z; reg[4 * p + 3] = v.w;
-  }
-  __device__ __forceinline__ void fetch_piece_gathered(const GemmProblem& P, int k0, int k_end, float (&reg)[NREG], int p) {
-    const int pi = (VEC && IS_X) ? p : 0;
-    const float4 v = *reinterpret_cast<const float4*>(base + (long)next_row[pi] * ld + colc);
-    reg[4 * p + 0] = v.x; reg[4 * p + 1] = v.y; reg[4 * p + 2] = v.z; reg[4 * p + 3] = v.w;
-    next_row[pi] = src_row(P, min(k0 + BK + p * RPV + (int)threadIdx.x / V, k_end - 1));
-  }
-  template <int S>
-  __device__ __forceinline__ void stash_piece(float (*lds)[S], const float (&reg)[NREG], int p) const {
-    const int tid = threadIdx.x;
-    const float4 v = make_float4(reg[4 * p], reg[4 * p + 1], reg[4 * p + 2], reg[4 * p + 3]);
-    *reinterpret_cast<float4*>(&lds[p * RPV + tid / V][4 * (tid % V)]) = v;
-  }
-
-  template <int S>
-  __device__ __forceinline__ void stash(float (*lds)[S], const float (&reg)[NREG]) const {
-    const int tid = threadIdx.x;
-    if constexpr (VEC) {
-#pragma unroll
-      for (int p = 0; p < BK / RPV; ++p) {
-        const float4 v = make_float4(reg[4 * p], reg[4 * p + 1], reg[4 * p + 2], reg[4 * p + 3]);
-        *reinterpret_cast<float4*>(&lds[p * RPV + tid / V][4 * (tid % V)]) = v;
-      }
-    } else {
-#pragma unroll
-      for (int p = 0; p < BK / RPS; ++p) lds[p * RPS + tid / Cw][tid % Cw] = reg[p];
+  __device__ __forceinline__ void look_up(int k0, int k_end) {
+    if constexpr (FORM != FORM_FAST) {
+      const int r = min(k0 + 4 * w + (int)(threadIdx.x & 3), k_end - 1);
+      const bool wrap = r >= idx_mod;
+      const int rr = wrap ? r - idx_mod : r;
+      next_row = (row_idx != nullptr ? row_idx[rr] : rr) + (wrap ? wrap_add : 0);
     }
+  }
+  __device__ __forceinline__ void fetch(const GemmProblem&, int k0, int k_end, float (&reg)[NREG], int p) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int kk = min(k0 + 4 * w + c, k_end - 1);   // uniform
+      const int row = FORM == FORM_FAST ? kk : __builtin_amdgcn_readlane(next_row, c);
+      const char* rowp = reinterpret_cast<const char*>(base + (long)row * ld);
+      if (MAPPED && kk >= map_from) reg[4 * p + c] = sg[MAPPED ? p : 0] * *reinterpret_cast<const float*>(rowp + cm[MAPPED ? p : 0]);
+      else reg[4 * p + c] = *reinterpret_cast<const float*>(rowp + col[p]);
+    }
+  }
+  __device__ __forceinline__ bool valid(int k0, int k_end, int c) const { return k0 + 4 * w + c < k_end; }
+  __device__ __forceinline__ void put(char* tile, const Quad& quad, int p) const {
+    const int lane = threadIdx.x & 63;
+    if (Cw >= 64 || lane < Cw) quad.template put<Cw>(tile, p * 64 + lane, w);
   }
 };
 
-// LDS floats of one tile configuration: two buffers of BK x (BM + PAD) and BK x (BN + PAD).
-template <int BM, int BN, int BK>
-constexpr int gemm_lds_floats() { return 2 * BK * (BM + PAD) + 2 * BK * (BN + PAD); }
+// ---- weights that were split once for the optimiser step (launch_pack_weights) -------------------------------
+// Memory holds the LDS image already: 16 bytes are one part of eight consecutive contraction indices of one column, the
+// contraction padded with zeros to whole steps.  Loads and LDS writes only.
+template <int Cw>
+struct Packed {
+  static constexpr int UNITS = 6 * Cw;                      // 16-byte units of a step
+  static constexpr int NP = (UNITS + NT - 1) / NT;
+  static constexpr int NREG = 4 * NP;
+  const char* base;
+  uint32_t off[NP], step;                                   // bytes
+  __device__ __forceinline__ void setup(const GemmProblem& P, int col0, int col_end) {
+    base = reinterpret_cast<const char*>(P.Bp);
+    step = 32u * (uint32_t)P.N;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int u = min(p * NT + (int)threadIdx.x, UNITS - 1);
+      const int plane = u / Cw;                             // 2 * part + k-group
+      off[p] = 16u * (uint32_t)(((plane >> 1) * P.kgroups + (plane & 1)) * P.N + min(col0 + u % Cw, col_end - 1));
+    }
+  }
+  __device__ __forceinline__ void fetch(const GemmProblem&, int k0, int, float (&reg)[NREG], int p) {
+    const char* b = base + (long)(k0 / BK) * step;          // uniform
+    const float4 v = *reinterpret_cast<const float4*>(b + off[p]);
+    reg[4 * p + 0] = v.x; reg[4 * p + 1] = v.y; reg[4 * p + 2] = v.z; reg[4 * p + 3] = v.w;
+  }
+  __device__ __forceinline__ void put_raw(char* tile, const float* v, int p) const {
+    const int u = p * NT + (int)threadIdx.x;
+    if (NP * NT == UNITS || u < UNITS)
+      *reinterpret_cast<float4*>(tile + (u / Cw) * plane_pitch<Cw>() + (u % Cw) * 16) = make_float4(v[0], v[1], v[2], v[3]);
+  }
+};
+
+// LDS bytes of one tile configuration: two buffers of split operand tiles, and the word that says whether a lane of the
+// workgroup met a non-finite sum.
+template <int BM, int BN>
+constexpr int gemm_lds_bytes() { return 2 * (tile_bytes<BM>() + tile_bytes<BN>()) + 16; }
+
+// The contraction of a tile on the fp32 matrix cores (v_mfma_f32_32x32x2_f32), element by element and without any
+// overlap: reached only by tiles with non-finite sums.
+template <int MODE, int BM, int BN, int WM, int WN>
+__device__ __forceinline__ void fp32_contract(const GemmProblem& P, int m0, int n0, int k_begin, int k_end, float* smem,
+                                           f32x16 (&acc)[BM / WM / 32][BN / WN / 32]) {
+  constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
+  float* As = smem;                    // [BK][BM]
+  float* Bs = smem + BK * BM;          // [BK][BN]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int g = lane >> 5, j = lane & 31;
+  const int a_off = (wave / WN) * (TM * 32) + j, b_off = (wave % WN) * (TN * 32) + j;
+  const int a_cols = (MODE == GEMM_DW && P.a_cols > P.M) ? P.a_cols : P.M;
+#pragma unroll
+  for (int x = 0; x < TM; ++x)
+#pragma unroll
+    for (int y = 0; y < TN; ++y)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
+  for (int k0 = k_begin; k0 < k_end; k0 += BK) {
+    __syncthreads();
+#pragma unroll 1
+    for (int e = tid; e < BK * BM; e += NT) {
+      const int m = m0 + e % BM, k = k0 + e / BM;
+      float v = 0.f;
+      if (MODE == GEMM_DX) {
+        if (m < P.M && k < k_end) v = P.A[(long)m * P.lda + k];
+      } else {
+        const int row = MODE == GEMM_DW ? k : m, col = MODE == GEMM_DW ? m : k;
+        if (row < (MODE == GEMM_DW ? k_end : P.M) && col < (MODE == GEMM_DW ? a_cols : k_end)) {
+          const float* rp = P.A + (long)src_row(P, row) * P.lda;
+          if (P.col_map != nullptr && row >= P.map_from) v = (P.col_sign != nullptr ? P.col_sign[col] : 1.0f) * rp[P.col_map[col]];
+          else v = rp[col];
+        }
+      }
+      As[e] = v;
+    }
+#pragma unroll 1
+    for (int e = tid; e < BK * BN; e += NT) {
+      const int n = n0 + e % BN, k = k0 + e / BN;
+      Bs[e] = (n < P.N && k < k_end) ? P.B[MODE == GEMM_DX ? (long)n * P.ldb + k : (long)k * P.ldb + n] : 0.f;
+    }
+    __syncthreads();
+    for (int kk = 0; kk < BK; kk += 2) {
+      float a[TM], b[TN];
+#pragma unroll
+      for (int t = 0; t < TM; ++t) a[t] = As[(kk + g) * BM + a_off + t * 32];
+#pragma unroll
+      for (int t = 0; t < TN; ++t) b[t] = Bs[(kk + g) * BN + b_off + t * 32];
+#pragma unroll
+      for (int x = 0; x < TM; ++x)
+#pragma unroll
+        for (int y = 0; y < TN; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[x], b[y], acc[x][y], 0, 0, 0);
+    }
+  }
+  __syncthreads();
+}
 
 // One output tile (one split of it for the weight gradient) of problem P.  `lin` numbers the workgroups of the
-// problem's grid of gx tiles x (total / gx) splits; `smem` holds gemm_lds_floats<BM, BN, BK>() floats.
-template <int MODE, int BM, int BN, int WM, int WN, int BK, bool AVEC, bool BVEC>
-__device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const int total, const int gx, float* smem) {
+// problem's grid of gx tiles x (total / gx) splits; `smem` holds gemm_lds_bytes<BM, BN>() bytes.
+template <int MODE, int BM, int BN, int WM, int WN, int FORM, bool PACK>
+__device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const int total, const int gx, char* smem) {
   static_assert(WM * WN == 4, "four wavefronts per workgroup");
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
   static_assert(TM >= 1 && TN >= 1, "wave tile must hold at least one 32x32 block");
-  constexpr int SA = BM + PAD, SB = BN + PAD;
-  float (*As)[BK][SA] = reinterpret_cast<float (*)[BK][SA]>(smem);
-  float (*Bs)[BK][SB] = reinterpret_cast<float (*)[BK][SB]>(smem + 2 * BK * SA);
+  constexpr int ABYTES = tile_bytes<BM>(), BBYTES = tile_bytes<BN>();
+  char* As = smem;                          // [2][ABYTES]
+  char* Bs = smem + 2 * ABYTES;             // [2][BBYTES]
+  int* flag = reinterpret_cast<int*>(smem + 2 * (ABYTES + BBYTES));
 
   const int tiles_n = (P.N + BN - 1) / BN;
   const int tiles_m = (P.M + BM - 1) / BM;
@@ -288,9 +315,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
   const int lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 5, j = lane & 31;
   const int wm = wave / WN, wn = wave % WN;
-  const int a_off = wm * (TM * 32) + j, b_off = wn * (TN * 32) + j;
 
-  float ra[BM * BK / NT], rb[BN * BK / NT];
   f32x16 acc[TM][TN];
 #pragma unroll
   for (int a = 0; a < TM; ++a)
@@ -298,202 +323,187 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
     for (int b = 0; b < TN; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-  float bsum = 0.f;   // DW: column sum of dZ for the bias gradient
 
   // operand A: DW reads X rows as contraction rows (M index contiguous); FWD / DX read rows with k contiguous.
-  // operand B: always N index contiguous (W, W^T or dZ).
-  KContig<BM, BK, MODE == GEMM_FWD, AVEC> a_k;
-  Direct<BM, BK, true, AVEC> a_d;
-  Direct<BN, BK, false, BVEC> b_d;
+  // operand B: DX reads rows of W (k contiguous); FWD and DW have the N index contiguous (W, dZ).
   const int a_cols = (MODE == GEMM_DW && P.a_cols > P.M) ? P.a_cols : P.M;   // DW: readable (zero-padded) width of X
-  if (MODE == GEMM_DW) a_d.setup(P, P.A, P.lda, m0, a_cols);
-  else a_k.setup(P, P.A, P.lda, m0, P.M);
-  b_d.setup(P, P.B, P.ldb, n0, P.N);
+  typename std::conditional<MODE == GEMM_DW, Direct<BM, FORM>, KContig<BM, MODE == GEMM_FWD, FORM>>::type la;
+  typename std::conditional<PACK, Packed<BN>, typename std::conditional<MODE == GEMM_DX, KContig<BN, false, FORM>,
+                                                                        Direct<BN, FORM_FAST>>::type>::type lb;
+  la.setup(P, P.A, P.lda, m0, a_cols);
+  if constexpr (PACK) lb.setup(P, n0, P.N);
+  else lb.setup(P, P.B, P.ldb, n0, P.N);
+  // values on their way to LDS: one step ahead; activation rows that meet weights two steps ahead, since they come from
+  // memory and there are registers left for them
+  constexpr int DA = MODE == GEMM_DW ? 1 : 2;
+  float ra[DA][decltype(la)::NREG], rb[decltype(lb)::NREG];
 
-  // DX with at most two 32x32 blocks per wave: the activation values that gate the result (ELU') are fetched
-  // ahead of the contraction loop and wait in registers, so the epilogue does not stall on them.
-  constexpr bool AUX_AHEAD = MODE == GEMM_DX && TM * TN <= 2;
-  float hpre[AUX_AHEAD ? TM * TN * 16 : 1];
+  // DW: column sums of dZ for the bias gradient, over the contraction rows of this lane
+  constexpr int NBS = MODE == GEMM_DW ? decltype(lb)::NP : 1;
+  float bsum[NBS];
+#pragma unroll
+  for (int p = 0; p < NBS; ++p) bsum[p] = 0.f;
+  // Sign of what the accumulators hold (see sign_flip_step): the weight gradient sums the negated terms in every other
+  // split, the contractions with split weights change sign on the way.
+  const int flip_t = PACK ? sign_flip_step(nk) : nk;
+  float flip = (MODE == GEMM_DW && (split & 1)) || (PACK && flip_t < nk) ? -1.0f : 1.0f;
+  const bool with_bias = MODE == GEMM_DW && tm == 0 && P.bias_off >= 0;
+
   const bool full_mn = m0 + BM <= P.M && n0 + BN <= P.N;
-  const bool aux_ahead = AUX_AHEAD && full_mn && P.aux != nullptr;
-  auto fetch_aux = [&]() {
-    if constexpr (AUX_AHEAD) {
-      if (aux_ahead) {
-        const int ld = P.ldc;
+
+  if (tid == 0) *flag = 0;
+  // The loop is a fixed sequence of slots, one matrix instruction each, with the other work dealt out between them: a
+  // wave that converts, loads or stores in one burst leaves its matrix cores idle meanwhile, and the other waves of the
+  // SIMD tend to be in the same phase.  Body t runs the last three products of step t - 1 and the first three of step
+  // t, so the operands of step t replace those of step t - 1 in their registers as these are used up, and the parts
+  // of step t + 1 have the whole body to be formed and written; one barrier per body.
+  // Steps past the end: the last body forms the parts of one step too many (nobody reads them), and where the range is
+  // no whole number of steps, the indices past its end meet a zero in one operand: the zero padding of packed weights, else
+  // zeros put in place of operand B's (weight gradient) or A's values.
+  constexpr int NA = decltype(la)::NP, NB = decltype(lb)::NP, NQ = NA + NB, TT = TM * TN;
+  {
+    bf16x8 a[3][TM], b[3][TN];
+    Quad quad;
+    // piece p of step kt: a pass of operand A (p < NA) or B; `par` = kt mod 2, known at compile time
+    auto fetch_piece = [&](int p, int kt) {
+      const int k0 = k_begin + min(kt, nk - 1) * BK;
+      if (p < NA) {
+        la.fetch(P, k0, k_end, ra[DA - 1], p < NA ? p : 0);
+        if constexpr (MODE == GEMM_DW) {
+          if (p == NA - 1) la.look_up(k_begin + min(kt + 1, nk - 1) * BK, k_end);
+        }
+      } else {
+        lb.fetch(P, k0, k_end, rb, p < NA ? 0 : p - NA);
+      }
+    };
+    auto split_piece = [&](int p, int kt, int half) {
+      if (PACK && p >= NA) return;
+      float* v = p < NA ? ra[0] + 4 * (p < NA ? p : 0) : rb + 4 * (p < NA ? 0 : p - NA);
+      if constexpr (!PACK) {
+        if ((MODE == GEMM_DW) == (p >= NA)) {
+          const int k0 = k_begin + kt * BK;
 #pragma unroll
-        for (int x = 0; x < TM; ++x)
+          for (int c = 2 * half; c < 2 * half + 2; ++c) v[c] = (MODE == GEMM_DW ? lb.valid(k0, k_end, c) : la.valid(k0, k_end, c)) ? v[c] : 0.f;
+        }
+      }
+      if (MODE == GEMM_DW && p >= NA) {
+        const float w[4] = {flip * v[0], flip * v[1], flip * v[2], flip * v[3]};
+        if (half == 0) quad.split_lo(w);
+        else quad.split_hi(w);
+      } else {
+        if (half == 0) quad.split_lo(v);
+        else quad.split_hi(v);
+      }
+    };
+    auto put_piece = [&](int p, int par) {
+      if (p < NA) {
+        la.put(As + par * ABYTES, quad, p);
+      } else {
+        const float* v = rb + 4 * (p < NA ? 0 : p - NA);
+        if constexpr (PACK) lb.put_raw(Bs + par * BBYTES, v, p - NA);
+        else lb.put(Bs + par * BBYTES, quad, p - NA);
+        if constexpr (MODE == GEMM_DW) bsum[p < NA ? 0 : p - NA] += (v[0] + v[1]) + (v[2] + v[3]);
+      }
+    };
+    auto body = [&](int t, auto g2_tag) {
+      constexpr bool G2 = decltype(g2_tag)::value;
+      const int par = t & 1;
+      constexpr int S = (G2 ? 6 : 3) * TT;
+      constexpr int PA[6] = {1, 0, 0, 1, 2, 0}, PB[6] = {0, 1, 0, 1, 0, 2};   // the parts that meet: step t - 1, then step t
+      const char* ab = As + par * ABYTES + g * plane_pitch<BM>() + (wm * (TM * 32) + j) * 16;
+      const char* bb = Bs + par * BBYTES + g * plane_pitch<BN>() + (wn * (TN * 32) + j) * 16;
+      auto read_a = [&](int s) {
 #pragma unroll
-          for (int y = 0; y < TN; ++y) {
-            const float* hp = P.aux + (long)(m0 + wm * (TM * 32) + x * 32 + 4 * g) * ld + (n0 + wn * (TN * 32) + y * 32 + j);
+        for (int i = 0; i < TM; ++i) a[s][i] = *reinterpret_cast<const bf16x8*>(ab + 2 * s * plane_pitch<BM>() + i * 512);
+      };
+      auto read_b = [&](int s) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) hpre[(x * TN + y) * 16 + r] = hp[(8 * (r / 4) + (r % 4)) * ld];
+        for (int i = 0; i < TN; ++i) b[s][i] = *reinterpret_cast<const bf16x8*>(bb + 2 * s * plane_pitch<BN>() + i * 512);
+      };
+      if (!G2) { read_a(1); read_b(1); read_b(0); read_a(0); }
+      read_a(2); read_b(2);
+#pragma unroll
+      for (int i = 0; i < S; ++i) {
+        const int q = i / TT + (G2 ? 0 : 3), x = i % TT / TN, y = i % TN;
+        if (PACK && G2 && i == 3 * TT && t == flip_t) {
+#pragma unroll
+          for (int u = 0; u < TM; ++u)
+#pragma unroll
+            for (int v = 0; v < TN; ++v) acc[u][v] = -acc[u][v];
+        }
+        if (G2 && i == 2 * TT) { read_a(1); read_b(1); }
+        if (G2 && i == 3 * TT) { read_b(0); read_a(0); }
+        acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[q]][x], b[PB[q]][y], acc[x][y], 0, 0, 0);
+#pragma unroll
+        for (int p = 0; p < NQ; ++p) {
+          if (i == 3 * p * S / (3 * NQ)) split_piece(p, t + 1, 0);
+          if (i == (3 * p + 1) * S / (3 * NQ)) split_piece(p, t + 1, 1);
+          if (i == (3 * p + 2) * S / (3 * NQ)) {
+            put_piece(p, par ^ 1);
+            if (DA == 2 && p < NA) {
+#pragma unroll
+              for (int c = 0; c < 4; ++c) ra[0][4 * p + c] = ra[DA - 1][4 * p + c];
+            }
+            fetch_piece(p, t + 1 + (p < NA ? DA : 1));
           }
-      }
-    }
-  };
-  auto stash = [&](int buf) {
-    if (MODE == GEMM_DW) a_d.template stash<SA>(As[buf], ra);
-    else a_k.template stash<SA>(As[buf], ra);
-    b_d.template stash<SB>(Bs[buf], rb);
-  };
-  // The general loop: every lane checks its bounds (scalar operand paths, contraction ranges that are no multiple
-  // of BK).
-  auto main_loop = [&]() {
-    auto fetch = [&](int k0) {
-      if (MODE == GEMM_DW) a_d.fetch(P, k0, k_end, ra);
-      else a_k.fetch(P, k0, k_end, ra);
-      b_d.fetch(P, k0, k_end, rb);
-    };
-    if (nk > 0) {
-      if (MODE == GEMM_DW) a_d.prime(P, k_begin, k_end);
-      fetch(k_begin);
-      stash(0);
-    }
-    fetch_aux();
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-      const int buf = kt & 1;
-      if (kt + 1 < nk) fetch(k_begin + (kt + 1) * BK);
-      // operands of step kk + 2 are read from LDS before the matrix-core instructions of step kk issue
-      float a_cur[TM], b_cur[TN], a_nxt[TM], b_nxt[TN];
-#pragma unroll
-      for (int t = 0; t < TM; ++t) a_cur[t] = As[buf][g][a_off + t * 32];
-#pragma unroll
-      for (int t = 0; t < TN; ++t) b_cur[t] = Bs[buf][g][b_off + t * 32];
-#pragma unroll
-      for (int kk = 0; kk < BK; kk += 2) {
-        if (kk + 2 < BK) {
-#pragma unroll
-          for (int t = 0; t < TM; ++t) a_nxt[t] = As[buf][kk + 2 + g][a_off + t * 32];
-#pragma unroll
-          for (int t = 0; t < TN; ++t) b_nxt[t] = Bs[buf][kk + 2 + g][b_off + t * 32];
-        }
-        __builtin_amdgcn_sched_barrier(0);   // keep the LDS reads ahead of the matrix-core instructions
-#pragma unroll
-        for (int x = 0; x < TM; ++x)
-#pragma unroll
-          for (int y = 0; y < TN; ++y)
-            acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(a_cur[x], b_cur[y], acc[x][y], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (kk + 2 < BK) {
-#pragma unroll
-          for (int t = 0; t < TM; ++t) a_cur[t] = a_nxt[t];
-#pragma unroll
-          for (int t = 0; t < TN; ++t) b_cur[t] = b_nxt[t];
-        }
-      }
-      if (MODE == GEMM_DW && tm == 0 && tid < BN) {
-#pragma unroll
-        for (int kk = 0; kk < BK; ++kk) bsum += Bs[buf][kk][tid];
-      }
-      if (kt + 1 < nk) stash(buf ^ 1);
-      __syncthreads();
-    }
-  };
-  // 16-byte operand paths over whole BK-tiles run the same double buffer without bounds checks (operand rows and
-  // columns past the matrix repeat valid ones; the outputs they feed are dropped by the epilogue) and with the other
-  // instructions dealt out between the matrix-core instructions, one per gap: the 16-byte loads of the next tile
-  // in the first steps of a tile, their LDS writes in the last steps, the LDS operand reads of the next step after
-  // the first matrix-core instruction of each step.  A wave then never issues a burst of memory instructions while
-  // its matrix-core queue runs dry (measured: 6 % faster forward, 11 % faster input gradient at 128 x 128).
-  // GATHERED: the weight gradient's contraction rows go through row_idx / wrap (looked up one tile ahead).
-  auto stream_loop = [&](auto gathered_tag) {
-    constexpr bool GATHERED = decltype(gathered_tag)::value;
-    constexpr int NA = MODE == GEMM_DW ? decltype(a_d)::NPIECE : decltype(a_k)::NPIECE;
-    constexpr int NB = decltype(b_d)::NPIECE;
-    constexpr int NP = NA + NB, STEPS = BK / 2;
-    static_assert(2 * NP <= STEPS, "loads and LDS writes of a tile take one step each");
-    auto load_piece = [&](int q, int k0) {
-#pragma unroll
-      for (int p = 0; p < NA; ++p)
-        if (q == p) {
-          if (MODE == GEMM_DW && GATHERED) a_d.fetch_piece_gathered(P, k0, k_end, ra, p);
-          else if (MODE == GEMM_DW) a_d.fetch_piece(k0, ra, p);
-          else a_k.fetch_piece(k0, ra, p);
-        }
-#pragma unroll
-      for (int p = 0; p < NB; ++p)
-        if (q == NA + p) b_d.fetch_piece(k0, rb, p);
-    };
-    auto stash_piece = [&](int q, int buf) {
-#pragma unroll
-      for (int p = 0; p < NA; ++p)
-        if (q == p) {
-          if (MODE == GEMM_DW) a_d.template stash_piece<SA>(As[buf], ra, p);
-          else a_k.template stash_piece<SA>(As[buf], ra, p);
-        }
-#pragma unroll
-      for (int p = 0; p < NB; ++p)
-        if (q == NA + p) b_d.template stash_piece<SB>(Bs[buf], rb, p);
-    };
-    if (GATHERED) a_d.prime(P, k_begin, k_end);
-#pragma unroll
-    for (int q = 0; q < NP; ++q) load_piece(q, k_begin);
-    stash(0);
-    fetch_aux();
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-      const int buf = kt & 1;
-      const int k_next = k_begin + min(kt + 1, nk - 1) * BK;   // the last tile fetches itself again: in bounds, unused
-      float a_cur[TM], b_cur[TN], a_nxt[TM], b_nxt[TN];
-#pragma unroll
-      for (int t = 0; t < TM; ++t) a_cur[t] = As[buf][g][a_off + t * 32];
-#pragma unroll
-      for (int t = 0; t < TN; ++t) b_cur[t] = Bs[buf][g][b_off + t * 32];
-#pragma unroll
-      for (int st = 0; st < STEPS; ++st) {
-        if (st + 1 < STEPS) {
-#pragma unroll
-          for (int t = 0; t < TM; ++t) a_nxt[t] = As[buf][2 * st + 2 + g][a_off + t * 32];
-#pragma unroll
-          for (int t = 0; t < TN; ++t) b_nxt[t] = Bs[buf][2 * st + 2 + g][b_off + t * 32];
-        }
-        if (st < NP) load_piece(st, k_next);
-        if (st >= STEPS - NP) stash_piece(st - (STEPS - NP), buf ^ 1);
-#pragma unroll
-        for (int x = 0; x < TM; ++x)
-#pragma unroll
-          for (int y = 0; y < TN; ++y)
-            acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(a_cur[x], b_cur[y], acc[x][y], 0, 0, 0);
-        // order within the step: masks 0x008 matrix core, 0x100 LDS read, 0x020 global load, 0x200 LDS write
-        if constexpr (TM * TN >= 4) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - 2, 0);
-          __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x200, 4, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        } else {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);
-          __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x200, 4, 0);
-          __builtin_amdgcn_sched_group_barrier(0x008, TM * TN - 1, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
-        if (st + 1 < STEPS) {
-#pragma unroll
-          for (int t = 0; t < TM; ++t) a_cur[t] = a_nxt[t];
-#pragma unroll
-          for (int t = 0; t < TN; ++t) b_cur[t] = b_nxt[t];
-        }
-      }
-      if (MODE == GEMM_DW && tm == 0 && tid < BN) {
-#pragma unroll
-        for (int kk = 0; kk < BK; ++kk) bsum += Bs[buf][kk][tid];
       }
       __syncthreads();
+    };
+    if constexpr (MODE == GEMM_DW) la.look_up(k_begin, k_end);
+#pragma unroll
+    for (int p = 0; p < NQ; ++p) fetch_piece(p, 0);
+    if (DA == 2) {
+#pragma unroll
+      for (int c = 0; c < 4 * NA; ++c) ra[0][c] = ra[DA - 1][c];
+#pragma unroll
+      for (int p = 0; p < NA; ++p) fetch_piece(p, 1);
     }
-  };
-  const bool whole_tiles = nk > 0 && (k_end - k_begin) % BK == 0;
-  const bool widths_ok = P.N >= 4 && (P.N & 3) == 0 && (MODE != GEMM_DW || (a_cols >= 4 && (a_cols & 3) == 0));
-  const bool plain_rows = MODE != GEMM_DW || (P.row_idx == nullptr && k_end <= P.idx_mod);
-  if constexpr (AVEC && BVEC) {
-    if (whole_tiles && widths_ok && plain_rows) stream_loop(std::false_type{});
-    else if (whole_tiles && widths_ok) stream_loop(std::true_type{});
-    else main_loop();
-  } else {
-    main_loop();
+#pragma unroll
+    for (int p = 0; p < NQ; ++p) {
+      split_piece(p, 0, 0); split_piece(p, 0, 1);
+      put_piece(p, 0);
+      if (DA == 2 && p < NA) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) ra[0][4 * p + c] = ra[DA - 1][4 * p + c];
+      }
+      fetch_piece(p, p < NA ? DA : 1);
+    }
+    __syncthreads();
+    body(0, std::false_type{});
+    for (int t = 1; t < nk; ++t) body(t, std::true_type{});
+#pragma unroll
+    for (int i = 0; i < 3 * TT; ++i) {
+      constexpr int PA[3] = {1, 0, 0}, PB[3] = {0, 1, 0};
+      const int q = i / TT, x = i % TT / TN, y = i % TN;
+      acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[q]][x], b[PB[q]][y], acc[x][y], 0, 0, 0);
+    }
+  }
+  {
+    float z = 0.f;                 // becomes NaN with any non-finite sum
+#pragma unroll
+    for (int x = 0; x < TM; ++x)
+#pragma unroll
+      for (int y = 0; y < TN; ++y)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z = fmaf(acc[x][y][r], 0.f, z);
+    if (!(z == 0.f)) *flag = 1;
+    __syncthreads();
+    if (*flag) {
+      fp32_contract<MODE, BM, BN, WM, WN>(P, m0, n0, k_begin, k_end, reinterpret_cast<float*>(smem), acc);
+      flip = 1.0f;
+    }
+  }
+  float bias_grad = 0.f;
+  if (with_bias) {                 // the four wavefronts hold different contraction rows of the same columns
+    float* red = reinterpret_cast<float*>(smem);
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < NBS; ++p)
+      if (BN >= 64 || lane < BN) red[wave * BN + p * 64 + lane] = bsum[p];
+    __syncthreads();
+    if (tid < BN) bias_grad = (red[tid] + red[BN + tid]) + (red[2 * BN + tid] + red[3 * BN + tid]);
   }
 
   // ---- epilogue -------------------------------------------------------------------------------
@@ -513,7 +523,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
     float bias[TN];
 #pragma unroll
     for (int y = 0; y < TN; ++y) bias[y] = (MODE == GEMM_FWD && aux != nullptr) ? aux[n0 + wn * (TN * 32) + y * 32 + j] : 0.f;
-    constexpr bool GATE_PIPE = MODE == GEMM_DX && !AUX_AHEAD;
+    constexpr bool GATE_PIPE = MODE == GEMM_DX;
     float hx[2][16];
     auto block_offset = [&](int b) {
       const int x = b / TN, y = b % TN;
@@ -530,17 +540,10 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
     for (int b = 0; b < TM * TN; ++b) {
       const int x = b / TN, y = b % TN;
       float* cp = Cb + block_offset(b);
-      if (MODE == GEMM_DX && aux != nullptr) {
-        if constexpr (AUX_AHEAD) {
-#pragma unroll
-          for (int r = 0; r < 16; ++r) hx[b & 1][r] = hpre[b * 16 + r];
-        } else if (b + 1 < TM * TN) {
-          load_gate(b + 1, hx[(b + 1) & 1]);
-        }
-      }
+      if (GATE_PIPE && aux != nullptr && b + 1 < TM * TN) load_gate(b + 1, hx[(b + 1) & 1]);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        float v = acc[x][y][r];
+        float v = MODE == GEMM_DW || PACK ? flip * acc[x][y][r] : acc[x][y][r];
         if (MODE == GEMM_FWD) {
           v += bias[y];
           if (elu) {
@@ -553,7 +556,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
         cp[(8 * (r / 4) + (r % 4)) * ldc] = v;
       }
     }
-    if (MODE == GEMM_DW && tm == 0 && bias_off >= 0 && tid < BN && n0 + tid < Nc) Cb[bias_off + n0 + tid] = bsum;
+    if (with_bias && tid < BN && n0 + tid < Nc) Cb[bias_off + n0 + tid] = bias_grad;
     return;
   }
 #pragma unroll
@@ -570,7 +573,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
       float out[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        float v = acc[x][y][r];
+        float v = MODE == GEMM_DW || PACK ? flip * acc[x][y][r] : acc[x][y][r];
         if (MODE == GEMM_FWD) {
           v += bias;
           if (elu) {
@@ -596,14 +599,17 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
       }
     }
   }
-  if (MODE == GEMM_DW && tm == 0 && bias_off >= 0 && tid < BN && n0 + tid < Nc) Cb[bias_off + n0 + tid] = bsum;
+  if (with_bias && tid < BN && n0 + tid < Nc) Cb[bias_off + n0 + tid] = bias_grad;
 }
 
-template <int MODE, int BM, int BN, int WM, int WN, int BK, bool AVEC, bool BVEC>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void gemm_kernel(const GemmBatch batch) {
-  __shared__ __align__(16) float smem[gemm_lds_floats<BM, BN, BK>()];
-  gemm_tile<MODE, BM, BN, WM, WN, BK, AVEC, BVEC>(batch.p[blockIdx.z], blockIdx.x + gridDim.x * blockIdx.y,
-                                                  gridDim.x * gridDim.y, gridDim.x, smem);
+// Workgroups resident per CU: three of 128 x 128 (50 KB of LDS, up to 168 registers), four of the smaller tiles.
+template <int BM, int BN> constexpr int waves_per_simd() { return BM * BN >= 128 * 128 ? 3 : 4; }
+
+template <int MODE, int BM, int BN, int WM, int WN, int FORM, bool PACK>
+__global__ __launch_bounds__(NT, (waves_per_simd<BM, BN>())) void gemm_kernel(const GemmBatch batch) {
+  __shared__ __align__(16) char smem[gemm_lds_bytes<BM, BN>()];
+  gemm_tile<MODE, BM, BN, WM, WN, FORM, PACK>(batch.p[blockIdx.z], blockIdx.x + gridDim.x * blockIdx.y, gridDim.x * gridDim.y,
+                                       gridDim.x, smem);
 }
 
 // Weight gradient and input gradient of one layer in one launch (both read the same dZ and neither reads the
@@ -611,66 +617,120 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void ge
 // one output phase disappear.  Workgroups [0, nw) belong to the weight gradient (gw tiles x sw splits per
 // problem), the next ne to an optional second weight gradient of narrow output (the network's output layer, whose
 // operands are ready at the same time: 128 x 32 tiles, ge tiles x se splits per problem), the rest to the input
-// gradient (gx tiles per problem).  16-byte operand paths only (the narrow one reads dZ with scalar loads).
-template <int WBM, int WBN, int WWM, int WWN, int XBM, int XBN, int XWM, int XWN, int BK>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void gemm_pair_kernel(
+// gradient (gx tiles per problem, 16-byte operand paths only).
+template <int WBM, int WBN, int WWM, int WWN, int XBM, int XBN, int XWM, int XWN>
+__global__ __launch_bounds__(NT, (waves_per_simd<(WBM > XBM ? WBM : XBM), WBN>())) void gemm_pair_kernel(
     const GemmBatch bw, const GemmBatch bx, const GemmBatch be, const int gw, const int sw, const int gx, const int ge,
     const int se) {
-  constexpr int LW = gemm_lds_floats<WBM, WBN, BK>(), LX = gemm_lds_floats<XBM, XBN, BK>();
-  constexpr int LE = gemm_lds_floats<128, 32, BK>();
+  constexpr int LW = gemm_lds_bytes<WBM, WBN>(), LX = gemm_lds_bytes<XBM, XBN>();
+  constexpr int LE = gemm_lds_bytes<128, 32>();
   constexpr int LWX = LW > LX ? LW : LX;
-  __shared__ __align__(16) float smem[LWX > LE ? LWX : LE];
+  __shared__ __align__(16) char smem[LWX > LE ? LWX : LE];
   const int per_w = gw * sw, per_e = ge * se;
   const int nw = bw.count * per_w, ne = be.count * per_e;
   const int b = blockIdx.x;
-  // When the weight-gradient workgroups alone fill the chip (4 resident workgroups on each of 256 CUs), the input
-  // gradient is the tail of the launch: its waves then issue ahead of the weight gradient's that are still running
-  // (measured: 4 % off such a launch; 5 % on, when the two kinds share the chip from the start).
-  if (b >= nw + ne && nw >= 1024) __builtin_amdgcn_s_setprio(3);
   if (b < nw) {
     const int z = b / per_w;
-    gemm_tile<GEMM_DW, WBM, WBN, WWM, WWN, BK, true, true>(bw.p[z], b - z * per_w, per_w, gw, smem);
+    gemm_tile<GEMM_DW, WBM, WBN, WWM, WWN, FORM_FAST, false>(bw.p[z], b - z * per_w, per_w, gw, smem);
   } else if (b < nw + ne) {
     const int c = b - nw;
     const int z = c / per_e;
-    gemm_tile<GEMM_DW, 128, 32, 4, 1, BK, true, false>(be.p[z], c - z * per_e, per_e, ge, smem);
+    gemm_tile<GEMM_DW, 128, 32, 4, 1, FORM_FAST, false>(be.p[z], c - z * per_e, per_e, ge, smem);
   } else {
     const int c = b - nw - ne;
     const int z = c / gx;
-    gemm_tile<GEMM_DX, XBM, XBN, XWM, XWN, BK, true, true>(bx.p[z], c - z * gx, gx, gx, smem);
+    gemm_tile<GEMM_DX, XBM, XBN, XWM, XWN, FORM_FAST, true>(bx.p[z], c - z * gx, gx, gx, smem);
   }
 }
 
-template <int MODE, int BM, int BN, int WM, int WN, int BK = 16>
-static hipError_t launch_cfg(const GemmBatch& batch, hipStream_t stream) {
-  int tiles = 0, splits = 1;
-  // 16-byte fetches need every grouped problem to allow them and at least one float4 per lane and tile
-  bool avec = BM * BK >= 4 * NT, bvec = BN * BK >= 4 * NT;
+// ---- splitting weights --------------------------------------------------------------------------------------
+// One lane forms the three parts of eight consecutive contraction indices of one column (negated past sign_flip_step).
+__global__ __launch_bounds__(256) void pack_weights_kernel(const PackBatch b) {
+  const PackJob& J = b.job[blockIdx.y];
+  const int u = (int)blockIdx.x * 256 + (int)threadIdx.x;
+  if (u >= J.kgroups * J.cols) return;
+  const int kg = u / J.cols, c = u - kg * J.cols;
+  const float* src = J.src + (long)c * J.stride_c + (long)(8 * kg) * J.stride_k;
+  float v[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = 8 * kg + i < J.K ? src[(long)i * J.stride_k] : 0.f;
+  if (kg / 2 >= sign_flip_step(J.kgroups / 2)) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = -v[i];
+  }
+  uint4 part[3];
+  split_pair(v[0], v[1], part[0].x, part[1].x, part[2].x);
+  split_pair(v[2], v[3], part[0].y, part[1].y, part[2].y);
+  split_pair(v[4], v[5], part[0].z, part[1].z, part[2].z);
+  split_pair(v[6], v[7], part[0].w, part[1].w, part[2].w);
+#pragma unroll
+  for (int s = 0; s < 3; ++s) reinterpret_cast<uint4*>(J.dst)[(long)s * J.kgroups * J.cols + u] = part[s];
+}
+
+hipError_t launch_pack_weights(const PackBatch& b, hipStream_t stream) {
+  int units = 0;
+  for (int i = 0; i < b.count; ++i) units = b.job[i].kgroups * b.job[i].cols > units ? b.job[i].kgroups * b.job[i].cols : units;
+  if (units == 0) return hipSuccess;
+  TraceScope ts(stream, "pack_weights", 0.0, 0.0);
+  hipLaunchKernelGGL(pack_weights_kernel, dim3((units + 255) / 256, b.count), dim3(256), 0, stream, b);
+  return hipGetLastError();
+}
+
+// Grid geometry of a batch for a tile shape, and the operand form that all its problems allow.
+struct BatchGeom {
+  int tiles = 0, splits = 1, form = FORM_FAST;
+  bool pack = true;                  // every problem has split weights
+  double flops = 0.0;
+};
+
+static BatchGeom batch_geom(GemmMode mode, const GemmBatch& batch, int BM, int BN) {
+  BatchGeom g;
   for (int i = 0; i < batch.count; ++i) {
     const GemmProblem& P = batch.p[i];
-    int t = ((P.M + BM - 1) / BM) * ((P.N + BN - 1) / BN);
-    tiles = t > tiles ? t : tiles;
-    if (MODE == GEMM_DW) splits = P.n_split > splits ? P.n_split : splits;
-    // the 16-byte paths address rows by 32-bit element offsets from the matrix base
-    const int64_t lim = (int64_t)1 << 32;
-    const int64_t a_rows = P.row_idx != nullptr ? P.a_src_rows : (MODE == GEMM_DW ? P.K : P.M);
-    const bool a_fits = a_rows > 0 && a_rows * (int64_t)P.lda < lim;
-    const bool b_fits = (int64_t)P.K * P.ldb < lim;
-    avec = avec && P.a_vec != 0 && a_fits;
-    bvec = bvec && P.b_vec != 0 && b_fits;
+    const int t = ((P.M + BM - 1) / BM) * ((P.N + BN - 1) / BN);
+    g.tiles = t > g.tiles ? t : g.tiles;
+    int form = FORM_FAST;
+    if (mode == GEMM_DW) {
+      g.splits = P.n_split > g.splits ? P.n_split : g.splits;
+      if (P.col_map != nullptr) form = FORM_GENERAL;
+      else if (P.row_idx != nullptr || P.idx_mod < P.K) form = FORM_GATHER;
+    } else {
+      // the 16-byte paths address the matrix by 32-bit byte offsets from its base
+      const int64_t lim = (int64_t)1 << 30;
+      const int64_t a_rows = P.row_idx != nullptr ? P.a_src_rows : P.M;
+      if (!P.a_vec || a_rows <= 0 || a_rows * (int64_t)P.lda >= lim) form = FORM_GENERAL;
+      if (mode == GEMM_DX && P.Bp == nullptr && (!P.b_vec || (int64_t)P.N * P.ldb >= lim)) form = FORM_GENERAL;
+      g.pack = g.pack && P.Bp != nullptr;
+    }
+    g.form = form > g.form ? form : g.form;
+    g.flops += 2.0 * P.M * (double)P.N * P.K;
   }
-  if (tiles == 0) return hipSuccess;
-  dim3 grid(tiles, splits, batch.count);
-  double flops = 0.0;
-  for (int i = 0; i < batch.count; ++i) flops += 2.0 * batch.p[i].M * (double)batch.p[i].N * batch.p[i].K;
+  return g;
+}
+
+template <int MODE, int BM, int BN, int WM, int WN, int FORM, bool PACK>
+static void launch_form(const GemmBatch& batch, const dim3 grid, hipStream_t stream) {
+  hipLaunchKernelGGL((gemm_kernel<MODE, BM, BN, WM, WN, FORM, PACK>), grid, dim3(NT), 0, stream, batch);
+}
+
+template <int MODE, int BM, int BN, int WM, int WN>
+static hipError_t launch_cfg(const GemmBatch& batch, hipStream_t stream) {
+  const BatchGeom g = batch_geom((GemmMode)MODE, batch, BM, BN);
+  if (g.tiles == 0) return hipSuccess;
   static const char* const mode_name[3] = {"fwd", "dx", "dw"};
   char name[48];
   snprintf(name, sizeof name, "gemm_%s_%dx%d", mode_name[MODE], BM, BN);
-  TraceScope ts(stream, name, flops, 0.0);
-  if (avec && bvec) hipLaunchKernelGGL((gemm_kernel<MODE, BM, BN, WM, WN, BK, true, true>), grid, dim3(NT), 0, stream, batch);
-  else if (avec) hipLaunchKernelGGL((gemm_kernel<MODE, BM, BN, WM, WN, BK, true, false>), grid, dim3(NT), 0, stream, batch);
-  else if (bvec) hipLaunchKernelGGL((gemm_kernel<MODE, BM, BN, WM, WN, BK, false, true>), grid, dim3(NT), 0, stream, batch);
-  else hipLaunchKernelGGL((gemm_kernel<MODE, BM, BN, WM, WN, BK, false, false>), grid, dim3(NT), 0, stream, batch);
+  TraceScope ts(stream, name, g.flops, 0.0);
+  const dim3 grid(g.tiles, g.splits, batch.count);
+  if constexpr (MODE == GEMM_DW) {
+    if (g.form == FORM_FAST) launch_form<MODE, BM, BN, WM, WN, FORM_FAST, false>(batch, grid, stream);
+    else if (g.form == FORM_GATHER) launch_form<MODE, BM, BN, WM, WN, FORM_GATHER, false>(batch, grid, stream);
+    else launch_form<MODE, BM, BN, WM, WN, FORM_GENERAL, false>(batch, grid, stream);
+  } else {
+    if (g.form == FORM_FAST && g.pack) launch_form<MODE, BM, BN, WM, WN, FORM_FAST, true>(batch, grid, stream);
+    else if (g.form == FORM_FAST) launch_form<MODE, BM, BN, WM, WN, FORM_FAST, false>(batch, grid, stream);
+    else launch_form<MODE, BM, BN, WM, WN, FORM_GENERAL, false>(batch, grid, stream);
+  }
   return hipGetLastError();
 }
 
@@ -695,7 +755,6 @@ static TileCfg pick_tile(GemmMode mode, const GemmBatch& batch) {
   if (maxN <= 64) return TILE_128x64;
   if (mode == GEMM_DW) return dw_big ? TILE_128x128 : TILE_64x128;
   if (minK <= 64 || tiles128 < 700) return TILE_64x128;
-  if (mode == GEMM_DX && maxN >= 512) return TILE_64x128;   // wide outputs: the ELU' operand reads favour more, smaller workgroups
   return TILE_128x128;
 }
 
@@ -716,60 +775,6 @@ static hipError_t launch_mode(const GemmBatch& batch, hipStream_t stream) {
   }
 }
 
-// ---- weight transposition --------------------------------------------------------------------------
-// The input-gradient contraction reads W^T; transposing the (small) weight matrices once per optimiser step
-// lets that kernel fetch both operands the way the forward kernel does instead of transposing W tiles in LDS
-// for every row block.
-__global__ __launch_bounds__(256) void transpose_kernel(const TransposeBatch b) {
-  __shared__ float t[32][33];
-  const TransposeJob& J = b.job[blockIdx.z];
-  const int tiles_c = (J.cols + 31) / 32;
-  const int tiles_r = (J.rows + 31) / 32;
-  if ((int)blockIdx.x >= tiles_c * tiles_r) return;
-  const int r0 = ((int)blockIdx.x / tiles_c) * 32, c0 = ((int)blockIdx.x % tiles_c) * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int i = ty; i < 32; i += 8)
-    if (r0 + i < J.rows && c0 + tx < J.cols) t[i][tx] = J.src[(long)(r0 + i) * J.cols + c0 + tx];
-  __syncthreads();
-  for (int i = ty; i < 32; i += 8)
-    if (c0 + i < J.cols && r0 + tx < J.rows) J.dst[(long)(c0 + i) * J.rows + r0 + tx] = t[tx][i];
-}
-
-hipError_t launch_transpose(const TransposeBatch& b, hipStream_t stream) {
-  int tiles = 0;
-  for (int i = 0; i < b.count; ++i) {
-    int t = ((b.job[i].rows + 31) / 32) * ((b.job[i].cols + 31) / 32);
-    tiles = t > tiles ? t : tiles;
-  }
-  if (tiles == 0 || b.count == 0) return hipSuccess;
-  TraceScope ts(stream, "transpose_weights", 0.0, 0.0);
-  hipLaunchKernelGGL(transpose_kernel, dim3(tiles, 1, b.count), dim3(256), 0, stream, b);
-  return hipGetLastError();
-}
-
-// Grid geometry of a batch for a tile shape and whether every problem may use the 16-byte operand paths.
-struct BatchGeom {
-  int tiles = 0, splits = 1;
-  bool vec = true;
-  double flops = 0.0;
-};
-
-static BatchGeom batch_geom(GemmMode mode, const GemmBatch& batch, int BM, int BN) {
-  BatchGeom g;
-  for (int i = 0; i < batch.count; ++i) {
-    const GemmProblem& P = batch.p[i];
-    const int t = ((P.M + BM - 1) / BM) * ((P.N + BN - 1) / BN);
-    g.tiles = t > g.tiles ? t : g.tiles;
-    if (mode == GEMM_DW) g.splits = P.n_split > g.splits ? P.n_split : g.splits;
-    const int64_t lim = (int64_t)1 << 32;
-    const int64_t a_rows = P.row_idx != nullptr ? P.a_src_rows : (mode == GEMM_DW ? P.K : P.M);
-    g.vec = g.vec && P.a_vec != 0 && P.b_vec != 0 && a_rows > 0 && a_rows * (int64_t)P.lda < lim &&
-            (int64_t)P.K * P.ldb < lim;
-    g.flops += 2.0 * P.M * (double)P.N * P.K;
-  }
-  return g;
-}
-
 template <int WBM, int WBN, int WWM, int WWN, int XBM, int XBN, int XWM, int XWN>
 static hipError_t launch_pair_cfg(const GemmBatch& bw, const GemmBatch& bx, const GemmBatch& be, const BatchGeom& gw,
                                   const BatchGeom& gx, const BatchGeom& ge, hipStream_t stream) {
@@ -777,21 +782,14 @@ static hipError_t launch_pair_cfg(const GemmBatch& bw, const GemmBatch& bx, cons
   snprintf(name, sizeof name, "gemm_dwdx_%dx%d_%dx%d", WBM, WBN, XBM, XBN);
   TraceScope ts(stream, name, gw.flops + gx.flops + ge.flops, 0.0);
   const int blocks = bw.count * gw.tiles * gw.splits + bx.count * gx.tiles + be.count * ge.tiles * ge.splits;
-  hipLaunchKernelGGL((gemm_pair_kernel<WBM, WBN, WWM, WWN, XBM, XBN, XWM, XWN, 16>), dim3(blocks), dim3(NT), 0, stream,
+  hipLaunchKernelGGL((gemm_pair_kernel<WBM, WBN, WWM, WWN, XBM, XBN, XWM, XWN>), dim3(blocks), dim3(NT), 0, stream,
                      bw, bx, be, gw.tiles, gw.splits, gx.tiles, ge.tiles, ge.splits);
   return hipGetLastError();
 }
 
-// The narrow weight gradient can ride in the paired launch when it takes 128 x 32 tiles and its X operand allows
-// 16-byte loads (what gemm_kernel<GEMM_DW, 128, 32, 4, 1, 16, true, false> needs).
+// The narrow weight gradient can ride in the paired launch when it takes 128 x 32 tiles.
 static bool narrow_dw_fits(const GemmBatch& be) {
-  if (be.count <= 0 || pick_tile(GEMM_DW, be) != TILE_128x32) return false;
-  for (int i = 0; i < be.count; ++i) {
-    const GemmProblem& P = be.p[i];
-    const int64_t a_rows = P.row_idx != nullptr ? P.a_src_rows : P.K;
-    if (!P.a_vec || a_rows <= 0 || a_rows * (int64_t)P.lda >= ((int64_t)1 << 32)) return false;
-  }
-  return true;
+  return be.count > 0 && pick_tile(GEMM_DW, be) == TILE_128x32 && batch_geom(GEMM_DW, be, 128, 32).form == FORM_FAST;
 }
 
 hipError_t launch_gemm_dw_dx(const GemmBatch& bw, const GemmBatch& bx, hipStream_t stream, const GemmBatch* narrow_dw) {
@@ -800,7 +798,7 @@ hipError_t launch_gemm_dw_dx(const GemmBatch& bw, const GemmBatch& bx, hipStream
   if (w_ok && x_ok && bw.count > 0 && bx.count > 0) {
     const BatchGeom gw = batch_geom(GEMM_DW, bw, tw == TILE_128x128 ? 128 : 64, 128);
     const BatchGeom gx = batch_geom(GEMM_DX, bx, tx == TILE_128x128 ? 128 : 64, 128);
-    if (gw.vec && gx.vec && gw.tiles > 0 && gx.tiles > 0) {
+    if (gw.form == FORM_FAST && gx.form == FORM_FAST && gx.pack && gw.tiles > 0 && gx.tiles > 0) {
       GemmBatch be;
       memset(&be, 0, sizeof be);
       BatchGeom ge;

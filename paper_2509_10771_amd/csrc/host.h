@@ -141,11 +141,39 @@ inline void set_x(GemmProblem& p, const XView& x) {
   p.idx_mod = x.idx_mod; p.map_from = x.map_from; p.a_src_rows = x.src_rows; p.wrap_add = x.wrap_add;
 }
 
+// Split copies of a network's weight matrices (launch_pack_weights): per layer one for the forward contraction (over
+// the layer's inputs) and, above the first layer or where the input's gradient is asked for, one for the input gradient
+// (over its outputs).  Valid for the weights as they were when packed.
+struct WeightPack {
+  uint16_t* base = nullptr;
+  static int padded(int k) { return (k + 15) / 16 * 16; }
+  static size_t fwd_count(const rslx_mlp& n, int l) { return (size_t)3 * padded(n.dims[l]) * n.dims[l + 1]; }
+  static size_t dx_count(const rslx_mlp& n, int l) { return (size_t)3 * padded(n.dims[l + 1]) * n.dims[l]; }
+  static size_t offset(const rslx_mlp& n, int l) {        // in elements; every copy is a multiple of 16 bytes long
+    size_t o = 0;
+    for (int i = 0; i < l; ++i) o += fwd_count(n, i) + dx_count(n, i);
+    return o;
+  }
+  const uint16_t* fwd(const rslx_mlp& n, int l) const { return base + offset(n, l); }
+  const uint16_t* dx(const rslx_mlp& n, int l) const { return base + offset(n, l) + fwd_count(n, l); }
+};
+
+// Adds the copies of one network to a batch (dx_from: first layer whose input gradient is needed).
+inline void pack_add_net(PackBatch& b, const rslx_mlp& n, const WeightPack& w, int dx_from) {
+  for (int l = 0; l < n.n_layers; ++l) {
+    const float* W = n.params + layer_offset(n, l);
+    const int K = n.dims[l], N = n.dims[l + 1];
+    b.job[b.count++] = PackJob{W, const_cast<uint16_t*>(w.fwd(n, l)), K, N, WeightPack::padded(K) / 8, N, 1};
+    if (l >= dx_from) b.job[b.count++] = PackJob{W, const_cast<uint16_t*>(w.dx(n, l)), N, K, WeightPack::padded(N) / 8, 1, N};
+  }
+}
+
 struct NetJob {
   const rslx_mlp* net;
   XView x;
   int32_t rows;
   NetBufs* bufs;
+  const WeightPack* pack = nullptr;
 };
 
 // Forward of up to two networks of equal depth, one grouped launch per layer.
@@ -175,6 +203,7 @@ inline int32_t forward_nets(const NetJob* jobs, int count, hipStream_t stream, b
       p.M = jobs[i].rows; p.N = n.dims[l + 1]; p.K = (l == 0 && jobs[i].x.cols) ? jobs[i].x.cols : n.dims[l];
       p.elu = (l + 1 < L) ? 1 : 0;
       p.alpha = n.elu_alpha;
+      if (jobs[i].pack) { p.Bp = jobs[i].pack->fwd(n, l); p.kgroups = WeightPack::padded(n.dims[l]) / 8; }
       p.a_vec = (p.K % 4 == 0 && p.lda % 4 == 0 && aligned16(p.A) && p.col_map == nullptr) ? 1 : 0;
       p.b_vec = (p.N % 4 == 0 && aligned16(p.B)) ? 1 : 0;
       b.p[i] = p;
@@ -206,7 +235,7 @@ struct SplitPlan {
 constexpr int DW_TARGET_WGS = 1024;
 constexpr int DW_TARGET_WGS_PAIRED = 256;
 constexpr int DW_TARGET_WGS_BIG = 768;
-constexpr int DW_TARGET_WGS_BIG_PAIRED = 512;
+constexpr int DW_TARGET_WGS_BIG_PAIRED = 768;
 
 // Plans layer l (an [M, N] weight reduced over `rows` rows) and appends it to p.
 inline void plan_layer(SplitPlan& p, int l, int M, int N, int32_t rows, int group, bool paired) {
@@ -246,47 +275,22 @@ struct BwdJob {
   int32_t rows;
   NetBufs* bufs;
   const float* d_out;    // [rows, dims[L]]
-  float* wt;             // scratch for the transposed weights (flat parameter layout)
   float* partials;       // split partials, laid out by `plan`
   const SplitPlan* plan;
   float* dx0 = nullptr;  // optional [rows, dims[0]]: gradient w.r.t. the network input (a memory in front of it)
+  const WeightPack* pack = nullptr;
 };
 
 // Backward of up to two networks of equal depth: per layer one grouped weight-gradient launch (split over
 // rows, partial sums) and one grouped input-gradient launch.
 // With skip_last_dx the input gradient of the output layer (dz of the last hidden layer) already exists.
-// Transposed copies of the weight matrices that the input-gradient contractions of backward_nets read.
-inline int32_t transpose_weights(const BwdJob* jobs, int count, hipStream_t stream, bool skip_last_dx) {
-  TransposeBatch tb;
-  tb.count = 0;
-  for (int i = 0; i < count; ++i) {
-    const rslx_mlp& n = *jobs[i].net;
-    for (int l = jobs[i].dx0 != nullptr ? 0 : 1; l < (skip_last_dx ? n.n_layers - 1 : n.n_layers); ++l)
-      tb.job[tb.count++] = TransposeJob{n.params + layer_offset(n, l), jobs[i].wt + layer_offset(n, l), n.dims[l], n.dims[l + 1]};
-  }
-  RSLX_HIP(launch_transpose(tb, stream));
-  return RSLX_OK;
-}
-
-// Lets the Adam launch keep a job's transposed weights current (see AdamSegment::wt).
-inline void adam_keeps_transposed(AdamSegment& sg, const rslx_mlp& n, float* wt, bool first_has_dx = false) {
-  sg.wt = wt;
-  sg.n_layers = n.n_layers;
-  sg.wt_from = first_has_dx ? 0 : 1;
-  for (int i = 0; i <= n.n_layers; ++i) sg.dims[i] = n.dims[i];
-}
-
-// wt_ready: the transposed weights in jobs[i].wt are current (transpose_weights at the start of the call, kept up
-// to date by the Adam launches since), so no transposition is launched here.
-inline int32_t backward_nets(const BwdJob* jobs, int count, hipStream_t stream, bool skip_last_dx = false,
-                             bool wt_ready = false) {
+inline int32_t backward_nets(const BwdJob* jobs, int count, hipStream_t stream, bool skip_last_dx = false) {
   if (count == 2 && jobs[0].net->n_layers != jobs[1].net->n_layers) {
-    RSLX_TRY(backward_nets(jobs, 1, stream, skip_last_dx, wt_ready));
-    return backward_nets(jobs + 1, 1, stream, skip_last_dx, wt_ready);
+    RSLX_TRY(backward_nets(jobs, 1, stream, skip_last_dx));
+    return backward_nets(jobs + 1, 1, stream, skip_last_dx);
   }
   const int L = jobs[0].net->n_layers;
   const bool dx_in = jobs[0].dx0 != nullptr;     // all jobs of a call agree on this
-  if (!wt_ready) RSLX_TRY(transpose_weights(jobs, count, stream, skip_last_dx));
   GemmBatch pending;
   bool has_pending = false;
   for (int l = L - 1; l >= 0; --l) {
@@ -318,13 +322,14 @@ inline int32_t backward_nets(const BwdJob* jobs, int count, hipStream_t stream, 
       if ((l > 0 || dx_in) && !(skip_last_dx && l == L - 1)) {
         GemmProblem q = blank_problem();
         q.A = dz; q.lda = n.dims[l + 1];
-        q.B = jobs[i].wt + layer_offset(n, l); q.ldb = n.dims[l];
+        q.B = n.params + layer_offset(n, l); q.ldb = n.dims[l + 1];
+        if (jobs[i].pack) { q.Bp = jobs[i].pack->dx(n, l); q.kgroups = WeightPack::padded(n.dims[l + 1]) / 8; }
         q.C = l > 0 ? jobs[i].bufs->dz[l - 1] : jobs[i].dx0; q.ldc = n.dims[l];
         q.aux = l > 0 ? jobs[i].bufs->out[l - 1] : nullptr;      // the network input is not an ELU output
         q.M = jobs[i].rows; q.N = n.dims[l]; q.K = n.dims[l + 1];
         q.alpha = n.elu_alpha;
         q.a_vec = (q.K % 4 == 0 && aligned16(q.A)) ? 1 : 0;
-        q.b_vec = (q.N % 4 == 0 && aligned16(q.B)) ? 1 : 0;
+        q.b_vec = (q.K % 4 == 0 && aligned16(q.B)) ? 1 : 0;
         bx.p[i] = q;
       }
     }
@@ -393,7 +398,7 @@ inline int64_t round4(int64_t n) { return (n + 3) / 4 * 4; }
 struct TrainBufs {        // per trained network
   NetBufs act;
   float* d_out = nullptr;
-  float* wt = nullptr;
+  WeightPack pack;
   float* partials = nullptr;
   SplitPlan plan;
   double* sumsq = nullptr;
@@ -403,7 +408,7 @@ struct TrainBufs {        // per trained network
 inline void carve_train(Carver& c, const rslx_mlp& n, int32_t rows, int group, TrainBufs& t, bool first_has_dx = false) {
   carve_net(c, n, rows, true, t.act);
   t.d_out = c.take<float>((size_t)rows * n.dims[n.n_layers]);
-  t.wt = c.take<float>((size_t)round4(weight_count(n)));
+  t.pack.base = c.take<uint16_t>(WeightPack::offset(n, n.n_layers));
   t.plan = plan_splits(n, rows, group, first_has_dx);
   t.partials = c.take<float>((size_t)t.plan.total);
   t.n_sumsq = t.plan.blocks;

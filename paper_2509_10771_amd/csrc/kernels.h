@@ -25,10 +25,9 @@ struct TraceScope {
 };
 
 // ---------------------------------------------------------------------------------------------
-// Dense fp32 contraction on the matrix cores, three operand arrangements of one kernel:
+// Dense contraction of fp32 operands on the matrix cores, three operand arrangements of one kernel:
 //   GEMM_FWD  C[r, n]   = act( sum_k X(r, k) W[k, n] + bias[n] )          (layer forward)
-//   GEMM_DX   C[r, kin] = ( sum_n dZ[r, n] Wt[n, kin] ) * ELU'(H[r, kin])  (input gradient; Wt = W^T,
-//             transposed once per step by launch_transpose)
+//   GEMM_DX   C[r, kin] = ( sum_n dZ[r, n] W[kin, n] ) * ELU'(H[r, kin])   (input gradient)
 //   GEMM_DW   C_s[kin, n] = sum_{r in split s} X(r, kin) dZ[r, n]          (weight gradient, split
 //             over rows; the block row holding kin = 0 also emits the column sums of dZ = db)
 // X(r, c) is a view of a row-major matrix with an optional row gather and column map:
@@ -40,7 +39,9 @@ enum GemmMode : int { GEMM_FWD = 0, GEMM_DX = 1, GEMM_DW = 2 };
 
 struct GemmProblem {
   const float* A;           // FWD/DW: X storage; DX: dZ
-  const float* B;           // FWD: W [K_in, N_out] row-major; DX: W^T [N_out, K_in] row-major; DW: dZ
+  const float* B;           // FWD, DX: W [K_in, N_out] row-major; DW: dZ
+  const uint16_t* Bp;       // FWD/DX: the same weights split for the matrix cores (launch_pack_weights), or null
+  int32_t kgroups;          // groups of eight contraction indices per part of Bp
   float* C;                 // FWD/DX: output; DW: base of split partial 0
   const float* aux;         // FWD: bias[N] or null; DX: H at C's coordinates (ldc) or null
   const int32_t* row_idx;   // optional row gather for X (device)
@@ -73,10 +74,12 @@ hipError_t launch_gemm(GemmMode mode, const GemmBatch& batch, hipStream_t stream
 // narrow_dw: optional further weight gradient whose operands are ready as well (the output layer's, a few columns
 // wide); it rides in the same launch when it can, else it is launched on its own first.
 hipError_t launch_gemm_dw_dx(const GemmBatch& bw, const GemmBatch& bx, hipStream_t stream, const GemmBatch* narrow_dw = nullptr);
-// Out-of-place transposes of up to 16 row-major matrices in one launch: dst[c, r] = src[r, c].
-struct TransposeJob { const float* src; float* dst; int32_t rows, cols; };
-struct TransposeBatch { TransposeJob job[16]; int32_t count; };
-hipError_t launch_transpose(const TransposeBatch& b, hipStream_t stream);
+// Weights split into three bf16 parts, [part][contraction index / 8][column][8]: of the element (k, c) at
+// src[k * stride_k + c * stride_c], zero for contraction indices K .. 8 * kgroups - 1 (kgroups is even); the last third or
+// so is negated (sign_flip_step in gemm.hip).
+struct PackJob { const float* src; uint16_t* dst; int32_t K, cols, kgroups, stride_k, stride_c; };
+struct PackBatch { PackJob job[32]; int32_t count; };   // two networks of up to eight layers, two copies each
+hipError_t launch_pack_weights(const PackBatch& b, hipStream_t stream);
 // Number of output tiles the weight-gradient kernel uses for an [M, N] layer (big = 128x128 tiles allowed).
 int gemm_dw_tiles(int32_t M, int32_t N, bool big);
 
@@ -165,12 +168,6 @@ hipError_t launch_sumsq(const float* g, int64_t n, double* sumsq_blocks, hipStre
 struct AdamSegment {
   float* params; const float* grads; float* m; float* v;
   int64_t n;
-  // Optional: every updated weight of layers >= wt_from is also written to its place in `wt`, the flat buffer of
-  // transposed weight matrices the input-gradient contraction reads (W_l^T at the layer's parameter offset), so
-  // that no transposition launch is needed before the next optimiser step.  dims: the MLP's layer widths.
-  float* wt;
-  int32_t n_layers, wt_from;
-  int32_t dims[9];
 };
 struct AdamArgs {
   AdamSegment seg[4];
