@@ -1,17 +1,20 @@
 // Layer-fused MLP inference for gfx950: the latency-critical path of act() and of the RND reward, where the
 // batch is a few thousand rows and per-layer launches would cost more than the arithmetic.
 //
-// One workgroup (8 wavefronts, two per SIMD) carries 32 batch rows of one network through every layer.
-// Activations stay in LDS, contraction-major, in two ping-pong buffers; weights are not staged at all but
-// streamed from L2 into the A operand of v_mfma_f32_16x16x4_f32.  A layer is cut into tasks of 64 output columns;
-// when a layer has fewer than 8 such groups the contraction range of a group is split over 2, 4 or 8 wavefronts,
-// so all 8 stay busy down to the narrow output layer.  Lane (m, kq) of a task owns columns col0 + 4 m .. + 3 at
-// contraction index k + kq: one 16-byte load per step of four indices feeds eight matrix-core instructions (four
-// column blocks x two 16-row halves of the batch tile), and the 16 lanes of a row read 256 contiguous bytes.
-// Partial sums meet in LDS; all 512 lanes then add them up in a fixed order, apply bias and ELU and leave the
-// result in the layout the next layer reads.  The last layer is also written to global memory; for the actor
-// the Gaussian head (noise, action, log-density) runs in the same launch, one lane per (row, action component).
+// One workgroup (8 wavefronts, two per SIMD) carries 32 batch rows of one network through every layer.  The products
+// run on the bf16 matrix cores (v_mfma_f32_16x16x32_bf16) with both operands split in three, six products each (see
+// gemm.hip): 96 matrix-core cycles per 32 contraction indices of a 16 x 16 block, where fp32 instructions take 256.
+// Activations stay in LDS, split, 16 bytes holding one part of eight consecutive contraction indices of a row; weights
+// are not staged at all but streamed from L2 as fp32 and split in registers (each is used by one wavefront of a
+// workgroup only).  A layer is cut into tasks of 64 output columns; when a layer has fewer than 8 such groups the
+// contraction range of a group is split over 2, 4 or 8 wavefronts, so all 8 stay busy down to the narrow output layer.
+// Lane (m, kq) of a task owns columns col0 + 4 m .. + 3 at contraction indices 8 kq .. + 7 of a step of 32: eight
+// 16-byte loads per step, of which the 16 lanes of a row read 256 contiguous bytes.  Partial sums meet in LDS; all 512
+// lanes then add them up in a fixed order, apply bias and ELU and leave the split result in place of the layer's
+// input.  The last layer is also written to global memory; for the actor the Gaussian head (noise, action,
+// log-density) runs in the same launch, one lane per (row, action component).
 #include "kernels.h"
+#include "split_bf16.h"
 #include <algorithm>
 #include <type_traits>
 
@@ -23,10 +26,11 @@ constexpr int FF_ROWS = 32;
 constexpr int FF_THREADS = 512;
 constexpr int FF_WAVES = FF_THREADS / 64;
 constexpr int FF_GROUP = 64;                   // output columns per task
-constexpr int FF_STEPS = 8;                    // contraction steps (of four indices) per weight chunk
-constexpr int FF_CHUNK = 4 * FF_STEPS;         // weight values per lane held in flight per register buffer
+constexpr int FF_STEP = 32;                    // contraction indices per step
 constexpr int FF_MAX_DIM = 512;
-constexpr int FF_BUF = FF_MAX_DIM * FF_ROWS;   // floats per LDS buffer: one activation matrix or all partial sums
+constexpr int FF_PART = FF_MAX_DIM * FF_ROWS * 2;   // LDS bytes of one part of an activation matrix
+constexpr int FF_SUMS = FF_WAVES * FF_GROUP * FF_ROWS * 4;   // LDS bytes of all partial sums
+constexpr int FF_LDS = 3 * FF_PART + FF_SUMS;  // 160 KB
 constexpr float FF_LOG_2PI = 1.8378770664093453f;
 
 __device__ __forceinline__ uint64_t ff_mix64(uint64_t x) {
@@ -36,18 +40,47 @@ __device__ __forceinline__ uint64_t ff_mix64(uint64_t x) {
   return x ^ (x >> 31);
 }
 
-// LDS position of activation (k, row): the two 16-row halves are interleaved so that one 8-byte read gives a lane
-// its B operand for both halves, and 64 lanes read or write 512 contiguous bytes.
-__device__ __forceinline__ int ff_at(int k, int row) { return k * FF_ROWS + ((row & 15) << 1) + (row >> 4); }
+// LDS position of output (column c, row) among fp32 sums: the two 16-row halves are interleaved, so that a lane writes
+// its two rows with one 8-byte access and 16 lanes write 128 contiguous bytes.
+__device__ __forceinline__ int ff_at(int c, int row) { return c * FF_ROWS + ((row & 15) << 1) + (row >> 4); }
+// LDS byte offset of part 0 of activations 8 g .. 8 g + 7 of a row.
+__device__ __forceinline__ int ff_unit(int g, int row) { return (g * FF_ROWS + row) * 16; }
 
 // ELU with the hardware exponential: alpha (e^x - 1) for x <= 0.  The absolute error (about 1e-7) is what
 // matters for a value that feeds the next layer's sums; the relative error near zero does not.
 __device__ __forceinline__ float ff_elu(float x, float alpha) { return x > 0.f ? x : alpha * (__expf(x) - 1.0f); }
 
-// Work of one wavefront in one layer: 64 columns from col0 and contraction steps [s_begin, s_end), a step being
-// four contraction indices.  Every part spans a whole number of chunk pairs (16 steps); the last one of a group
-// runs into zero activations (the LDS rows from K up to the next multiple of 64 are kept at zero), so no chunk
-// needs a partial form.
+// Splits eight consecutive activations of a row and writes them to LDS.  The sum of the parts is the value in every case:
+// a finite value that would round to infinity has its first part cut off instead, an infinite one has zero lower parts.
+__device__ __forceinline__ void ff_put(char* acts, int g, int row, const float (&v)[8]) {
+  uint32_t p[3][4];
+  float most = 0.f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    split_pair(v[2 * i], v[2 * i + 1], p[0][i], p[1][i], p[2][i]);
+    most = fmaxf(most, fmaxf(fabsf(v[2 * i]), fabsf(v[2 * i + 1])));
+  }
+  if (most >= __uint_as_float(0x7f7f8000u)) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (!(fabsf(v[i]) >= __uint_as_float(0x7f7f8000u))) continue;
+      const uint32_t hi = __float_as_uint(v[i]) & 0xffff0000u;
+      uint32_t p0 = hi >> 16, p1 = 0, p2 = 0, none;
+      if ((hi & 0x7f800000u) != 0x7f800000u) split_pair(v[i] - __uint_as_float(hi), 0.f, p1, p2, none);
+      const int sh = 16 * (i & 1);
+      const uint32_t keep = 0xffff0000u >> sh;
+      p[0][i / 2] = (p[0][i / 2] & keep) | (p0 << sh);
+      p[1][i / 2] = (p[1][i / 2] & keep) | ((p1 & 0xffffu) << sh);
+      p[2][i / 2] = (p[2][i / 2] & keep) | ((p2 & 0xffffu) << sh);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < 3; ++s)
+    *reinterpret_cast<uint4*>(acts + s * FF_PART + ff_unit(g, row)) = make_uint4(p[s][0], p[s][1], p[s][2], p[s][3]);
+}
+
+// Work of one wavefront in one layer: 64 columns from col0 and contraction steps [s_begin, s_end).  Activations
+// between K and the next multiple of 32 are kept at zero in LDS, so no step needs a partial form.
 struct FfTask {
   int col0, kpart, parts, s_begin, s_end;   // parts: how many wavefronts share a group's contraction
   bool active;
@@ -64,100 +97,134 @@ __device__ __forceinline__ FfTask ff_task(const FusedNet& net, int l, int wave) 
   t.kpart = wave & ((1 << shift) - 1);
   t.col0 = group * FF_GROUP;
   t.parts = net.split_parts[l];
-  const int steps = (K + 3) / 4;
+  const int steps = (K + FF_STEP - 1) / FF_STEP;
   t.s_begin = min(steps, t.kpart * per);
   t.s_end = min(steps, t.s_begin + per);
   t.active = group < ff_groups(N) && t.kpart < t.parts;
   return t;
 }
 
-// Weight stream of a task.  Register 4 s + cb of the chunk at step s0 is W[4 (s0 + s) + kq][col0 + 4 m + cb].
+// Weight stream of a task.  Register 4 i + cb of the chunk of step s is W[32 s + 8 kq + i][col0 + 4 m + cb].
 // Rows and columns are clamped into the matrix: rows past K meet zero activations, columns past N only feed
 // accumulator rows that are dropped later.
+constexpr int FF_CHUNK = 32;
 struct FfWeights {
   const float* W;
-  int ldw, K, N, m, kq;
-  bool vec;             // rows are 16-byte aligned and N % 4 == 0: one 16-byte load per step
+  int ldw, K, m, kq;
+  bool vec;             // rows are 16-byte aligned and N % 4 == 0: one 16-byte load per contraction index
   int col[4];           // clamped columns col0 + 4 m + cb
 
-  __device__ __forceinline__ void setup(const float* W_, int K_, int N_, int col0, int m_, int kq_) {
-    W = W_; ldw = N_; K = K_; N = N_; m = m_; kq = kq_;
-    vec = (N_ & 3) == 0 && (reinterpret_cast<uintptr_t>(W_) & 15) == 0;
+  __device__ __forceinline__ void setup(const float* W_, int K_, int N, int col0, int m_, int kq_) {
+    W = W_; ldw = N; K = K_; m = m_; kq = kq_;
+    vec = (N & 3) == 0 && (reinterpret_cast<uintptr_t>(W_) & 15) == 0;
     const int c = vec ? min(col0 + 4 * m, N - 4) : col0 + 4 * m;
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb) col[cb] = min(c + cb, N - 1);
   }
   template <bool VEC>
-  __device__ __forceinline__ void load(int s0, float (&dst)[FF_CHUNK]) const {
-    if constexpr (VEC) {
+  __device__ __forceinline__ void load(int s, float (&dst)[FF_CHUNK]) const {
 #pragma unroll
-      for (int s = 0; s < FF_STEPS; ++s) {
-        const int row = min(4 * (s0 + s) + kq, K - 1);
-        const float4 v = *reinterpret_cast<const float4*>(W + (long)row * ldw + col[0]);
-        dst[4 * s + 0] = v.x; dst[4 * s + 1] = v.y; dst[4 * s + 2] = v.z; dst[4 * s + 3] = v.w;
-      }
-    } else {
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t row = 4u * (uint32_t)(min(FF_STEP * s + 8 * kq + i, K - 1) * ldw);     // 32-bit lane offset, uniform base
+      const char* base = reinterpret_cast<const char*>(W);
+      if constexpr (VEC) {
+        const float4 v = *reinterpret_cast<const float4*>(base + (row + 4u * (uint32_t)col[0]));
+        dst[4 * i + 0] = v.x; dst[4 * i + 1] = v.y; dst[4 * i + 2] = v.z; dst[4 * i + 3] = v.w;
+      } else {
 #pragma unroll
-      for (int s = 0; s < FF_STEPS; ++s) {
-        const float* wr = W + (long)min(4 * (s0 + s) + kq, K - 1) * ldw;
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb) dst[4 * s + cb] = wr[col[cb]];
+        for (int cb = 0; cb < 4; ++cb) dst[4 * i + cb] = *reinterpret_cast<const float*>(base + (row + 4u * (uint32_t)col[cb]));
       }
     }
   }
 };
 
 // acc[cb][h] += W[:, col0 + 4 m + cb]^T (A operand) x activations of row half h (B operand) over the task's
-// contraction range.  `w0` arrives holding the task's first chunk, fetched by the caller ahead of time.  Two
-// register buffers alternate without copies so that the loads of chunk c + 1 stay in flight under the matrix-core
-// instructions of chunk c.
+// contraction range.  `w0` arrives holding the task's first chunk, fetched by the caller ahead of time.  A step has two
+// halves of 24 matrix instructions, two column blocks each; under each the other pair of column blocks is split, so the
+// splitting (88 vector instructions per half) hides behind the matrix cores.  The chunk after next is requested as
+// soon as a step's weights have been split.
 template <bool VEC>
-__device__ __forceinline__ void ff_contract(const FfWeights& wt, const FfTask& task, const float* actIn,
+__device__ __forceinline__ void ff_contract(const FfWeights& wt, const FfTask& task, const char* acts,
                                             float (&w0)[FF_CHUNK], f32x4 (&acc)[4][2]) {
   float w1[FF_CHUNK];
-  const float* bp = actIn + (task.s_begin * 4 + wt.kq) * FF_ROWS + 2 * wt.m;
-  const int nch = (task.s_end - task.s_begin + FF_STEPS - 1) / FF_STEPS;
-  auto read_b = [&](int c, int s) { return *reinterpret_cast<const float2*>(bp + (c * FF_STEPS + s) * 4 * FF_ROWS); };
-  // One chunk: its matrix-core instructions with, dealt out between them, the loads of the following chunk into
-  // the other register buffer and the LDS reads of the activations two steps ahead; the first two steps' activations
-  // arrive in `bh`, read under the previous chunk (the last chunk reads its own again).
-  float2 bh[2] = {read_b(0, 0), read_b(0, 1)};
-  auto chunk = [&](int c, int s_next, const float (&src)[FF_CHUNK], float (&dst)[FF_CHUNK]) {
-    wt.load<VEC>(s_next, dst);
-    float2 b[FF_STEPS + 2];
-    b[0] = bh[0]; b[1] = bh[1];
-    const int cn = min(c + 1, ((nch + 1) & ~1) - 1);   // chunks come in pairs; an odd count's twin meets zero activations
+  const char* bp = acts + ff_unit(wt.kq, wt.m);
+  bf16x8 b[3][2];
+  auto read_b = [&](int s) {
 #pragma unroll
-    for (int s = 2; s < FF_STEPS + 2; ++s) b[s] = s < FF_STEPS ? read_b(c, s) : read_b(cn, s - FF_STEPS);
+    for (int p = 0; p < 3; ++p)
 #pragma unroll
-    for (int s = 0; s < FF_STEPS; ++s)
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb) {
-        acc[cb][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(src[4 * s + cb], b[s].x, acc[cb][0], 0, 0, 0);
-        acc[cb][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(src[4 * s + cb], b[s].y, acc[cb][1], 0, 0, 0);
-      }
-    bh[0] = b[FF_STEPS]; bh[1] = b[FF_STEPS + 1];
-    // masks: 0x008 matrix core, 0x100 LDS read, 0x020 global load.  Per pair of steps (16 matrix-core instructions):
-    // the LDS read of the pair after next, then two groups of loads (one 16-byte load, or four 4-byte loads, per step)
-#pragma unroll
-    for (int pr = 0; pr < FF_STEPS / 2; ++pr) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-      __builtin_amdgcn_sched_group_barrier(0x020, VEC ? 1 : 4, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 6, 0);
-      __builtin_amdgcn_sched_group_barrier(0x020, VEC ? 1 : 4, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
+      for (int h = 0; h < 2; ++h)
+        b[p][h] = *reinterpret_cast<const bf16x8*>(bp + p * FF_PART + s * (FF_STEP / 8 * FF_ROWS * 16) + h * 256);
   };
-  // A task spans an even number of chunks (see the split plan), and the fetch of the following chunk is issued
-  // without a test (rows are clamped: a chunk past the range reads valid memory and is not used).  The loop body
-  // is therefore free of branches, and the compiler's count of the loads in flight is exact: the matrix-core
-  // instructions of one buffer wait for that buffer's loads only, not for the ones just issued into the other.
-  for (int c = 0; c < nch; c += 2) {
-    chunk(c, task.s_begin + (c + 1) * FF_STEPS, w0, w1);
-    chunk(c + 1, task.s_begin + (c + 2) * FF_STEPS, w1, w0);
+  struct Pair { uint4 part[2][3]; };       // two column blocks, three parts
+  auto split = [&](const float (&w)[FF_CHUNK], int cb0, Pair& a) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int cb = cb0 + c;
+      split_pair(w[cb], w[4 + cb], a.part[c][0].x, a.part[c][1].x, a.part[c][2].x);
+      split_pair(w[8 + cb], w[12 + cb], a.part[c][0].y, a.part[c][1].y, a.part[c][2].y);
+      split_pair(w[16 + cb], w[20 + cb], a.part[c][0].z, a.part[c][1].z, a.part[c][2].z);
+      split_pair(w[24 + cb], w[28 + cb], a.part[c][0].w, a.part[c][1].w, a.part[c][2].w);
+    }
+  };
+  auto multiply = [&](const Pair& a, int cb0) {
+    constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          acc[cb0 + c][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.part[c][PA[q]]), b[PB[q]][h],
+                                                                    acc[cb0 + c][h], 0, 0, 0);
+  };
+  Pair lo, hi;
+  const int last = task.s_end - 1;
+  wt.load<VEC>(task.s_begin + 1, w1);
+  split(w0, 0, lo);
+  auto step = [&](int s, float (&w)[FF_CHUNK], float (&wn)[FF_CHUNK]) {
+    read_b(s);
+    split(w, 2, hi);
+    multiply(lo, 0);
+    wt.load<VEC>(s + 2, w);                // clamped: past the range it reads valid weights that nobody uses
+    split(wn, 0, lo);
+    multiply(hi, 2);
+  };
+  for (int s = task.s_begin;; s += 2) {
+    step(s, w0, w1);
+    if (s + 1 > last) break;
+    step(s + 1, w1, w0);
+    if (s + 2 > last) break;
+  }
+}
+
+// The same sums in plain fp32 arithmetic, for tasks that met a non-finite one (see gemm.hip): infinite inputs have no
+// split.  Each lane forms its 16 columns x 2 rows from the fp32 weights and the sum of the activations' parts.
+__device__ __forceinline__ void ff_contract_plain(const float* W, int K, int N, const FfTask& task, const char* acts, int m, int kq,
+                                                  f32x4 (&acc)[4][2]) {
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) acc[cb][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int k_end = min(K, task.s_end * FF_STEP);
+#pragma unroll 1
+  for (int k = task.s_begin * FF_STEP; k < k_end; ++k) {
+    float x[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const char* u = acts + ff_unit(k >> 3, m + 16 * h) + 2 * (k & 7);
+      x[h] = 0.f;
+#pragma unroll
+      for (int p = 2; p >= 0; --p) x[h] += __uint_as_float((uint32_t)*reinterpret_cast<const uint16_t*>(u + p * FF_PART) << 16);
+    }
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float w = W[(long)k * N + min(task.col0 + 16 * kq + 4 * r + cb, N - 1)];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) acc[cb][h][r] = fmaf(w, x[h], acc[cb][h][r]);
+      }
   }
 }
 
@@ -172,7 +239,7 @@ __device__ __forceinline__ void ff_first_chunk(const float* __restrict__ W, int 
 }
 
 __global__ __launch_bounds__(FF_THREADS) void fused_forward_kernel(const FusedForwardArgs args) {
-  extern __shared__ float lds[];
+  extern __shared__ __align__(16) char lds[];
   const FusedNet& net = args.net[blockIdx.y];
   const int row0 = blockIdx.x * FF_ROWS;
   if (row0 >= args.n_rows) return;
@@ -180,9 +247,9 @@ __global__ __launch_bounds__(FF_THREADS) void fused_forward_kernel(const FusedFo
   // the wavefront index decides which columns and contraction range a wavefront works on: held in a scalar
   // register, every test on it is a scalar branch
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int m = lane & 15, kq = lane >> 4;
-  float* bufA = lds;
-  float* bufB = lds + FF_BUF;
+  int m = lane & 15, kq = lane >> 4;
+  char* acts = lds;                                          // [3 parts][K / 8][32 rows][8]
+  float* sums = reinterpret_cast<float*>(lds + 3 * FF_PART);  // [part][column][32 rows], see ff_at
 
   // The first weight chunk of the first layer and the head's per-component inputs do not depend on any
   // activation: they are requested before the input rows, so their latency passes under the staging.
@@ -199,169 +266,186 @@ __global__ __launch_bounds__(FF_THREADS) void fused_forward_kernel(const FusedFo
     if (!args.deterministic && args.eps != nullptr && n < args.n_rows) head_eps = args.eps[n * A + (tid >> 5)];
   }
 
-  // ---- input rows -> LDS; rows from K0 to the next multiple of 64 are zero ----
+  // Lane (row, g) finishes units of eight values: row tid % 32, units g = tid / 32 + 16 i.
+  int urow = tid & 31, ug = tid >> 5;
+  // ---- input rows -> LDS; values from K0 to the next multiple of 32 are zero ----
   {
     const int K0 = net.dims[0];
-    const int Kp = (K0 + 63) & ~63;
-    if (net.col_map == nullptr && (net.ldx & 3) == 0 && (K0 & 3) == 0 && (reinterpret_cast<uintptr_t>(net.x) & 15) == 0) {
-      // 16-byte loads, lanes along a row; every load is issued before the first one is used
-      const int q4 = K0 >> 2;                           // float4 per row
-      constexpr int PASS = FF_MAX_DIM * FF_ROWS / 4 / FF_THREADS;
-      float4 v[PASS];
+    const int units = (K0 + FF_STEP - 1) / FF_STEP * (FF_STEP / 8);
+    const bool vec = net.col_map == nullptr && (net.ldx & 3) == 0 && (K0 & 3) == 0 && (reinterpret_cast<uintptr_t>(net.x) & 15) == 0;
+    const int row = row0 + urow;
+    const float* xr = net.x + (long)min(row, args.n_rows - 1) * net.ldx;
 #pragma unroll
-      for (int i = 0; i < PASS; ++i) {
-        const int e = tid + FF_THREADS * i;
-        if (FF_THREADS * i >= FF_ROWS * q4) break;
-        const int r = e / q4, c4 = e - r * q4;
-        v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (e < FF_ROWS * q4 && row0 + r < args.n_rows)
-          v[i] = *reinterpret_cast<const float4*>(net.x + (long)(row0 + r) * net.ldx + 4 * c4);
-      }
+    for (int i = 0; i < FF_MAX_DIM / 8 / 16; ++i) {
+      const int g = ug + 16 * i;
+      if (16 * i >= units) break;
+      if (g >= units) continue;
+      float v[8];
+      if (vec) {
 #pragma unroll
-      for (int i = 0; i < PASS; ++i) {
-        const int e = tid + FF_THREADS * i;
-        if (FF_THREADS * i >= FF_ROWS * q4) break;
-        if (e < FF_ROWS * q4) {
-          const int r = e / q4, c4 = e - r * q4;
-          bufA[ff_at(4 * c4 + 0, r)] = v[i].x; bufA[ff_at(4 * c4 + 1, r)] = v[i].y;
-          bufA[ff_at(4 * c4 + 2, r)] = v[i].z; bufA[ff_at(4 * c4 + 3, r)] = v[i].w;
+        for (int c = 0; c < 8; c += 4) {
+          float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (8 * g + c < K0) q = *reinterpret_cast<const float4*>(xr + 8 * g + c);
+          v[c] = q.x; v[c + 1] = q.y; v[c + 2] = q.z; v[c + 3] = q.w;
+        }
+      } else {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          const int k = 8 * g + c;
+          v[c] = k < K0 ? xr[net.col_map ? net.col_map[k] : k] : 0.f;
         }
       }
-      for (int e = tid; e < (Kp - K0) * FF_ROWS; e += FF_THREADS) bufA[K0 * FF_ROWS + e] = 0.f;
-    } else {
-      const int r = tid & 31;
-      const int row = row0 + r;
-      for (int k = tid >> 5; k < Kp; k += FF_THREADS / 32) {
-        float v = 0.f;
-        if (row < args.n_rows && k < K0) {
-          const int c = net.col_map ? net.col_map[k] : k;
-          v = net.x[(long)row * net.ldx + c];
-        }
-        bufA[ff_at(k, r)] = v;
+      if (row >= args.n_rows) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) v[c] = 0.f;
       }
+      ff_put(acts, g, urow, v);
     }
   }
   __syncthreads();
 
-  float* in = bufA;
-  float* out = bufB;
+  const float* mu = sums;        // the last layer's outputs, see ff_at
   long woff = 0;
+  int K = net.dims[0], N = net.dims[1];
   for (int l = 0; l < net.n_layers; ++l) {
-    const int K = net.dims[l], N = net.dims[l + 1];
+    // opaque from here on, or every address formed from them below would be computed once, kept for all layers and spilled
+    asm volatile("" : "+v"(m), "+v"(kq), "+v"(urow), "+v"(ug));
     const float* W = net.params + woff;
     const float* bias = W + (long)K * N;
     const bool last = (l + 1 == net.n_layers);
     float* gout = last ? net.out : nullptr;
     const int plane = ff_groups(N) * FF_GROUP * FF_ROWS;     // floats between the partial sums of two parts
+    const int units = (N + FF_STEP - 1) / FF_STEP * (FF_STEP / 8);
 
-    // bias values of the outputs this lane finishes, requested ahead of the contraction: with the contraction of
-    // a group shared among wavefronts, the sums are finished by all lanes after an exchange through LDS (lane ->
-    // outputs tid + 512 i); otherwise each wavefront finishes its own accumulators in registers
     const bool shared = task.parts > 1;
-    constexpr int FIN = FF_MAX_DIM * (FF_ROWS / 2) / FF_THREADS;   // outputs (column, row pair) per lane at most
-    float bfin[FIN];
-    if (shared) {
-#pragma unroll
-      for (int i = 0; i < FIN; ++i) {
-        if (FF_THREADS * i >= N * 16) break;
-        const int e = tid + FF_THREADS * i;
-        bfin[i] = bias[min(e >> 4, N - 1)];
-      }
-    } else if (task.active) {
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) bfin[4 * cb + r] = bias[min(task.col0 + 16 * kq + 4 * r + cb, N - 1)];
-    }
     const FfTask next = last ? task : ff_task(net, l + 1, wave);
+    const int N2 = last ? 0 : net.dims[l + 2];       // read ahead like `next`: nothing waits for it between the layers
+    f32x4 acc[4][2];
     if (task.active) {
-      f32x4 acc[4][2];
 #pragma unroll
       for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
         for (int h = 0; h < 2; ++h) acc[cb][h] = f32x4{0.f, 0.f, 0.f, 0.f};
       FfWeights wt;
       wt.setup(W, K, N, task.col0, m, kq);
-      if (wt.vec) ff_contract<true>(wt, task, in, wpre, acc);
-      else ff_contract<false>(wt, task, in, wpre, acc);
-      // the next layer's first chunk is requested before this layer's sums are exchanged
-      if (!last) ff_first_chunk(bias + N, N, net.dims[l + 2], next, m, kq, wpre);
-      // accumulator register r of block cb: column col0 + 16 kq + 4 r + cb, batch rows m (half 0) and 16 + m
-      float* part = out + task.kpart * plane;
+      if (wt.vec) ff_contract<true>(wt, task, acts, wpre, acc);
+      else ff_contract<false>(wt, task, acts, wpre, acc);
+      float z = 0.f;                 // becomes NaN with any non-finite sum
 #pragma unroll
       for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int c = task.col0 + 16 * kq + 4 * r + cb;
-          float2 v = make_float2(acc[cb][0][r], acc[cb][1][r]);
-          if (!shared) {
-            v.x += bfin[4 * cb + r]; v.y += bfin[4 * cb + r];
-            if (!last) {
-              v.x = ff_elu(v.x, net.alpha);
-              v.y = ff_elu(v.y, net.alpha);
-            }
-            if (gout != nullptr && c < N) {
-              if (row0 + m < args.n_rows) gout[(long)(row0 + m) * N + c] = v.x;
-              if (row0 + 16 + m < args.n_rows) gout[(long)(row0 + 16 + m) * N + c] = v.y;
-            }
-          }
-          *reinterpret_cast<float2*>(part + c * FF_ROWS + 2 * m) = v;
-        }
-    } else if (!last) {
-      ff_first_chunk(bias + N, N, net.dims[l + 2], next, m, kq, wpre);
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) z = fmaf(acc[cb][h][r], 0.f, z);
+      if (__any(!(z == 0.f))) ff_contract_plain(W, K, N, task, acts, m, kq, acc);
     }
-    __syncthreads();
-
-    // ---- all lanes: sum the parts in order, bias, activation; result in place of part 0 ----
-    // (reads first, then arithmetic, then writes: the LDS latency is paid once, not per output)
-    const int parts = task.parts;
+    // bias values of the outputs this lane finishes, requested before the sums are exchanged: with the contraction of
+    // a group shared among wavefronts, the sums are finished by all lanes after an exchange through LDS; otherwise
+    // each wavefront finishes its own accumulators in registers
+    constexpr int FIN = 2;         // units per lane at most: shared layers have at most four groups of 64 columns
+    float bfin[8 * FIN];
     if (shared) {
-      float2 fv[FIN];
 #pragma unroll
       for (int i = 0; i < FIN; ++i) {
-        if (FF_THREADS * i >= N * 16) break;
-        const int e = min(tid + FF_THREADS * i, N * 16 - 1);
-        const float* p0 = out + (e >> 4) * FF_ROWS + 2 * (e & 15);
-        float2 v = *reinterpret_cast<const float2*>(p0);
-        for (int p = 1; p < parts; ++p) {
-          const float2 u = *reinterpret_cast<const float2*>(p0 + p * plane);
-          v.x += u.x; v.y += u.y;
-        }
-        fv[i] = v;
-      }
+        if (16 * i >= units) break;
 #pragma unroll
-      for (int i = 0; i < FIN; ++i) {
-        if (FF_THREADS * i >= N * 16) break;
-        const int e = tid + FF_THREADS * i;
-        if (e < N * 16) {
-          const int c = e >> 4, mp = e & 15;
-          float2 v = fv[i];
-          v.x += bfin[i]; v.y += bfin[i];
-          if (!last) {
-            v.x = ff_elu(v.x, net.alpha);
-            v.y = ff_elu(v.y, net.alpha);
-          }
-          *reinterpret_cast<float2*>(out + c * FF_ROWS + 2 * mp) = v;
-          if (gout != nullptr) {
-            if (row0 + mp < args.n_rows) gout[(long)(row0 + mp) * N + c] = v.x;
-            if (row0 + 16 + mp < args.n_rows) gout[(long)(row0 + 16 + mp) * N + c] = v.y;
-          }
-        }
+        for (int c = 0; c < 8; ++c) bfin[8 * i + c] = bias[min(8 * (ug + 16 * i) + c, N - 1)];
       }
+    } else if (task.active) {
+#pragma unroll
+      for (int c = 0; c < 16; ++c) bfin[c] = bias[min(task.col0 + 16 * kq + c, N - 1)];
     }
-    // rows from N to the next multiple of 64 are the zero padding the next layer's last chunks run into
-    for (int e = tid; e < (((N + 63) & ~63) - N) * 16; e += FF_THREADS)
-      *reinterpret_cast<float2*>(out + (N + (e >> 4)) * FF_ROWS + 2 * (e & 15)) = make_float2(0.f, 0.f);
+    // the next layer's first chunk is requested before this layer's sums are exchanged as well
+    if (!last) ff_first_chunk(bias + N, N, N2, next, m, kq, wpre);
+    // accumulator register r of block cb: column col0 + 16 kq + 4 r + cb, batch rows m (half 0) and 16 + m
+    if (shared && task.active) {
+      float* part = sums + task.kpart * plane;
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          *reinterpret_cast<float2*>(part + ff_at(task.col0 + 16 * kq + 4 * r + cb, m)) = make_float2(acc[cb][0][r], acc[cb][1][r]);
+    }
+    __syncthreads();                 // every wavefront has read its activations; the partial sums are there
+
+    if (!shared) {
+      if (task.active) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          float v[16];
+#pragma unroll
+          for (int c = 0; c < 16; ++c) {
+            v[c] = acc[c & 3][h][c >> 2] + bfin[c];
+            if (!last) v[c] = ff_elu(v[c], net.alpha);
+          }
+          const int c0 = task.col0 + 16 * kq;
+          if (last) {
+            const int row = row0 + m + 16 * h;
+#pragma unroll
+            for (int c = 0; c < 16; ++c) {
+              sums[ff_at(c0 + c, m + 16 * h)] = v[c];
+              if (c0 + c < N && row < args.n_rows) gout[(long)row * N + c0 + c] = v[c];
+            }
+          } else {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              float x[8];
+#pragma unroll
+              for (int c = 0; c < 8; ++c) x[c] = c0 + 8 * u + c < N ? v[8 * u + c] : 0.f;
+              ff_put(acts, (c0 >> 3) + u, m + 16 * h, x);
+            }
+          }
+        }
+      }
+    } else {
+      // all lanes: sum the parts in order, bias, activation
+      float* muw = reinterpret_cast<float*>(acts);
+      float fv[FIN][8];
+#pragma unroll
+      for (int i = 0; i < FIN; ++i) {
+        if (16 * i >= units) break;
+        const float* p0 = sums + ff_at(8 * min(ug + 16 * i, units - 1), urow);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) fv[i][c] = p0[c * FF_ROWS];
+        for (int p = 1; p < task.parts; ++p)
+#pragma unroll
+          for (int c = 0; c < 8; ++c) fv[i][c] += p0[p * plane + c * FF_ROWS];
+      }
+#pragma unroll
+      for (int i = 0; i < FIN; ++i) {
+        const int g = ug + 16 * i;
+        if (16 * i >= units) break;
+        if (g >= units) continue;
+        float v[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          v[c] = fv[i][c] + bfin[8 * i + c];
+          if (!last) v[c] = ff_elu(v[c], net.alpha);
+          if (8 * g + c >= N) v[c] = 0.f;
+        }
+        if (last) {
+          const int row = row0 + urow;
+#pragma unroll
+          for (int c = 0; c < 8; ++c) {
+            muw[ff_at(8 * g + c, urow)] = v[c];
+            if (8 * g + c < N && row < args.n_rows) gout[(long)row * N + 8 * g + c] = v[c];
+          }
+        } else {
+          ff_put(acts, g, urow, v);
+        }
+      }
+      if (last) mu = muw;
+    }
     __syncthreads();
     task = next;
-    float* tmp = in; in = out; out = tmp;
     woff += (long)K * N + N;
+    K = N; N = N2;
   }
 
-  // ---- Gaussian head (actor only): `in` now holds mu; one lane per (row, action component) ----
+  // ---- Gaussian head (actor only): `mu` holds the means; one lane per (row, action component) ----
   if (net.head) {
     const float* log_std = net.params + woff;
-    float* z2 = out;                       // [A][32]; the other activation buffer is free by now
+    float* z2 = mu == sums ? reinterpret_cast<float*>(acts) : sums;   // [A][32], in the buffer that is free by now
     float* lsb = z2 + FF_ROWS * A;         // [A] log_std, for the per-row sums
     for (int e = tid; e < FF_ROWS * A; e += FF_THREADS) {
       const int r = e & 31, jj = e >> 5;
@@ -372,7 +456,7 @@ __global__ __launch_bounds__(FF_THREADS) void fused_forward_kernel(const FusedFo
       if (n < args.n_rows) {
         const long o = n * A + jj;
         const float sg = expf(ls);
-        const float mu = in[ff_at(jj, r)];
+        const float mean = mu[ff_at(jj, r)];
         float eps;
         if (args.deterministic) {
           eps = 0.f;
@@ -385,8 +469,8 @@ __global__ __launch_bounds__(FF_THREADS) void fused_forward_kernel(const FusedFo
           const float u2 = (float)((uint32_t)(h >> 8) & 0xFFFFFFu) * 5.9604644775390625e-08f;
           eps = sqrtf(-2.0f * logf(u1)) * cospif(2.0f * u2);
         }
-        const float act = mu + sg * eps;
-        const float z = (act - mu) / sg;
+        const float act = mean + sg * eps;
+        const float z = (act - mean) / sg;
         zz = z * z;
         args.actions[o] = act;
         args.sigma[o] = sg;
@@ -412,11 +496,10 @@ bool fused_forward_supported(const FusedForwardArgs& a) {
 
 hipError_t launch_fused_forward(const FusedForwardArgs& a, hipStream_t stream) {
   if (a.n_rows <= 0) return hipSuccess;
-  const size_t lds_bytes = (size_t)2 * FF_BUF * sizeof(float);
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_forward_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 2 * FF_BUF * (int)sizeof(float));
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, FF_LDS);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
@@ -429,14 +512,14 @@ hipError_t launch_fused_forward(const FusedForwardArgs& a, hipStream_t stream) {
     for (int l = 0; l < b.net[i].n_layers; ++l) {
       const int g = ff_groups(b.net[i].dims[l + 1]);
       const int shift = g > FF_WAVES / 2 ? 0 : g > FF_WAVES / 4 ? 1 : g > FF_WAVES / 8 ? 2 : 3;
-      const int steps = (b.net[i].dims[l] + 3) / 4;
-      const int per = (((steps + (1 << shift) - 1) >> shift) + 2 * FF_STEPS - 1) / (2 * FF_STEPS) * (2 * FF_STEPS);
+      const int steps = (b.net[i].dims[l] + FF_STEP - 1) / FF_STEP;
+      const int per = (steps + (1 << shift) - 1) >> shift;
       b.net[i].split_shift[l] = shift;
       b.net[i].split_steps[l] = per;
       b.net[i].split_parts[l] = std::max(1, (steps + per - 1) / per);
     }
   dim3 grid((b.n_rows + FF_ROWS - 1) / FF_ROWS, b.n_nets);
-  hipLaunchKernelGGL(fused_forward_kernel, grid, dim3(FF_THREADS), lds_bytes, stream, b);
+  hipLaunchKernelGGL(fused_forward_kernel, grid, dim3(FF_THREADS), FF_LDS, stream, b);
   return hipGetLastError();
 }
 

@@ -1,0 +1,110 @@
+"""The contractions run on the bf16 matrix cores on operands split in three parts: the results must keep fp32 accuracy
+over the whole exponent range, at every remainder of the tiles, and infinite inputs must give what fp32 arithmetic
+gives.  More than 8192 rows take the tiled per-layer launches, fewer the layer-fused one."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+LAYERED, FUSED = 8193, 70
+
+
+@pytest.fixture(scope="module")
+def rx():
+    import paper_2509_10771_amd as m
+    m.rslx_device_check()
+    return m
+
+
+def _critic(rx, dims, seed):
+    g = np.random.default_rng(seed)
+    flat = np.concatenate([np.concatenate([(g.normal(size=a * b) / np.sqrt(a)), 0.1 * g.normal(size=b)]) for a, b in zip(dims, dims[1:])])
+    flat = flat.astype(np.float32)
+    return rx.Mlp(dims, torch.from_numpy(flat).cuda()), flat
+
+
+def _values(rx, net, obs, N):
+    out = torch.empty(N, device="cuda")
+    ws = rx.workspace(rx.rslx_act_workspace_bytes(None, net, N))
+    rx.rslx_act(None, net, None, torch.from_numpy(obs).cuda(), N, 0, 0, None, None, None, out, None, None, rx.ACT_VALUES_ONLY, ws)
+    torch.cuda.synchronize()
+    return out.cpu().numpy()
+
+
+@pytest.mark.parametrize("N", [FUSED, LAYERED])
+@pytest.mark.parametrize("D", [1, 4, 31, 32, 33, 100, 512])
+def test_linear_layer_keeps_fp32_accuracy_over_the_exponent_range(rx, D, N):
+    """One linear layer on rows scaled by powers of ten from 1e-30 to 1e30.  Bound: D + 1 roundings of fp32 (2^-24 each)
+    and the 2^-25 of the products left out, against the sum of the terms' sizes; a sum of bf16 products would be off by
+    2^-9 of it."""
+    net, flat = _critic(rx, (D, 1), 3)
+    g = np.random.default_rng(D)
+    obs = (g.normal(size=(N, D)) * 10.0 ** g.integers(-30, 31, size=(N, 1))).astype(np.float32)
+    got = _values(rx, net, obs, N)
+    w, b = flat[:D].astype(np.float64), float(flat[D])
+    ref = obs.astype(np.float64) @ w + b
+    size = np.abs(obs.astype(np.float64)) @ np.abs(w) + abs(b)
+    assert np.all(np.abs(got - ref) <= (D + 3) * 2.0 ** -24 * size)
+
+
+@pytest.mark.parametrize("N", [FUSED, LAYERED])
+@pytest.mark.parametrize("dims", [(13, 20, 1), (48, 128, 72, 1), (37, 100, 300, 12, 1), (64, 512, 512, 1), (5, 3, 2, 1)])
+def test_networks_of_ragged_widths(rx, dims, N):
+    """fp32 accuracy through several layers: each adds at most a few 1e-7 (sums of up to 512 terms, ELU)."""
+    from oracle import mlp
+    net, flat = _critic(rx, dims, 5)
+    obs = np.random.default_rng(N).normal(size=(N, dims[0])).astype(np.float32)
+    ref, _ = mlp.forward(mlp.unpack(flat, dims), obs)
+    got = _values(rx, net, obs, N)
+    assert np.linalg.norm(got - ref[:, 0]) <= 2e-6 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("N", [FUSED, LAYERED])
+def test_infinite_and_nan_inputs_give_what_fp32_gives(rx, N):
+    D = 40
+    net, flat = _critic(rx, (D, 1), 7)
+    obs = np.random.default_rng(1).normal(size=(N, D)).astype(np.float32)
+    big = np.float32(3.4e38)                       # finite, but rounds to infinity in bf16
+    obs[3, 5], obs[20, 0], obs[33, 7], obs[69, 39], obs[40, 1] = np.inf, -np.inf, np.nan, big, np.inf
+    obs[40, 2] = -np.inf * np.sign(flat[1] * flat[2])       # meets the other infinity with the opposite sign
+    got = _values(rx, net, obs, N)
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = (obs * flat[:D]).astype(np.float64).sum(1) + float(flat[D])
+    assert np.isnan(ref[33]) and np.isnan(ref[40]) and np.isinf(ref[3]) and np.isinf(ref[20]) and np.isfinite(ref[69])
+    np.testing.assert_allclose(got, ref, rtol=2e-5, atol=1e-5)      # also compares NaN and infinity places
+
+
+@pytest.mark.parametrize("cell", ["gru", "lstm"])
+def test_infinite_observation_saturates_the_gates(rx, cell):
+    """The input-side gates of an infinite observation are infinite, the new state is finite."""
+    N, D, H = 100, 48, 64
+    G = 4 if cell == "lstm" else 3
+    g = np.random.default_rng(2)
+    flat = g.uniform(-0.1, 0.1, size=G * H * (D + H + 2)).astype(np.float32)
+    mem = rx.Memory(rx.CELL_LSTM if cell == "lstm" else rx.CELL_GRU, D, H, torch.from_numpy(flat).cuda())
+    obs = g.normal(size=(N, D)).astype(np.float32)
+    obs[7, 3], obs[64, 0] = np.inf, -np.inf
+    S = 2 * H if cell == "lstm" else H
+    h0 = (0.5 * g.normal(size=(N, S))).astype(np.float32)
+    h = torch.from_numpy(h0).cuda()
+    ws = rx.workspace(rx.rslx_memory_step_workspace_bytes(mem, N))
+    rx.rslx_memory_step(mem, torch.from_numpy(obs).cuda(), N, h, None, None, None, ws)
+    torch.cuda.synchronize()
+    w_ih, o = flat[:D * G * H].reshape(D, G * H).astype(np.float64), (D + 1) * G * H
+    gi = np.empty((N, G * H))
+    with np.errstate(invalid="ignore"):
+        for r in range(N):
+            gi[r] = (obs[r].astype(np.float64)[:, None] * w_ih).sum(0)
+    gi += flat[D * G * H:o]
+    gh = h0[:, :H].astype(np.float64) @ flat[o:o + H * G * H].reshape(H, G * H) + flat[o + H * G * H:]
+    sig = lambda a: np.where(a > 0, 1 / (1 + np.exp(-np.abs(a))), np.exp(-np.abs(a)) / (1 + np.exp(-np.abs(a))))
+    if cell == "gru":
+        r, z = sig(gi[:, :H] + gh[:, :H]), sig(gi[:, H:2 * H] + gh[:, H:2 * H])
+        ref = (1 - z) * np.tanh(gi[:, 2 * H:] + r * gh[:, 2 * H:]) + z * h0
+    else:
+        a = gi + gh
+        c = sig(a[:, H:2 * H]) * h0[:, H:] + sig(a[:, :H]) * np.tanh(a[:, 2 * H:3 * H])
+        ref = np.concatenate([sig(a[:, 3 * H:]) * np.tanh(c), c], 1)
+    got = h.cpu().numpy()
+    assert np.isfinite(ref).all() and np.isfinite(got).all()
+    assert np.abs(got - ref).max() < 1e-5
