@@ -48,9 +48,9 @@ __device__ __forceinline__ int src_row(const GemmProblem& P, int r) {
 // whole minibatches are such sums: the offset has the same sign in every row and on every optimiser step.  So a part of
 // every contraction is summed with its sign reversed, and the offsets cancel: the weight gradient negates its terms in
 // every other split; weights that are split once per optimiser step are stored negated from step sign_flip_step on, and
-// the accumulators change sign there, at six tenths of the way: the offset follows the size of the sum, for random signs
+// the accumulators change sign there, two thirds of the way: the offset follows the size of the sum, for random signs
 // the root of the index reached, and has done about half of its work by then (the mean over a minibatch falls to a tenth).
-__host__ __device__ __forceinline__ int sign_flip_step(int steps) { return steps < 2 ? steps : (steps * 59 + 50) / 100; }
+__host__ __device__ __forceinline__ int sign_flip_step(int steps) { return steps < 2 ? steps : (steps * 66 + 50) / 100; }
 
 // LDS image of one operand tile of R rows: plane (part s, k-group kg) at (2 s + kg) * pitch, 16 bytes per row.  The 64
 // bytes between planes put the two k-groups of a row in different banks when they are written together.
@@ -409,7 +409,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
       constexpr bool G2 = decltype(g2_tag)::value;
       const int par = t & 1;
       constexpr int S = (G2 ? 6 : 3) * TT;
-      constexpr int PA[6] = {1, 0, 0, 1, 2, 0}, PB[6] = {0, 1, 0, 1, 0, 2};   // the parts that meet: step t - 1, then step t
+      constexpr int PA[6] = {0, 1, 0, 1, 0, 2}, PB[6] = {1, 0, 0, 1, 2, 0};   // the parts that meet: step t - 1, then step t
       const char* ab = As + par * ABYTES + g * plane_pitch<BM>() + (wm * (TM * 32) + j) * 16;
       const char* bb = Bs + par * BBYTES + g * plane_pitch<BN>() + (wn * (TN * 32) + j) * 16;
       auto read_a = [&](int s) {
@@ -475,7 +475,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
     for (int t = 1; t < nk; ++t) body(t, std::true_type{});
 #pragma unroll
     for (int i = 0; i < 3 * TT; ++i) {
-      constexpr int PA[3] = {1, 0, 0}, PB[3] = {0, 1, 0};
+      constexpr int PA[3] = {0, 1, 0}, PB[3] = {1, 0, 0};
       const int q = i / TT, x = i % TT / TN, y = i % TN;
       acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[q]][x], b[PB[q]][y], acc[x][y], 0, 0, 0);
     }
