@@ -191,23 +191,23 @@ struct Direct {
 };
 
 // ---- weights that were split once for the optimiser step (launch_pack_weights) -------------------------------
-// Memory holds the LDS image already: 16 bytes are one part of eight consecutive contraction indices of one column, the
-// contraction padded with zeros to whole steps.  Loads and LDS writes only.
+// Memory holds the LDS image already, step by step: 16 bytes are one part of eight consecutive contraction indices of one
+// column, the contraction padded with zeros to whole steps.  Loads and LDS writes only.  A step's six planes lie together,
+// so that a lane's place in them fits 32 bits (96 bytes per column) whatever the length of the contraction.
 template <int Cw>
 struct Packed {
   static constexpr int UNITS = 6 * Cw;                      // 16-byte units of a step
   static constexpr int NP = (UNITS + NT - 1) / NT;
   static constexpr int NREG = 4 * NP;
   const char* base;
-  uint32_t off[NP], step;                                   // bytes
+  uint32_t off[NP], step;                                   // bytes: the lane's units within a step, a whole step
   __device__ __forceinline__ void setup(const GemmProblem& P, int col0, int col_end) {
     base = reinterpret_cast<const char*>(P.Bp);
-    step = 32u * (uint32_t)P.N;
+    step = 96u * (uint32_t)P.N;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       const int u = min(p * NT + (int)threadIdx.x, UNITS - 1);
-      const int plane = u / Cw;                             // 2 * part + k-group
-      off[p] = 16u * (uint32_t)(((plane >> 1) * P.kgroups + (plane & 1)) * P.N + min(col0 + u % Cw, col_end - 1));
+      off[p] = 16u * (uint32_t)(u / Cw * P.N + min(col0 + u % Cw, col_end - 1));   // plane u / Cw: 2 * part + k-group
     }
   }
   __device__ __forceinline__ void fetch(const GemmProblem&, int k0, int, float (&reg)[NREG], int p) {
@@ -648,13 +648,13 @@ __global__ __launch_bounds__(NT, (waves_per_simd<(WBM > XBM ? WBM : XBM), WBN>()
 __global__ __launch_bounds__(256) void pack_weights_kernel(const PackBatch b) {
   const PackJob& J = b.job[blockIdx.y];
   const int u = (int)blockIdx.x * 256 + (int)threadIdx.x;
-  if (u >= J.kgroups * J.cols) return;
+  if (u >= 2 * J.steps * J.cols) return;
   const int kg = u / J.cols, c = u - kg * J.cols;
   const float* src = J.src + (long)c * J.stride_c + (long)(8 * kg) * J.stride_k;
   float v[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) v[i] = 8 * kg + i < J.K ? src[(long)i * J.stride_k] : 0.f;
-  if (kg / 2 >= sign_flip_step(J.kgroups / 2)) {
+  if ((kg >> 1) >= sign_flip_step(J.steps)) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = -v[i];
   }
@@ -664,12 +664,12 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const PackBatch b) {
   split_pair(v[4], v[5], part[0].z, part[1].z, part[2].z);
   split_pair(v[6], v[7], part[0].w, part[1].w, part[2].w);
 #pragma unroll
-  for (int s = 0; s < 3; ++s) reinterpret_cast<uint4*>(J.dst)[(long)s * J.kgroups * J.cols + u] = part[s];
+  for (int s = 0; s < 3; ++s) reinterpret_cast<uint4*>(J.dst)[(long)((kg >> 1) * 6 + 2 * s + (kg & 1)) * J.cols + c] = part[s];
 }
 
 hipError_t launch_pack_weights(const PackBatch& b, hipStream_t stream) {
   int units = 0;
-  for (int i = 0; i < b.count; ++i) units = b.job[i].kgroups * b.job[i].cols > units ? b.job[i].kgroups * b.job[i].cols : units;
+  for (int i = 0; i < b.count; ++i) units = 2 * b.job[i].steps * b.job[i].cols > units ? 2 * b.job[i].steps * b.job[i].cols : units;
   if (units == 0) return hipSuccess;
   TraceScope ts(stream, "pack_weights", 0.0, 0.0);
   hipLaunchKernelGGL(pack_weights_kernel, dim3((units + 255) / 256, b.count), dim3(256), 0, stream, b);

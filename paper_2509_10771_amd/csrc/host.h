@@ -163,8 +163,8 @@ inline void pack_add_net(PackBatch& b, const rslx_mlp& n, const WeightPack& w, i
   for (int l = 0; l < n.n_layers; ++l) {
     const float* W = n.params + layer_offset(n, l);
     const int K = n.dims[l], N = n.dims[l + 1];
-    b.job[b.count++] = PackJob{W, const_cast<uint16_t*>(w.fwd(n, l)), K, N, WeightPack::padded(K) / 8, N, 1};
-    if (l >= dx_from) b.job[b.count++] = PackJob{W, const_cast<uint16_t*>(w.dx(n, l)), N, K, WeightPack::padded(N) / 8, 1, N};
+    b.job[b.count++] = PackJob{W, const_cast<uint16_t*>(w.fwd(n, l)), K, N, WeightPack::padded(K) / 16, N, 1};
+    if (l >= dx_from) b.job[b.count++] = PackJob{W, const_cast<uint16_t*>(w.dx(n, l)), N, K, WeightPack::padded(N) / 16, 1, N};
   }
 }
 
@@ -203,7 +203,7 @@ inline int32_t forward_nets(const NetJob* jobs, int count, hipStream_t stream, b
       p.M = jobs[i].rows; p.N = n.dims[l + 1]; p.K = (l == 0 && jobs[i].x.cols) ? jobs[i].x.cols : n.dims[l];
       p.elu = (l + 1 < L) ? 1 : 0;
       p.alpha = n.elu_alpha;
-      if (jobs[i].pack) { p.Bp = jobs[i].pack->fwd(n, l); p.kgroups = WeightPack::padded(n.dims[l]) / 8; }
+      if (jobs[i].pack) p.Bp = jobs[i].pack->fwd(n, l);
       p.a_vec = (p.K % 4 == 0 && p.lda % 4 == 0 && aligned16(p.A) && p.col_map == nullptr) ? 1 : 0;
       p.b_vec = (p.N % 4 == 0 && aligned16(p.B)) ? 1 : 0;
       b.p[i] = p;
@@ -323,7 +323,7 @@ inline int32_t backward_nets(const BwdJob* jobs, int count, hipStream_t stream, 
         GemmProblem q = blank_problem();
         q.A = dz; q.lda = n.dims[l + 1];
         q.B = n.params + layer_offset(n, l); q.ldb = n.dims[l + 1];
-        if (jobs[i].pack) { q.Bp = jobs[i].pack->dx(n, l); q.kgroups = WeightPack::padded(n.dims[l + 1]) / 8; }
+        if (jobs[i].pack) q.Bp = jobs[i].pack->dx(n, l);
         q.C = l > 0 ? jobs[i].bufs->dz[l - 1] : jobs[i].dx0; q.ldc = n.dims[l];
         q.aux = l > 0 ? jobs[i].bufs->out[l - 1] : nullptr;      // the network input is not an ELU output
         q.M = jobs[i].rows; q.N = n.dims[l]; q.K = n.dims[l + 1];

@@ -41,7 +41,6 @@ struct GemmProblem {
   const float* A;           // FWD/DW: X storage; DX: dZ
   const float* B;           // FWD, DX: W [K_in, N_out] row-major; DW: dZ
   const uint16_t* Bp;       // FWD/DX: the same weights split for the matrix cores (launch_pack_weights), or null
-  int32_t kgroups;          // groups of eight contraction indices per part of Bp
   float* C;                 // FWD/DX: output; DW: base of split partial 0
   const float* aux;         // FWD: bias[N] or null; DX: H at C's coordinates (ldc) or null
   const int32_t* row_idx;   // optional row gather for X (device)
@@ -74,10 +73,10 @@ hipError_t launch_gemm(GemmMode mode, const GemmBatch& batch, hipStream_t stream
 // narrow_dw: optional further weight gradient whose operands are ready as well (the output layer's, a few columns
 // wide); it rides in the same launch when it can, else it is launched on its own first.
 hipError_t launch_gemm_dw_dx(const GemmBatch& bw, const GemmBatch& bx, hipStream_t stream, const GemmBatch* narrow_dw = nullptr);
-// Weights split into three bf16 parts, [part][contraction index / 8][column][8]: of the element (k, c) at
-// src[k * stride_k + c * stride_c], zero for contraction indices K .. 8 * kgroups - 1 (kgroups is even); the last third or
-// so is negated (sign_flip_step in gemm.hip).
-struct PackJob { const float* src; uint16_t* dst; int32_t K, cols, kgroups, stride_k, stride_c; };
+// Weights split into three bf16 parts, [step of 16 contraction indices][part][group of eight][column][8]: of the element
+// (k, c) at src[k * stride_k + c * stride_c], zero for contraction indices K .. 16 * steps - 1; the last third or so is
+// negated (sign_flip_step in gemm.hip).
+struct PackJob { const float* src; uint16_t* dst; int32_t K, cols, steps, stride_k, stride_c; };
 struct PackBatch { PackJob job[32]; int32_t count; };   // two networks of up to eight layers, two copies each
 hipError_t launch_pack_weights(const PackBatch& b, hipStream_t stream);
 // Number of output tiles the weight-gradient kernel uses for an [M, N] layer (big = 128x128 tiles allowed).

@@ -1,6 +1,8 @@
 """The contractions run on the bf16 matrix cores on operands split in three parts: the results must keep fp32 accuracy
 over the whole exponent range, at every remainder of the tiles, and infinite inputs must give what fp32 arithmetic
 gives.  More than 8192 rows take the tiled per-layer launches, fewer the layer-fused one."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -108,3 +110,44 @@ def test_infinite_observation_saturates_the_gates(rx, cell):
     got = h.cpu().numpy()
     assert np.isfinite(ref).all() and np.isfinite(got).all()
     assert np.abs(got - ref).max() < 1e-5
+
+
+def test_layer_of_more_than_two_to_the_thirty_weights(rx):
+    """A hidden layer [1040, 2^20]: its split weights take more than 2^32 bytes, forward and input gradient.  Gradients
+    of the whole network against float64 on the GPU.  Bound: the input gradient's sums run over 2^20 terms in 6 x 65 536
+    matrix instructions, each rounding by up to 2^-24 of the sum so far; with random signs sqrt(393 216) x 2^-24 = 4e-5 of
+    the largest sum, and the bias gradient, a sum over rows with random signs, is smaller than its terms' sizes add up
+    to by sqrt(48): 2.6e-4.  A part of the weights read at the wrong place is an error of order one."""
+    dims, rows = (8, 1040, 1 << 20, 2), 48
+    n = [a * b for a, b in zip(dims, dims[1:])]
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    net = rx.Mlp(dims, torch.zeros(sum(n) + sum(dims[1:]), device="cuda"), trainable=True)
+    views, o = [], 0
+    for k, (a, b) in enumerate(zip(dims, dims[1:])):
+        w = net.params[o:o + a * b].view(a, b)
+        w.uniform_(-1, 1, generator=gen).mul_((3.0 / a) ** 0.5)
+        views.append((w, net.params[o + a * b:o + a * b + b].uniform_(-0.1, 0.1, generator=gen), o))
+        o += a * b + b
+    x = torch.randn(rows, dims[0], generator=gen, device="cuda")
+    y = torch.randn(rows, dims[-1], generator=gen, device="cuda")
+    elu = lambda z: torch.where(z > 0, z, torch.expm1(torch.clamp(z, max=0.0)))  # noqa: E731
+    hs = [x.double()]
+    for k, (w, b, _) in enumerate(views):
+        z = hs[-1] @ w.double() + b.double()
+        hs.append(elu(z) if k < 2 else z)
+    d = 2.0 * (hs[-1] - y.double()) / y.numel()
+    ref = [None] * 3
+    for k in (2, 1, 0):
+        ref[k] = (hs[k].T.contiguous() @ d, d.sum(0))
+        if k:
+            d = (d @ views[k][0].double().T.contiguous()) * torch.where(hs[k] > 0, 1.0, hs[k] + 1.0)
+    cfg = rx.BcCfg(lr=1e-9, epochs=1, minibatches=1, max_grad_norm=0.0, seed=1, call_index=0)
+    stats, step = torch.zeros(1, rx.NSTATS, device="cuda"), C.c_int64(0)
+    ws = rx.workspace(rx.rslx_bc_update_workspace_bytes(net, None, rows, cfg))
+    rx.rslx_bc_update(net, None, x, None, y, rows, cfg, step, stats, ws)
+    torch.cuda.synchronize()
+    for k, (w, b, o) in enumerate(views):
+        for name, r, o_ in (("W", ref[k][0], o), ("b", ref[k][1], o + w.numel())):
+            got = net.grads[o_:o_ + r.numel()].view_as(r)
+            err = float((got.double() - r).norm() / r.norm())
+            assert err <= 2.6e-4, (k, name, err)
