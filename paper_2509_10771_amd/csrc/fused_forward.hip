@@ -50,33 +50,42 @@ __device__ __forceinline__ int ff_unit(int g, int row) { return (g * FF_ROWS + r
 // matters for a value that feeds the next layer's sums; the relative error near zero does not.
 __device__ __forceinline__ float ff_elu(float x, float alpha) { return x > 0.f ? x : alpha * (__expf(x) - 1.0f); }
 
-// Splits eight consecutive activations of a row and writes them to LDS.  The sum of the parts is the value in every case:
-// a finite value that would round to infinity has its first part cut off instead, an infinite one has zero lower parts.
+// Splits eight consecutive activations of a row and writes them to LDS.  Values without a split (2^111 and above,
+// infinite) have NaN for their first part and the two halves of their bits for the others: their row's sums come out NaN,
+// and ff_value finds the value for the repetition in fp32.
 __device__ __forceinline__ void ff_put(char* acts, int g, int row, const float (&v)[8]) {
   uint32_t p[3][4];
   float most = 0.f;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    split_pair(v[2 * i], v[2 * i + 1], p[0][i], p[1][i], p[2][i]);
+    split_pair(SPLIT_SCALE * v[2 * i], SPLIT_SCALE * v[2 * i + 1], p[0][i], p[1][i], p[2][i]);
     most = fmaxf(most, fmaxf(fabsf(v[2 * i]), fabsf(v[2 * i + 1])));
   }
-  if (most >= __uint_as_float(0x7f7f8000u)) {
+  if (most >= 0x1p111f) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      if (!(fabsf(v[i]) >= __uint_as_float(0x7f7f8000u))) continue;
-      const uint32_t hi = __float_as_uint(v[i]) & 0xffff0000u;
-      uint32_t p0 = hi >> 16, p1 = 0, p2 = 0, none;
-      if ((hi & 0x7f800000u) != 0x7f800000u) split_pair(v[i] - __uint_as_float(hi), 0.f, p1, p2, none);
+      if (!(fabsf(v[i]) >= 0x1p111f)) continue;
+      const uint32_t bits = __float_as_uint(v[i]);
       const int sh = 16 * (i & 1);
       const uint32_t keep = 0xffff0000u >> sh;
-      p[0][i / 2] = (p[0][i / 2] & keep) | (p0 << sh);
-      p[1][i / 2] = (p[1][i / 2] & keep) | ((p1 & 0xffffu) << sh);
-      p[2][i / 2] = (p[2][i / 2] & keep) | ((p2 & 0xffffu) << sh);
+      p[0][i / 2] = (p[0][i / 2] & keep) | (0x7fc0u << sh);
+      p[1][i / 2] = (p[1][i / 2] & keep) | ((bits >> 16) << sh);
+      p[2][i / 2] = (p[2][i / 2] & keep) | ((bits & 0xffffu) << sh);
     }
   }
 #pragma unroll
   for (int s = 0; s < 3; ++s)
     *reinterpret_cast<uint4*>(acts + s * FF_PART + ff_unit(g, row)) = make_uint4(p[s][0], p[s][1], p[s][2], p[s][3]);
+}
+
+// Activation k of a row as ff_put was given it (NaN for NaN).
+__device__ __forceinline__ float ff_value(const char* acts, int k, int row) {
+  const char* u = acts + ff_unit(k >> 3, row) + 2 * (k & 7);
+  uint32_t p[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) p[i] = *reinterpret_cast<const uint16_t*>(u + i * FF_PART);
+  if ((p[0] & 0x7fffu) > 0x7f80u) return __uint_as_float((p[1] << 16) | p[2]);
+  return (__uint_as_float(p[2] << 16) + __uint_as_float(p[1] << 16) + __uint_as_float(p[0] << 16)) * (1.0f / SPLIT_SCALE);
 }
 
 // Work of one wavefront in one layer: 64 columns from col0 and contraction steps [s_begin, s_end).  Activations
@@ -123,12 +132,16 @@ struct FfWeights {
   }
   template <bool VEC>
   __device__ __forceinline__ void load(int s, float (&dst)[FF_CHUNK]) const {
+    // byte offsets of the lane from the uniform base: one product for the step (both factors fit 24 bits, FF_MAX_DIM),
+    // rows past the end clamped by their offset
+    const uint32_t ldb = 4u * (uint32_t)ldw, c0 = VEC ? 4u * (uint32_t)col[0] : 0u;
+    const uint32_t first = __umul24((uint32_t)(FF_STEP * s + 8 * kq), ldb) + c0, end = (uint32_t)(K - 1) * ldb + c0;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const uint32_t row = 4u * (uint32_t)(min(FF_STEP * s + 8 * kq + i, K - 1) * ldw);     // 32-bit lane offset, uniform base
+      const uint32_t row = min(first + (uint32_t)i * ldb, end);
       const char* base = reinterpret_cast<const char*>(W);
       if constexpr (VEC) {
-        const float4 v = *reinterpret_cast<const float4*>(base + (row + 4u * (uint32_t)col[0]));
+        const float4 v = *reinterpret_cast<const float4*>(base + row);
         dst[4 * i + 0] = v.x; dst[4 * i + 1] = v.y; dst[4 * i + 2] = v.z; dst[4 * i + 3] = v.w;
       } else {
 #pragma unroll
@@ -161,10 +174,13 @@ __device__ __forceinline__ void ff_contract(const FfWeights& wt, const FfTask& t
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       const int cb = cb0 + c;
-      split_pair(w[cb], w[4 + cb], a.part[c][0].x, a.part[c][1].x, a.part[c][2].x);
-      split_pair(w[8 + cb], w[12 + cb], a.part[c][0].y, a.part[c][1].y, a.part[c][2].y);
-      split_pair(w[16 + cb], w[20 + cb], a.part[c][0].z, a.part[c][1].z, a.part[c][2].z);
-      split_pair(w[24 + cb], w[28 + cb], a.part[c][0].w, a.part[c][1].w, a.part[c][2].w);
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = SPLIT_SCALE * w[4 * i + cb];
+      split_pair(v[0], v[1], a.part[c][0].x, a.part[c][1].x, a.part[c][2].x);
+      split_pair(v[2], v[3], a.part[c][0].y, a.part[c][1].y, a.part[c][2].y);
+      split_pair(v[4], v[5], a.part[c][0].z, a.part[c][1].z, a.part[c][2].z);
+      split_pair(v[6], v[7], a.part[c][0].w, a.part[c][1].w, a.part[c][2].w);
     }
   };
   auto multiply = [&](const Pair& a, int cb0) {
@@ -196,10 +212,14 @@ __device__ __forceinline__ void ff_contract(const FfWeights& wt, const FfTask& t
     step(s + 1, w1, w0);
     if (s + 2 > last) break;
   }
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) acc[cb][h] *= SPLIT_UNSCALE;
 }
 
-// The same sums in plain fp32 arithmetic, for tasks that met a non-finite one (see gemm.hip): infinite inputs have no
-// split.  Each lane forms its 16 columns x 2 rows from the fp32 weights and the sum of the activations' parts.
+// The same sums in plain fp32 arithmetic, for tasks that met a non-finite one (see gemm.hip): such inputs have no
+// split.  Each lane forms its 16 columns x 2 rows from the fp32 weights and the activations' values.
 __device__ __forceinline__ void ff_contract_plain(const float* W, int K, int N, const FfTask& task, const char* acts, int m, int kq,
                                                   f32x4 (&acc)[4][2]) {
 #pragma unroll
@@ -211,12 +231,7 @@ __device__ __forceinline__ void ff_contract_plain(const float* W, int K, int N, 
   for (int k = task.s_begin * FF_STEP; k < k_end; ++k) {
     float x[2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const char* u = acts + ff_unit(k >> 3, m + 16 * h) + 2 * (k & 7);
-      x[h] = 0.f;
-#pragma unroll
-      for (int p = 2; p >= 0; --p) x[h] += __uint_as_float((uint32_t)*reinterpret_cast<const uint16_t*>(u + p * FF_PART) << 16);
-    }
+    for (int h = 0; h < 2; ++h) x[h] = ff_value(acts, k, m + 16 * h);
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb)
 #pragma unroll

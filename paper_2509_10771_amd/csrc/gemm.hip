@@ -5,11 +5,12 @@
 //   a = a0 + a1 + a2,   a0 = bf16(a), a1 = bf16(a - a0), a2 = bf16(a - a0 - a1)      (exact: 3 x 8 significant bits)
 //   a b ~ a0 b0 + (a0 b1 + a1 b0) + (a1 b1 + a0 b2 + a2 b0)
 //
-// What is left out (a1 b2, a2 b1, a2 b2) is below 2^-25 of the product, less than half the rounding of an fp32 product,
-// and bf16 has the exponent range of fp32, so no scaling is needed.  Six products at sixteen times the rate are 2.7
-// times the fp32 peak.  Operands that have no such split (infinite, or rounded to infinity) make their outputs
-// non-finite; a tile that finds a non-finite sum repeats its contraction on the fp32 matrix cores (fp32_contract), so
-// the results of such inputs are those of fp32 arithmetic.
+// What is left out (a1 b2, a2 b1, a2 b2) is below 2^-24 of the product, as the rounding of an fp32 product is (largest seen
+// over four million random pairs 0.9 of that bound, root mean square 0.09 of it).  Operands are scaled by 2^16, so that
+// the split is exact down to the smallest fp32 value (SPLIT_SCALE).  Six products at sixteen times the rate are 2.7 times
+// the fp32 peak.  Operands that have no such split (infinite, or 2^111 and above) make their outputs non-finite; a tile
+// that finds a non-finite sum repeats its contraction on the fp32 matrix cores (fp32_contract), so the results of such
+// inputs are those of fp32 arithmetic.
 //
 // Tiling: one workgroup = 4 wavefronts (256 lanes) computes a BM x BN block of C in steps of 16 contraction indices.
 // The operand tile of step k + 1 is split in registers and written to LDS, and the fp32 values of step k + 2 are
@@ -346,7 +347,8 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
   // Sign of what the accumulators hold (see sign_flip_step): the weight gradient sums the negated terms in every other
   // split, the contractions with split weights change sign on the way.
   const int flip_t = PACK ? sign_flip_step(nk) : nk;
-  float flip = (MODE == GEMM_DW && (split & 1)) || (PACK && flip_t < nk) ? -1.0f : 1.0f;
+  const float b_scale = MODE == GEMM_DW && (split & 1) ? -SPLIT_SCALE : SPLIT_SCALE;   // operand B, unless it is packed
+  float unscale = (MODE == GEMM_DW && (split & 1)) || (PACK && flip_t < nk) ? -SPLIT_UNSCALE : SPLIT_UNSCALE;
   const bool with_bias = MODE == GEMM_DW && tm == 0 && P.bias_off >= 0;
 
   const bool full_mn = m0 + BM <= P.M && n0 + BN <= P.N;
@@ -386,14 +388,10 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
           for (int c = 2 * half; c < 2 * half + 2; ++c) v[c] = (MODE == GEMM_DW ? lb.valid(k0, k_end, c) : la.valid(k0, k_end, c)) ? v[c] : 0.f;
         }
       }
-      if (MODE == GEMM_DW && p >= NA) {
-        const float w[4] = {flip * v[0], flip * v[1], flip * v[2], flip * v[3]};
-        if (half == 0) quad.split_lo(w);
-        else quad.split_hi(w);
-      } else {
-        if (half == 0) quad.split_lo(v);
-        else quad.split_hi(v);
-      }
+      const float s = p < NA ? SPLIT_SCALE : b_scale;
+      const float w[4] = {s * v[0], s * v[1], s * v[2], s * v[3]};
+      if (half == 0) quad.split_lo(w);
+      else quad.split_hi(w);
     };
     auto put_piece = [&](int p, int par) {
       if (p < NA) {
@@ -492,7 +490,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
     __syncthreads();
     if (*flag) {
       fp32_contract<MODE, BM, BN, WM, WN>(P, m0, n0, k_begin, k_end, reinterpret_cast<float*>(smem), acc);
-      flip = 1.0f;
+      unscale = 1.0f;
     }
   }
   float bias_grad = 0.f;
@@ -543,7 +541,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
       if (GATE_PIPE && aux != nullptr && b + 1 < TM * TN) load_gate(b + 1, hx[(b + 1) & 1]);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        float v = MODE == GEMM_DW || PACK ? flip * acc[x][y][r] : acc[x][y][r];
+        float v = unscale * acc[x][y][r];
         if (MODE == GEMM_FWD) {
           v += bias[y];
           if (elu) {
@@ -573,7 +571,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
       float out[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        float v = MODE == GEMM_DW || PACK ? flip * acc[x][y][r] : acc[x][y][r];
+        float v = unscale * acc[x][y][r];
         if (MODE == GEMM_FWD) {
           v += bias;
           if (elu) {
@@ -653,7 +651,7 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const PackBatch b) {
   const float* src = J.src + (long)c * J.stride_c + (long)(8 * kg) * J.stride_k;
   float v[8];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) v[i] = 8 * kg + i < J.K ? src[(long)i * J.stride_k] : 0.f;
+  for (int i = 0; i < 8; ++i) v[i] = 8 * kg + i < J.K ? SPLIT_SCALE * src[(long)i * J.stride_k] : 0.f;
   if ((kg >> 1) >= sign_flip_step(J.steps)) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = -v[i];

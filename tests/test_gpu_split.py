@@ -33,20 +33,25 @@ def _values(rx, net, obs, N):
     return out.cpu().numpy()
 
 
-@pytest.mark.parametrize("N", [FUSED, LAYERED])
+@pytest.mark.parametrize("N,A", [(FUSED, 1), (FUSED, 200), (LAYERED, 1), (LAYERED, 50), (LAYERED, 200), (LAYERED, 1400)])
 @pytest.mark.parametrize("D", [1, 4, 31, 32, 33, 100, 512])
-def test_linear_layer_keeps_fp32_accuracy_over_the_exponent_range(rx, D, N):
-    """One linear layer on rows scaled by powers of ten from 1e-30 to 1e30.  Bound: D + 1 roundings of fp32 (2^-24 each)
-    and the 2^-25 of the products left out, against the sum of the terms' sizes; a sum of bf16 products would be off by
-    2^-9 of it."""
-    net, flat = _critic(rx, (D, 1), 3)
+def test_linear_layer_keeps_fp32_accuracy_over_the_exponent_range(rx, D, N, A):
+    """One linear layer without a bias on rows scaled by powers of ten from 1e-44 (where fp32 has four bits left) to 1e37;
+    the output widths of the layered calls are one for each tile shape.  Bound: D + 1 roundings of fp32 (2^-24 each) and
+    the 2^-24 of the products left out, against the sum of the terms' sizes (2^-150 each where the sum is subnormal); a
+    sum of bf16 products would be off by 2^-9 of it, one without the third parts by 2^-17."""
     g = np.random.default_rng(D)
-    obs = (g.normal(size=(N, D)) * 10.0 ** g.integers(-30, 31, size=(N, 1))).astype(np.float32)
-    got = _values(rx, net, obs, N)
-    w, b = flat[:D].astype(np.float64), float(flat[D])
-    ref = obs.astype(np.float64) @ w + b
-    size = np.abs(obs.astype(np.float64)) @ np.abs(w) + abs(b)
-    assert np.all(np.abs(got - ref) <= (D + 3) * 2.0 ** -24 * size)
+    w = (g.normal(size=(D, A)) / np.sqrt(D)).astype(np.float32)
+    net = rx.Mlp((D, A), torch.from_numpy(np.concatenate([w.ravel(), np.zeros(A, np.float32)])).cuda())
+    obs = torch.from_numpy((g.normal(size=(N, D)) * 10.0 ** g.integers(-44, 38, size=(N, 1))).astype(np.float32)).cuda()
+    got, twin = torch.full((N, A), 7.0, device="cuda"), torch.empty(N, A, device="cuda")
+    rx.rslx_bc_collect(net, net, obs, obs, N, got, twin, rx.workspace(rx.rslx_bc_collect_workspace_bytes(net, net, N)))
+    w64, x64 = torch.from_numpy(w).cuda().double(), obs.double()
+    ref, size = x64 @ w64, x64.abs() @ w64.abs()
+    over = (got.double() - ref).abs() - (D + 3) * (2.0 ** -24 * size + 2.0 ** -150)
+    worst = int(over.amax(1).argmax())
+    assert bool((over <= 0).all()), (float(over[worst].max()), worst, float(obs[worst].abs().max()))
+    assert torch.equal(got, twin)
 
 
 @pytest.mark.parametrize("N", [FUSED, LAYERED])
