@@ -55,10 +55,11 @@ __device__ __forceinline__ float ff_elu(float x, float alpha) { return x > 0.f ?
 // and ff_value finds the value for the repetition in fp32.
 __device__ __forceinline__ void ff_put(char* acts, int g, int row, const float (&v)[8]) {
   uint32_t p[3][4];
+  const float scale = split_scale(row);
   float most = 0.f;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    split_pair(SPLIT_SCALE * v[2 * i], SPLIT_SCALE * v[2 * i + 1], p[0][i], p[1][i], p[2][i]);
+    split_pair(scale * v[2 * i], scale * v[2 * i + 1], p[0][i], p[1][i], p[2][i]);
     most = fmaxf(most, fmaxf(fabsf(v[2 * i]), fabsf(v[2 * i + 1])));
   }
   if (most >= 0x1p111f) {
@@ -85,7 +86,7 @@ __device__ __forceinline__ float ff_value(const char* acts, int k, int row) {
 #pragma unroll
   for (int i = 0; i < 3; ++i) p[i] = *reinterpret_cast<const uint16_t*>(u + i * FF_PART);
   if ((p[0] & 0x7fffu) > 0x7f80u) return __uint_as_float((p[1] << 16) | p[2]);
-  return (__uint_as_float(p[2] << 16) + __uint_as_float(p[1] << 16) + __uint_as_float(p[0] << 16)) * (1.0f / SPLIT_SCALE);
+  return (__uint_as_float(p[2] << 16) + __uint_as_float(p[1] << 16) + __uint_as_float(p[0] << 16)) * (SPLIT_UNSCALE * split_scale(row));
 }
 
 // Work of one wavefront in one layer: 64 columns from col0 and contraction steps [s_begin, s_end).  Activations
@@ -215,7 +216,7 @@ __device__ __forceinline__ void ff_contract(const FfWeights& wt, const FfTask& t
 #pragma unroll
   for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) acc[cb][h] *= SPLIT_UNSCALE;
+    for (int h = 0; h < 2; ++h) acc[cb][h] *= split_unscale(wt.m);     // batch rows m and 16 + m
 }
 
 // The same sums in plain fp32 arithmetic, for tasks that met a non-finite one (see gemm.hip): such inputs have no

@@ -43,16 +43,6 @@ __device__ __forceinline__ int src_row(const GemmProblem& P, int r) {
   return r >= P.idx_mod ? v + P.wrap_add : v;
 }
 
-// The bf16 matrix instructions round their sums down a little more often than up: by about 1.2e-11 of the sum's size
-// per instruction (mean error of 256 x 128 sums of 4096 random terms -2.1e-7 of their rms, at a total error of 1.0e-6; no
-// such offset on the fp32 matrix cores).  One result does not notice, but sums over many results do, and gradients over
-// whole minibatches are such sums: the offset has the same sign in every row and on every optimiser step.  So a part of
-// every contraction is summed with its sign reversed, and the offsets cancel: the weight gradient negates its terms in
-// every other split; weights that are split once per optimiser step are stored negated from step sign_flip_step on, and
-// the accumulators change sign there, two thirds of the way: the offset follows the size of the sum, for random signs
-// the root of the index reached, and has done about half of its work by then (the mean over a minibatch falls to a tenth).
-__host__ __device__ __forceinline__ int sign_flip_step(int steps) { return steps < 2 ? steps : (steps * 66 + 50) / 100; }
-
 // LDS image of one operand tile of R rows: plane (part s, k-group kg) at (2 s + kg) * pitch, 16 bytes per row.  The 64
 // bytes between planes put the two k-groups of a row in different banks when they are written together.
 template <int R> constexpr int plane_pitch() { return R * 16 + 64; }
@@ -344,11 +334,10 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
   float bsum[NBS];
 #pragma unroll
   for (int p = 0; p < NBS; ++p) bsum[p] = 0.f;
-  // Sign of what the accumulators hold (see sign_flip_step): the weight gradient sums the negated terms in every other
-  // split, the contractions with split weights change sign on the way.
-  const int flip_t = PACK ? sign_flip_step(nk) : nk;
-  const float b_scale = MODE == GEMM_DW && (split & 1) ? -SPLIT_SCALE : SPLIT_SCALE;   // operand B, unless it is packed
-  float unscale = (MODE == GEMM_DW && (split & 1)) || (PACK && flip_t < nk) ? -SPLIT_UNSCALE : SPLIT_UNSCALE;
+  // Odd result rows are computed negated (see split_scale), the weight gradient's by turns from split to split.  A lane
+  // splits rows of one parity: tile rows tid / 4 + 64 p, the weight gradient's tid % 64 + 64 p.
+  const int turn = MODE == GEMM_DW ? split & 1 : 0;
+  const float a_scale = split_scale(MODE == GEMM_DW ? tid + turn : tid >> 2);
   const bool with_bias = MODE == GEMM_DW && tm == 0 && P.bias_off >= 0;
 
   const bool full_mn = m0 + BM <= P.M && n0 + BN <= P.N;
@@ -388,7 +377,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
           for (int c = 2 * half; c < 2 * half + 2; ++c) v[c] = (MODE == GEMM_DW ? lb.valid(k0, k_end, c) : la.valid(k0, k_end, c)) ? v[c] : 0.f;
         }
       }
-      const float s = p < NA ? SPLIT_SCALE : b_scale;
+      const float s = p < NA ? a_scale : SPLIT_SCALE;
       const float w[4] = {s * v[0], s * v[1], s * v[2], s * v[3]};
       if (half == 0) quad.split_lo(w);
       else quad.split_hi(w);
@@ -423,12 +412,6 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
 #pragma unroll
       for (int i = 0; i < S; ++i) {
         const int q = i / TT + (G2 ? 0 : 3), x = i % TT / TN, y = i % TN;
-        if (PACK && G2 && i == 3 * TT && t == flip_t) {
-#pragma unroll
-          for (int u = 0; u < TM; ++u)
-#pragma unroll
-            for (int v = 0; v < TN; ++v) acc[u][v] = -acc[u][v];
-        }
         if (G2 && i == 2 * TT) { read_a(1); read_b(1); }
         if (G2 && i == 3 * TT) { read_b(0); read_a(0); }
         acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[q]][x], b[PB[q]][y], acc[x][y], 0, 0, 0);
@@ -485,13 +468,13 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
 #pragma unroll
       for (int y = 0; y < TN; ++y)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) z = fmaf(acc[x][y][r], 0.f, z);
+        for (int r = 0; r < 16; ++r) {
+          acc[x][y][r] *= split_unscale(r + turn);           // register r holds a row of r's parity
+          z = fmaf(acc[x][y][r], 0.f, z);
+        }
     if (!(z == 0.f)) *flag = 1;
     __syncthreads();
-    if (*flag) {
-      fp32_contract<MODE, BM, BN, WM, WN>(P, m0, n0, k_begin, k_end, reinterpret_cast<float*>(smem), acc);
-      unscale = 1.0f;
-    }
+    if (*flag) fp32_contract<MODE, BM, BN, WM, WN>(P, m0, n0, k_begin, k_end, reinterpret_cast<float*>(smem), acc);
   }
   float bias_grad = 0.f;
   if (with_bias) {                 // the four wavefronts hold different contraction rows of the same columns
@@ -541,7 +524,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
       if (GATE_PIPE && aux != nullptr && b + 1 < TM * TN) load_gate(b + 1, hx[(b + 1) & 1]);
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        float v = unscale * acc[x][y][r];
+        float v = acc[x][y][r];
         if (MODE == GEMM_FWD) {
           v += bias[y];
           if (elu) {
@@ -571,7 +554,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
       float out[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        float v = unscale * acc[x][y][r];
+        float v = acc[x][y][r];
         if (MODE == GEMM_FWD) {
           v += bias;
           if (elu) {
@@ -642,7 +625,7 @@ __global__ __launch_bounds__(NT, (waves_per_simd<(WBM > XBM ? WBM : XBM), WBN>()
 }
 
 // ---- splitting weights --------------------------------------------------------------------------------------
-// One lane forms the three parts of eight consecutive contraction indices of one column (negated past sign_flip_step).
+// One lane forms the three parts of eight consecutive contraction indices of one column.
 __global__ __launch_bounds__(256) void pack_weights_kernel(const PackBatch b) {
   const PackJob& J = b.job[blockIdx.y];
   const int u = (int)blockIdx.x * 256 + (int)threadIdx.x;
@@ -652,10 +635,6 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const PackBatch b) {
   float v[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) v[i] = 8 * kg + i < J.K ? SPLIT_SCALE * src[(long)i * J.stride_k] : 0.f;
-  if ((kg >> 1) >= sign_flip_step(J.steps)) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = -v[i];
-  }
   uint4 part[3];
   split_pair(v[0], v[1], part[0].x, part[1].x, part[2].x);
   split_pair(v[2], v[3], part[0].y, part[1].y, part[2].y);

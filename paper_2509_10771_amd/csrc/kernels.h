@@ -74,8 +74,7 @@ hipError_t launch_gemm(GemmMode mode, const GemmBatch& batch, hipStream_t stream
 // wide); it rides in the same launch when it can, else it is launched on its own first.
 hipError_t launch_gemm_dw_dx(const GemmBatch& bw, const GemmBatch& bx, hipStream_t stream, const GemmBatch* narrow_dw = nullptr);
 // Weights split into three bf16 parts, [step of 16 contraction indices][part][group of eight][column][8]: of the element
-// (k, c) at src[k * stride_k + c * stride_c], zero for contraction indices K .. 16 * steps - 1; the last third or so is
-// negated (sign_flip_step in gemm.hip).
+// (k, c) at src[k * stride_k + c * stride_c], zero for contraction indices K .. 16 * steps - 1 (split_bf16.h).
 struct PackJob { const float* src; uint16_t* dst; int32_t K, cols, steps, stride_k, stride_c; };
 struct PackBatch { PackJob job[32]; int32_t count; };   // two networks of up to eight layers, two copies each
 hipError_t launch_pack_weights(const PackBatch& b, hipStream_t stream);

@@ -21,6 +21,18 @@ __device__ __forceinline__ uint32_t pack_bf16(float x, float y) {
 // are computed in fp32 (see gemm.hip).
 constexpr float SPLIT_SCALE = 65536.0f, SPLIT_UNSCALE = 0x1p-32f;
 
+// The bf16 matrix instructions cut the low bits of the smaller addends off downwards: a sum of random terms comes out low
+// by 7e-9 to 1e-8 of its rms over 16 to 128 contraction indices and by 5e-11 of it per index over more (fp32 matrix
+// instructions: below 1e-10), where its random error is 3e-8 (16 indices) to 1e-6 (4096).  One result does not notice,
+// but sums over the rows of a minibatch do: the offset has the same sign in every one.  So every other row of a result is
+// computed with its sign reversed: odd rows of the operand whose index becomes the result's row are negated by the
+// factor of the scaling, and their sums by that of the unscaling.  Their offset is upward, and it cancels in sums over
+// rows, to below 1e-10 at every length.  (The last bits of a row depend on the parity of its place for that.  Where a
+// layer's inputs hardly differ from row to row, the cut of the third parts' products is common to all rows beyond its
+// offset: 4e-8 of the rms in a column's mean for inputs of 20 +- 1, where a single result's error is 2e-7.)
+__device__ __forceinline__ float split_scale(int row) { return row & 1 ? -SPLIT_SCALE : SPLIT_SCALE; }
+__device__ __forceinline__ float split_unscale(int row) { return row & 1 ? -SPLIT_UNSCALE : SPLIT_UNSCALE; }
+
 // x = p0.lo + p1.lo + p2.lo, y = p0.hi + p1.hi + p2.hi: both remainders are exact, and the last one has at most eight
 // significant bits, so the three parts together are the value itself (multiples of 2^-133).  Infinities, and values
 // that round to infinity, leave NaN in the lower parts.

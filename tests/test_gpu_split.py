@@ -156,3 +156,61 @@ def test_layer_of_more_than_two_to_the_thirty_weights(rx):
             got = net.grads[o_:o_ + r.numel()].view_as(r)
             err = float((got.double() - r).norm() / r.norm())
             assert err <= 2.6e-4, (k, name, err)
+
+
+# Rounding must not have a direction: gradients are sums over minibatches, where an offset of 1e-8 of a result's size in
+# every row adds up while random errors of 1e-7 cancel.  Bound: six standard deviations of a mean of independent errors.
+def _mean_is_random(err, rms, what):
+    mean, dev = float(err.mean() / rms), float(err.std() / rms)
+    assert abs(mean) <= 6 * dev / err.numel() ** 0.5, (what, mean, dev)
+
+
+@pytest.mark.parametrize("N", [8192, 16384])
+@pytest.mark.parametrize("K,A", [(16, 200), (48, 256), (200, 40), (512, 12), (512, 200)])
+def test_layer_outputs_have_no_rounding_offset(rx, K, A, N):
+    gen = torch.Generator(device="cuda").manual_seed(K + A)
+    for _ in range(3):
+        w = torch.randn(K, A, generator=gen, device="cuda") / K ** 0.5
+        x = torch.randn(N, K, generator=gen, device="cuda")
+        net = rx.Mlp((K, A), torch.cat([w.ravel(), torch.zeros(A, device="cuda")]))
+        got, twin = torch.empty(N, A, device="cuda"), torch.empty(N, A, device="cuda")
+        rx.rslx_bc_collect(net, net, x, x, N, got, twin, rx.workspace(rx.rslx_bc_collect_workspace_bytes(net, net, N)))
+        ref = x.double() @ w.double()
+        _mean_is_random(got.double() - ref, ref.pow(2).mean().sqrt(), "forward")
+
+
+def _bc_grads(rx, dims, params, x, y):
+    net = rx.Mlp(dims, params, trainable=True)
+    cfg = rx.BcCfg(lr=1e-9, epochs=1, minibatches=1, max_grad_norm=0.0, seed=1, call_index=0)
+    stats, step = torch.zeros(1, rx.NSTATS, device="cuda"), C.c_int64(0)
+    ws = rx.workspace(rx.rslx_bc_update_workspace_bytes(net, None, x.shape[0], cfg))
+    rx.rslx_bc_update(net, None, x, None, y, x.shape[0], cfg, step, stats, ws)
+    torch.cuda.synchronize()
+    return net.grads
+
+
+@pytest.mark.parametrize("rows", [128, 384, 24576])
+@pytest.mark.parametrize("K", [16, 48, 512])
+def test_gradients_have_no_rounding_offset(rx, K, rows):
+    """Forward with packed weights: with zero targets the bias gradient is the column mean of the outputs.  Weight gradient:
+    one, an odd and an even number of row splits.  Input gradient: with the first layer zero its units are 0, their slope
+    is one, and its bias gradient is the column sum of the input gradient."""
+    gen = torch.Generator(device="cuda").manual_seed(K + rows)
+    normal = lambda *s: torch.randn(*s, generator=gen, device="cuda")  # noqa: E731
+    H = 256
+    offset = dict(forward=[], weight=[], input=[])
+    for _ in range(3):
+        w, x = normal(K, H) / K ** 0.5, normal(rows, K)
+        g = _bc_grads(rx, (K, H), torch.cat([w.ravel(), torch.zeros(H, device="cuda")]), x, torch.zeros(rows, H, device="cuda")).double()
+        d = 2.0 * (x.double() @ w.double()) / (rows * H)
+        offset["forward"].append((g[K * H:] - d.sum(0)) / (rows * d.pow(2).mean().sqrt()))
+        gw = x.double().T.contiguous() @ d
+        offset["weight"].append((g[:K * H].view(K, H) - gw) / gw.pow(2).mean().sqrt())
+        w, x, y = normal(H, K) / K ** 0.5, normal(rows, 32), normal(rows, K)
+        flat = torch.cat([torch.zeros(32 * H + H, device="cuda"), w.ravel(), torch.zeros(K, device="cuda")])
+        g = _bc_grads(rx, (32, H, K), flat, x, y).double()
+        dz = (-2.0 * y.double() / (rows * K)) @ w.double().T.contiguous()
+        offset["input"].append((g[32 * H:32 * H + H] - dz.sum(0)) / (rows * dz.pow(2).mean().sqrt()))
+    for what, parts in offset.items():
+        err = torch.stack(parts)
+        assert abs(float(err.mean())) <= 6 * float(err.std()) / err.numel() ** 0.5, (what, float(err.mean()), float(err.std()))
