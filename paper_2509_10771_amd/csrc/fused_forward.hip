@@ -219,29 +219,45 @@ __device__ __forceinline__ void ff_contract(const FfWeights& wt, const FfTask& t
     for (int h = 0; h < 2; ++h) acc[cb][h] *= split_unscale(wt.m);     // batch rows m and 16 + m
 }
 
-// The same sums in plain fp32 arithmetic, for tasks that met a non-finite one (see gemm.hip): such inputs have no
-// split.  Each lane forms its 16 columns x 2 rows from the fp32 weights and the activations' values.
-__device__ __forceinline__ void ff_contract_plain(const float* W, int K, int N, const FfTask& task, const char* acts, int m, int kq,
-                                                  f32x4 (&acc)[4][2]) {
+// Puts the sums of fp32 products (v_mfma_f32_16x16x4_f32, from the fp32 weights and the activations' values) in place of
+// the non-finite ones of a task (see gemm.hip): such inputs have no split.  The other rows keep their sums.
+__device__ __forceinline__ void ff_repeat_fp32(const float* W, int K, int N, const FfTask& task, const char* acts, int m, int kq,
+                                               f32x4 (&acc)[4][2]) {
+  f32x4 c[4][2];
 #pragma unroll
   for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-    for (int h = 0; h < 2; ++h) acc[cb][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int h = 0; h < 2; ++h) c[cb][h] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int k_end = min(K, task.s_end * FF_STEP);
+  constexpr int AHEAD = 4;             // contraction indices per lane whose operands are requested together
 #pragma unroll 1
-  for (int k = task.s_begin * FF_STEP; k < k_end; ++k) {
-    float x[2];
+  for (int k0 = task.s_begin * FF_STEP; k0 < k_end; k0 += 4 * AHEAD) {
+    float w[AHEAD][4];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) x[h] = ff_value(acts, k, m + 16 * h);
+    for (int i = 0; i < AHEAD; ++i)
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float w = W[(long)k * N + min(task.col0 + 16 * kq + 4 * r + cb, N - 1)];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) acc[cb][h][r] = fmaf(w, x[h], acc[cb][h][r]);
+      for (int cb = 0; cb < 4; ++cb) {
+        const int k = k0 + 4 * i + kq;
+        w[i][cb] = k < K ? W[(long)k * N + min(task.col0 + 4 * m + cb, N - 1)] : 0.f;
       }
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) {
+      float x[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) x[h] = ff_value(acts, k0 + 4 * i + kq, m + 16 * h);
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) c[cb][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i][cb], x[h], c[cb][h], 0, 0, 0);
+    }
   }
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (!__builtin_isfinite(acc[cb][h][r])) acc[cb][h][r] = c[cb][h][r];
 }
 
 // First weight chunk of a task.
@@ -353,7 +369,7 @@ __global__ __launch_bounds__(FF_THREADS) void fused_forward_kernel(const FusedFo
         for (int h = 0; h < 2; ++h)
 #pragma unroll
           for (int r = 0; r < 4; ++r) z = fmaf(acc[cb][h][r], 0.f, z);
-      if (__any(!(z == 0.f))) ff_contract_plain(W, K, N, task, acts, m, kq, acc);
+      if (__any(!(z == 0.f))) ff_repeat_fp32(W, K, N, task, acts, m, kq, acc);
     }
     // bias values of the outputs this lane finishes, requested before the sums are exchanged: with the contraction of
     // a group shared among wavefronts, the sums are finished by all lanes after an exchange through LDS; otherwise

@@ -8,9 +8,9 @@
 // What is left out (a1 b2, a2 b1, a2 b2) is below 2^-24 of the product, as the rounding of an fp32 product is (largest seen
 // over four million random pairs 0.9 of that bound, root mean square 0.09 of it).  Operands are scaled by 2^16, so that
 // the split is exact down to the smallest fp32 value (SPLIT_SCALE).  Six products at sixteen times the rate are 2.7 times
-// the fp32 peak.  Operands that have no such split (infinite, or 2^111 and above) make their outputs non-finite; a tile
-// that finds a non-finite sum repeats its contraction on the fp32 matrix cores (fp32_contract), so the results of such
-// inputs are those of fp32 arithmetic.
+// the fp32 peak.  Operands that have no such split (infinite, or 2^111 and above) make their outputs non-finite; a
+// wavefront that finds non-finite sums forms those on the fp32 matrix cores (fp32_repeat), so the results of such inputs
+// are those of fp32 arithmetic and all others what they are without them.
 //
 // Tiling: one workgroup = 4 wavefronts (256 lanes) computes a BM x BN block of C in steps of 16 contraction indices.
 // The operand tile of step k + 1 is split in registers and written to LDS, and the fp32 values of step k + 2 are
@@ -213,66 +213,52 @@ struct Packed {
   }
 };
 
-// LDS bytes of one tile configuration: two buffers of split operand tiles, and the word that says whether a lane of the
-// workgroup met a non-finite sum.
+// LDS bytes of one tile configuration: two buffers of split operand tiles.
 template <int BM, int BN>
-constexpr int gemm_lds_bytes() { return 2 * (tile_bytes<BM>() + tile_bytes<BN>()) + 16; }
+constexpr int gemm_lds_bytes() { return 2 * (tile_bytes<BM>() + tile_bytes<BN>()); }
 
-// The contraction of a tile on the fp32 matrix cores (v_mfma_f32_32x32x2_f32), element by element and without any
-// overlap: reached only by tiles with non-finite sums.
-template <int MODE, int BM, int BN, int WM, int WN>
-__device__ __forceinline__ void fp32_contract(const GemmProblem& P, int m0, int n0, int k_begin, int k_end, float* smem,
-                                           f32x16 (&acc)[BM / WM / 32][BN / WN / 32]) {
-  constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
-  float* As = smem;                    // [BK][BM]
-  float* Bs = smem + BK * BM;          // [BK][BN]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int g = lane >> 5, j = lane & 31;
-  const int a_off = (wave / WN) * (TM * 32) + j, b_off = (wave % WN) * (TN * 32) + j;
+// Puts the sums of fp32 products (v_mfma_f32_32x32x2_f32, operands element by element from memory) in place of the
+// non-finite ones among a wavefront's accumulators; `blocks` holds a bit per 32 x 32 block that has any.  The other sums
+// stay, so that a row's result does not depend on what else is in its tile.
+template <int MODE, int WN, int TM, int TN>
+__device__ __forceinline__ void fp32_repeat(const GemmProblem& P, int tid, int m0, int n0, int k_begin, int k_end, uint32_t blocks,
+                                            f32x16 (&acc)[TM][TN]) {
+  constexpr int AHEAD = 4;             // products whose operands are requested together
+  const int g = (tid >> 5) & 1, j = tid & 31, wave = tid >> 6;
+  const int row0 = m0 + wave / WN * (TM * 32), col0 = n0 + wave % WN * (TN * 32);
   const int a_cols = (MODE == GEMM_DW && P.a_cols > P.M) ? P.a_cols : P.M;
 #pragma unroll
-  for (int x = 0; x < TM; ++x)
+  for (int b = 0; b < TM * TN; ++b) {
+    if (!((blocks >> b) & 1u)) continue;
+    const int m = row0 + b / TN * 32 + j, n = col0 + b % TN * 32 + j;
+    const bool m_ok = m < (MODE == GEMM_DW ? a_cols : P.M), n_ok = n < P.N;
+    const float* arow = P.A;                                    // operand A's row, where it is one along the contraction
+    if (m_ok && MODE != GEMM_DW) arow += (long)(MODE == GEMM_FWD ? src_row(P, m) : m) * P.lda;
+    f32x16 c;
 #pragma unroll
-    for (int y = 0; y < TN; ++y)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[x][y][r] = 0.f;
-  for (int k0 = k_begin; k0 < k_end; k0 += BK) {
-    __syncthreads();
+    for (int r = 0; r < 16; ++r) c[r] = 0.f;
 #pragma unroll 1
-    for (int e = tid; e < BK * BM; e += NT) {
-      const int m = m0 + e % BM, k = k0 + e / BM;
-      float v = 0.f;
-      if (MODE == GEMM_DX) {
-        if (m < P.M && k < k_end) v = P.A[(long)m * P.lda + k];
-      } else {
-        const int row = MODE == GEMM_DW ? k : m, col = MODE == GEMM_DW ? m : k;
-        if (row < (MODE == GEMM_DW ? k_end : P.M) && col < (MODE == GEMM_DW ? a_cols : k_end)) {
-          const float* rp = P.A + (long)src_row(P, row) * P.lda;
-          if (P.col_map != nullptr && row >= P.map_from) v = (P.col_sign != nullptr ? P.col_sign[col] : 1.0f) * rp[P.col_map[col]];
-          else v = rp[col];
-        }
+    for (int k0 = k_begin; k0 < k_end; k0 += 2 * AHEAD) {
+      float a[AHEAD], w[AHEAD];
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) {
+        const int k = k0 + 2 * i + g;
+        a[i] = w[i] = 0.f;
+        if (k >= k_end) continue;
+        if (n_ok) w[i] = P.B[MODE == GEMM_DX ? (long)n * P.ldb + k : (long)k * P.ldb + n];
+        if (!m_ok) continue;
+        const float* rp = MODE == GEMM_DW ? P.A + (long)src_row(P, k) * P.lda : arow;
+        const int col = MODE == GEMM_DW ? m : k;
+        const bool mapped = MODE != GEMM_DX && P.col_map != nullptr && (MODE == GEMM_DW ? k : m) >= P.map_from;
+        a[i] = mapped ? (P.col_sign != nullptr ? P.col_sign[col] : 1.0f) * rp[P.col_map[col]] : rp[col];
       }
-      As[e] = v;
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], w[i], c, 0, 0, 0);
     }
-#pragma unroll 1
-    for (int e = tid; e < BK * BN; e += NT) {
-      const int n = n0 + e % BN, k = k0 + e / BN;
-      Bs[e] = (n < P.N && k < k_end) ? P.B[MODE == GEMM_DX ? (long)n * P.ldb + k : (long)k * P.ldb + n] : 0.f;
-    }
-    __syncthreads();
-    for (int kk = 0; kk < BK; kk += 2) {
-      float a[TM], b[TN];
 #pragma unroll
-      for (int t = 0; t < TM; ++t) a[t] = As[(kk + g) * BM + a_off + t * 32];
-#pragma unroll
-      for (int t = 0; t < TN; ++t) b[t] = Bs[(kk + g) * BN + b_off + t * 32];
-#pragma unroll
-      for (int x = 0; x < TM; ++x)
-#pragma unroll
-        for (int y = 0; y < TN; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[x], b[y], acc[x][y], 0, 0, 0);
-    }
+    for (int r = 0; r < 16; ++r)
+      if (!__builtin_isfinite(acc[b / TN][b % TN][r])) acc[b / TN][b % TN][r] = c[r];
   }
-  __syncthreads();
 }
 
 // One output tile (one split of it for the weight gradient) of problem P.  `lin` numbers the workgroups of the
@@ -285,7 +271,6 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
   constexpr int ABYTES = tile_bytes<BM>(), BBYTES = tile_bytes<BN>();
   char* As = smem;                          // [2][ABYTES]
   char* Bs = smem + 2 * ABYTES;             // [2][BBYTES]
-  int* flag = reinterpret_cast<int*>(smem + 2 * (ABYTES + BBYTES));
 
   const int tiles_n = (P.N + BN - 1) / BN;
   const int tiles_m = (P.M + BM - 1) / BM;
@@ -302,10 +287,10 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
   const int k_end = (MODE == GEMM_DW) ? min(P.K, k_begin + P.k_chunk) : P.K;
   const int nk = (k_end - k_begin + BK - 1) / BK;
 
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int g = lane >> 5, j = lane & 31;
-  const int wm = wave / WN, wn = wave % WN;
+  int tid = threadIdx.x;
+  int lane = tid & 63, wave = tid >> 6;
+  int g = lane >> 5, j = lane & 31;
+  int wm = wave / WN, wn = wave % WN;
 
   f32x16 acc[TM][TN];
 #pragma unroll
@@ -342,7 +327,6 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
 
   const bool full_mn = m0 + BM <= P.M && n0 + BN <= P.N;
 
-  if (tid == 0) *flag = 0;
   // The loop is a fixed sequence of slots, one matrix instruction each, with the other work dealt out between them: a
   // wave that converts, loads or stores in one burst leaves its matrix cores idle meanwhile, and the other waves of the
   // SIMD tend to be in the same phase.  Body t runs the last three products of step t - 1 and the first three of step
@@ -461,20 +445,27 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
       acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[q]][x], b[PB[q]][y], acc[x][y], 0, 0, 0);
     }
   }
+  // What follows is formed anew from an opaque lane number: addresses for it would otherwise be computed before the loop
+  // and take registers from it.
+  asm volatile("" : "+v"(tid));
+  lane = tid & 63; wave = tid >> 6;
+  g = lane >> 5; j = lane & 31;
+  wm = wave / WN; wn = wave % WN;
   {
-    float z = 0.f;                 // becomes NaN with any non-finite sum
+    uint32_t blocks = 0;           // those with non-finite sums
 #pragma unroll
     for (int x = 0; x < TM; ++x)
 #pragma unroll
-      for (int y = 0; y < TN; ++y)
+      for (int y = 0; y < TN; ++y) {
+        float z = 0.f;             // becomes NaN with any
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           acc[x][y][r] *= split_unscale(r + turn);           // register r holds a row of r's parity
           z = fmaf(acc[x][y][r], 0.f, z);
         }
-    if (!(z == 0.f)) *flag = 1;
-    __syncthreads();
-    if (*flag) fp32_contract<MODE, BM, BN, WM, WN>(P, m0, n0, k_begin, k_end, reinterpret_cast<float*>(smem), acc);
+        if (__any(!(z == 0.f))) blocks |= 1u << (x * TN + y);
+      }
+    if (blocks) fp32_repeat<MODE, WN>(P, tid, m0, n0, k_begin, k_end, blocks, acc);
   }
   float bias_grad = 0.f;
   if (with_bias) {                 // the four wavefronts hold different contraction rows of the same columns

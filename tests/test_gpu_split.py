@@ -214,3 +214,65 @@ def test_gradients_have_no_rounding_offset(rx, K, rows):
     for what, parts in offset.items():
         err = torch.stack(parts)
         assert abs(float(err.mean())) <= 6 * float(err.std()) / err.numel() ** 0.5, (what, float(err.mean()), float(err.std()))
+
+
+@pytest.mark.parametrize("N,dims", [(FUSED, (48, 128, 72, 12)), (FUSED, (33, 512, 300, 7)), (LAYERED, (48, 128, 72, 12)), (LAYERED, (45, 300, 1400))])
+def test_rows_without_a_split_leave_the_others_alone(rx, N, dims):
+    """Rows with infinite, NaN or very large inputs are repeated in fp32; the rows beside them keep every bit."""
+    g = np.random.default_rng(3)
+    flat = np.concatenate([np.concatenate([g.normal(size=a * b) / np.sqrt(a), 0.1 * g.normal(size=b)]) for a, b in zip(dims, dims[1:])])
+    net = rx.Mlp(dims, torch.from_numpy(flat.astype(np.float32)).cuda())
+    obs = torch.from_numpy(g.normal(size=(N, dims[0])).astype(np.float32)).cuda()
+    out = [torch.empty(N, dims[-1], device="cuda") for _ in range(3)]
+    ws = rx.workspace(rx.rslx_bc_collect_workspace_bytes(net, net, N))
+    rx.rslx_bc_collect(net, net, obs, obs, N, out[0], out[2], ws)
+    odd = obs.clone()
+    for row, col, v in ((3, 5, np.inf), (20, 0, -np.inf), (33, 7, np.nan), (47, 1, 3e38), (N - 2, 31, 6e33)):
+        odd[row, col] = float(v)
+    rx.rslx_bc_collect(net, net, odd, odd, N, out[1], out[2], ws)
+    keep = torch.ones(N, dtype=torch.bool, device="cuda")
+    keep[[3, 20, 33, 47, N - 2]] = False
+    assert torch.equal(out[0][keep], out[1][keep])
+    assert bool(torch.isnan(out[1][33]).all()) and bool(torch.isfinite(out[1][N - 2]).all())
+
+
+@pytest.mark.parametrize("rows,dims", [(384, (200, 256, 8)), (384, (37, 300, 100, 5)), (384, (1024, 1024, 16)), (11264, (64, 1024, 1024, 16))])
+def test_update_with_values_beyond_the_split(rx, rows, dims):
+    """Finite values of 2^112 and above in the observations, the weights and the loss gradient that meet small ones, so that
+    every sum of fp32 products is finite: packed forward, input gradient and weight gradients (three row splits at 384 rows, even
+    and odd counts at 11 264; 64 x 128 and 128 x 128 tiles, inside and at the edge), against float64, element by element.
+    Bound: 2^-24 of the terms' sizes for every index of the contraction, for each contraction on the way."""
+    gen = torch.Generator(device="cuda").manual_seed(rows + dims[0])
+    L, W, b, flat = len(dims) - 1, [], [], []
+    for a, c in zip(dims, dims[1:]):
+        W.append(torch.randn(a, c, generator=gen, device="cuda") / a ** 0.5)
+        b.append(0.1 * torch.randn(c, generator=gen, device="cuda"))
+    x = torch.randn(rows, dims[0], generator=gen, device="cuda")
+    y = torch.randn(rows, dims[-1], generator=gen, device="cuda")
+    # input column 3 of some rows is huge, its weights are tiny; output column 1 has tiny weights and huge targets
+    x[5::70, 3] = 2e38
+    W[0][3] *= 1e-39
+    W[-1][:, 1] *= 1e-37
+    y[11::50, 1] = 1e38
+    for w, c in zip(W, b):
+        flat += [w.ravel(), c]
+    g = _bc_grads(rx, dims, torch.cat(flat), x, y).double()
+    hs, size = [x.double()], []
+    for k in range(L):
+        z = hs[-1] @ W[k].double() + b[k].double()
+        hs.append(torch.where(z > 0, z, torch.expm1(torch.clamp(z, max=0.0))) if k < L - 1 else z)
+    d = 2.0 * (hs[-1] - y.double()) / y.numel()
+    size, eps, o = d.abs() + 2.0 * hs[-1].abs() / y.numel(), 2.0 ** -24, sum(a * c + c for a, c in zip(dims, dims[1:]))
+    terms = sum(dims[:-1])                                # roundings behind a value so far
+    for k in range(L - 1, -1, -1):
+        a, c = dims[k], dims[k + 1]
+        o -= a * c + c
+        for got, ref, s in ((g[o:o + a * c].view(a, c), hs[k].T.contiguous() @ d, hs[k].abs().T.contiguous() @ size),
+                            (g[o + a * c:o + a * c + c], d.sum(0), size.sum(0))):
+            assert bool(torch.isfinite(got).all())
+            over = (got - ref).abs() / ((terms + rows) * eps * s + 1e-38)
+            assert float(over.max()) <= 1.0, (k, float(over.max()), int(over.argmax()))
+        if k:
+            slope = torch.where(hs[k] > 0, 1.0, hs[k] + 1.0)
+            d, size = (d @ W[k].double().T.contiguous()) * slope, (size @ W[k].double().abs().T.contiguous()) * slope
+            terms += c
