@@ -622,10 +622,12 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const PackBatch b) {
   const int u = (int)blockIdx.x * 256 + (int)threadIdx.x;
   if (u >= 2 * J.steps * J.cols) return;
   const int kg = u / J.cols, c = u - kg * J.cols;
-  const float* src = J.src + (long)c * J.stride_c + (long)(8 * kg) * J.stride_k;
+  const float* src = J.src + (long)c * J.stride_c;
   float v[8];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) v[i] = 8 * kg + i < J.K ? SPLIT_SCALE * src[(long)i * J.stride_k] : 0.f;
+  for (int i = 0; i < 8; ++i) v[i] = src[(long)min(8 * kg + i, J.K - 1) * J.stride_k];   // all requested before the first is used
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = 8 * kg + i < J.K ? SPLIT_SCALE * v[i] : 0.f;
   uint4 part[3];
   split_pair(v[0], v[1], part[0].x, part[1].x, part[2].x);
   split_pair(v[2], v[3], part[0].y, part[1].y, part[2].y);
