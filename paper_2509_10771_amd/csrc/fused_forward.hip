@@ -197,8 +197,6 @@ __device__ __forceinline__ void ff_contract(const FfWeights& wt, const FfTask& t
   };
   Pair lo, hi;
   const int last = task.s_end - 1;
-  wt.load<VEC>(task.s_begin + 1, w1);
-  split(w0, 0, lo);
   auto step = [&](int s, float (&w)[FF_CHUNK], float (&wn)[FF_CHUNK]) {
     read_b(s);
     split(w, 2, hi);
@@ -207,11 +205,21 @@ __device__ __forceinline__ void ff_contract(const FfWeights& wt, const FfTask& t
     split(wn, 0, lo);
     multiply(hi, 2);
   };
-  for (int s = task.s_begin;; s += 2) {
-    step(s, w0, w1);
-    if (s + 1 > last) break;
-    step(s + 1, w1, w0);
-    if (s + 2 > last) break;
+  if (last == task.s_begin) {              // narrow layers: nothing is fetched and split for a step that does not come
+    read_b(last);
+    split(w0, 0, lo);
+    split(w0, 2, hi);
+    multiply(lo, 0);
+    multiply(hi, 2);
+  } else {
+    wt.load<VEC>(task.s_begin + 1, w1);
+    split(w0, 0, lo);
+    for (int s = task.s_begin;; s += 2) {
+      step(s, w0, w1);
+      if (s + 1 > last) break;
+      step(s + 1, w1, w0);
+      if (s + 2 > last) break;
+    }
   }
 #pragma unroll
   for (int cb = 0; cb < 4; ++cb)
