@@ -61,8 +61,9 @@ struct Quad {
   }
 };
 
-// How an operand is read.  FORM_FAST: 16-byte loads of rows that are contiguous along the contraction; plain rows where
-// the M / N index is contiguous.  FORM_GATHER (weight gradient): its contraction rows are gathered.  FORM_GENERAL: any
+// How an operand is read.  FORM_FAST: 16-byte loads of rows that are contiguous along the contraction, by 32-bit offsets
+// (from the tile's first row; gathered rows from the matrix, which must be smaller than 4 GiB); plain rows where the
+// M / N index is contiguous.  FORM_GATHER (weight gradient): its contraction rows are gathered.  FORM_GENERAL: any size,
 // alignment, gather and column map.
 enum Form { FORM_FAST, FORM_GATHER, FORM_GENERAL };
 
@@ -79,18 +80,21 @@ struct KContig {
   const float* ptr[VEC ? 1 : NP];
   uint32_t off[VEC ? NP : 1];   // bytes from `base`
   uint32_t mapped;              // bit p: the row of pass p reads through col_map / col_sign (never with VEC)
+  bool vec;                     // without VEC: the rows allow 16-byte loads all the same
   int q;
 
   __device__ __forceinline__ void setup(const GemmProblem& P, const float* b, int ld, int row0, int row_end) {
-    base = b;
+    const int first = IS_X && P.row_idx != nullptr ? 0 : row0;
+    base = b + (long)first * ld;
     q = threadIdx.x & 3;
     mapped = 0;
+    vec = IS_X ? P.a_vec != 0 : false;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       const int row = min(row0 + p * 64 + (int)(threadIdx.x >> 2), row_end - 1);
       const int sr = IS_X ? src_row(P, row) : row;
       if constexpr (VEC) {
-        off[p] = 4u * ((uint32_t)sr * (uint32_t)ld);
+        off[p] = 4u * ((uint32_t)(sr - first) * (uint32_t)ld);
       } else {
         ptr[p] = b + (long)sr * ld;
         if (IS_X && P.col_map != nullptr && row >= P.map_from) mapped |= 1u << p;
@@ -103,6 +107,9 @@ struct KContig {
     if constexpr (VEC) {
       const uint32_t kb = 4u * (uint32_t)min(k0 + 4 * q, k_end - 4);
       const float4 v = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(base) + (off[p] + kb));
+      reg[4 * p + 0] = v.x; reg[4 * p + 1] = v.y; reg[4 * p + 2] = v.z; reg[4 * p + 3] = v.w;
+    } else if (vec) {
+      const float4 v = *reinterpret_cast<const float4*>(ptr[p] + min(k0 + 4 * q, k_end - 4));
       reg[4 * p + 0] = v.x; reg[4 * p + 1] = v.y; reg[4 * p + 2] = v.z; reg[4 * p + 3] = v.w;
     } else {
 #pragma unroll
@@ -665,11 +672,9 @@ static BatchGeom batch_geom(GemmMode mode, const GemmBatch& batch, int BM, int B
       if (P.col_map != nullptr) form = FORM_GENERAL;
       else if (P.row_idx != nullptr || P.idx_mod < P.K) form = FORM_GATHER;
     } else {
-      // the 16-byte paths address the matrix by 32-bit byte offsets from its base
-      const int64_t lim = (int64_t)1 << 30;
-      const int64_t a_rows = P.row_idx != nullptr ? P.a_src_rows : P.M;
-      if (!P.a_vec || a_rows <= 0 || a_rows * (int64_t)P.lda >= lim) form = FORM_GENERAL;
-      if (mode == GEMM_DX && P.Bp == nullptr && (!P.b_vec || (int64_t)P.N * P.ldb >= lim)) form = FORM_GENERAL;
+      if (!P.a_vec) form = FORM_GENERAL;
+      if (P.row_idx != nullptr && (P.a_src_rows <= 0 || P.a_src_rows * (int64_t)P.lda >= (int64_t)1 << 30)) form = FORM_GENERAL;
+      if (mode == GEMM_DX && P.Bp == nullptr && !P.b_vec) form = FORM_GENERAL;
       g.pack = g.pack && P.Bp != nullptr;
     }
     g.form = form > g.form ? form : g.form;

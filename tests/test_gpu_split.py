@@ -276,3 +276,36 @@ def test_update_with_values_beyond_the_split(rx, rows, dims):
             slope = torch.where(hs[k] > 0, 1.0, hs[k] + 1.0)
             d, size = (d @ W[k].double().T.contiguous()) * slope, (size @ W[k].double().abs().T.contiguous()) * slope
             terms += c
+
+
+@pytest.mark.parametrize("gathered", [False, True])
+def test_observations_of_more_than_four_gibibytes(rx, gathered):
+    """2^24 + 77 rows of 64: layered inference reads them by offsets from each tile's first row, the update (gathered rows) by
+    64-bit addresses.  Outputs of the last rows, and of some far apart, to fp32 accuracy; gradients against float64 sums to
+    2e-5 (sums of 1.7e7 rows by 128 to 65 536 at a time)."""
+    rows, dims = (1 << 24) + 77, (64, 8, 1)
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    x = torch.empty(rows, 64, device="cuda").normal_(generator=gen)
+    parts = []
+    for a, c in zip(dims, dims[1:]):
+        parts += [torch.randn(a, c, generator=gen, device="cuda") / a ** 0.5, 0.1 * torch.randn(c, generator=gen, device="cuda")]
+    flat = torch.cat([p.ravel() for p in parts])
+    if not gathered:
+        net, out = rx.Mlp(dims, flat), torch.empty(rows, device="cuda")
+        ws = rx.workspace(rx.rslx_act_workspace_bytes(None, net, rows))
+        rx.rslx_act(None, net, None, x, rows, 0, 0, None, None, None, out, None, None, rx.ACT_VALUES_ONLY, ws)
+        pick = torch.cat([torch.arange(0, rows, 99991, device="cuda"), torch.arange(rows - 200, rows, device="cuda")])
+        h = x[pick].double() @ parts[0].double() + parts[1].double()
+        ref = (torch.where(h > 0, h, torch.expm1(torch.clamp(h, max=0.0))) @ parts[2].double() + parts[3].double())[:, 0]
+        assert float((out[pick].double() - ref).abs().max()) <= 2e-6 * float(ref.abs().max())
+        return
+    y = torch.empty(rows, 1, device="cuda").normal_(generator=gen)
+    g, ref = _bc_grads(rx, dims, flat, x, y).double(), torch.zeros(flat.numel(), dtype=torch.float64, device="cuda")
+    for s in range(0, rows, 1 << 21):
+        xs = x[s:s + (1 << 21)].double()
+        h = xs @ parts[0].double() + parts[1].double()
+        e = torch.where(h > 0, h, torch.expm1(torch.clamp(h, max=0.0)))
+        d = 2.0 * (e @ parts[2].double() + parts[3].double() - y[s:s + (1 << 21)].double()) / rows
+        dz = (d @ parts[2].double().T.contiguous()) * torch.where(h > 0, 1.0, e + 1.0)
+        ref += torch.cat([(xs.T.contiguous() @ dz).ravel(), dz.sum(0), (e.T.contiguous() @ d).ravel(), d.sum(0)])
+    assert float((g - ref).norm() / ref.norm()) <= 2e-5
