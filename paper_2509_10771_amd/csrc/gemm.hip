@@ -63,9 +63,9 @@ struct Quad {
 
 // How an operand is read.  FORM_FAST: 16-byte loads of rows that are contiguous along the contraction, by 32-bit offsets
 // (from the tile's first row; gathered rows from the matrix, which must be smaller than 4 GiB); plain rows where the
-// M / N index is contiguous.  FORM_GATHER (weight gradient): its contraction rows are gathered.  FORM_GENERAL: any size,
-// alignment, gather and column map.
-enum Form { FORM_FAST, FORM_GATHER, FORM_GENERAL };
+// M / N index is contiguous.  FORM_GATHER (weight gradient): its contraction rows are gathered.  FORM_FAR (forward): as
+// FORM_FAST with gathered rows of a larger matrix.  FORM_GENERAL: any alignment, gather and column map.
+enum Form { FORM_FAST, FORM_GATHER, FORM_FAR, FORM_GENERAL };
 
 // ---- operand with the contraction index contiguous in memory (tile rows = M or N index) ---------------------
 // Lane -> row tid / 4 (+ 64 per pass), contraction indices 4 (tid % 4) .. + 3: four lanes read the 64 bytes of a row's
@@ -79,8 +79,7 @@ struct KContig {
   const float* base;
   const float* ptr[VEC ? 1 : NP];
   uint32_t off[VEC ? NP : 1];   // bytes from `base`
-  uint32_t mapped;              // bit p: the row of pass p reads through col_map / col_sign (never with VEC)
-  bool vec;                     // without VEC: the rows allow 16-byte loads all the same
+  uint32_t mapped;              // bit p: the row of pass p reads through col_map / col_sign (FORM_GENERAL)
   int q;
 
   __device__ __forceinline__ void setup(const GemmProblem& P, const float* b, int ld, int row0, int row_end) {
@@ -88,7 +87,6 @@ struct KContig {
     base = b + (long)first * ld;
     q = threadIdx.x & 3;
     mapped = 0;
-    vec = IS_X ? P.a_vec != 0 : false;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       const int row = min(row0 + p * 64 + (int)(threadIdx.x >> 2), row_end - 1);
@@ -108,7 +106,7 @@ struct KContig {
       const uint32_t kb = 4u * (uint32_t)min(k0 + 4 * q, k_end - 4);
       const float4 v = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(base) + (off[p] + kb));
       reg[4 * p + 0] = v.x; reg[4 * p + 1] = v.y; reg[4 * p + 2] = v.z; reg[4 * p + 3] = v.w;
-    } else if (vec) {
+    } else if constexpr (FORM == FORM_FAR) {
       const float4 v = *reinterpret_cast<const float4*>(ptr[p] + min(k0 + 4 * q, k_end - 4));
       reg[4 * p + 0] = v.x; reg[4 * p + 1] = v.y; reg[4 * p + 2] = v.z; reg[4 * p + 3] = v.w;
     } else {
@@ -317,8 +315,9 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
   if constexpr (PACK) lb.setup(P, n0, P.N);
   else lb.setup(P, P.B, P.ldb, n0, P.N);
   // values on their way to LDS: one step ahead; activation rows that meet weights two steps ahead, since they come from
-  // memory and there are registers left for them
-  constexpr int DA = MODE == GEMM_DW ? 1 : 2;
+  // memory, where the loads' own addresses leave registers for them (general rows, packed weights, 128 x 128: 22 registers
+  // spilled at two steps; update with [301, 150, 75] at 24 576 rows 9.30 ms at two, 8.61 at one, 8.99 without the packed weights)
+  constexpr int DA = MODE != GEMM_DW && FORM == FORM_FAST ? 2 : 1;
   float ra[DA][decltype(la)::NREG], rb[decltype(lb)::NREG];
 
   // DW: column sums of dZ for the bias gradient, over the contraction rows of this lane
@@ -673,7 +672,7 @@ static BatchGeom batch_geom(GemmMode mode, const GemmBatch& batch, int BM, int B
       else if (P.row_idx != nullptr || P.idx_mod < P.K) form = FORM_GATHER;
     } else {
       if (!P.a_vec) form = FORM_GENERAL;
-      if (P.row_idx != nullptr && (P.a_src_rows <= 0 || P.a_src_rows * (int64_t)P.lda >= (int64_t)1 << 30)) form = FORM_GENERAL;
+      else if (P.row_idx != nullptr && (P.a_src_rows <= 0 || P.a_src_rows * (int64_t)P.lda >= (int64_t)1 << 30)) form = FORM_FAR;
       if (mode == GEMM_DX && P.Bp == nullptr && !P.b_vec) form = FORM_GENERAL;
       g.pack = g.pack && P.Bp != nullptr;
     }
@@ -702,9 +701,13 @@ static hipError_t launch_cfg(const GemmBatch& batch, hipStream_t stream) {
     else if (g.form == FORM_GATHER) launch_form<MODE, BM, BN, WM, WN, FORM_GATHER, false>(batch, grid, stream);
     else launch_form<MODE, BM, BN, WM, WN, FORM_GENERAL, false>(batch, grid, stream);
   } else {
-    if (g.form == FORM_FAST && g.pack) launch_form<MODE, BM, BN, WM, WN, FORM_FAST, true>(batch, grid, stream);
-    else if (g.form == FORM_FAST) launch_form<MODE, BM, BN, WM, WN, FORM_FAST, false>(batch, grid, stream);
-    else launch_form<MODE, BM, BN, WM, WN, FORM_GENERAL, false>(batch, grid, stream);
+    auto launch = [&](auto form) {
+      if (g.pack) launch_form<MODE, BM, BN, WM, WN, decltype(form)::value, true>(batch, grid, stream);
+      else launch_form<MODE, BM, BN, WM, WN, decltype(form)::value, false>(batch, grid, stream);
+    };
+    if (g.form == FORM_FAST) launch(std::integral_constant<int, FORM_FAST>{});
+    else if (MODE == GEMM_FWD && g.form == FORM_FAR) launch(std::integral_constant<int, MODE == GEMM_FWD ? FORM_FAR : FORM_GENERAL>{});
+    else launch(std::integral_constant<int, FORM_GENERAL>{});
   }
   return hipGetLastError();
 }

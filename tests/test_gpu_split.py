@@ -236,11 +236,12 @@ def test_rows_without_a_split_leave_the_others_alone(rx, N, dims):
     assert bool(torch.isnan(out[1][33]).all()) and bool(torch.isfinite(out[1][N - 2]).all())
 
 
-@pytest.mark.parametrize("rows,dims", [(384, (200, 256, 8)), (384, (37, 300, 100, 5)), (384, (1024, 1024, 16)), (11264, (64, 1024, 1024, 16))])
+@pytest.mark.parametrize("rows,dims", [(384, (200, 256, 8)), (384, (37, 300, 100, 5)), (384, (37, 301, 133, 70, 5)), (384, (1024, 1024, 16)), (11264, (64, 1024, 1024, 16))])
 def test_update_with_values_beyond_the_split(rx, rows, dims):
     """Finite values of 2^112 and above in the observations, the weights and the loss gradient that meet small ones, so that
     every sum of fp32 products is finite: packed forward, input gradient and weight gradients (three row splits at 384 rows, even
-    and odd counts at 11 264; 64 x 128 and 128 x 128 tiles, inside and at the edge), against float64, element by element.
+    and odd counts at 11 264; 64 x 128 and 128 x 128 tiles, inside and at the edge, widths that allow 16-byte loads and
+    others), against float64, element by element.
     Bound: 2^-24 of the terms' sizes for every index of the contraction, for each contraction on the way."""
     gen = torch.Generator(device="cuda").manual_seed(rows + dims[0])
     L, W, b, flat = len(dims) - 1, [], [], []
