@@ -43,7 +43,6 @@ GemmProblem gate_problem(const XView& x, int K, const float* W, const float* b, 
   p.M = M; p.N = H3; p.K = K;
   p.elu = 0; p.alpha = 1.f;
   p.a_vec = (K % 4 == 0 && p.lda % 4 == 0 && aligned16(p.A) && p.col_map == nullptr) ? 1 : 0;
-  p.b_vec = (H3 % 4 == 0 && aligned16(W)) ? 1 : 0;
   return p;
 }
 
@@ -310,8 +309,6 @@ GemmProblem gate_dw_problem(const XView& x, int M, const float* dG, int H3, int3
   p.split_stride = b.plan.pitch[l];
   p.bias_off = M * H3;
   p.dw_big = b.plan.big[l];
-  p.a_vec = (M % 4 == 0 && p.lda % 4 == 0 && aligned16(p.A) && p.col_map == nullptr) ? 1 : 0;
-  p.b_vec = (H3 % 4 == 0 && aligned16(dG)) ? 1 : 0;
   return p;
 }
 

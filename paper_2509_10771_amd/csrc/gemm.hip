@@ -67,7 +67,7 @@ struct Quad {
 // FORM_FAST with gathered rows of a larger matrix.  FORM_GENERAL: any alignment, gather and column map.
 enum Form { FORM_FAST, FORM_GATHER, FORM_FAR, FORM_GENERAL };
 
-// ---- operand with the contraction index contiguous in memory (tile rows = M or N index) ---------------------
+// ---- operand with the contraction index contiguous in memory (rows of X or dZ) ------------------------------
 // Lane -> row tid / 4 (+ 64 per pass), contraction indices 4 (tid % 4) .. + 3: four lanes read the 64 bytes of a row's
 // step.  Everything that does not change along the contraction (row offsets with the gather applied) is set up once
 // per tile.  Rows past the end repeat the last one; the outputs they feed are dropped.
@@ -306,11 +306,11 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
       for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
 
   // operand A: DW reads X rows as contraction rows (M index contiguous); FWD / DX read rows with k contiguous.
-  // operand B: DX reads rows of W (k contiguous); FWD and DW have the N index contiguous (W, dZ).
+  // operand B: split weights (FWD, DX), else rows with the N index contiguous (FWD: W, DW: dZ).
   const int a_cols = (MODE == GEMM_DW && P.a_cols > P.M) ? P.a_cols : P.M;   // DW: readable (zero-padded) width of X
   typename std::conditional<MODE == GEMM_DW, Direct<BM, FORM>, KContig<BM, MODE == GEMM_FWD, FORM>>::type la;
-  typename std::conditional<PACK, Packed<BN>, typename std::conditional<MODE == GEMM_DX, KContig<BN, false, FORM>,
-                                                                        Direct<BN, FORM_FAST>>::type>::type lb;
+  static_assert(PACK || MODE != GEMM_DX, "input gradients have split weights");
+  typename std::conditional<PACK, Packed<BN>, Direct<BN, FORM_FAST>>::type lb;
   la.setup(P, P.A, P.lda, m0, a_cols);
   if constexpr (PACK) lb.setup(P, n0, P.N);
   else lb.setup(P, P.B, P.ldb, n0, P.N);
@@ -673,7 +673,6 @@ static BatchGeom batch_geom(GemmMode mode, const GemmBatch& batch, int BM, int B
     } else {
       if (!P.a_vec) form = FORM_GENERAL;
       else if (P.row_idx != nullptr && (P.a_src_rows <= 0 || P.a_src_rows * (int64_t)P.lda >= (int64_t)1 << 30)) form = FORM_FAR;
-      if (mode == GEMM_DX && P.Bp == nullptr && !P.b_vec) form = FORM_GENERAL;
       g.pack = g.pack && P.Bp != nullptr;
     }
     g.form = form > g.form ? form : g.form;
@@ -691,6 +690,7 @@ template <int MODE, int BM, int BN, int WM, int WN>
 static hipError_t launch_cfg(const GemmBatch& batch, hipStream_t stream) {
   const BatchGeom g = batch_geom((GemmMode)MODE, batch, BM, BN);
   if (g.tiles == 0) return hipSuccess;
+  if (MODE == GEMM_DX && !g.pack) return hipErrorInvalidValue;
   static const char* const mode_name[3] = {"fwd", "dx", "dw"};
   char name[48];
   snprintf(name, sizeof name, "gemm_%s_%dx%d", mode_name[MODE], BM, BN);
@@ -702,8 +702,9 @@ static hipError_t launch_cfg(const GemmBatch& batch, hipStream_t stream) {
     else launch_form<MODE, BM, BN, WM, WN, FORM_GENERAL, false>(batch, grid, stream);
   } else {
     auto launch = [&](auto form) {
-      if (g.pack) launch_form<MODE, BM, BN, WM, WN, decltype(form)::value, true>(batch, grid, stream);
-      else launch_form<MODE, BM, BN, WM, WN, decltype(form)::value, false>(batch, grid, stream);
+      constexpr int F = decltype(form)::value;
+      if (g.pack) launch_form<MODE, BM, BN, WM, WN, F, true>(batch, grid, stream);
+      else launch_form<MODE, BM, BN, WM, WN, F, MODE == GEMM_DX>(batch, grid, stream);
     };
     if (g.form == FORM_FAST) launch(std::integral_constant<int, FORM_FAST>{});
     else if (MODE == GEMM_FWD && g.form == FORM_FAR) launch(std::integral_constant<int, MODE == GEMM_FWD ? FORM_FAR : FORM_GENERAL>{});

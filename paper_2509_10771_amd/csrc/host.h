@@ -205,7 +205,6 @@ inline int32_t forward_nets(const NetJob* jobs, int count, hipStream_t stream, b
       p.alpha = n.elu_alpha;
       if (jobs[i].pack) p.Bp = jobs[i].pack->fwd(n, l);
       p.a_vec = (p.K % 4 == 0 && p.lda % 4 == 0 && aligned16(p.A) && p.col_map == nullptr) ? 1 : 0;
-      p.b_vec = (p.N % 4 == 0 && aligned16(p.B)) ? 1 : 0;
       b.p[i] = p;
     }
     RSLX_HIP(launch_gemm(GEMM_FWD, b, stream));
@@ -277,8 +276,8 @@ struct BwdJob {
   const float* d_out;    // [rows, dims[L]]
   float* partials;       // split partials, laid out by `plan`
   const SplitPlan* plan;
-  float* dx0 = nullptr;  // optional [rows, dims[0]]: gradient w.r.t. the network input (a memory in front of it)
-  const WeightPack* pack = nullptr;
+  float* dx0;            // optional [rows, dims[0]]: gradient w.r.t. the network input (a memory in front of it)
+  const WeightPack* pack;
 };
 
 // Backward of up to two networks of equal depth: per layer one grouped weight-gradient launch (split over
@@ -316,20 +315,17 @@ inline int32_t backward_nets(const BwdJob* jobs, int count, hipStream_t stream, 
       p.split_stride = sp.pitch[l];
       p.bias_off = n.dims[l] * n.dims[l + 1];
       p.dw_big = sp.big[l];
-      p.a_vec = ((p.a_cols ? p.a_cols : p.M) % 4 == 0 && p.lda % 4 == 0 && aligned16(p.A) && p.col_map == nullptr) ? 1 : 0;
-      p.b_vec = (p.N % 4 == 0 && aligned16(p.B)) ? 1 : 0;
       bw.p[i] = p;
       if ((l > 0 || dx_in) && !(skip_last_dx && l == L - 1)) {
         GemmProblem q = blank_problem();
         q.A = dz; q.lda = n.dims[l + 1];
         q.B = n.params + layer_offset(n, l); q.ldb = n.dims[l + 1];
-        if (jobs[i].pack) q.Bp = jobs[i].pack->dx(n, l);
+        q.Bp = jobs[i].pack->dx(n, l);
         q.C = l > 0 ? jobs[i].bufs->dz[l - 1] : jobs[i].dx0; q.ldc = n.dims[l];
         q.aux = l > 0 ? jobs[i].bufs->out[l - 1] : nullptr;      // the network input is not an ELU output
         q.M = jobs[i].rows; q.N = n.dims[l]; q.K = n.dims[l + 1];
         q.alpha = n.elu_alpha;
         q.a_vec = (q.K % 4 == 0 && aligned16(q.A)) ? 1 : 0;
-        q.b_vec = (q.K % 4 == 0 && aligned16(q.B)) ? 1 : 0;
         bx.p[i] = q;
       }
     }

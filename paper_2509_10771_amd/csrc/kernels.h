@@ -40,7 +40,7 @@ enum GemmMode : int { GEMM_FWD = 0, GEMM_DX = 1, GEMM_DW = 2 };
 struct GemmProblem {
   const float* A;           // FWD/DW: X storage; DX: dZ
   const float* B;           // FWD, DX: W [K_in, N_out] row-major; DW: dZ
-  const uint16_t* Bp;       // FWD/DX: the same weights split for the matrix cores (launch_pack_weights), or null
+  const uint16_t* Bp;       // the same weights split for the matrix cores (launch_pack_weights); FWD: or null
   float* C;                 // FWD/DX: output; DW: base of split partial 0
   const float* aux;         // FWD: bias[N] or null; DX: H at C's coordinates (ldc) or null
   const int32_t* row_idx;   // optional row gather for X (device)
@@ -58,7 +58,7 @@ struct GemmProblem {
   int64_t split_stride;     // DW: floats between consecutive partial buffers
   int32_t bias_off;         // DW: offset of the db partial inside a partial buffer, -1 = none
   int32_t dw_big;           // DW: 1 = 128x128 tiles were planned for this layer, 0 = 64x128
-  int32_t a_vec, b_vec;     // 1 = operand may be fetched with 16-byte loads
+  int32_t a_vec;            // FWD/DX: 1 = the rows of X / dZ may be fetched with 16-byte loads
   int64_t a_src_rows;       // rows of the matrix that row_idx gathers from (0 = unknown)
   int32_t a_cols;           // DW: readable width of X's rows when it exceeds M (zero-padded storage), 0 = M
 };
