@@ -368,12 +368,49 @@ def _nearest_kinks(case, ref, limit):
     return sorted(out)[:limit]
 
 
+# A row taken on another side of its kink moves the gradient norm of that very step by 1e-6 and more (a row or two of
+# 49 152); the rounding of a step leaves up to 3e-7 there.
+FLIP_IN_NORM = 6e-7
+
+
+def _follow_gradient_norms(case, stats, violations, limit=16):
+    """The oracle's trajectory with the kink rows taken as the GPU took them, found step by step: the first step whose
+    gradient norm differs has a row on its other side, the nearest one or two that bring the norms together are it, and
+    so on from there.  Returns what is still violated (empty: agreement), and a log.  At most `limit` re-runs."""
+    ref, sides, log, runs = case.ref, {}, [], 0
+    off = lambda r, k: abs(stats[k, 4] - r["stats"][k, 4]) / r["stats"][k, 4]
+    while True:
+        bad, _ = violations(ref)
+        log.append((sides, bad))
+        k = next((i for i in range(len(ref["trace"])) if off(ref, i) > FLIP_IN_NORM), None)
+        if not bad or k is None:
+            return bad, log
+        pol, val, _ = kink_rows(case, ref["trace"][k])
+        best = None
+        for more in itertools.islice(_side_candidates(ref["trace"][k], pol, val), 1, None):
+            if runs == limit:
+                return bad, log
+            runs += 1
+            trial = dict(sides)
+            old = sides.get(k, dict(policy={}, value={}))
+            trial[k] = {kind: {**old[kind], **more[kind]} for kind in ("policy", "value")}
+            r = case.rerun(trial, record=True)
+            print("free-running: step %d with %s: gradient norm off by %.2e" % (k, trial[k], off(r, k)))
+            if best is None or off(r, k) < off(best[1], k):
+                best = (trial, r)
+            if off(r, k) <= FLIP_IN_NORM:
+                break
+        if best is None or off(best[1], k) > 0.5 * off(ref, k):
+            return bad, log
+        sides, ref = best
+
+
 def check_free_running(rx, case, found=None, later_tol=2e-2, param_tol=None, grad_tol=1e-3):
     """One whole multi-step call against the oracle's trajectory: first step's loss terms and the final parameters
     to 1e-4, the last gradient to 1e-3.  If that fails and the oracle's trajectory has rows on a kink of the clipped
-    losses, the oracle is re-run with the nearest such rows (one at a time, at most two together) taken on their
-    other side, and the GPU must agree with one of these trajectories to the same bounds.  `found` (what the
-    step-forced comparison identified) is tried first."""
+    losses, the oracle is re-run with such rows taken on their other side, and the GPU must agree with one of these
+    trajectories to the same bounds: with what the step-forced comparison identified (`found`), then with what the
+    gradient norms of the steps point at, then with the nearest rows (one at a time, at most two together)."""
     w = case.w
     a, c, rnd = _nets(rx, case, case.actor0, case.critic0)
     n = case.epochs * w.minibatches
@@ -390,6 +427,10 @@ def check_free_running(rx, case, found=None, later_tol=2e-2, param_tol=None, gra
         if not bad:
             return a, c, stats
         log.append((found, bad))
+    bad, steps = _follow_gradient_norms(case, stats, lambda ref: _free_running_violations(case, ref, *args))
+    if not bad:
+        return a, c, stats
+    log += steps
     base, base_sides = case.ref, {}
     for depth in range(2):
         best = None
