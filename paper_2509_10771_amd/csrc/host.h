@@ -225,16 +225,16 @@ struct SplitPlan {
   int32_t blocks = 0;      // workgroups of the reduction = entries of the squared-norm list
 };
 
-// Enough workgroups to fill the 256 CUs once, but at least 128 rows per split: four 64-row-tile workgroups per CU,
-// three of the 128x128 ones (measured: 768 of those beat 1024).  A weight gradient that shares its launch with the
-// layer's input gradient (every layer but the first) needs fewer - the input gradient's workgroups take the other
-// slots - which also shrinks its partial sums: two per CU for 128x128 tiles, one per CU for 64-row tiles (measured
-// on the 256x128 layer at 24 576 rows: 256 weight-gradient + 768 input-gradient workgroups are one resident round
-// of 1024; 192 and 320..1024 are all slower, 128 makes the weight gradient the launch's long pole).
+// Enough workgroups to fill the 256 CUs once, but at least 128 rows per split: four 64-row-tile workgroups per CU
+// (the first layer's launch of the 4096-environment update takes 40 us with 1024 of them, 47 with 1152), three of the
+// 128x128 ones.  A weight gradient that shares its launch with the layer's input gradient (every layer but the first)
+// needs fewer - the input gradient's workgroups take the other slots - which also shrinks its partial sums: two per CU for
+// 128x128 tiles (whole update at 4096 environments, [512, 256, 128]: 8.65 ms with 512, 8.72 with 768, 8.85 with 1024), one
+// per CU for 64-row tiles (whole bc update on [256, 256, 128]: 1.60 ms with 256, 1.69 with 192, 1.63 with 512).
 constexpr int DW_TARGET_WGS = 1024;
 constexpr int DW_TARGET_WGS_PAIRED = 256;
 constexpr int DW_TARGET_WGS_BIG = 768;
-constexpr int DW_TARGET_WGS_BIG_PAIRED = 768;
+constexpr int DW_TARGET_WGS_BIG_PAIRED = 512;
 
 // Plans layer l (an [M, N] weight reduced over `rows` rows) and appends it to p.
 inline void plan_layer(SplitPlan& p, int l, int M, int N, int32_t rows, int group, bool paired) {
