@@ -17,7 +17,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-FP32_MFMA_PEAK_TFLOPS = 157.3
+FP32_MFMA_PEAK_TFLOPS = 157.3        # the recurrent step kernels
+SPLIT_MFMA_PEAK_TFLOPS = 2516.6 / 6  # dense layers: six bf16 products (dense bf16 peak) for every fp32 product
 HBM_PEAK_GBS = 8000.0
 
 
@@ -487,8 +488,9 @@ def summarize_trace(trace, w, steps):
     dom = max(kinds, key=lambda k: kinds[k]["ms"])
     d = kinds[dom]
     achieved = d["flops"] / (d["ms"] * 1e-3) / 1e12
-    roofline = dict(bound="mfma", kernel=dom, achieved=round(achieved, 2), peak=FP32_MFMA_PEAK_TFLOPS, unit="TFLOP/s",
-                    frac=round(achieved / FP32_MFMA_PEAK_TFLOPS, 4),
+    peak = FP32_MFMA_PEAK_TFLOPS if "_step_" in dom else SPLIT_MFMA_PEAK_TFLOPS
+    roofline = dict(bound="mfma", kernel=dom, achieved=round(achieved, 2), peak=round(peak, 1), unit="TFLOP/s",
+                    frac=round(achieved / peak, 4),
                     traffic=hbm_traffic_per_launch(w.name, dom),
                     traffic_source="profiles/%s_iteration_hbm_traffic.txt (rocprofv3 FETCH_SIZE / WRITE_SIZE of these kernel sources)" % w.name,
                     launches=d["n"], avg_launch_us=round(d["ms"] * 1e3 / d["n"], 2),

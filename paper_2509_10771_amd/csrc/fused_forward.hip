@@ -155,7 +155,7 @@ struct FfWeights {
 // acc[cb][h] += W[:, col0 + 4 m + cb]^T (A operand) x activations of row half h (B operand) over the task's
 // contraction range.  `w0` arrives holding the task's first chunk, fetched by the caller ahead of time.  A step has two
 // halves of 24 matrix instructions, two column blocks each; under each the other pair of column blocks is split, so the
-// splitting (88 vector instructions per half) hides behind the matrix cores.  The chunk after next is requested as
+// scaling and splitting (104 vector instructions per half) hide behind the matrix cores.  The chunk after next is requested as
 // soon as a step's weights have been split.
 template <bool VEC>
 __device__ __forceinline__ void ff_contract(const FfWeights& wt, const FfTask& task, const char* acts,

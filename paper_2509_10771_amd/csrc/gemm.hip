@@ -713,9 +713,10 @@ static hipError_t launch_cfg(const GemmBatch& batch, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Tile selection.  Measured on MI355X: one 128x128 workgroup per CU reaches ~40 % of the matrix-core peak,
-// four resident workgroups per CU reach ~65 %, so the tile shrinks (64x128) whenever 128x128 tiles would leave
-// fewer than about three workgroups per CU, and short contractions (K <= 64, epilogue-bound) also use it.
+// Tile selection.  Three 128x128 workgroups are resident per CU; where there are fewer than about that many (700 tiles
+// over 256 CUs), 64x128 tiles fill the chip better (whole updates with a limit of 350 tiles: 0.6 % slower at 4096
+// environments and [512, 256, 128], 2.2 % at 1501 and [400, 200, 100]; with 1400: 1.2 % slower and the same), and short
+// contractions (K <= 64, bound by their output) also use them.
 enum TileCfg { TILE_128x128, TILE_64x128, TILE_128x64, TILE_128x32 };
 
 static TileCfg pick_tile(GemmMode mode, const GemmBatch& batch) {
