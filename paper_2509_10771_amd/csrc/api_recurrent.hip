@@ -221,6 +221,9 @@ struct RnnBufs {          // per memory, one column-wise minibatch (rows = T * n
   float* direct = nullptr;  // [nb, H] carried between backward steps (GRU: dh z, LSTM: gradient w.r.t. c)
   SplitPlan plan;           // layer 0: W_ih / b_ih, layer 1: W_hh / b_hh
   float* partials = nullptr;
+  uint16_t* pack_ih = nullptr;    // split weights (launch_pack_weights): W_ih, W_hh and its transpose
+  uint16_t* pack_hh = nullptr;
+  uint16_t* pack_hh_t = nullptr;
 };
 
 struct RnnPlan {
@@ -248,6 +251,41 @@ void carve_memory(Carver& c, const rslx_memory& g, int32_t rows, int32_t nb, Rnn
   plan_layer(b.plan, 0, g.in_dim, (int)GH, rows, group, false);
   plan_layer(b.plan, 1, g.hidden, (int)GH, rows, group, false);
   b.partials = c.take<float>((size_t)b.plan.total);
+  b.pack_ih = c.take<uint16_t>((size_t)3 * WeightPack::padded(g.in_dim) * GH);
+  if (seq_supported(g.cell, g.hidden)) {
+    b.pack_hh = c.take<uint16_t>(3 * H * GH);
+    b.pack_hh_t = c.take<uint16_t>(3 * H * GH);
+  }
+}
+
+// Adds a memory's split weights to a batch.
+void pack_add_memory(PackBatch& b, const rslx_memory& g, const RnnBufs& m) {
+  const int H = g.hidden, GH = gate_width(g);
+  const float* w_hh = g.params + gru_off_whh(g);
+  b.job[b.count++] = PackJob{g.params, m.pack_ih, g.in_dim, GH, WeightPack::padded(g.in_dim) / 16, GH, 1, 0};
+  if (m.pack_hh) {
+    b.job[b.count++] = PackJob{w_hh, m.pack_hh, H, GH, H / 16, GH, 1, H};
+    b.job[b.count++] = PackJob{w_hh, m.pack_hh_t, GH, H, GH / 16, 1, GH, H};
+  }
+}
+
+// The roll-out of all memories of a call goes through one launch each way where their common width has that kernel.
+bool memories_seq(const rslx_memory* const* mem, int count) {
+  for (int k = 0; k < count; ++k)
+    if (!seq_supported(mem[k]->cell, mem[k]->hidden) || mem[k]->hidden != mem[0]->hidden) return false;
+  return true;
+}
+
+SeqArgs seq_args(const rslx_memory* const* mem, RnnBufs* const* mb, int count, const int32_t* ridx, const uint8_t* dones, int T, int nb) {
+  SeqArgs a;
+  memset(&a, 0, sizeof a);
+  a.n_nets = count; a.nb = nb; a.T = T; a.H = mem[0]->hidden; a.cell = mem[0]->cell; a.done = dones; a.ridx = ridx;
+  for (int k = 0; k < count; ++k) {
+    const rslx_memory& g = *mem[k];
+    a.net[k] = SeqNet{mb[k]->pack_hh, mb[k]->pack_hh_t, g.params + gru_off_whh(g), g.params + gru_off_bhh(g), mb[k]->gi, mb[k]->gh,
+                      mb[k]->hin, mb[k]->hs, mb[k]->dh, mb[k]->dgi, mb[k]->dgh};
+  }
+  return a;
 }
 
 void rnn_plan(Carver& c, const rslx_memory* ga, const rslx_mlp* actor, const rslx_memory* gc, const rslx_mlp* critic,
@@ -313,7 +351,8 @@ GemmProblem gate_dw_problem(const XView& x, int M, const float* dG, int H3, int3
 }
 
 // Memories forward over one column-wise minibatch: the input-side gates of all T steps in one GEMM (rows gathered
-// from the roll-out through ridx), then one fused step launch per time step for all `count` memories.
+// from the roll-out through ridx), then the recurrence of all `count` memories: one launch for the roll-out, or one fused step
+// launch per time step.  The weights' split copies (pack_add_memory) must be current.
 int32_t memories_forward(const rslx_memory* const* mem, RnnBufs* const* mb, int count, const float* const* obs,
                          const float* const* h0, const int32_t* envs, const int32_t* ridx, const uint8_t* dones, int T,
                          int nb, int N, hipStream_t s) {
@@ -330,9 +369,12 @@ int32_t memories_forward(const rslx_memory* const* mem, RnnBufs* const* mb, int 
     x.base = obs[k]; x.ld = mem[k]->in_dim; x.row_idx = ridx; x.src_rows = (int64_t)T * N;
     bi.p[k] = gate_problem(x, mem[k]->in_dim, mem[k]->params, mem[k]->params + gru_off_bih(*mem[k]), mb[k]->gi, rows,
                            gate_width(*mem[k]));
+    bi.p[k].Bp = mb[k]->pack_ih;
   }
   RSLX_HIP(launch_gemm(GEMM_FWD, bi, s));
-  for (int t = 0; t < T; ++t) {
+  const bool seq = memories_seq(mem, count);
+  if (seq) RSLX_HIP(launch_seq_fwd(seq_args(mem, mb, count, ridx, dones, T, nb), s));
+  for (int t = 0; t < (seq ? 0 : T); ++t) {
     StepFwdArgs sa;
     memset(&sa, 0, sizeof sa);
     sa.n_nets = count; sa.nb = nb; sa.cell = mem[0]->cell; sa.done = dones; sa.done_idx = ridx + (size_t)t * nb;
@@ -348,13 +390,15 @@ int32_t memories_forward(const rslx_memory* const* mem, RnnBufs* const* mb, int 
   return RSLX_OK;
 }
 
-// Back-propagation through time from mb[k]->dh (the gradient w.r.t. every step's new hidden state): one fused step
-// launch per time step, last to first, then the weight gradients of both sides of the gates over all steps at once
+// Back-propagation through time from mb[k]->dh (the gradient w.r.t. every step's new hidden state): one launch, or one
+// fused step launch per time step, last to first, then the weight gradients of both sides of the gates over all steps at once
 // (split partials, to be summed by the caller's reduction).
 int32_t memories_backward(const rslx_memory* const* mem, RnnBufs* const* mb, int count, const float* const* obs,
                           const int32_t* ridx, const uint8_t* dones, int T, int nb, int N, hipStream_t s) {
   const int rows = T * nb;
-  for (int t = T - 1; t >= 0; --t) {
+  const bool seq = memories_seq(mem, count);
+  if (seq) RSLX_HIP(launch_seq_bwd(seq_args(mem, mb, count, ridx, dones, T, nb), s));
+  for (int t = seq ? -1 : T - 1; t >= 0; --t) {
     StepBwdArgs sb;
     memset(&sb, 0, sizeof sb);
     sb.n_nets = count; sb.nb = nb; sb.cell = mem[0]->cell; sb.done = dones; sb.done_idx = ridx + (size_t)t * nb;
@@ -450,17 +494,19 @@ int32_t ppo_update_recurrent_impl(rslx_memory* gru_actor, rslx_mlp* actor, rslx_
       const int32_t* ridx = p.rows_all + ((size_t)e * cfg->minibatches + m) * rows;
       float* stats_row = stats + ((size_t)e * cfg->minibatches + m) * RSLX_NSTATS;
 
+      {
+        PackBatch pb;                  // at most 12 layers (rnn_validate) and six copies of the memories
+        pb.count = 0;
+        pack_add_net(pb, *actor, p.actor.pack, 0);
+        pack_add_net(pb, *critic, p.critic.pack, 0);
+        pack_add_memory(pb, *gru_actor, p.ma);
+        pack_add_memory(pb, *gru_critic, p.mc);
+        RSLX_HIP(launch_pack_weights(pb, s));
+      }
       RSLX_TRY(memories_forward(mem, mb, 2, obs, h0, envs, ridx, dones, T, nb, p.N, s));
 
       // ---- MLPs on the hidden states, loss head, MLP backward down to the hidden states ----
       XView xa = plain_view(p.ma.hs, gru_actor->hidden), xc = plain_view(p.mc.hs, gru_critic->hidden);
-      {
-        PackBatch pb;
-        pb.count = 0;
-        pack_add_net(pb, *actor, p.actor.pack, 0);
-        pack_add_net(pb, *critic, p.critic.pack, 0);
-        RSLX_HIP(launch_pack_weights(pb, s));
-      }
       NetJob fj[2] = {NetJob{actor, xa, rows, &p.actor.act, &p.actor.pack}, NetJob{critic, xc, rows, &p.critic.act, &p.critic.pack}};
       RSLX_TRY(forward_nets(fj, 2, s, p.fused_head));
       PpoLossArgs la;
@@ -675,12 +721,13 @@ int32_t rslx_bc_update_recurrent(rslx_memory* gru, rslx_mlp* student, const floa
       const int32_t* ridx = p.rows_all + ((size_t)e * cfg->minibatches + m) * rows;
       float* stats_row = stats + ((size_t)e * cfg->minibatches + m) * RSLX_NSTATS;
       RSLX_HIP(launch_fill(stats_row, RSLX_NSTATS, 0.f, s));
-      RSLX_TRY(memories_forward(mem, mb, 1, obs, h0s, envs, ridx, dones, T, nb, N, s));
-      XView xs = plain_view(p.mem.hs, gru->hidden);
       PackBatch pb;
       pb.count = 0;
       pack_add_net(pb, *student, p.student.pack, 0);
+      pack_add_memory(pb, *gru, p.mem);
       RSLX_HIP(launch_pack_weights(pb, s));
+      RSLX_TRY(memories_forward(mem, mb, 1, obs, h0s, envs, ridx, dones, T, nb, N, s));
+      XView xs = plain_view(p.mem.hs, gru->hidden);
       NetJob fj{student, xs, rows, &p.student.act, &p.student.pack};
       RSLX_TRY(forward_nets(&fj, 1, s));
       RSLX_HIP(launch_mse(p.student.act.out[Ls - 1], targets, ridx, rows, A, p.student.d_out, p.mse_partials, s));

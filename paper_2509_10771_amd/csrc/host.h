@@ -163,8 +163,8 @@ inline void pack_add_net(PackBatch& b, const rslx_mlp& n, const WeightPack& w, i
   for (int l = 0; l < n.n_layers; ++l) {
     const float* W = n.params + layer_offset(n, l);
     const int K = n.dims[l], N = n.dims[l + 1];
-    b.job[b.count++] = PackJob{W, const_cast<uint16_t*>(w.fwd(n, l)), K, N, WeightPack::padded(K) / 16, N, 1};
-    if (l >= dx_from) b.job[b.count++] = PackJob{W, const_cast<uint16_t*>(w.dx(n, l)), N, K, WeightPack::padded(N) / 16, 1, N};
+    b.job[b.count++] = PackJob{W, const_cast<uint16_t*>(w.fwd(n, l)), K, N, WeightPack::padded(K) / 16, N, 1, 0};
+    if (l >= dx_from) b.job[b.count++] = PackJob{W, const_cast<uint16_t*>(w.dx(n, l)), N, K, WeightPack::padded(N) / 16, 1, N, 0};
   }
 }
 

@@ -75,7 +75,10 @@ hipError_t launch_gemm(GemmMode mode, const GemmBatch& batch, hipStream_t stream
 hipError_t launch_gemm_dw_dx(const GemmBatch& bw, const GemmBatch& bx, hipStream_t stream, const GemmBatch* narrow_dw = nullptr);
 // Weights split into three bf16 parts, [step of 16 contraction indices][part][group of eight][column][8]: of the element
 // (k, c) at src[k * stride_k + c * stride_c], zero for contraction indices K .. 16 * steps - 1 (split_bf16.h).
-struct PackJob { const float* src; uint16_t* dst; int32_t K, cols, steps, stride_k, stride_c; };
+// units > 0 (launch_seq_fwd / _bwd; units % 128 == 0, K % 32 == 0): instead in blocks of 16 columns, 32 contraction indices and
+// one part, [index / 8][column][8] inside, in the order in which the eight wavefronts use them: the columns are gates of
+// `units` each, wavefront w takes units w units / 8 onwards, and blocks are ordered [step of 32][16 units][gate][part][wavefront].
+struct PackJob { const float* src; uint16_t* dst; int32_t K, cols, steps, stride_k, stride_c, units; };
 struct PackBatch { PackJob job[32]; int32_t count; };   // two networks of up to eight layers, two copies each
 hipError_t launch_pack_weights(const PackBatch& b, hipStream_t stream);
 // Number of output tiles the weight-gradient kernel uses for an [M, N] layer (big = 128x128 tiles allowed).
@@ -302,6 +305,33 @@ struct StepBwdArgs {
   const int32_t* done_idx;
 };
 hipError_t launch_step_bwd(const StepBwdArgs& a, hipStream_t stream);
+
+// All T steps of a memory in one launch each way (recurrent.hip), for up to two memories of the same cell and width.
+// Rows are step-major, r = t nb + i.  Forward: gi holds the input-side gate terms and is replaced by the activated gates
+// (GRU r, z, n; LSTM i, f, g, o); hin holds the states that the first step starts from and receives those of the others
+// (new state * (1 - done)).  Backward: reads what the forward pass left.
+struct SeqNet {
+  const uint16_t* packed;     // W_hh split (launch_pack_weights), contraction over H
+  const uint16_t* packed_t;   // the same transposed, contraction over G H
+  const float* w_hh;          // [H, G H] row-major
+  const float* b_hh;          // [G H]
+  float* gi;                  // [T nb, G H]
+  float* ghn;                 // [T nb, H] (GRU): hidden-side term of the candidate
+  float* hin;                 // [T nb, S] packed states
+  float* hs;                  // [T nb, H] new hidden states
+  const float* dh;            // [T nb, H] backward: gradient arriving from the layers above
+  float* dgi;                 // [T nb, G H] (GRU)
+  float* dg;                  // [T nb, G H]
+};
+struct SeqArgs {
+  SeqNet net[2];
+  int32_t n_nets, nb, T, H, cell;
+  const uint8_t* done;        // episode-end flags (null = none); row r reads done[ridx ? ridx[r] : i]
+  const int32_t* ridx;        // [T nb]
+};
+bool seq_supported(int32_t cell, int32_t H);
+hipError_t launch_seq_fwd(const SeqArgs& a, hipStream_t stream);
+hipError_t launch_seq_bwd(const SeqArgs& a, hipStream_t stream);
 
 // dst[i, :] = src[idx ? idx[i] : i, :] * (reset && reset[i] ? 0 : 1) for up to two [*, H] matrices; a second
 // copy of the result goes to dst2 when it is not null.

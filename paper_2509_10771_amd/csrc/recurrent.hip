@@ -1,7 +1,8 @@
-// Recurrent memory cells (GRU, LSTM), one time step per launch: the hidden-side contraction on the matrix cores with
-// the gate stage (forward) or the gate derivatives (back-propagation through time) as its epilogue, and the index
-// plumbing of column-wise minibatches.  The input-side contractions and the weight gradients run in the GEMM kernel.
+// Recurrent memory cells (GRU, LSTM): the hidden-side contraction on the matrix cores with the gate stage (forward) or the
+// gate derivatives (back-propagation through time) as its epilogue, one time step per launch or a whole roll-out, and
+// the index plumbing of column-wise minibatches.  The input-side contractions and the weight gradients run in the GEMM kernel.
 #include "kernels.h"
+#include "split_bf16.h"
 
 namespace rslx {
 namespace {
@@ -398,6 +399,389 @@ __global__ __launch_bounds__(GS_THREADS) void step_bwd_kernel(const StepBwdArgs 
   }
 }
 
+// ---- a whole roll-out in one launch each way ---------------------------------------------------------------
+// The update path's recurrence, for the width whose weights fit one CU: the states, and in the backward pass the gradients
+// and the carried term, stay in the workgroup from step to step.
+//
+// A workgroup of 8 wavefronts owns 16 batch rows of one memory and all its hidden units: no step waits for another
+// workgroup.  Wavefront w owns the hidden units w H / 8 .. (w + 1) H / 8 and all their gates, so the gate stage works on
+// the lane's own accumulators.  The products run on the bf16 matrix cores (v_mfma_f32_16x16x32_bf16) on operands split in
+// three (gemm.hip has the arithmetic): operand A holds 16 weight columns (forward: one gate of 16 hidden units; backward:
+// 16 hidden units), operand B the 16 rows, D[4 * (lane / 16) + r][lane % 16] the four consecutive units of a row.
+//
+// The split weights stay in registers and LDS for all steps (295 KB for a GRU of 128; what a width of 256 has, 1.2 MB, does
+// not fit and would be streamed from the L2 on every step: 12 to 17 us a step, where a launch per step takes 10 to 19).
+// What is left of a step is the contraction (1 us of matrix instructions), the gate stage and two barriers, one after the
+// other; its own operands are requested a whole step ahead.  Measured at 16 to 1024 rows and two memories of 128, us a step,
+// one launch per step in brackets: GRU forward 3.6 to 3.9 (6.7 to 7.8), backward 3.7 to 4.3 (6.2 to 8.3); LSTM forward 4.7 to
+// 5.0 (7.0 to 8.9), backward 4.0 to 4.3 (7.3 to 8.5).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int SQ_ROWS = 16;
+constexpr int SQ_WAVES = 8;
+constexpr int SQ_THREADS = 64 * SQ_WAVES;
+constexpr int SQ_BLOCK = 1024;         // bytes of one part of a 16-column, 32-index operand block
+
+// Operand B in LDS: 16 bytes are one part of eight consecutive contraction indices of a row, [part][index / 8][row].
+template <int K> __device__ __forceinline__ int sq_unit(int part, int k8, int row) { return part * (K * 32) + (k8 * SQ_ROWS + row) * 16; }
+
+// Splits the values of contraction indices k .. k + 3 (k % 4 == 0) of a row and writes them to LDS.
+template <int K>
+__device__ __forceinline__ void sq_put(char* x, int k, int row, f4 v, float scale) {
+  uint2 p[3];
+  split_pair(scale * v[0], scale * v[1], p[0].x, p[1].x, p[2].x);
+  split_pair(scale * v[2], scale * v[3], p[0].y, p[1].y, p[2].y);
+#pragma unroll
+  for (int s = 0; s < 3; ++s) *reinterpret_cast<uint2*>(x + sq_unit<K>(s, k >> 3, row) + (k & 4) * 2) = p[s];
+}
+
+// The contraction of one step: acc[tile] += W(tile)^T X over K indices, TILES tiles of 16 weight columns per wavefront.  Blocks
+// (16 columns, 32 indices, one part) are numbered in the order of their use; the first NREG live in registers, the others in LDS.
+template <int K, int TILES, int NREG>
+struct SeqContract {
+  static constexpr int KS = K / 32, GB = 3 * TILES, NB = KS * GB, NLDS = NB - NREG;
+  static constexpr int LDS_BYTES = NLDS * SQ_WAVES * SQ_BLOCK;
+
+  u32x4 reg[NREG];
+  char* lw;                                // the lane's place in the wavefront's blocks in LDS
+
+  __device__ __forceinline__ void setup(const uint16_t* packed, int wave, int lane, char* lds) {
+    const char* w = reinterpret_cast<const char*>(packed) + wave * SQ_BLOCK + lane * 16;
+    lw = lds + (wave * NLDS) * SQ_BLOCK + lane * 16;
+#pragma unroll
+    for (int n = 0; n < NREG; ++n) reg[n] = *reinterpret_cast<const u32x4*>(w + n * (SQ_WAVES * SQ_BLOCK));
+#pragma unroll
+    for (int n = NREG; n < NB; ++n)
+      *reinterpret_cast<u32x4*>(lw + (n - NREG) * SQ_BLOCK) = *reinterpret_cast<const u32x4*>(w + n * (SQ_WAVES * SQ_BLOCK));
+#pragma unroll
+    for (int n = 0; n < NREG; ++n) asm volatile("" : "+v"(reg[n]));     // held, not loaded again
+  }
+  // NACC: TILES, or 2 TILES with alternate steps of 32 in sums of their own (shorter chains where there are few tiles)
+  template <int NACC>
+  __device__ __forceinline__ void run(const char* x, int lane, f4 (&acc)[NACC]) {
+    const int kq = lane >> 4, m = lane & 15;
+    const char* xb = x + sq_unit<K>(0, kq, m);
+    bf16x8 b[2][3];
+    auto read_x = [&](int ks) {
+#pragma unroll
+      for (int s = 0; s < 3; ++s) b[ks & 1][s] = *reinterpret_cast<const bf16x8*>(xb + s * (K * 32) + ks * (4 * SQ_ROWS * 16));
+    };
+    read_x(0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      if (ks + 1 < KS) read_x(ks + 1);
+      bf16x8 a[GB];
+#pragma unroll
+      for (int n = 0; n < GB; ++n) {
+        const int id = ks * GB + n;
+        a[n] = __builtin_bit_cast(bf16x8, id < NREG ? reg[id < NREG ? id : 0] : *reinterpret_cast<const u32x4*>(lw + (id - NREG) * SQ_BLOCK));
+      }
+      constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+      for (int p = 0; p < 6; ++p)
+#pragma unroll
+        for (int i = 0; i < TILES; ++i) {
+          const int at = i + (NACC == 2 * TILES ? (ks & 1) * TILES : 0);
+          acc[at] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[3 * i + PA[p]], b[ks & 1][PB[p]], acc[at], 0, 0, 0);
+        }
+    }
+  }
+};
+
+// Sums of fp32 products in place of the non-finite ones of a tile (such inputs have no split, see gemm.hip).  w: element
+// (k, column) at w[k * wk + column * wc], `col` the tile's first column; x: the lane's row, contiguous along k.
+__device__ __forceinline__ void sq_repeat_fp32(const float* w, long wk, long wc, const float* x, int K, int lane, f4& acc) {
+  const int kq = lane >> 4, m = lane & 15;
+  f4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+  for (int k0 = 0; k0 < K; k0 += 16) {
+    float a[4], b[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      a[i] = w[(long)(k0 + 4 * i + kq) * wk + m * wc];
+      b[i] = x[k0 + 4 * i + kq];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[i], c, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (!__builtin_isfinite(acc[r])) acc[r] = c[r];
+}
+
+// Blocks in registers, as many as it takes for the rest to fit LDS, forward and backward.
+template <int CELL, int H> struct SeqShape;
+template <> struct SeqShape<CELL_GRU, 128> { static constexpr int G = 3, REGF = 18, REGB = 21; };
+template <> struct SeqShape<CELL_LSTM, 128> { static constexpr int G = 4, REGF = 30, REGB = 34; };
+
+template <int CELL, int H> struct SeqFwd {
+  using S = SeqShape<CELL, H>;
+  static constexpr int UT = H / (16 * SQ_WAVES), W = CELL == CELL_LSTM ? 2 * H : H;      // unit tiles per wavefront, state width
+  using C = SeqContract<H, S::G * UT, S::REGF>;
+  static constexpr int X_BYTES = H * 96, BIAS = X_BYTES, WEIGHTS = BIAS + S::G * H * 4;
+  static constexpr int LDS = WEIGHTS + C::LDS_BYTES;
+};
+
+template <int CELL, int H>
+__global__ __launch_bounds__(SQ_THREADS, 2) void seq_fwd_kernel(const SeqArgs a) {
+  using F = SeqFwd<CELL, H>;
+  constexpr int G = F::S::G, UT = F::UT, W = F::W, GH = G * H;
+  extern __shared__ __align__(16) char lds[];
+  const SeqNet& n = a.net[blockIdx.y];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b = lane & 15, kq = lane >> 4, j0 = wave * (H / SQ_WAVES);
+  const int nb = a.nb, row = min((int)blockIdx.x * SQ_ROWS + b, nb - 1);
+  const bool ok = (int)blockIdx.x * SQ_ROWS + b < nb;       // rows past the end repeat the last one and store nothing
+  float* bias = reinterpret_cast<float*>(lds + F::BIAS);
+  for (int i = tid; i < GH; i += SQ_THREADS) bias[i] = n.b_hh[i];
+  const int ju = j0 + 4 * kq;                               // the lane's units: ju + 16 u + 0 .. 3
+  const float scale = split_scale(b), unscale = split_unscale(b);
+
+  f4 gi[UT][G], gi_next[UT][G], st[UT], h[UT];           // st: what the gates blend with (GRU: h, LSTM: c)
+#pragma unroll
+  for (int u = 0; u < UT; ++u) {
+    const float* s0 = n.hin + (long)row * W + ju + 16 * u;
+    const f4 h0 = ld4(s0);
+    st[u] = CELL == CELL_LSTM ? ld4(s0 + H) : h0;
+    sq_put<H>(lds, ju + 16 * u, b, h0, scale);
+#pragma unroll
+    for (int g = 0; g < G; ++g) gi[u][g] = ld4(n.gi + (long)row * GH + g * H + ju + 16 * u);
+  }
+  // episode ends: the flag of a step is requested one step ahead, its place two steps ahead
+  auto place = [&](int t) { return a.ridx ? a.ridx[(long)min(t, a.T - 1) * nb + row] : row; };
+  int flag = a.done ? a.done[place(0)] : 0, flag_next = 0, at = place(1), at_next = 0;
+  typename F::C c;
+  c.setup(n.packed, wave, lane, lds + F::WEIGHTS);
+  __syncthreads();
+
+#pragma unroll 1
+  for (int t = 0; t < a.T; ++t) {
+    const long r0 = (long)t * nb + row, r1 = (long)min(t + 1, a.T - 1) * nb + row;
+#pragma unroll
+    for (int u = 0; u < UT; ++u)
+#pragma unroll
+      for (int g = 0; g < G; ++g) gi_next[u][g] = ld4(n.gi + r1 * GH + g * H + ju + 16 * u);
+    if (a.done) flag_next = a.done[at];
+    at_next = place(t + 2);
+    f4 acc[UT * G];
+#pragma unroll
+    for (int i = 0; i < UT * G; ++i) acc[i] = f4{0.f, 0.f, 0.f, 0.f};
+    c.run(lds, lane, acc);
+    float z = 0.f;                                          // becomes NaN with any non-finite sum
+#pragma unroll
+    for (int i = 0; i < UT * G; ++i) {
+      acc[i] *= unscale;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) z = fmaf(acc[i][r], 0.f, z);
+    }
+    if (__any(!(z == 0.f))) {
+#pragma unroll
+      for (int i = 0; i < UT * G; ++i) sq_repeat_fp32(n.w_hh + i % G * H + j0 + 16 * (i / G), GH, 1, n.hin + r0 * W, H, lane, acc[i]);
+    }
+    const float keep = flag ? 0.f : 1.f;
+    f4 out[UT][G + 1];                                   // the gates as the backward pass reads them, and ghn
+#pragma unroll
+    for (int u = 0; u < UT; ++u) {
+      f4 bv[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) bv[g] = ld4(bias + g * H + ju + 16 * u);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if constexpr (CELL == CELL_GRU) {
+          const float ghr = acc[u * G][r] + bv[0][r], ghz = acc[u * G + 1][r] + bv[1][r], ghn = acc[u * G + 2][r] + bv[2][r];
+          const float rr = sigmoidf_(gi[u][0][r] + ghr);
+          const float zz = sigmoidf_(gi[u][1][r] + ghz);
+          const float nn = tanhf_(gi[u][2][r] + rr * ghn);
+          h[u][r] = (1.0f - zz) * nn + zz * st[u][r];
+          out[u][0][r] = rr; out[u][1][r] = zz; out[u][2][r] = nn; out[u][3][r] = ghn;
+          st[u][r] = h[u][r] * keep;
+        } else {
+          float pre[4];
+#pragma unroll
+          for (int g = 0; g < 4; ++g) pre[g] = gi[u][g][r] + acc[u * G + g][r] + bv[g][r];
+          const float ii = sigmoidf_(pre[0]), ff = sigmoidf_(pre[1]), gg = tanhf_(pre[2]), oo = sigmoidf_(pre[3]);
+          const float cn = ff * st[u][r] + ii * gg;
+          h[u][r] = oo * tanhf_(cn);
+          out[u][0][r] = ii; out[u][1][r] = ff; out[u][2][r] = gg; out[u][3][r] = oo;
+          st[u][r] = cn * keep;
+        }
+      }
+    }
+    __syncthreads();                                        // every wavefront has read the old states
+    const bool more = t + 1 < a.T;
+#pragma unroll
+    for (int u = 0; u < UT; ++u) sq_put<H>(lds, ju + 16 * u, b, h[u] * keep, scale);
+#pragma unroll
+    for (int u = 0; u < UT; ++u)
+#pragma unroll
+      for (int g = 0; g < G; ++g) gi[u][g] = gi_next[u][g];
+    flag = flag_next;
+    at = at_next;
+    if (ok) {
+#pragma unroll
+      for (int u = 0; u < UT; ++u) {
+        const int j = ju + 16 * u;
+        st4(n.hs + r0 * H + j, h[u]);
+        if (more) {
+          float* nx = n.hin + (r0 + nb) * W + j;
+          st4(nx, h[u] * keep);
+          if (CELL == CELL_LSTM) st4(nx + H, st[u]);
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) st4(n.gi + r0 * GH + g * H + j, out[u][g]);
+        if (CELL == CELL_GRU) st4(n.ghn + r0 * H + j, out[u][3]);
+      }
+    }
+    __syncthreads();
+  }
+}
+
+template <int CELL, int H> struct SeqBwd {
+  using S = SeqShape<CELL, H>;
+  static constexpr int UT = H / (16 * SQ_WAVES), W = CELL == CELL_LSTM ? 2 * H : H, GH = S::G * H;
+  using C = SeqContract<GH, UT, S::REGB>;
+  static constexpr int X_BYTES = GH * 96, WEIGHTS = X_BYTES;
+  static constexpr int LDS = WEIGHTS + C::LDS_BYTES;
+};
+
+// With keep = 1 - done of the step and back = dg(t + 1) W_hh^T:
+//   GRU:  dh = dh_ext + keep (back + carry);  dgi = [dr, dz, dn], dg = [dr, dz, dn r] (pre-activation gradients), carry = dh z
+//   LSTM: dh = dh_ext + keep back, dc = keep carry;  dg = d loss / d pre-activations,  carry = (dc + dh o (1 - tanh^2 c')) f
+template <int CELL, int H>
+__global__ __launch_bounds__(SQ_THREADS, 2) void seq_bwd_kernel(const SeqArgs a) {
+  using F = SeqBwd<CELL, H>;
+  constexpr int G = F::S::G, UT = F::UT, W = F::W, GH = F::GH;
+  extern __shared__ __align__(16) char lds[];
+  const SeqNet& n = a.net[blockIdx.y];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b = lane & 15, kq = lane >> 4, j0 = wave * (H / SQ_WAVES);
+  const int nb = a.nb, row = min((int)blockIdx.x * SQ_ROWS + b, nb - 1);
+  const bool ok = (int)blockIdx.x * SQ_ROWS + b < nb;
+  const int ju = j0 + 4 * kq;
+  const float scale = split_scale(b), unscale = split_unscale(b);
+
+  struct Operands { f4 gate[UT][4], st[UT], dh[UT]; };   // gate: GRU r, z, n, ghn; LSTM i, f, g, o.  st: h or c before the step
+  auto operands = [&](int t, Operands& o) {
+    const long r0 = (long)t * nb + row;
+#pragma unroll
+    for (int u = 0; u < UT; ++u) {
+      const int j = ju + 16 * u;
+#pragma unroll
+      for (int g = 0; g < G; ++g) o.gate[u][g] = ld4(n.gi + r0 * GH + g * H + j);
+      if (CELL == CELL_GRU) o.gate[u][3] = ld4(n.ghn + r0 * H + j);
+      o.st[u] = ld4(n.hin + r0 * W + (CELL == CELL_LSTM ? H : 0) + j);
+      o.dh[u] = ld4(n.dh + r0 * H + j);
+    }
+  };
+  Operands now, next;
+  operands(a.T - 1, now);
+  f4 carry[UT];
+#pragma unroll
+  for (int u = 0; u < UT; ++u) carry[u] = f4{0.f, 0.f, 0.f, 0.f};
+  // the flag of step t gates what step t + 1 sends back: requested one step ahead, its place two steps ahead
+  auto place = [&](int t) { return a.ridx ? a.ridx[(long)max(t, 0) * nb + row] : row; };
+  int flag = 0, flag_next = 0, at = place(a.T - 2), at_next = 0;
+  typename F::C c;
+  c.setup(n.packed_t, wave, lane, lds + F::WEIGHTS);
+
+#pragma unroll 1
+  for (int t = a.T - 1; t >= 0; --t) {
+    const long r0 = (long)t * nb + row;
+    operands(max(t - 1, 0), next);
+    if (a.done) flag_next = a.done[at];
+    at_next = place(t - 2);
+    f4 back[UT];
+#pragma unroll
+    for (int u = 0; u < UT; ++u) back[u] = f4{0.f, 0.f, 0.f, 0.f};
+    if (t + 1 < a.T) {
+      f4 acc[2 * UT];
+#pragma unroll
+      for (int i = 0; i < 2 * UT; ++i) acc[i] = f4{0.f, 0.f, 0.f, 0.f};
+      c.run(lds, lane, acc);
+      float z = 0.f;
+#pragma unroll
+      for (int u = 0; u < UT; ++u) {
+        back[u] = (acc[u] + acc[UT + u]) * unscale;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) z = fmaf(back[u][r], 0.f, z);
+      }
+      if (__any(!(z == 0.f))) {
+#pragma unroll
+        for (int u = 0; u < UT; ++u)
+          sq_repeat_fp32(n.w_hh + (long)(j0 + 16 * u) * GH, 1, GH, n.dg + (r0 + nb) * GH, GH, lane, back[u]);
+      }
+    }
+    const float keep = flag ? 0.f : 1.f;
+    f4 d[UT][G], dn[UT];
+#pragma unroll
+    for (int u = 0; u < UT; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if constexpr (CELL == CELL_GRU) {
+          float dh = now.dh[u][r];
+          if (t + 1 < a.T) dh += (back[u][r] + carry[u][r]) * keep;
+          const float rr = now.gate[u][0][r], zz = now.gate[u][1][r], nn = now.gate[u][2][r], ghn = now.gate[u][3][r];
+          const float dz = dh * (now.st[u][r] - nn);
+          const float dn_pre = dh * (1.0f - zz) * (1.0f - nn * nn);
+          d[u][0][r] = dn_pre * ghn * rr * (1.0f - rr);
+          d[u][1][r] = dz * zz * (1.0f - zz);
+          d[u][2][r] = dn_pre * rr;
+          dn[u][r] = dn_pre;
+          carry[u][r] = dh * zz;
+        } else {
+          float dh = now.dh[u][r], dc = 0.f;
+          if (t + 1 < a.T) { dh += back[u][r] * keep; dc = carry[u][r] * keep; }
+          const float ii = now.gate[u][0][r], ff = now.gate[u][1][r], gg = now.gate[u][2][r], oo = now.gate[u][3][r];
+          const float tc = tanhf_(ff * now.st[u][r] + ii * gg);
+          const float dct = dc + dh * oo * (1.0f - tc * tc);
+          carry[u][r] = dct * ff;
+          d[u][0][r] = dct * gg * ii * (1.0f - ii);
+          d[u][1][r] = dct * now.st[u][r] * ff * (1.0f - ff);
+          d[u][2][r] = dct * ii * (1.0f - gg * gg);
+          d[u][G - 1][r] = dh * tc * oo * (1.0f - oo);
+        }
+      }
+    __syncthreads();                                        // every wavefront has read the gradients of the step after
+    if (t > 0) {
+#pragma unroll
+      for (int u = 0; u < UT; ++u)
+#pragma unroll
+        for (int g = 0; g < G; ++g) sq_put<GH>(lds, g * H + ju + 16 * u, b, d[u][g], scale);
+    }
+    now = next;
+    flag = flag_next;
+    at = at_next;
+    if (ok) {
+#pragma unroll
+      for (int u = 0; u < UT; ++u) {
+        const long o = r0 * GH + ju + 16 * u;
+#pragma unroll
+        for (int g = 0; g < G; ++g) st4(n.dg + o + g * H, d[u][g]);
+        if (CELL == CELL_GRU) { st4(n.dgi + o, d[u][0]); st4(n.dgi + o + H, d[u][1]); st4(n.dgi + o + 2 * H, dn[u]); }
+      }
+    }
+    __syncthreads();
+  }
+}
+
+template <int CELL, int H>
+hipError_t seq_launch(const SeqArgs& a, bool backward, hipStream_t stream) {
+  const dim3 grid((a.nb + SQ_ROWS - 1) / SQ_ROWS, a.n_nets);
+  const void* kernel = backward ? reinterpret_cast<const void*>(seq_bwd_kernel<CELL, H>) : reinterpret_cast<const void*>(seq_fwd_kernel<CELL, H>);
+  const int bytes = backward ? SeqBwd<CELL, H>::LDS : SeqFwd<CELL, H>::LDS;
+  static_assert(SeqBwd<CELL, H>::LDS <= 160 * 1024 && SeqFwd<CELL, H>::LDS <= 160 * 1024, "LDS");
+  hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e != hipSuccess) return e;
+  if (backward) hipLaunchKernelGGL((seq_bwd_kernel<CELL, H>), grid, dim3(SQ_THREADS), bytes, stream, a);
+  else hipLaunchKernelGGL((seq_fwd_kernel<CELL, H>), grid, dim3(SQ_THREADS), bytes, stream, a);
+  return hipGetLastError();
+}
+
+hipError_t seq_dispatch(const SeqArgs& a, bool backward, hipStream_t stream) {
+  if (a.nb <= 0 || a.n_nets <= 0 || a.T <= 0) return hipSuccess;
+  return a.cell == CELL_LSTM ? seq_launch<CELL_LSTM, 128>(a, backward, stream) : seq_launch<CELL_GRU, 128>(a, backward, stream);
+}
+
 __global__ __launch_bounds__(256) void row_gather_kernel(const RowGatherArgs a) {
   const RowGatherJob& J = a.job[blockIdx.y];
   const int q = J.H >> 2;
@@ -470,6 +854,20 @@ hipError_t launch_step_bwd(const StepBwdArgs& a, hipStream_t stream) {
   if (a.cell == CELL_LSTM) hipLaunchKernelGGL(step_bwd_kernel<CELL_LSTM>, grid, dim3(GS_THREADS), 0, stream, a);
   else hipLaunchKernelGGL(step_bwd_kernel<CELL_GRU>, grid, dim3(GS_THREADS), 0, stream, a);
   return hipGetLastError();
+}
+
+bool seq_supported(int32_t cell, int32_t H) { return (cell == CELL_GRU || cell == CELL_LSTM) && H == 128; }
+
+hipError_t launch_seq_fwd(const SeqArgs& a, hipStream_t stream) {
+  const double G = a.cell == CELL_LSTM ? 4 : 3;
+  TraceScope ts(stream, a.cell == CELL_LSTM ? "lstm_seq_fwd" : "gru_seq_fwd", 2.0 * a.n_nets * a.T * (double)a.nb * G * a.H * a.H, 0.0);
+  return seq_dispatch(a, false, stream);
+}
+
+hipError_t launch_seq_bwd(const SeqArgs& a, hipStream_t stream) {
+  const double G = a.cell == CELL_LSTM ? 4 : 3;
+  TraceScope ts(stream, a.cell == CELL_LSTM ? "lstm_seq_bwd" : "gru_seq_bwd", 2.0 * a.n_nets * (a.T - 1) * (double)a.nb * G * a.H * a.H, 0.0);
+  return seq_dispatch(a, true, stream);
 }
 
 hipError_t launch_row_gather(const RowGatherArgs& a, hipStream_t stream) {
