@@ -176,7 +176,10 @@ def _ptr(t):
 
 
 def _stream():
-    """torch's current stream; without a GPU (host-side argument checks only) the NULL stream."""
+    """torch's current stream; without a GPU (host-side argument checks only) the NULL stream.  Once torch runs on the GPU its
+    handle is asked for directly: 0.3 us a call, where is_available() and a Stream object take 4.6 of a small call's 11."""
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
 
 
