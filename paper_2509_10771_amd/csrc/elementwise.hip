@@ -44,15 +44,15 @@ hipError_t launch_fill(float* p, int64_t n, float value, hipStream_t stream) {
 
 // ---- GAE ----------------------------------------------------------------------------------------------
 // One lane per environment column: loads are coalesced across n, the T-step recurrence runs in registers.
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void gae_scan_kernel(const float* __restrict__ rewards, const float* __restrict__ values,
+constexpr int GAE_COLS = 64;           // environments per workgroup of the kernel below, and of this one's partial sums
+__global__ __launch_bounds__(256) void gae_scan_kernel(const float* __restrict__ rewards, const float* __restrict__ values,
                                                          const float* __restrict__ last_values,
                                                          const uint8_t* __restrict__ dones,
                                                          const uint8_t* __restrict__ timeouts, int T, int N, float gamma,
                                                          float lam, float* __restrict__ adv, float* __restrict__ ret,
                                                          double* __restrict__ partials) {
-  __shared__ double smem[BLOCK / WAVE];
-  const int n = blockIdx.x * BLOCK + threadIdx.x;
+  __shared__ double smem[4];
+  const int n = blockIdx.x * 256 + threadIdx.x;
   double s = 0.0, q = 0.0;
   if (n < N) {
     float a_next = 0.f;
@@ -77,6 +77,89 @@ __global__ __launch_bounds__(BLOCK) void gae_scan_kernel(const float* __restrict
   if (partials != nullptr) {
     double ts = block_sum(s, smem);
     double tq = block_sum(q, smem);
+    if (threadIdx.x == 0) {
+      partials[2 * blockIdx.x] = ts;
+      partials[2 * blockIdx.x + 1] = tq;
+    }
+  }
+}
+
+// The same for fewer columns than fill the chip with one lane each: what a column costs there is the latency of its loads, one
+// batch of steps after the other.  Here 8 wavefronts share 64 columns: each takes every eighth step, so all of up to
+// GAE_CHUNK steps are requested at once, the first wavefront runs the recurrence from LDS, and all write the results.  Whole
+// calls of 24 steps, one lane per column and this: 10.3 and 8.5 us at 4096 columns, 11.0 and 9.2 at 16 384, 20.3 and 17.9 at
+// 65 535; of 8 steps the same below 40 000, 11.3 and 13.0 at 65 535; of 48 steps 15.2 and 11.5, 16.5 and 12.9, 31.7 and 27.9.
+constexpr int GAE_WAVES = 8, GAE_CHUNK = 32, GAE_STEPS = GAE_CHUNK / GAE_WAVES;
+__global__ __launch_bounds__(64 * GAE_WAVES) void gae_scan_narrow_kernel(const float* __restrict__ rewards, const float* __restrict__ values,
+                                                                         const float* __restrict__ last_values,
+                                                                         const uint8_t* __restrict__ dones,
+                                                                         const uint8_t* __restrict__ timeouts, int T, int N, float gamma,
+                                                                         float lam, float* __restrict__ adv, float* __restrict__ ret,
+                                                                         double* __restrict__ partials) {
+  __shared__ float delta[GAE_CHUNK][GAE_COLS], decay[GAE_CHUNK][GAE_COLS];   // decay: gamma lambda (1 - done); then the advantage
+  __shared__ double smem[GAE_WAVES];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n = blockIdx.x * GAE_COLS + lane, nc = min(n, N - 1);
+  const float gl = gamma * lam;
+  double s = 0.0, q = 0.0;
+  float a_next = 0.f;
+  const float v_last = last_values[nc];
+  for (int t_end = T; t_end > 0; t_end -= GAE_CHUNK) {
+    const int t0 = max(t_end - GAE_CHUNK, 0);
+    float r[GAE_STEPS], v[GAE_STEPS], v_next[GAE_STEPS];
+    uint8_t done[GAE_STEPS], late[GAE_STEPS];
+#pragma unroll
+    for (int i = 0; i < GAE_STEPS; ++i) {
+      const int t = min(t0 + wave + GAE_WAVES * i, t_end - 1);       // past the end: the last step again, not used
+      const long o = (long)t * N + nc;
+      r[i] = rewards[o];
+      v[i] = values[o];
+      v_next[i] = values[t + 1 < T ? o + N : o];
+      done[i] = dones[o];
+      late[i] = timeouts != nullptr ? timeouts[o] : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < GAE_STEPS; ++i) {
+      const int c = wave + GAE_WAVES * i;
+      if (t0 + c >= t_end) break;
+      const float nd = done[i] ? 0.f : 1.f;
+      const float rw = late[i] ? r[i] + gamma * v[i] : r[i];
+      delta[c][lane] = rw + gamma * nd * (t0 + c + 1 < T ? v_next[i] : v_last) - v[i];
+      decay[c][lane] = gl * nd;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      for (int c = t_end - t0 - 1; c >= 0; c -= 8) {
+        float d[8], g[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) { d[k] = delta[max(c - k, 0)][lane]; g[k] = decay[max(c - k, 0)][lane]; }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          if (c - k < 0) break;
+          a_next = d[k] + g[k] * a_next;
+          decay[c - k][lane] = a_next;
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < GAE_STEPS; ++i) {
+      const int c = wave + GAE_WAVES * i;
+      if (t0 + c >= t_end) break;
+      if (n < N) {
+        const float a = decay[c][lane];
+        const long o = (long)(t0 + c) * N + n;
+        adv[o] = a;
+        ret[o] = a + v[i];
+        s += (double)a;
+        q += (double)a * (double)a;
+      }
+    }
+    __syncthreads();
+  }
+  if (partials != nullptr) {
+    const double ts = block_sum(s, smem);
+    const double tq = block_sum(q, smem);
     if (threadIdx.x == 0) {
       partials[2 * blockIdx.x] = ts;
       partials[2 * blockIdx.x + 1] = tq;
@@ -113,6 +196,9 @@ __global__ __launch_bounds__(256) void adv_normalize_kernel(float* __restrict__ 
   __shared__ double smem[4];
   __shared__ float s_mi[2];
   float mean, inv;
+  const long i0 = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
+  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (i0 + 3 < count) v = *reinterpret_cast<const float4*>(adv + i0);      // requested before the sums that it waits for
   if (mean_inv != nullptr) {
     mean = mean_inv[0]; inv = mean_inv[1];
   } else {
@@ -133,17 +219,15 @@ __global__ __launch_bounds__(256) void adv_normalize_kernel(float* __restrict__ 
     __syncthreads();
     mean = s_mi[0]; inv = s_mi[1];
   }
-  long i = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
-  if (i + 3 < count) {
-    float4 v = *reinterpret_cast<float4*>(adv + i);
+  if (i0 + 3 < count) {
     v.x = (v.x - mean) * inv; v.y = (v.y - mean) * inv; v.z = (v.z - mean) * inv; v.w = (v.w - mean) * inv;
-    *reinterpret_cast<float4*>(adv + i) = v;
+    *reinterpret_cast<float4*>(adv + i0) = v;
   } else {
-    for (; i < count; ++i) adv[i] = (adv[i] - mean) * inv;
+    for (long i = i0; i < count; ++i) adv[i] = (adv[i] - mean) * inv;
   }
 }
 
-static int gae_block(int32_t N) { return N >= 65536 ? 256 : 64; }
+static int gae_block(int32_t N) { return N >= 65536 ? 256 : GAE_COLS; }
 int gae_num_blocks(int32_t N) { int b = gae_block(N); return (N + b - 1) / b; }
 
 hipError_t launch_gae(const float* rewards, const float* values, const float* last_values, const uint8_t* dones,
@@ -154,10 +238,10 @@ hipError_t launch_gae(const float* rewards, const float* values, const float* la
   TraceScope ts(stream, normalize ? "gae_scan+normalize" : "gae_scan", 0.0,
                 (double)T * N * (normalize ? 25.0 : 17.0) + 4.0 * N);
   if (gae_block(N) == 256)
-    hipLaunchKernelGGL((gae_scan_kernel<256>), dim3(nb), dim3(256), 0, stream, rewards, values, last_values, dones,
+    hipLaunchKernelGGL(gae_scan_kernel, dim3(nb), dim3(256), 0, stream, rewards, values, last_values, dones,
                        timeouts, T, N, gamma, lam, adv, ret, part);
   else
-    hipLaunchKernelGGL((gae_scan_kernel<64>), dim3(nb), dim3(64), 0, stream, rewards, values, last_values, dones,
+    hipLaunchKernelGGL(gae_scan_narrow_kernel, dim3(nb), dim3(64 * GAE_WAVES), 0, stream, rewards, values, last_values, dones,
                        timeouts, T, N, gamma, lam, adv, ret, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !normalize) return e;
@@ -1338,6 +1422,9 @@ hipError_t launch_stage_input(const float* in, int32_t ld, int32_t B, int32_t D,
 }
 
 // ---- RND reward ---------------------------------------------------------------------------------------
+// 16 lanes share a row, 64 rows a workgroup: a row is read 256 bytes at a time.  16 384 rows of 64: 4.9 us; one lane per row,
+// which walks its own row 4 bytes at a time, takes 18.5.
+constexpr int RND_ROWS = 64, RND_LANES = 16;
 int rnd_num_blocks(int32_t N) { return (N + 255) / 256; }
 
 __global__ __launch_bounds__(256) void rnd_raw_kernel(const float* __restrict__ yp, const float* __restrict__ yt, int N,
