@@ -872,7 +872,7 @@ static size_t rnd_carve(Carver& c, const rslx_mlp* net, int32_t N, NetBufs* bp, 
   NetBufs p, t;
   carve_net(c, *net, N, false, p);
   carve_net(c, *net, N, false, t);
-  double* pp = c.take<double>((size_t)rnd_num_blocks(N) * 2 + 2);
+  double* pp = c.take<double>((size_t)rnd_num_blocks(N) * 2 + 2);       // the sums, and a copy of the three statistics
   if (bp) *bp = p;
   if (bt) *bt = t;
   if (partials) *partials = pp;

@@ -1425,22 +1425,47 @@ hipError_t launch_stage_input(const float* in, int32_t ld, int32_t B, int32_t D,
 // 16 lanes share a row, 64 rows a workgroup: a row is read 256 bytes at a time.  16 384 rows of 64: 4.9 us; one lane per row,
 // which walks its own row 4 bytes at a time, takes 18.5.
 constexpr int RND_ROWS = 64, RND_LANES = 16;
-int rnd_num_blocks(int32_t N) { return (N + 255) / 256; }
+int rnd_num_blocks(int32_t N) { return (N + RND_ROWS - 1) / RND_ROWS; }
 
+// `running` is copied to running_old for the launch that follows, whose workgroups all read the statistics from before the
+// update that one of them writes.
 __global__ __launch_bounds__(256) void rnd_raw_kernel(const float* __restrict__ yp, const float* __restrict__ yt, int N,
-                                                      int K, float* __restrict__ raw, double* __restrict__ partials) {
+                                                      int K, float* __restrict__ raw, double* __restrict__ partials,
+                                                      const float* __restrict__ running, float* __restrict__ running_old) {
   __shared__ double smem[4];
-  const int n = blockIdx.x * 256 + threadIdx.x;
+  constexpr int PER = RND_ROWS * RND_LANES / 256;         // rows per lane
+  const int sub = threadIdx.x & (RND_LANES - 1);
+  if (blockIdx.x == 0 && threadIdx.x < 3) running_old[threadIdx.x] = running[threadIdx.x];
   double s = 0.0, q = 0.0;
-  if (n < N) {
-    float acc = 0.f;
-    for (int k = 0; k < K; ++k) {
-      const float d = yp[(long)n * K + k] - yt[(long)n * K + k];
-      acc += d * d;
+  float acc[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    const int n = blockIdx.x * RND_ROWS + (int)(threadIdx.x / RND_LANES) + i * (256 / RND_LANES);
+    const long o = (long)min(n, N - 1) * K;
+    acc[i] = 0.f;
+    if ((K & 3) == 0) {                                   // both matrices start 16-byte aligned
+      for (int k = 4 * sub; k < K; k += 4 * RND_LANES) {
+        const float4 a = *reinterpret_cast<const float4*>(yp + o + k), b = *reinterpret_cast<const float4*>(yt + o + k);
+        const float d0 = a.x - b.x, d1 = a.y - b.y, d2 = a.z - b.z, d3 = a.w - b.w;
+        acc[i] += (d0 * d0 + d1 * d1) + (d2 * d2 + d3 * d3);
+      }
+    } else {
+      for (int k = sub; k < K; k += RND_LANES) {
+        const float d = yp[o + k] - yt[o + k];
+        acc[i] += d * d;
+      }
     }
-    raw[n] = acc;
-    s = (double)acc;
-    q = s * s;
+  }
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+#pragma unroll
+    for (int off = 1; off < RND_LANES; off <<= 1) acc[i] += __shfl_xor(acc[i], off, WAVE);
+    const int n = blockIdx.x * RND_ROWS + (int)(threadIdx.x / RND_LANES) + i * (256 / RND_LANES);
+    if (sub == 0 && n < N) {
+      raw[n] = acc[i];
+      s += (double)acc[i];
+      q += (double)acc[i] * (double)acc[i];
+    }
   }
   double ts = block_sum(s, smem);
   double tq = block_sum(q, smem);
@@ -1450,20 +1475,28 @@ __global__ __launch_bounds__(256) void rnd_raw_kernel(const float* __restrict__ 
   }
 }
 
-// Single workgroup: batch moments, pairwise merge into running = {mean, var, count}, 1/sqrt(var + 1e-8).
-__global__ __launch_bounds__(256) void rnd_stats_kernel(const double* __restrict__ partials, int blocks, int N,
-                                                        float* __restrict__ running, int update,
-                                                        float* __restrict__ inv_out) {
+// Every workgroup forms the batch moments from the partial sums, merges them pairwise with running_old = {mean, var, count}
+// and applies 1 / sqrt(var + 1e-8); the first one stores the merged statistics.
+__global__ __launch_bounds__(256) void rnd_apply_kernel(const double* __restrict__ partials, int blocks, int N,
+                                                        const float* __restrict__ running_old, float* __restrict__ running,
+                                                        int update, float weight, float* __restrict__ r_int,
+                                                        float* __restrict__ rewards) {
   __shared__ double smem[4];
-  double s = 0.0, q = 0.0;
-  for (int i = threadIdx.x; i < blocks; i += 256) {
-    s += partials[2 * i];
-    q += partials[2 * i + 1];
+  __shared__ float s_inv;
+  const int n = blockIdx.x * 256 + threadIdx.x;
+  const float raw = n < N ? r_int[n] : 0.f, reward = n < N && rewards != nullptr ? rewards[n] : 0.f;
+  double mean = running_old[0], var = running_old[1], count = running_old[2];
+  double ts = 0.0, tq = 0.0;
+  if (update) {
+    double s = 0.0, q = 0.0;
+    for (int i = threadIdx.x; i < blocks; i += 256) {
+      s += partials[2 * i];
+      q += partials[2 * i + 1];
+    }
+    ts = block_sum(s, smem);
+    tq = block_sum(q, smem);
   }
-  double ts = block_sum(s, smem);
-  double tq = block_sum(q, smem);
   if (threadIdx.x == 0) {
-    double mean = running[0], var = running[1], count = running[2];
     if (update) {
       const double nb = (double)N;
       const double mb = ts / nb;
@@ -1475,30 +1508,28 @@ __global__ __launch_bounds__(256) void rnd_stats_kernel(const double* __restrict
       mean = mean + delta * nb / tot;
       var = m2 / tot;
       count = tot;
-      running[0] = (float)mean;
-      running[1] = (float)var;
-      running[2] = (float)count;
+      if (blockIdx.x == 0) {
+        running[0] = (float)mean;
+        running[1] = (float)var;
+        running[2] = (float)count;
+      }
     }
-    *inv_out = (float)(1.0 / sqrt(var + 1e-8));
+    s_inv = (float)(1.0 / sqrt(var + 1e-8));
   }
-}
-
-__global__ __launch_bounds__(256) void rnd_apply_kernel(float* __restrict__ r_int, int N, const float* __restrict__ inv,
-                                                        float weight, float* __restrict__ rewards) {
-  const int n = blockIdx.x * 256 + threadIdx.x;
+  __syncthreads();
   if (n >= N) return;
-  const float r = r_int[n] * inv[0];
+  const float r = raw * s_inv;
   r_int[n] = r;
-  if (rewards != nullptr) rewards[n] += weight * r;
+  if (rewards != nullptr) rewards[n] = reward + weight * r;
 }
 
 hipError_t launch_rnd_reward(const float* yp, const float* yt, int32_t N, int32_t K, float* running, float weight,
                              int32_t update_stats, float* r_int, float* rewards, double* partials, hipStream_t stream) {
   const int nb = rnd_num_blocks(N);
-  float* inv = reinterpret_cast<float*>(partials + 2 * (size_t)nb);
-  hipLaunchKernelGGL(rnd_raw_kernel, dim3(nb), dim3(256), 0, stream, yp, yt, N, K, r_int, partials);
-  hipLaunchKernelGGL(rnd_stats_kernel, dim3(1), dim3(256), 0, stream, partials, nb, N, running, update_stats, inv);
-  hipLaunchKernelGGL(rnd_apply_kernel, dim3(nb), dim3(256), 0, stream, r_int, N, inv, weight, rewards);
+  float* running_old = reinterpret_cast<float*>(partials + 2 * (size_t)nb);
+  hipLaunchKernelGGL(rnd_raw_kernel, dim3(nb), dim3(256), 0, stream, yp, yt, N, K, r_int, partials, running, running_old);
+  hipLaunchKernelGGL(rnd_apply_kernel, dim3((N + 255) / 256), dim3(256), 0, stream, partials, nb, N, running_old, running, update_stats,
+                     weight, r_int, rewards);
   return hipGetLastError();
 }
 
