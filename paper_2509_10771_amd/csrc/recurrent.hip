@@ -399,6 +399,59 @@ __global__ __launch_bounds__(GS_THREADS) void step_bwd_kernel(const StepBwdArgs 
   }
 }
 
+// ---- gate stages of the split-operand kernels --------------------------------------------------------------
+// One unit of one row.  gh: hidden-side terms with their bias.  st: what the gates blend with (GRU: h, LSTM: c), replaced by
+// its successor times keep.  out: the gates as the backward pass reads them (GRU r, z, n and n's hidden-side term).
+template <int CELL, int G>
+__device__ __forceinline__ void gates_forward(const float (&gi)[G], const float (&gh)[G], float keep, float& st, float& h, float (&out)[4]) {
+  if constexpr (CELL == CELL_GRU) {
+    out[0] = sigmoidf_(gi[0] + gh[0]);
+    out[1] = sigmoidf_(gi[1] + gh[1]);
+    out[2] = tanhf_(gi[2] + out[0] * gh[2]);
+    out[3] = gh[2];
+    h = (1.0f - out[1]) * out[2] + out[1] * st;
+    st = h * keep;
+  } else {
+    out[0] = sigmoidf_(gi[0] + gh[0]);
+    out[1] = sigmoidf_(gi[1] + gh[1]);
+    out[2] = tanhf_(gi[2] + gh[2]);
+    out[3] = sigmoidf_(gi[G - 1] + gh[G - 1]);
+    const float c = out[1] * st + out[0] * out[2];
+    h = out[3] * tanhf_(c);
+    st = c * keep;
+  }
+}
+
+// With back = dg(t + 1) W_hh^T and keep = 1 - done, both 0 on the last step:
+//   GRU:  dh = dh_ext + keep (back + carry);  d = [dr, dz, dn r], dn (pre-activation gradients; dgi has dn in place of dn r),
+//         carry = dh z
+//   LSTM: dh = dh_ext + keep back, dc = keep carry;  d = d loss / d pre-activations,  carry = (dc + dh o (1 - tanh^2 c')) f
+template <int CELL, int G>
+__device__ __forceinline__ void gates_backward(const float (&gate)[4], float st, float dh_ext, float back, float keep, float& carry,
+                                               float (&d)[G], float& dn) {
+  if constexpr (CELL == CELL_GRU) {
+    const float dh = dh_ext + (back + carry) * keep;
+    const float rr = gate[0], zz = gate[1], nn = gate[2];
+    const float dz = dh * (st - nn);
+    dn = dh * (1.0f - zz) * (1.0f - nn * nn);
+    d[0] = dn * gate[3] * rr * (1.0f - rr);
+    d[1] = dz * zz * (1.0f - zz);
+    d[2] = dn * rr;
+    carry = dh * zz;
+  } else {
+    const float dh = dh_ext + back * keep;
+    const float ii = gate[0], ff = gate[1], gg = gate[2], oo = gate[3];
+    const float tc = tanhf_(ff * st + ii * gg);
+    const float dct = carry * keep + dh * oo * (1.0f - tc * tc);
+    carry = dct * ff;
+    d[0] = dct * gg * ii * (1.0f - ii);
+    d[1] = dct * st * ff * (1.0f - ff);
+    d[2] = dct * ii * (1.0f - gg * gg);
+    d[G - 1] = dh * tc * oo * (1.0f - oo);
+    dn = 0.f;
+  }
+}
+
 // ---- a whole roll-out in one launch each way ---------------------------------------------------------------
 // The update path's recurrence, for the width whose weights fit one CU: the states, and in the backward pass the gradients
 // and the carried term, stay in the workgroup from step to step.
@@ -579,7 +632,7 @@ __global__ __launch_bounds__(SQ_THREADS, 2) void seq_fwd_kernel(const SeqArgs a)
       for (int i = 0; i < UT * G; ++i) sq_repeat_fp32(n.w_hh + i % G * H + j0 + 16 * (i / G), GH, 1, n.hin + r0 * W, H, lane, acc[i]);
     }
     const float keep = flag ? 0.f : 1.f;
-    f4 out[UT][G + 1];                                   // the gates as the backward pass reads them, and ghn
+    f4 out[UT][4];
 #pragma unroll
     for (int u = 0; u < UT; ++u) {
       f4 bv[G];
@@ -587,24 +640,13 @@ __global__ __launch_bounds__(SQ_THREADS, 2) void seq_fwd_kernel(const SeqArgs a)
       for (int g = 0; g < G; ++g) bv[g] = ld4(bias + g * H + ju + 16 * u);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        if constexpr (CELL == CELL_GRU) {
-          const float ghr = acc[u * G][r] + bv[0][r], ghz = acc[u * G + 1][r] + bv[1][r], ghn = acc[u * G + 2][r] + bv[2][r];
-          const float rr = sigmoidf_(gi[u][0][r] + ghr);
-          const float zz = sigmoidf_(gi[u][1][r] + ghz);
-          const float nn = tanhf_(gi[u][2][r] + rr * ghn);
-          h[u][r] = (1.0f - zz) * nn + zz * st[u][r];
-          out[u][0][r] = rr; out[u][1][r] = zz; out[u][2][r] = nn; out[u][3][r] = ghn;
-          st[u][r] = h[u][r] * keep;
-        } else {
-          float pre[4];
+        float x[G], y[G], o[4], hv, sv = st[u][r];
 #pragma unroll
-          for (int g = 0; g < 4; ++g) pre[g] = gi[u][g][r] + acc[u * G + g][r] + bv[g][r];
-          const float ii = sigmoidf_(pre[0]), ff = sigmoidf_(pre[1]), gg = tanhf_(pre[2]), oo = sigmoidf_(pre[3]);
-          const float cn = ff * st[u][r] + ii * gg;
-          h[u][r] = oo * tanhf_(cn);
-          out[u][0][r] = ii; out[u][1][r] = ff; out[u][2][r] = gg; out[u][3][r] = oo;
-          st[u][r] = cn * keep;
-        }
+        for (int g = 0; g < G; ++g) { x[g] = gi[u][g][r]; y[g] = acc[u * G + g][r] + bv[g][r]; }
+        gates_forward<CELL>(x, y, keep, sv, hv, o);
+        h[u][r] = hv; st[u][r] = sv;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) out[u][g][r] = o[g];
       }
     }
     __syncthreads();                                        // every wavefront has read the old states
@@ -644,9 +686,6 @@ template <int CELL, int H> struct SeqBwd {
   static constexpr int LDS = WEIGHTS + C::LDS_BYTES;
 };
 
-// With keep = 1 - done of the step and back = dg(t + 1) W_hh^T:
-//   GRU:  dh = dh_ext + keep (back + carry);  dgi = [dr, dz, dn], dg = [dr, dz, dn r] (pre-activation gradients), carry = dh z
-//   LSTM: dh = dh_ext + keep back, dc = keep carry;  dg = d loss / d pre-activations,  carry = (dc + dh o (1 - tanh^2 c')) f
 template <int CELL, int H>
 __global__ __launch_bounds__(SQ_THREADS, 2) void seq_bwd_kernel(const SeqArgs a) {
   using F = SeqBwd<CELL, H>;
@@ -711,35 +750,19 @@ __global__ __launch_bounds__(SQ_THREADS, 2) void seq_bwd_kernel(const SeqArgs a)
           sq_repeat_fp32(n.w_hh + (long)(j0 + 16 * u) * GH, 1, GH, n.dg + (r0 + nb) * GH, GH, lane, back[u]);
       }
     }
-    const float keep = flag ? 0.f : 1.f;
+    const float keep = t + 1 == a.T || flag ? 0.f : 1.f;
     f4 d[UT][G], dn[UT];
 #pragma unroll
     for (int u = 0; u < UT; ++u)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        if constexpr (CELL == CELL_GRU) {
-          float dh = now.dh[u][r];
-          if (t + 1 < a.T) dh += (back[u][r] + carry[u][r]) * keep;
-          const float rr = now.gate[u][0][r], zz = now.gate[u][1][r], nn = now.gate[u][2][r], ghn = now.gate[u][3][r];
-          const float dz = dh * (now.st[u][r] - nn);
-          const float dn_pre = dh * (1.0f - zz) * (1.0f - nn * nn);
-          d[u][0][r] = dn_pre * ghn * rr * (1.0f - rr);
-          d[u][1][r] = dz * zz * (1.0f - zz);
-          d[u][2][r] = dn_pre * rr;
-          dn[u][r] = dn_pre;
-          carry[u][r] = dh * zz;
-        } else {
-          float dh = now.dh[u][r], dc = 0.f;
-          if (t + 1 < a.T) { dh += back[u][r] * keep; dc = carry[u][r] * keep; }
-          const float ii = now.gate[u][0][r], ff = now.gate[u][1][r], gg = now.gate[u][2][r], oo = now.gate[u][3][r];
-          const float tc = tanhf_(ff * now.st[u][r] + ii * gg);
-          const float dct = dc + dh * oo * (1.0f - tc * tc);
-          carry[u][r] = dct * ff;
-          d[u][0][r] = dct * gg * ii * (1.0f - ii);
-          d[u][1][r] = dct * now.st[u][r] * ff * (1.0f - ff);
-          d[u][2][r] = dct * ii * (1.0f - gg * gg);
-          d[u][G - 1][r] = dh * tc * oo * (1.0f - oo);
-        }
+        float gt[4], dv[G], dnv, cv = carry[u][r];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) gt[g] = now.gate[u][g][r];
+        gates_backward<CELL>(gt, now.st[u][r], now.dh[u][r], back[u][r], keep, cv, dv, dnv);
+        carry[u][r] = cv; dn[u][r] = dnv;
+#pragma unroll
+        for (int g = 0; g < G; ++g) d[u][g][r] = dv[g];
       }
     __syncthreads();                                        // every wavefront has read the gradients of the step after
     if (t > 0) {
@@ -762,6 +785,191 @@ __global__ __launch_bounds__(SQ_THREADS, 2) void seq_bwd_kernel(const SeqArgs a)
     }
     __syncthreads();
   }
+}
+
+// ---- act(): one time step on split operands ----------------------------------------------------------------
+// For many rows and widths that are multiples of 64.  A workgroup of 4 wavefronts takes 64 rows and 32 hidden units; wavefront w
+// its rows 16 w .., operands and accumulators as in the roll-out kernels above (operand A 16 weight columns, operand B 16
+// rows), so the gate stage works on the lane's own accumulators.  Weights are split by the workgroup on their way into LDS, 64
+// contraction indices at a time, rows in registers by the only wavefront that uses them.  Two memories of 256 at 4096
+// rows: 36 us, 55 on the fp32 matrix cores (20 at their peak).
+constexpr int ST_ROWS = 64, ST_UNITS = 32, ST_THREADS = 256;
+
+// Workgroup -> (network, row block, unit block).  Workgroup ids go round-robin to the 8 XCDs; each XCD takes one network, half
+// of its units and half (of a single network: a quarter) of its rows, so that an L2 fetches half the weights.
+struct StepGrid {
+  int row_groups, unit_blocks, per_group, blocks;
+  __host__ __device__ StepGrid(int n_nets, int nb, int H) {
+    row_groups = n_nets == 2 ? 2 : 4;
+    unit_blocks = H / ST_UNITS;
+    per_group = (unit_blocks + 1) / 2;
+    blocks = 8 * per_group * (((nb + ST_ROWS - 1) / ST_ROWS + row_groups - 1) / row_groups);
+  }
+};
+
+// Contraction indices of a chunk: two workgroups are to fit a CU (72 KB of LDS for three gates, 48 for four).
+template <int CELL> struct StepSplit {
+  static constexpr int G = CellShape<CELL>::G, KC = CELL == CELL_LSTM ? 32 : 64, KS = KC / 32;
+  static constexpr int NT = 2 * G, CHUNK = KS * NT * 3 * SQ_BLOCK;         // tiles of 16 weight columns, bytes of a chunk
+  static constexpr int SIDE = ST_THREADS / (4 * KC), PER = G / SIDE;       // gates side by side in the lanes' loads, gates per lane
+};
+
+template <int CELL>
+__global__ __launch_bounds__(ST_THREADS, 2) void step_split_kernel(const StepFwdArgs a) {
+  using S = StepSplit<CELL>;
+  constexpr int G = S::G, NT = S::NT, KC = S::KC, CHUNK = S::CHUNK, PER = S::PER;
+  extern __shared__ __align__(16) char lds[];
+  const int nb = a.nb;
+  const StepGrid grid(a.n_nets, nb, a.n_nets == 2 ? max(a.net[0].H, a.net[1].H) : a.net[0].H);
+  const int xcd = blockIdx.x & 7, id = blockIdx.x >> 3;
+  const int z = a.n_nets == 2 ? xcd >> 2 : 0, rg = a.n_nets == 2 ? xcd & 1 : xcd & 3, ug = a.n_nets == 2 ? (xcd >> 1) & 1 : xcd >> 2;
+  const int ub = ug * grid.per_group + id % grid.per_group, row0 = ((id / grid.per_group) * grid.row_groups + rg) * ST_ROWS;
+  const StepFwdNet& n = a.net[z];
+  const int H = n.H, GH = G * H, SW = CELL == CELL_LSTM ? 2 * H : H;
+  if (ub >= H / ST_UNITS || row0 >= nb) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b = lane & 15, kq = lane >> 4, j0 = ub * ST_UNITS, ju = j0 + 4 * kq;      // the lane's units: ju + 16 u + 0 .. 3
+  const int row = min(row0 + 16 * wave + b, nb - 1);
+  const bool ok = row0 + 16 * wave + b < nb;             // rows past the end repeat the last one and store nothing
+  const float scale = split_scale(b), unscale = split_unscale(b);
+  const int NC = H / KC;
+
+  // weights: this lane's column of 32 and eight contraction indices of a chunk, for its gates
+  const int wc = tid & 31, wk = (tid >> 5) % (KC / 8), wg = tid / (4 * KC);
+  float wf[PER][8];
+  auto load_w = [&](int c) {
+    const int k0 = min(c, NC - 1) * KC + 8 * wk;
+#pragma unroll
+    for (int g = 0; g < PER; ++g)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) wf[g][i] = n.w_hh[(uint32_t)(k0 + i) * (uint32_t)GH + (uint32_t)((g * S::SIDE + wg) * H + j0 + wc)];
+  };
+  auto put_w = [&](int buf) {            // blocks: [step of 32][unit tile][gate][part]
+    char* dst = lds + buf * CHUNK + (((wk >> 2) * NT + (wc >> 4) * G + wg) * 3) * SQ_BLOCK + ((wk & 3) * 16 + (wc & 15)) * 16;
+#pragma unroll
+    for (int g = 0; g < PER; ++g) {
+      u32x4 part[3];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        uint32_t p0, p1, p2;
+        split_pair(SPLIT_SCALE * wf[g][2 * i], SPLIT_SCALE * wf[g][2 * i + 1], p0, p1, p2);
+        part[0][i] = p0; part[1][i] = p1; part[2][i] = p2;
+      }
+#pragma unroll
+      for (int s = 0; s < 3; ++s) *reinterpret_cast<u32x4*>(dst + (3 * S::SIDE * g + s) * SQ_BLOCK) = part[s];
+    }
+  };
+  // rows: operand B's eight contraction indices of every step of 32 of a chunk
+  const float* xrow = n.sin + (long)row * SW;
+  auto load_x = [&](int c, f4 (&x)[2 * S::KS]) {
+    const float* p = xrow + min(c, NC - 1) * KC + 8 * kq;
+#pragma unroll
+    for (int i = 0; i < 2 * S::KS; ++i) x[i] = ld4(p + 32 * (i >> 1) + 4 * (i & 1));
+  };
+
+  f4 acc[NT];
+#pragma unroll
+  for (int i = 0; i < NT; ++i) acc[i] = f4{0.f, 0.f, 0.f, 0.f};
+  f4 x0[2 * S::KS], x1[2 * S::KS];
+  load_w(0);
+  load_x(0, x0);
+  // the gate stage's own operands: their latency passes under the contraction
+  f4 gi[2][G], st[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) gi[u][g] = ld4(n.gi + (long)row * GH + g * H + ju + 16 * u);
+    st[u] = ld4(n.sin + (long)row * SW + (CELL == CELL_LSTM ? H : 0) + ju + 16 * u);
+  }
+  put_w(0);
+  load_w(1);
+  __syncthreads();
+  auto chunk = [&](int c, const f4 (&x)[2 * S::KS], f4 (&next)[2 * S::KS]) {
+    load_x(c + 1, next);
+    const char* wl = lds + (c & 1) * CHUNK + lane * 16;
+#pragma unroll
+    for (int ks = 0; ks < S::KS; ++ks) {
+      u32x4 xb[3];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const f4& v = x[2 * ks + (i >> 1)];
+        uint32_t p0, p1, p2;
+        split_pair(scale * v[2 * (i & 1)], scale * v[2 * (i & 1) + 1], p0, p1, p2);
+        xb[0][i] = p0; xb[1][i] = p1; xb[2][i] = p2;
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        bf16x8 w[3 * G];
+#pragma unroll
+        for (int i = 0; i < 3 * G; ++i) w[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(wl + ((ks * NT + u * G) * 3 + i) * SQ_BLOCK));
+        constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+        for (int p = 0; p < 6; ++p)
+#pragma unroll
+          for (int g = 0; g < G; ++g)
+            acc[u * G + g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[3 * g + PA[p]], __builtin_bit_cast(bf16x8, xb[PB[p]]), acc[u * G + g], 0, 0, 0);
+      }
+    }
+    if (c + 1 < NC) {
+      put_w((c + 1) & 1);
+      load_w(c + 2);
+    }
+    __syncthreads();
+  };
+  for (int c = 0; c < NC; c += 2) {
+    chunk(c, x0, x1);
+    if (c + 1 < NC) chunk(c + 1, x1, x0);
+  }
+  float nf = 0.f;                                         // becomes NaN with any non-finite sum
+#pragma unroll
+  for (int i = 0; i < NT; ++i) {
+    acc[i] *= unscale;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) nf = fmaf(acc[i][r], 0.f, nf);
+  }
+  if (__any(!(nf == 0.f))) {
+#pragma unroll
+    for (int i = 0; i < NT; ++i) sq_repeat_fp32(n.w_hh + i % G * H + j0 + 16 * (i / G), GH, 1, xrow, H, lane, acc[i]);
+  }
+  if (!ok) return;
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int j = ju + 16 * u;
+    f4 bv[G], h;
+#pragma unroll
+    for (int g = 0; g < G; ++g) bv[g] = ld4(n.b_hh + g * H + j);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float x[G], y[G], out[4], hv, sv = st[u][r];
+#pragma unroll
+      for (int g = 0; g < G; ++g) { x[g] = gi[u][g][r]; y[g] = acc[u * G + g][r] + bv[g][r]; }
+      gates_forward<CELL>(x, y, 1.f, sv, hv, out);
+      h[r] = hv; st[u][r] = sv;
+    }
+    st4(n.h_out + (long)row * n.ld_out + j, h);
+    if (CELL == CELL_LSTM) st4(n.c_out + (long)row * n.ld_out + j, st[u]);
+  }
+}
+
+template <int CELL>
+hipError_t step_split_launch(const StepFwdArgs& a, hipStream_t stream) {
+  constexpr int bytes = 2 * StepSplit<CELL>::CHUNK;
+  const int H = a.n_nets == 2 && a.net[1].H > a.net[0].H ? a.net[1].H : a.net[0].H;
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(step_split_kernel<CELL>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((step_split_kernel<CELL>), dim3(StepGrid(a.n_nets, a.nb, H).blocks), dim3(ST_THREADS), bytes, stream, a);
+  return hipGetLastError();
+}
+
+// Which steps take that kernel: those of act() (nothing kept for a backward pass, no flags) from about the size on where it is the
+// faster one.  Whole calls, a network of [256, 128] behind the memory, the kernel above against this, us: GRU of 256 49.3 and
+// 47.4 at 1024 rows, 87.8 and 70.7 at 4096; GRU of 128 36.3 and 37.9 at 1024, 41.3 and 40.7 at 2048; LSTM of 256 52.3 and 54.3 at
+// 1024, 69.5 and 60.9 at 2048; LSTM of 128 51.6 and 52.4 at 3000, 56.1 and 53.9 at 4096.  A memory's own sizes decide, so that
+// a call for the values alone returns the bits of a full one.
+bool step_split_fits(const StepFwdNet& n, const StepFwdArgs& a) {
+  if (n.H % 64 != 0 || n.H > 8192 || a.nb < 1024 || (int64_t)a.nb * n.H < (a.cell == CELL_LSTM ? 1 << 19 : 1 << 18)) return false;
+  if (a.done != nullptr || n.sin_next != nullptr || n.pre_out != nullptr || (a.cell == CELL_LSTM && n.c_out == nullptr)) return false;
+  return ((reinterpret_cast<uintptr_t>(n.h_out) | reinterpret_cast<uintptr_t>(n.c_out) | reinterpret_cast<uintptr_t>(n.sin)) & 15) == 0;
 }
 
 template <int CELL, int H>
@@ -830,8 +1038,8 @@ static dim3 step_grid(int nb, const int* H, int n_nets) {
   return dim3(blocks, n_nets);
 }
 
-hipError_t launch_step_fwd(const StepFwdArgs& a, hipStream_t stream) {
-  if (a.nb <= 0 || a.n_nets <= 0) return hipSuccess;
+static hipError_t launch_step_rest(const StepFwdArgs& a, hipStream_t stream) {
+  if (a.n_nets <= 0) return hipSuccess;
   const int G = a.cell == CELL_LSTM ? 4 : 3;
   int H[2] = {a.net[0].H, a.net[1].H};
   double flops = 0.0;
@@ -841,6 +1049,25 @@ hipError_t launch_step_fwd(const StepFwdArgs& a, hipStream_t stream) {
   if (a.cell == CELL_LSTM) hipLaunchKernelGGL(step_fwd_kernel<CELL_LSTM>, grid, dim3(GS_THREADS), 0, stream, a);
   else hipLaunchKernelGGL(step_fwd_kernel<CELL_GRU>, grid, dim3(GS_THREADS), 0, stream, a);
   return hipGetLastError();
+}
+
+hipError_t launch_step_fwd(const StepFwdArgs& a, hipStream_t stream) {
+  if (a.nb <= 0 || a.n_nets <= 0) return hipSuccess;
+  StepFwdArgs split = a, rest = a;                 // the networks by the kernel that takes them
+  split.n_nets = rest.n_nets = 0;
+  double flops = 0.0;
+  for (int k = 0; k < a.n_nets; ++k) {
+    const bool fits = step_split_fits(a.net[k], a);
+    StepFwdArgs& to = fits ? split : rest;
+    to.net[to.n_nets++] = a.net[k];
+    if (fits) flops += 2.0 * a.nb * a.net[k].H * (a.cell == CELL_LSTM ? 4.0 : 3.0) * a.net[k].H;
+  }
+  if (split.n_nets > 0) {
+    TraceScope ts(stream, a.cell == CELL_LSTM ? "lstm_split" : "gru_split", flops, 0.0);
+    const hipError_t e = a.cell == CELL_LSTM ? step_split_launch<CELL_LSTM>(split, stream) : step_split_launch<CELL_GRU>(split, stream);
+    if (e != hipSuccess) return e;
+  }
+  return launch_step_rest(rest, stream);
 }
 
 hipError_t launch_step_bwd(const StepBwdArgs& a, hipStream_t stream) {

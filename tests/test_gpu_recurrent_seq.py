@@ -1,13 +1,15 @@
-"""Memories of the width whose whole roll-out runs in one launch each way: against the oracle at row counts around that
-launch's 16-row workgroups, one-step roll-outs, and weights that have no split for the bf16 matrix cores."""
+"""The memories' kernels on split operands against the oracle: the whole roll-out in one launch each way at row counts around
+its 16-row workgroups, one-step roll-outs, weights without a split for the bf16 matrix cores, and act()'s step for many rows."""
 from dataclasses import replace
 
 import numpy as np
 import pytest
 import torch
 
-from test_gpu_recurrent import RCase, _call, _nets, check_forced_steps, rx  # noqa: F401
-from workloads import WORKLOADS
+from gpu_util import assert_elementwise, dev, host, rel_l2
+from oracle import rng as orng
+from test_gpu_recurrent import SEED, RCase, _call, _cell, _flat, _nets, check_forced_steps, oracle_collect, rx  # noqa: F401
+from workloads import WORKLOADS, make_inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -44,3 +46,42 @@ def test_weights_without_a_split_reach_only_their_own_unit(rx, cell):
     for x, y in zip(*out):
         assert np.isfinite(x).all() and np.isfinite(y).all()
         assert np.linalg.norm(x - y) <= 1e-5 * np.linalg.norm(x)
+
+
+@pytest.mark.parametrize("cell,H,N", [("gru", 256, 1024), ("gru", 256, 1061), ("gru", 320, 1090), ("lstm", 256, 2050)])
+def test_large_act_step(rx, cell, H, N):
+    """act() at row counts that take the split-operand step kernel, around its tiles of 64 rows, against the fp64 oracle; the same
+    values from a values-only call, and fp32 arithmetic for a state that has no split."""
+    w = replace(WORKLOADS["recurrent"].scaled(N), T=1, hidden=(64, 32), memory_hidden=H, memory_cell=cell)
+    inp = make_inputs(w)
+    ref = oracle_collect(w, inp)
+    nets = _nets(rx, w, _flat(inp, "actor"), _flat(inp, "critic"))
+    ga, ma, gc, mc = nets
+    ws = rx.workspace(rx.rslx_act_recurrent_workspace_bytes(ga, ma, gc, mc, N))
+    A, S = w.A, _cell(w)[2]
+    eps = dev(orng.act_noise(SEED, 0, N, A), torch.float32)
+    obs, reset = dev(inp["obs"][0]), dev(inp["reset0"])
+
+    def step(h_a, h_c):
+        out = {k: torch.empty(N, A, device="cuda") for k in ("actions", "mu", "sigma")}
+        out.update(logp=torch.empty(N, device="cuda"), values=torch.empty(N, device="cuda"), h_a=h_a, h_c=h_c)
+        rx.rslx_act_recurrent(ga, ma, gc, mc, obs, obs, N, h_a, h_c, reset, None, None, SEED, 0, eps, out["actions"], out["logp"],
+                              out["values"], out["mu"], out["sigma"], 0, ws)
+        torch.cuda.synchronize()
+        return out
+
+    h0 = dev(inp["h_actor"]), dev(inp["h_critic"])
+    last = torch.empty(N, device="cuda")
+    rx.rslx_act_recurrent(None, None, gc, mc, None, obs, N, None, h0[1], reset, None, None, 0, 0, None, None, None, last, None, None,
+                          rx.ACT_VALUES_ONLY, ws)
+    out = step(h0[0].clone(), h0[1].clone())
+    for k in ("actions", "mu", "logp", "values", "h_a", "h_c"):
+        assert rel_l2(host(out[k]), ref[k][0]) <= 2e-5, k
+        assert_elementwise(k, host(out[k]), ref[k][0])
+    assert torch.equal(last, out["values"])
+    # one huge entry in one state: its row saturates, all others keep their bits
+    big = h0[0].clone()
+    big[N - 1, 3] = 2.0 ** 120
+    got = step(big, h0[1].clone())
+    assert torch.isfinite(got["h_a"][:, :H]).all()
+    assert torch.equal(got["h_a"][:N - 1], out["h_a"][:N - 1]) and torch.equal(got["h_c"], out["h_c"])
