@@ -524,7 +524,7 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
                                 sym ? sym->sign_obs_a : nullptr, idx);
       const XView xc = obs_view(ro->obs_critic, ro->Dc, p.stage_c, p.dp_c, sym ? sym->perm_obs_c : nullptr,
                                 sym ? sym->sign_obs_c : nullptr, idx);
-      {
+      if (e == 0 && m == 0) {                // from then on the optimiser keeps the split weights current
         PackBatch pb;
         pb.count = 0;
         pack_add_net(pb, *actor, p.actor.pack, 1);
@@ -581,18 +581,18 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
       }
 
       const int64_t t = *adam_step + 1;
-      AdamArgs aa;
-      memset(&aa, 0, sizeof aa);
-      aa.seg[0] = AdamSegment{actor->params, actor->grads, actor->adam_m, actor->adam_v, param_count(*actor)};
-      aa.seg[1] = AdamSegment{critic->params, critic->grads, critic->adam_m, critic->adam_v, param_count(*critic)};
-      aa.n_seg = 2;
+      AdamLayersArgs al;
+      memset(&al, 0, sizeof al);
+      adam_add_net(al, *actor, p.actor.pack, 1, true);
+      adam_add_net(al, *critic, p.critic.pack, 1, true);
+      AdamArgs& aa = al.a;
       aa.sumsq_blocks = p.sumsq_all; aa.n_sumsq = p.actor.n_sumsq + p.critic.n_sumsq + 1;
       aa.max_grad_norm = cfg->max_grad_norm;
       aa.lr = cfg->lr; aa.beta1 = cfg->beta1; aa.beta2 = cfg->beta2; aa.eps = cfg->adam_eps;
       aa.bc1 = bias_correction(cfg->beta1, t); aa.bc2 = bias_correction(cfg->beta2, t);
       if (counters) { aa.step_dev = &counters->adam_step; aa.step_off = (int32_t)t; }
       aa.grad_norm_out = stats_row + RSLX_STAT_GRAD_NORM;
-      RSLX_HIP(launch_adam(aa, s));
+      RSLX_HIP(launch_adam_layers(al, s));
       *adam_step = t;
 
       if (rnd) {
@@ -601,11 +601,13 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
         XView xr;
         xr.base = ro->obs_actor; xr.ld = ro->Da; xr.row_idx = idx; xr.src_rows = p.B;
         if (rnd->subset_idx) { xr.col_map = rnd->subset_idx; xr.map_from = 0; }
-        PackBatch pb;
-        pb.count = 0;
-        pack_add_net(pb, pr, p.pred.pack, 1);
-        if (e == 0 && m == 0) pack_add_net(pb, *rnd->target, p.targ_pack, rnd->target->n_layers);
-        RSLX_HIP(launch_pack_weights(pb, s));
+        if (e == 0 && m == 0) {
+          PackBatch pb;
+          pb.count = 0;
+          pack_add_net(pb, pr, p.pred.pack, 1);
+          pack_add_net(pb, *rnd->target, p.targ_pack, rnd->target->n_layers);
+          RSLX_HIP(launch_pack_weights(pb, s));
+        }
         NetJob rj[2] = {NetJob{&pr, xr, p.mb, &p.pred.act, &p.pred.pack}, NetJob{rnd->target, xr, p.mb, &p.targ, &p.targ_pack}};
         RSLX_TRY(forward_nets(rj, 2, s));
         const int nbm = mse_num_blocks((int64_t)p.mb * K);
@@ -616,16 +618,16 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
         RSLX_TRY(backward_nets(&rb, 1, s));
         RSLX_TRY(reduce_net(pr, p.pred, s));
         const int64_t tr = *rnd_step + 1;
-        AdamArgs ar;
-        memset(&ar, 0, sizeof ar);
-        ar.seg[0] = AdamSegment{pr.params, pr.grads, pr.adam_m, pr.adam_v, param_count(pr)};
-        ar.n_seg = 1;
+        AdamLayersArgs rl;
+        memset(&rl, 0, sizeof rl);
+        adam_add_net(rl, pr, p.pred.pack, 1, true);
+        AdamArgs& ar = rl.a;
         ar.sumsq_blocks = p.pred.sumsq; ar.n_sumsq = 0;
         ar.max_grad_norm = 0.f;
         ar.lr = rnd->lr; ar.beta1 = cfg->beta1; ar.beta2 = cfg->beta2; ar.eps = cfg->adam_eps;
         ar.bc1 = bias_correction(cfg->beta1, tr); ar.bc2 = bias_correction(cfg->beta2, tr);
         if (counters) { ar.step_dev = &counters->rnd_adam_step; ar.step_off = (int32_t)tr; }
-        RSLX_HIP(launch_adam(ar, s));
+        RSLX_HIP(launch_adam_layers(rl, s));
         *rnd_step = tr;
       }
     }
@@ -751,10 +753,12 @@ int32_t bc_update_impl(rslx_mlp* student, const rslx_mlp* teacher, const float* 
       const int32_t* idx = p.perms + (size_t)e * B + (size_t)m * p.mb;
       float* stats_row = stats + ((size_t)e * cfg->minibatches + m) * RSLX_NSTATS;
       XView xs; xs.base = obs_student; xs.ld = student->dims[0]; xs.row_idx = idx; xs.src_rows = B;
-      PackBatch pb;
-      pb.count = 0;
-      pack_add_net(pb, *student, p.student.pack, 1);
-      RSLX_HIP(launch_pack_weights(pb, s));
+      if (e == 0 && m == 0) {                // from then on the optimiser keeps the split weights current
+        PackBatch pb;
+        pb.count = 0;
+        pack_add_net(pb, *student, p.student.pack, 1);
+        RSLX_HIP(launch_pack_weights(pb, s));
+      }
       NetJob fj{student, xs, p.mb, &p.student.act, &p.student.pack};
       RSLX_TRY(forward_nets(&fj, 1, s));
       RSLX_HIP(launch_mse(p.student.act.out[Ls - 1], targets, idx, p.mb, A, p.student.d_out, p.mse_partials, s));
@@ -763,17 +767,17 @@ int32_t bc_update_impl(rslx_mlp* student, const rslx_mlp* teacher, const float* 
       RSLX_TRY(backward_nets(&bj, 1, s));
       RSLX_TRY(reduce_net(*student, p.student, s));
       const int64_t t = *adam_step + 1;
-      AdamArgs aa;
-      memset(&aa, 0, sizeof aa);
-      aa.seg[0] = AdamSegment{student->params, student->grads, student->adam_m, student->adam_v, weight_count(*student)};
-      aa.n_seg = 1;
+      AdamLayersArgs al;
+      memset(&al, 0, sizeof al);
+      adam_add_net(al, *student, p.student.pack, 1, false);
+      AdamArgs& aa = al.a;
       aa.sumsq_blocks = p.student.sumsq; aa.n_sumsq = p.student.n_sumsq;
       aa.max_grad_norm = cfg->max_grad_norm;
       aa.lr = cfg->lr; aa.beta1 = cfg->beta1; aa.beta2 = cfg->beta2; aa.eps = cfg->adam_eps;
       aa.bc1 = bias_correction(cfg->beta1, t); aa.bc2 = bias_correction(cfg->beta2, t);
       if (counters) { aa.step_dev = &counters->adam_step; aa.step_off = (int32_t)t; }
       aa.grad_norm_out = stats_row + RSLX_STAT_GRAD_NORM;
-      RSLX_HIP(launch_adam(aa, s));
+      RSLX_HIP(launch_adam_layers(al, s));
       *adam_step = t;
     }
   }

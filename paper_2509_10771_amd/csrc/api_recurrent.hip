@@ -269,6 +269,14 @@ void pack_add_memory(PackBatch& b, const rslx_memory& g, const RnnBufs& m) {
   }
 }
 
+// Adds a memory to an optimiser step that keeps its split weights current.
+void adam_add_memory(AdamLayersArgs& a, const rslx_memory& g, const RnnBufs& m) {
+  const int H = g.hidden, GH = gate_width(g);
+  const int64_t o = gru_off_whh(g);
+  a.layer[a.n_layers++] = AdamLayer{g.params, g.grads, g.adam_m, g.adam_v, m.pack_ih, nullptr, g.in_dim, GH, 0};
+  a.layer[a.n_layers++] = AdamLayer{g.params + o, g.grads + o, g.adam_m + o, g.adam_v + o, m.pack_hh, m.pack_hh_t, H, GH, m.pack_hh ? H : 0};
+}
+
 // The roll-out of all memories of a call goes through one launch each way where their common width has that kernel.
 bool memories_seq(const rslx_memory* const* mem, int count) {
   for (int k = 0; k < count; ++k)
@@ -494,7 +502,7 @@ int32_t ppo_update_recurrent_impl(rslx_memory* gru_actor, rslx_mlp* actor, rslx_
       const int32_t* ridx = p.rows_all + ((size_t)e * cfg->minibatches + m) * rows;
       float* stats_row = stats + ((size_t)e * cfg->minibatches + m) * RSLX_NSTATS;
 
-      {
+      if (e == 0 && m == 0) {          // from then on the optimiser keeps the split weights current
         PackBatch pb;                  // at most 12 layers (rnn_validate) and six copies of the memories
         pb.count = 0;
         pack_add_net(pb, *actor, p.actor.pack, 0);
@@ -556,20 +564,20 @@ int32_t ppo_update_recurrent_impl(rslx_memory* gru_actor, rslx_mlp* actor, rslx_
         RSLX_HIP(launch_reduce_partials(ra, s));
       }
       const int64_t t1 = *adam_step + 1;
-      AdamArgs aa;
-      memset(&aa, 0, sizeof aa);
-      aa.seg[0] = AdamSegment{actor->params, actor->grads, actor->adam_m, actor->adam_v, param_count(*actor)};
-      aa.seg[1] = AdamSegment{critic->params, critic->grads, critic->adam_m, critic->adam_v, param_count(*critic)};
-      aa.seg[2] = AdamSegment{gru_actor->params, gru_actor->grads, gru_actor->adam_m, gru_actor->adam_v, gru_count(*gru_actor)};
-      aa.seg[3] = AdamSegment{gru_critic->params, gru_critic->grads, gru_critic->adam_m, gru_critic->adam_v, gru_count(*gru_critic)};
-      aa.n_seg = 4;
+      AdamLayersArgs al;
+      memset(&al, 0, sizeof al);
+      adam_add_net(al, *actor, p.actor.pack, 0, true);
+      adam_add_net(al, *critic, p.critic.pack, 0, true);
+      adam_add_memory(al, *gru_actor, p.ma);
+      adam_add_memory(al, *gru_critic, p.mc);
+      AdamArgs& aa = al.a;
       aa.sumsq_blocks = p.sumsq_all; aa.n_sumsq = p.n_sumsq;
       aa.max_grad_norm = cfg->max_grad_norm;
       aa.lr = cfg->lr; aa.beta1 = cfg->beta1; aa.beta2 = cfg->beta2; aa.eps = cfg->adam_eps;
       aa.bc1 = bias_correction(cfg->beta1, t1); aa.bc2 = bias_correction(cfg->beta2, t1);
       if (counters) { aa.step_dev = &counters->adam_step; aa.step_off = (int32_t)t1; }
       aa.grad_norm_out = stats_row + RSLX_STAT_GRAD_NORM;
-      RSLX_HIP(launch_adam(aa, s));
+      RSLX_HIP(launch_adam_layers(al, s));
       *adam_step = t1;
     }
   }
@@ -721,11 +729,13 @@ int32_t rslx_bc_update_recurrent(rslx_memory* gru, rslx_mlp* student, const floa
       const int32_t* ridx = p.rows_all + ((size_t)e * cfg->minibatches + m) * rows;
       float* stats_row = stats + ((size_t)e * cfg->minibatches + m) * RSLX_NSTATS;
       RSLX_HIP(launch_fill(stats_row, RSLX_NSTATS, 0.f, s));
-      PackBatch pb;
-      pb.count = 0;
-      pack_add_net(pb, *student, p.student.pack, 0);
-      pack_add_memory(pb, *gru, p.mem);
-      RSLX_HIP(launch_pack_weights(pb, s));
+      if (e == 0 && m == 0) {
+        PackBatch pb;
+        pb.count = 0;
+        pack_add_net(pb, *student, p.student.pack, 0);
+        pack_add_memory(pb, *gru, p.mem);
+        RSLX_HIP(launch_pack_weights(pb, s));
+      }
       RSLX_TRY(memories_forward(mem, mb, 1, obs, h0s, envs, ridx, dones, T, nb, N, s));
       XView xs = plain_view(p.mem.hs, gru->hidden);
       NetJob fj{student, xs, rows, &p.student.act, &p.student.pack};
@@ -744,17 +754,17 @@ int32_t rslx_bc_update_recurrent(rslx_memory* gru, rslx_mlp* student, const floa
         RSLX_HIP(launch_reduce_partials(ra, s));
       }
       const int64_t t1 = *adam_step + 1;
-      AdamArgs aa;
-      memset(&aa, 0, sizeof aa);
-      aa.seg[0] = AdamSegment{student->params, student->grads, student->adam_m, student->adam_v, weight_count(*student)};
-      aa.seg[1] = AdamSegment{gru->params, gru->grads, gru->adam_m, gru->adam_v, gru_count(*gru)};
-      aa.n_seg = 2;
+      AdamLayersArgs al;
+      memset(&al, 0, sizeof al);
+      adam_add_net(al, *student, p.student.pack, 0, false);
+      adam_add_memory(al, *gru, p.mem);
+      AdamArgs& aa = al.a;
       aa.sumsq_blocks = p.sumsq_all; aa.n_sumsq = p.n_sumsq;
       aa.max_grad_norm = cfg->max_grad_norm;
       aa.lr = cfg->lr; aa.beta1 = cfg->beta1; aa.beta2 = cfg->beta2; aa.eps = cfg->adam_eps;
       aa.bc1 = bias_correction(cfg->beta1, t1); aa.bc2 = bias_correction(cfg->beta2, t1);
       aa.grad_norm_out = stats_row + RSLX_STAT_GRAD_NORM;
-      RSLX_HIP(launch_adam(aa, s));
+      RSLX_HIP(launch_adam_layers(al, s));
       *adam_step = t1;
     }
   }

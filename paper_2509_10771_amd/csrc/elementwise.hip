@@ -3,6 +3,7 @@
 // squared-norm, fused clip + Adam, Gaussian policy head, PPO loss head, MSE head, mirror augmentation,
 // RND reward normalisation.  Wavefronts are 64 lanes wide throughout.
 #include "kernels.h"
+#include "split_bf16.h"
 
 namespace rslx {
 
@@ -554,21 +555,10 @@ hipError_t launch_sumsq(const float* g, int64_t n, double* sumsq_blocks, hipStre
 // ---- fused clip + Adam ------------------------------------------------------------------------------
 // Every workgroup re-reduces the (short) list of per-block squared norms in the same order, so the clip
 // scale is identical everywhere and no extra launch or atomic is needed.
-__global__ __launch_bounds__(256) void adam_kernel(const AdamArgs a) {
+struct AdamScalars { float scale, inv_bc1, inv_bc2; };
+__device__ __forceinline__ AdamScalars adam_scalars(const AdamArgs& a, bool report) {
   __shared__ double smem[4];
   __shared__ float s_scale, s_bc1, s_bc2;
-  // the lane's parameter, gradient and moment loads are requested before the squared-norm list is summed, so the
-  // two memory latencies overlap
-  const AdamSegment& sg = a.seg[blockIdx.y];
-  const long i0 = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
-  const bool whole = i0 + 3 < sg.n;
-  float4 p = make_float4(0.f, 0.f, 0.f, 0.f), g = p, m = p, v = p;
-  if (whole) {
-    p = *reinterpret_cast<const float4*>(sg.params + i0);
-    g = *reinterpret_cast<const float4*>(sg.grads + i0);
-    m = *reinterpret_cast<const float4*>(sg.m + i0);
-    v = *reinterpret_cast<const float4*>(sg.v + i0);
-  }
   double q = 0.0;
   for (int i = threadIdx.x; i < a.n_sumsq; i += 256) q += a.sumsq_blocks[i];
   double tot = block_sum(q, smem);
@@ -584,34 +574,110 @@ __global__ __launch_bounds__(256) void adam_kernel(const AdamArgs a) {
     float s = 1.0f;
     if (a.max_grad_norm > 0.f && a.max_grad_norm < 3.0e38f) s = fminf(1.0f, a.max_grad_norm / (norm + 1e-6f));
     s_scale = s;
-    if (a.grad_norm_out != nullptr && blockIdx.x == 0 && blockIdx.y == 0) *a.grad_norm_out = norm;
+    if (a.grad_norm_out != nullptr && report) *a.grad_norm_out = norm;
   }
   __syncthreads();
-  const float scale = s_scale;
+  return AdamScalars{s_scale, 1.0f / s_bc1, 1.0f / s_bc2};
+}
+__device__ __forceinline__ void adam_element(const AdamArgs& a, const AdamScalars& k, float g, float& p, float& m, float& v) {
   const float ob1 = 1.0f - a.beta1, ob2 = 1.0f - a.beta2;
-  const float inv_bc1 = 1.0f / s_bc1, inv_bc2 = 1.0f / s_bc2;
+  const float gg = g * k.scale;
+  m = a.beta1 * m + ob1 * gg;
+  v = a.beta2 * v + ob2 * gg * gg;
+  p -= a.lr * (m * k.inv_bc1) / (sqrtf(v * k.inv_bc2) + a.eps);
+}
+
+__global__ __launch_bounds__(256) void adam_kernel(const AdamArgs a) {
+  // the lane's parameter, gradient and moment loads are requested before the squared-norm list is summed, so the
+  // two memory latencies overlap
+  const AdamSegment& sg = a.seg[blockIdx.y];
+  const long i0 = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
+  const bool whole = i0 + 3 < sg.n;
+  float4 p = make_float4(0.f, 0.f, 0.f, 0.f), g = p, m = p, v = p;
+  if (whole) {
+    p = *reinterpret_cast<const float4*>(sg.params + i0);
+    g = *reinterpret_cast<const float4*>(sg.grads + i0);
+    m = *reinterpret_cast<const float4*>(sg.m + i0);
+    v = *reinterpret_cast<const float4*>(sg.v + i0);
+  }
+  const AdamScalars k = adam_scalars(a, blockIdx.x == 0 && blockIdx.y == 0);
   if (i0 >= sg.n) return;
   if (whole) {
     float* pp = &p.x; float* gp = &g.x; float* mp = &m.x; float* vp = &v.x;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const float gg = gp[c] * scale;
-      mp[c] = a.beta1 * mp[c] + ob1 * gg;
-      vp[c] = a.beta2 * vp[c] + ob2 * gg * gg;
-      pp[c] -= a.lr * (mp[c] * inv_bc1) / (sqrtf(vp[c] * inv_bc2) + a.eps);
-    }
+    for (int c = 0; c < 4; ++c) adam_element(a, k, gp[c], pp[c], mp[c], vp[c]);
     *reinterpret_cast<float4*>(sg.params + i0) = p;
     *reinterpret_cast<float4*>(sg.m + i0) = m;
     *reinterpret_cast<float4*>(sg.v + i0) = v;
   } else {
     for (long i = i0; i < sg.n; ++i) {
-      const float gg = sg.grads[i] * scale;
-      const float m = a.beta1 * sg.m[i] + ob1 * gg;
-      const float v = a.beta2 * sg.v[i] + ob2 * gg * gg;
-      sg.m[i] = m;
-      sg.v[i] = v;
-      sg.params[i] -= a.lr * (m * inv_bc1) / (sqrtf(v * inv_bc2) + a.eps);
+      float p1 = sg.params[i], m1 = sg.m[i], v1 = sg.v[i];
+      adam_element(a, k, sg.grads[i], p1, m1, v1);
+      sg.m[i] = m1;
+      sg.v[i] = v1;
+      sg.params[i] = p1;
     }
+  }
+}
+
+// A wavefront takes four rows and 64 columns of a layer, so that each lane ends up with half a unit of the forward copy (eight
+// contraction indices of a column); the units of the other copy (eight columns of a row) are put together in LDS.
+// One optimiser step of [48, 512, 256, 128, 12] twice: 10.8 us, where the step and a launch that splits its result took 7.3 + 5.3;
+// [48, 128, 128, 12] twice 5.7, 4.2 + 3.6 (eight rows a lane: 10.5 and 7.4).
+constexpr int AL_ROWS = 4, AL_COLS = 64;
+__global__ __launch_bounds__(256) void adam_layers_kernel(const AdamLayersArgs args) {
+  __shared__ __align__(16) uint16_t turn[4][3][AL_ROWS][AL_COLS];
+  const AdamArgs& a = args.a;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const AdamLayer& L = args.layer[blockIdx.y];
+  const int K = L.K, N = L.N, across = (N + AL_COLS - 1) / AL_COLS;
+  if ((int)blockIdx.x * 4 >= across * ((K + AL_ROWS) / AL_ROWS)) return;   // a smaller layer than the largest
+  const int t = blockIdx.x * 4 + wave, down = t / across, c = (t - down * across) * AL_COLS + lane, k0 = down * AL_ROWS;
+  const int rows = min(AL_ROWS, K + 1 - k0);                               // row K is the bias; none in the last block's spare wavefronts
+  const long o = (long)k0 * N + c;
+  float p[AL_ROWS], g[AL_ROWS], m[AL_ROWS], v[AL_ROWS];
+#pragma unroll
+  for (int i = 0; i < AL_ROWS; ++i) {
+    p[i] = g[i] = m[i] = v[i] = 0.f;
+    if (i < rows && c < N) {
+      const long e = o + (long)i * N;
+      p[i] = L.params[e]; g[i] = L.grads[e]; m[i] = L.m[e]; v[i] = L.v[e];
+    }
+  }
+  const AdamScalars k = adam_scalars(a, blockIdx.x == 0 && blockIdx.y == 0);
+#pragma unroll
+  for (int i = 0; i < AL_ROWS; ++i) {
+    if (i < rows && c < N) {
+      const long e = o + (long)i * N;
+      adam_element(a, k, g[i], p[i], m[i], v[i]);
+      L.params[e] = p[i]; L.m[e] = m[i]; L.v[e] = v[i];
+    }
+  }
+  if (rows <= 0 || L.fwd == nullptr || k0 >= K) return;                    // uniform in the wavefront
+#pragma unroll
+  for (int i = 0; i < AL_ROWS; ++i) p[i] = k0 + i < K ? SPLIT_SCALE * p[i] : 0.f;       // 0 past the matrix: c >= N has p = 0
+  uint2 part[3];
+  split_pair(p[0], p[1], part[0].x, part[1].x, part[2].x);
+  split_pair(p[2], p[3], part[0].y, part[1].y, part[2].y);
+  if (c < N) {
+    const PackPlace to = pack_place(k0 >> 3, c, N, L.units);
+#pragma unroll
+    for (int s = 0; s < 3; ++s) reinterpret_cast<uint2*>(L.fwd)[2 * (to.at + (long)s * to.step) + (k0 >> 2 & 1)] = part[s];
+  }
+  if (L.dx == nullptr) return;
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    const uint32_t w[2] = {part[s].x, part[s].y};
+#pragma unroll
+    for (int i = 0; i < AL_ROWS; ++i) turn[wave][s][i][lane] = (uint16_t)(w[i >> 1] >> (16 * (i & 1)));
+  }
+  asm volatile("" ::: "memory");                                           // the compiler keeps the order, the LDS does for one wavefront
+  const int row = lane & 3, cg = lane >> 2, kg = (c - lane) / 8 + cg;
+  if (cg < 8 && k0 + row < K && 8 * kg < N) {
+    const PackPlace to = pack_place(kg, k0 + row, K, L.units);
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+      reinterpret_cast<uint4*>(L.dx)[to.at + (long)s * to.step] = *reinterpret_cast<const uint4*>(&turn[wave][s][row][8 * cg]);
   }
 }
 
@@ -625,14 +691,17 @@ __global__ __launch_bounds__(1024) void sumsq_fold_kernel(const double* __restri
   if (threadIdx.x == 0) *out = t;
 }
 
+static void fold_sumsq(AdamArgs& a, hipStream_t stream) {
+  if (a.n_sumsq <= ADAM_MAX_INLINE_SUMSQ) return;
+  double* total = const_cast<double*>(a.sumsq_blocks) + a.n_sumsq;        // caller reserved one extra slot behind the list
+  hipLaunchKernelGGL(sumsq_fold_kernel, dim3(1), dim3(1024), 0, stream, a.sumsq_blocks, a.n_sumsq, total);
+  a.sumsq_blocks = total;
+  a.n_sumsq = 1;
+}
+
 hipError_t launch_adam(const AdamArgs& a_in, hipStream_t stream) {
   AdamArgs a = a_in;
-  if (a.n_sumsq > ADAM_MAX_INLINE_SUMSQ) {     // caller reserved one extra slot behind the list
-    double* total = const_cast<double*>(a.sumsq_blocks) + a.n_sumsq;
-    hipLaunchKernelGGL(sumsq_fold_kernel, dim3(1), dim3(1024), 0, stream, a.sumsq_blocks, a.n_sumsq, total);
-    a.sumsq_blocks = total;
-    a.n_sumsq = 1;
-  }
+  fold_sumsq(a, stream);
   int64_t nmax = 0;
   for (int i = 0; i < a.n_seg; ++i) nmax = a.seg[i].n > nmax ? a.seg[i].n : nmax;
   if (nmax <= 0) return hipSuccess;
@@ -641,6 +710,23 @@ hipError_t launch_adam(const AdamArgs& a_in, hipStream_t stream) {
   TraceScope ts(stream, "adam", 0.0, 28.0 * n_all);
   dim3 grid((unsigned)((nmax + 1023) / 1024), a.n_seg);
   hipLaunchKernelGGL(adam_kernel, grid, dim3(256), 0, stream, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_adam_layers(const AdamLayersArgs& a_in, hipStream_t stream) {
+  AdamLayersArgs a = a_in;
+  fold_sumsq(a.a, stream);
+  int tiles = 0;
+  double n_all = 0.0;
+  for (int i = 0; i < a.n_layers; ++i) {
+    const AdamLayer& L = a.layer[i];
+    const int t = ((L.K + AL_ROWS) / AL_ROWS) * ((L.N + AL_COLS - 1) / AL_COLS);
+    tiles = t > tiles ? t : tiles;
+    n_all += (double)(L.K + 1) * L.N;
+  }
+  if (tiles == 0) return hipSuccess;
+  TraceScope ts(stream, "adam", 0.0, 28.0 * n_all);
+  hipLaunchKernelGGL(adam_layers_kernel, dim3((tiles + 3) / 4, a.n_layers), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

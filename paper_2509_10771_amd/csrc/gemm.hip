@@ -639,15 +639,9 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(const PackBatch b) {
   split_pair(v[2], v[3], part[0].y, part[1].y, part[2].y);
   split_pair(v[4], v[5], part[0].z, part[1].z, part[2].z);
   split_pair(v[6], v[7], part[0].w, part[1].w, part[2].w);
-  if (J.units > 0) {               // blocks of 64 lanes; waves on neighbouring blocks keep all channels of the L2 busy
-    const int gate = c / J.units, j = c - gate * J.units, per = J.units >> 3, wave = j / per, tile = (j - wave * per) >> 4;
-    const int first = (((kg >> 2) * (per >> 4) + tile) * (J.cols / J.units) + gate) * 3;
+  const PackPlace to = pack_place(kg, c, J.cols, J.units);
 #pragma unroll
-    for (int s = 0; s < 3; ++s) reinterpret_cast<uint4*>(J.dst)[(long)((first + s) * 8 + wave) * 64 + (kg & 3) * 16 + (j & 15)] = part[s];
-    return;
-  }
-#pragma unroll
-  for (int s = 0; s < 3; ++s) reinterpret_cast<uint4*>(J.dst)[(long)((kg >> 1) * 6 + 2 * s + (kg & 1)) * J.cols + c] = part[s];
+  for (int s = 0; s < 3; ++s) reinterpret_cast<uint4*>(J.dst)[to.at + (long)s * to.step] = part[s];
 }
 
 hipError_t launch_pack_weights(const PackBatch& b, hipStream_t stream) {

@@ -186,6 +186,20 @@ struct AdamArgs {
 // which the caller must have reserved.
 constexpr int ADAM_MAX_INLINE_SUMSQ = 4096;
 hipError_t launch_adam(const AdamArgs& a, hipStream_t stream);
+// The same step for layers [W [K, N]; b [N]] (K = 0: a vector alone) that also refreshes the split copies of their new weights,
+// where they have them: fwd (contraction over K) and dx (over N), packed once before by launch_pack_weights, which wrote
+// the padding.  a.seg is not read.
+struct AdamLayer {
+  float* params; const float* grads; float* m; float* v;
+  uint16_t* fwd; uint16_t* dx;
+  int32_t K, N, units;
+};
+struct AdamLayersArgs {
+  AdamArgs a;
+  AdamLayer layer[24];
+  int32_t n_layers;
+};
+hipError_t launch_adam_layers(const AdamLayersArgs& a, hipStream_t stream);
 
 // Gaussian head of act(): noise, action, log-density.
 // step_dev != null: the noise base is mix64(noise_pre ^ *step_dev) instead of noise_base.

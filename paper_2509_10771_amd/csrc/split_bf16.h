@@ -46,4 +46,16 @@ __device__ __forceinline__ void split_pair(float x, float y, uint32_t& p0, uint3
   p2 = pack_bf16(x, y);
 }
 
+// Place of a 16-byte unit (eight consecutive contraction indices, group kg, of column c; part 0) among the units of a split
+// weight matrix, and the distance to its next part: the layouts of PackJob (kernels.h).
+struct PackPlace { long at; int step; };
+__device__ __forceinline__ PackPlace pack_place(int kg, int c, int cols, int units) {
+  if (units > 0) {                 // blocks of 64 lanes
+    const int gate = c / units, j = c - gate * units, per = units >> 3, wave = j / per, tile = (j - wave * per) >> 4;
+    const int first = (((kg >> 2) * (per >> 4) + tile) * (cols / units) + gate) * 3;
+    return {(long)(first * 8 + wave) * 64 + (kg & 3) * 16 + (j & 15), 8 * 64};
+  }
+  return {(long)((kg >> 1) * 6 + (kg & 1)) * cols + c, 2 * cols};
+}
+
 }  // namespace rslx
