@@ -972,12 +972,16 @@ __global__ __launch_bounds__(256) void ppo_loss_kernel(const PpoLossArgs a) {
 // last hidden activations of actor and critic into LDS, applies both output layers (A + 1 dot products per row),
 // evaluates the PPO loss terms, and back-propagates through the output layers into the pre-activation gradient of
 // the last hidden layer.  Three launches and two passes over the activations collapse into one.
-// Every phase spreads over all 256 lanes: global loads are issued together before the first one is used, the
+// Every phase spreads over all lanes: global loads are issued together before the first one is used, the
 // output-layer dot products are cut into 8 contraction ranges per row, the loss runs on (row, action component)
 // pairs with the row sums taken through LDS in a fixed order, and the input gradient reads a row's d_mu with
 // 16-byte broadcasts.
 constexpr int HEAD_ROWS = 32;
-constexpr int HEAD_KPARTS = 8;      // lanes that share one row's output-layer dot products (and: 256 / HEAD_ROWS)
+// A block is a chain of phases, and small updates wait for one block: 13.9 us at 384 rows with 512 lanes, 18.6 with 256; updates of
+// [48, 128, 128, 12] 7 % faster up to 1024 environments, of 4096 environments and [512, 256, 128] 0.5 % (1024 lanes: 4 and -2 %).
+constexpr int HEAD_THREADS = 512, HEAD_WAVES = HEAD_THREADS / 64;
+constexpr int HEAD_KPARTS = 8;      // lanes that share one of a row's output-layer dot products
+constexpr int HEAD_JGROUPS = HEAD_THREADS / HEAD_ROWS;     // lanes per row
 constexpr int HEAD_PAD = 4;         // LDS row padding of the activations: rows stay 16-byte aligned, and the lanes
                                     // (row, part) of the output-layer phase spread evenly over the banks
 
@@ -1010,7 +1014,7 @@ struct HeadLds {
 };
 
 template <int AM>
-__global__ __launch_bounds__(256) void ppo_head_kernel(const PpoHeadArgs h) {
+__global__ __launch_bounds__(HEAD_THREADS) void ppo_head_kernel(const PpoHeadArgs h) {
   extern __shared__ float lds[];
   const PpoLossArgs& a = h.loss;
   const int A = a.A, Ha = h.Ha, Hc = h.Hc;
@@ -1048,29 +1052,29 @@ __global__ __launch_bounds__(256) void ppo_head_kernel(const PpoHeadArgs h) {
   //      addresses of the gather), the output-layer weights (cached, short), the activations (the long HBM reads),
   //      then, once the permutation entries are there, the gathered rollout rows.  Each group is written to LDS in
   //      the same order, so no wait covers more than it has to. ----
-  constexpr int GROWS = HEAD_ROWS / 4;                    // rows gathered per wave: r = wave + 4 i
+  constexpr int GROWS = HEAD_ROWS / HEAD_WAVES;           // rows gathered per wave: r = wave + HEAD_WAVES i
   int gb[GROWS];
 #pragma unroll
   for (int i = 0; i < GROWS; ++i) {
-    const int r = wave + 4 * i;
+    const int r = wave + HEAD_WAVES * i;
     gb[i] = (r < r_orig && i0 + r < a.mb) ? a.idx[i0 + r] : -1;
   }
-  constexpr int WROUND = 8;                               // weight loads in flight per lane
+  constexpr int WROUND = 2048 / HEAD_THREADS;             // weight loads in flight per lane
   const int w_elems = (Ha + 1) * AM;
   float wv[WROUND];
 #pragma unroll
   for (int i = 0; i < WROUND; ++i) {                      // first round (all of W for A <= 12 at 128 hidden units)
-    const int e = tid + 256 * i;
+    const int e = tid + HEAD_THREADS * i;
     const int k = e / AM, jj = e - k * AM;
     wv[i] = (e < w_elems && jj < A) ? h.w_a[k * A + jj] : 0.f;
   }
-  constexpr int HP = 8;                                   // 16-byte pieces per lane and network (H <= 256)
+  constexpr int HP = 2048 / HEAD_THREADS;                 // 16-byte pieces per lane and network (H <= 256)
   float4 ra[HP], rc[HP];
   const int pa = Ha >> 2, pc = Hc >> 2;                   // pieces per row (powers of two)
   const int sha = __ffs(pa) - 1, shc = __ffs(pc) - 1;
 #pragma unroll
   for (int i = 0; i < HP; ++i) {
-    const int e = tid + 256 * i;
+    const int e = tid + HEAD_THREADS * i;
     ra[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     rc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (e < HEAD_ROWS * pa) {
@@ -1082,8 +1086,8 @@ __global__ __launch_bounds__(256) void ppo_head_kernel(const PpoHeadArgs h) {
       if (gr >= 0) rc[i] = *reinterpret_cast<const float4*>(h.h_c + gr * Hc + 4 * (e & (pc - 1)));
     }
   }
-  // rollout rows, gathered through the permutation: wavefront w takes rows w, w + 4, ..; lanes run over the row
-  // [adv, ret, v_old, logp_old, actions[A], mu_old[A], sigma_old[A]]; the loads of all 8 rows are in flight together
+  // rollout rows, gathered through the permutation: wavefront w takes rows w, w + HEAD_WAVES, ..; lanes run over the row
+  // [adv, ret, v_old, logp_old, actions[A], mu_old[A], sigma_old[A]]; the loads of all its rows are in flight together
   const int gw = 4 + 3 * A;
   auto gather_src = [&](int c, const float*& src, int& stride, int& off) {
     stride = 1; off = 0;
@@ -1104,23 +1108,23 @@ __global__ __launch_bounds__(256) void ppo_head_kernel(const PpoHeadArgs h) {
   }
 #pragma unroll
   for (int i = 0; i < WROUND; ++i) {
-    const int e = tid + 256 * i;
+    const int e = tid + HEAD_THREADS * i;
     if (e < w_elems) wa[e] = wv[i];
   }
-  for (int e0 = 256 * WROUND; e0 < w_elems; e0 += 256 * WROUND) {   // wider heads: the rest of W, rows padded with zeros
+  for (int e0 = HEAD_THREADS * WROUND; e0 < w_elems; e0 += HEAD_THREADS * WROUND) {   // wider heads: the rest of W, rows padded with zeros
 #pragma unroll
     for (int i = 0; i < WROUND; ++i) {
-      const int e = e0 + tid + 256 * i;
+      const int e = e0 + tid + HEAD_THREADS * i;
       const int k = e / AM, jj = e - k * AM;
       wv[i] = (e < w_elems && jj < A) ? h.w_a[k * A + jj] : 0.f;
     }
 #pragma unroll
     for (int i = 0; i < WROUND; ++i) {
-      const int e = e0 + tid + 256 * i;
+      const int e = e0 + tid + HEAD_THREADS * i;
       if (e < w_elems) wa[e] = wv[i];
     }
   }
-  for (int e = tid; e < Hc + 1; e += 256) wc[e] = h.w_c[e];
+  for (int e = tid; e < Hc + 1; e += HEAD_THREADS) wc[e] = h.w_c[e];
   if (tid < A) {
     const float ls = a.log_std[tid];
     const float inv = expf(-ls);
@@ -1128,10 +1132,10 @@ __global__ __launch_bounds__(256) void ppo_head_kernel(const PpoHeadArgs h) {
     cst[4 * tid + 3] = sym ? a.sign_act[tid] : 1.0f;
     pact[tid] = sym ? a.perm_act[tid] : tid;
   }
-  for (int e = tid; e < HEAD_ROWS * A4; e += 256) dmu[e] = 0.f;    // also the padding the 16-byte reads touch
+  for (int e = tid; e < HEAD_ROWS * A4; e += HEAD_THREADS) dmu[e] = 0.f;    // also the padding the 16-byte reads touch
 #pragma unroll
   for (int i = 0; i < HP; ++i) {
-    const int e = tid + 256 * i;
+    const int e = tid + HEAD_THREADS * i;
     if (e < HEAD_ROWS * pa) {
       *reinterpret_cast<float4*>(ha + (e >> sha) * sa + 4 * (e & (pa - 1))) = ra[i];
     }
@@ -1142,7 +1146,7 @@ __global__ __launch_bounds__(256) void ppo_head_kernel(const PpoHeadArgs h) {
   if (lane < gw) {
 #pragma unroll
     for (int i = 0; i < GROWS; ++i) {
-      const int r = wave + 4 * i;
+      const int r = wave + HEAD_WAVES * i;
       if (r < r_orig) gat[r * gp + lane] = gv[i];
     }
   }
@@ -1153,55 +1157,57 @@ __global__ __launch_bounds__(256) void ppo_head_kernel(const PpoHeadArgs h) {
     for (int i = 0; i < GROWS; ++i) gv[i] = gb[i] >= 0 ? src[(long)gb[i] * stride + off] : 0.f;
 #pragma unroll
     for (int i = 0; i < GROWS; ++i) {
-      const int r = wave + 4 * i;
+      const int r = wave + HEAD_WAVES * i;
       if (r < r_orig) gat[r * gp + c] = gv[i];
     }
   }
   __syncthreads();
 
-  // ---- phase 2: output layers.  The 8 lanes (row, p) of a row take every 8th hidden unit each and form the
-  //      A + 1 dot products over them; a butterfly over the 8 lanes adds the parts in a fixed order ----
+  // ---- phase 2: output layers.  The 16 lanes of a row are two halves of HEAD_KPARTS: the lanes of a half take every eighth
+  //      hidden unit each and form the dot products over them of half the components (the value's in both, one writes
+  //      it); a butterfly over the eight lanes adds the parts in a fixed order ----
   {
-    const int p8 = lane & (HEAD_KPARTS - 1), row = wave * 8 + (lane >> 3);
-    float acc[AM + 1];
+    constexpr int AH = AM / 2;
+    const int p8 = lane & (HEAD_KPARTS - 1), half = (lane / HEAD_KPARTS) & 1, row = tid / (2 * HEAD_KPARTS);
+    float acc[AH + 1];
 #pragma unroll
-    for (int jj = 0; jj <= AM; ++jj) acc[jj] = 0.f;
+    for (int jj = 0; jj <= AH; ++jj) acc[jj] = 0.f;
     // trip counts are uniform (the lane only shifts the start), so the loops carry no lane mask
 #pragma unroll 4
     for (int i = 0; i < Ha / HEAD_KPARTS; ++i) {
       const int k = HEAD_KPARTS * i + p8;
       const float hv = ha[row * sa + k];
-      const float4* wr = reinterpret_cast<const float4*>(wa + k * AM);
+      const float2* wr = reinterpret_cast<const float2*>(wa + k * AM + half * AH);
 #pragma unroll
-      for (int q = 0; q < AM / 4; ++q) {
-        const float4 w4 = wr[q];
-        acc[4 * q] += hv * w4.x; acc[4 * q + 1] += hv * w4.y; acc[4 * q + 2] += hv * w4.z; acc[4 * q + 3] += hv * w4.w;
+      for (int q = 0; q < AH / 2; ++q) {
+        const float2 w2 = wr[q];
+        acc[2 * q] += hv * w2.x; acc[2 * q + 1] += hv * w2.y;
       }
     }
 #pragma unroll 4
     for (int i = 0; i < Hc / HEAD_KPARTS; ++i) {
       const int k = HEAD_KPARTS * i + p8;
-      acc[AM] += hc[row * sc + k] * wc[k];
+      acc[AH] += hc[row * sc + k] * wc[k];
     }
-    // butterfly over the 8 lanes of a row; all exchanges of a step are issued together
+    // butterfly over the lanes of a half; all exchanges of a step are issued together
 #pragma unroll
     for (int off = 1; off < HEAD_KPARTS; off <<= 1) {
-      float t[AM + 1];
+      float t[AH + 1];
 #pragma unroll
-      for (int jj = 0; jj <= AM; ++jj) t[jj] = __shfl_xor(acc[jj], off, 64);
+      for (int jj = 0; jj <= AH; ++jj) t[jj] = __shfl_xor(acc[jj], off, 64);
 #pragma unroll
-      for (int jj = 0; jj <= AM; ++jj) acc[jj] += t[jj];
+      for (int jj = 0; jj <= AH; ++jj) acc[jj] += t[jj];
     }
     if (p8 == 0) {
 #pragma unroll
-      for (int jj = 0; jj < AM; ++jj) mu[row * A4 + jj] = acc[jj] + wa[Ha * AM + jj];
-      vv[row] = acc[AM] + wc[Hc];
+      for (int jj = 0; jj < AH; ++jj) mu[row * A4 + half * AH + jj] = acc[jj] + wa[Ha * AM + half * AH + jj];
+      if (half) vv[row] = acc[AH] + wc[Hc];
     }
   }
   __syncthreads();
 
-  // ---- phase 3: loss.  Lane (row, jg) handles components jg, jg + 8, .. of a row (and of its twin) ----
-  constexpr int JPT = (AM + HEAD_KPARTS - 1) / HEAD_KPARTS;
+  // ---- phase 3: loss.  Lane (row, jg) handles components jg, jg + HEAD_JGROUPS, .. of a row (and of its twin) ----
+  constexpr int JPT = (AM + HEAD_JGROUPS - 1) / HEAD_JGROUPS;
   const int lr = tid & (HEAD_ROWS - 1), jg = tid >> 5;
   const bool row_ok = lr < r_orig && i0 + lr < a.mb;
   const int lt = lr + r_orig;                       // twin's local row (symmetry only)
@@ -1211,7 +1217,7 @@ __global__ __launch_bounds__(256) void ppo_head_kernel(const PpoHeadArgs h) {
   double kl_acc = 0.0, mir_acc = 0.0;
 #pragma unroll
   for (int t = 0; t < JPT; ++t) {
-    const int jj = jg + HEAD_KPARTS * t;
+    const int jj = jg + HEAD_JGROUPS * t;
     zj[t] = 0.f; zmj[t] = 0.f; diffj[t] = 0.f;
     if (jj < A) {
       float zz = 0.f, zzm = 0.f;
@@ -1276,7 +1282,7 @@ __global__ __launch_bounds__(256) void ppo_head_kernel(const PpoHeadArgs h) {
     const float msc = sym ? a.mirror_coef * 2.0f / ((float)a.mb * (float)A) : 0.f;
 #pragma unroll
     for (int t = 0; t < JPT; ++t) {
-      const int jj = jg + HEAD_KPARTS * t;
+      const int jj = jg + HEAD_JGROUPS * t;
       double g = 0.0;
       if (jj < A && lr < r_orig) {
         const float inv = cst[4 * jj + 1];
@@ -1294,7 +1300,7 @@ __global__ __launch_bounds__(256) void ppo_head_kernel(const PpoHeadArgs h) {
     }
   }
   {
-    __shared__ double wpart[4][PPO_NPART_FIXED];
+    __shared__ double wpart[HEAD_WAVES][PPO_NPART_FIXED];
     const double v5[PPO_NPART_FIXED] = {surr_acc, vl_acc, kl_acc, clip_acc, mir_acc};
 #pragma unroll
     for (int c = 0; c < PPO_NPART_FIXED; ++c) {
@@ -1303,12 +1309,15 @@ __global__ __launch_bounds__(256) void ppo_head_kernel(const PpoHeadArgs h) {
     }
     __syncthreads();
     double* block_out = a.partials + (long)blockIdx.x * (PPO_NPART_FIXED + A);
-    if (tid < PPO_NPART_FIXED) block_out[tid] = wpart[0][tid] + wpart[1][tid] + wpart[2][tid] + wpart[3][tid];
-    else if (tid < PPO_NPART_FIXED + A) block_out[tid] = reinterpret_cast<const double*>(dls_out)[tid - PPO_NPART_FIXED];
+    if (tid < PPO_NPART_FIXED) {
+      double r = wpart[0][tid];
+      for (int w = 1; w < HEAD_WAVES; ++w) r += wpart[w][tid];
+      block_out[tid] = r;
+    } else if (tid < PPO_NPART_FIXED + A) block_out[tid] = reinterpret_cast<const double*>(dls_out)[tid - PPO_NPART_FIXED];
   }
 
   // ---- phase 4: output-layer gradients for the weight-gradient contraction (d_mu, d_v to global memory) ----
-  for (int e = tid; e < HEAD_ROWS * A; e += 256) {
+  for (int e = tid; e < HEAD_ROWS * A; e += HEAD_THREADS) {
     const int r = e / A, jj = e - r * A;
     const long gr = grow(r);
     if (gr >= 0) a.d_mu[gr * A + jj] = dmu[r * A4 + jj];
@@ -1320,7 +1329,7 @@ __global__ __launch_bounds__(256) void ppo_head_kernel(const PpoHeadArgs h) {
   // ---- input gradient of the output layers, times ELU'(h): lane = hidden unit, its weight row in registers, a
   //      row's d_mu read with 16-byte broadcasts ----
   {
-    const int k = tid % Ha, rstep = 256 / Ha;
+    const int k = tid % Ha, rstep = HEAD_THREADS / Ha;
     float wrow[AM];
 #pragma unroll
     for (int q = 0; q < AM / 4; ++q) {
@@ -1343,7 +1352,7 @@ __global__ __launch_bounds__(256) void ppo_head_kernel(const PpoHeadArgs h) {
     }
   }
   {
-    const int k = tid % Hc, rstep = 256 / Hc;
+    const int k = tid % Hc, rstep = HEAD_THREADS / Hc;
     const float wk = wc[k];
 #pragma unroll 4
     for (int i = 0; i < HEAD_ROWS / rstep; ++i) {
@@ -1379,7 +1388,7 @@ static hipError_t launch_ppo_head_width(const PpoHeadArgs& h, size_t lds_bytes, 
     attr_set = true;
   }
   const dim3 grid(ppo_head_num_blocks(h.loss.mb, h.loss.rows > h.loss.mb));
-  hipLaunchKernelGGL(ppo_head_kernel<AM>, grid, dim3(256), lds_bytes, stream, h);
+  hipLaunchKernelGGL(ppo_head_kernel<AM>, grid, dim3(HEAD_THREADS), lds_bytes, stream, h);
   return hipGetLastError();
 }
 
