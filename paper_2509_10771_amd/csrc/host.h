@@ -260,7 +260,12 @@ inline void plan_layer(SplitPlan& p, int l, int M, int N, int32_t rows, int grou
   const int target = p.big[l] ? (paired ? DW_TARGET_WGS_BIG_PAIRED : DW_TARGET_WGS_BIG)
                               : (small_shares ? DW_TARGET_WGS_PAIRED : DW_TARGET_WGS);
   int s = (target + tiles * group - 1) / (tiles * group);
-  const int smax = rows / 128 > 1 ? rows / 128 : 1;
+  // Rows per split: 128, down to 32 where the launch would leave three quarters of the CUs idle (a split's steps run one after the
+  // other, about 0.7 us each).  Whole update of 5 x 4 steps, [48, 128, 128, 12] twice: 64 environments 1117 us at 128 rows, 1033
+  // here, 400 environments 1333 and 1233; [48, 512, 256, 128, 12]: 64 environments 1920 and 1819, 200 environments 2342 and 2343.
+  int least = 128;
+  while (least > 32 && tiles * group * (rows / least) < 64) least /= 2;
+  const int smax = rows / least > 1 ? rows / least : 1;
   if (s > smax) s = smax;
   if (s < 1) s = 1;
   int c = (rows + s - 1) / s;
