@@ -1013,11 +1013,14 @@ struct HeadLds {
   }
 };
 
+// Width at which a last hidden layer lies in LDS: zeros behind its units, which the sums do not notice.
+__host__ __device__ inline int head_pad(int H) { return H <= 32 ? 32 : H <= 64 ? 64 : H <= 128 ? 128 : 256; }
+
 template <int AM>
 __global__ __launch_bounds__(HEAD_THREADS) void ppo_head_kernel(const PpoHeadArgs h) {
   extern __shared__ float lds[];
   const PpoLossArgs& a = h.loss;
-  const int A = a.A, Ha = h.Ha, Hc = h.Hc;
+  const int A = a.A, Ra = h.Ha, Rc = h.Hc, Ha = head_pad(Ra), Hc = head_pad(Rc);
   const HeadLds L(Ha, Hc, A, AM);
   constexpr int A4 = AM;
   const int gp = L.gp;
@@ -1060,13 +1063,14 @@ __global__ __launch_bounds__(HEAD_THREADS) void ppo_head_kernel(const PpoHeadArg
     gb[i] = (r < r_orig && i0 + r < a.mb) ? a.idx[i0 + r] : -1;
   }
   constexpr int WROUND = 2048 / HEAD_THREADS;             // weight loads in flight per lane
-  const int w_elems = (Ha + 1) * AM;
+  const int w_elems = (Ha + 1) * AM;                      // the bias behind the padded rows
+  auto weight = [&](int k, int jj) { return jj < A && (k < Ra || k == Ha) ? h.w_a[min(k, Ra) * A + jj] : 0.f; };
   float wv[WROUND];
 #pragma unroll
   for (int i = 0; i < WROUND; ++i) {                      // first round (all of W for A <= 12 at 128 hidden units)
     const int e = tid + HEAD_THREADS * i;
     const int k = e / AM, jj = e - k * AM;
-    wv[i] = (e < w_elems && jj < A) ? h.w_a[k * A + jj] : 0.f;
+    wv[i] = weight(k, jj);
   }
   constexpr int HP = 2048 / HEAD_THREADS;                 // 16-byte pieces per lane and network (H <= 256)
   float4 ra[HP], rc[HP];
@@ -1079,11 +1083,13 @@ __global__ __launch_bounds__(HEAD_THREADS) void ppo_head_kernel(const PpoHeadArg
     rc[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (e < HEAD_ROWS * pa) {
       const long gr = grow(e >> sha);
-      if (gr >= 0) ra[i] = *reinterpret_cast<const float4*>(h.h_a + gr * Ha + 4 * (e & (pa - 1)));
+      const int c = 4 * (e & (pa - 1));
+      if (gr >= 0 && c < Ra) ra[i] = *reinterpret_cast<const float4*>(h.h_a + gr * Ra + c);
     }
     if (e < HEAD_ROWS * pc) {
       const long gr = grow(e >> shc);
-      if (gr >= 0) rc[i] = *reinterpret_cast<const float4*>(h.h_c + gr * Hc + 4 * (e & (pc - 1)));
+      const int c = 4 * (e & (pc - 1));
+      if (gr >= 0 && c < Rc) rc[i] = *reinterpret_cast<const float4*>(h.h_c + gr * Rc + c);
     }
   }
   // rollout rows, gathered through the permutation: wavefront w takes rows w, w + HEAD_WAVES, ..; lanes run over the row
@@ -1116,7 +1122,7 @@ __global__ __launch_bounds__(HEAD_THREADS) void ppo_head_kernel(const PpoHeadArg
     for (int i = 0; i < WROUND; ++i) {
       const int e = e0 + tid + HEAD_THREADS * i;
       const int k = e / AM, jj = e - k * AM;
-      wv[i] = (e < w_elems && jj < A) ? h.w_a[k * A + jj] : 0.f;
+      wv[i] = weight(k, jj);
     }
 #pragma unroll
     for (int i = 0; i < WROUND; ++i) {
@@ -1124,7 +1130,7 @@ __global__ __launch_bounds__(HEAD_THREADS) void ppo_head_kernel(const PpoHeadArg
       if (e < w_elems) wa[e] = wv[i];
     }
   }
-  for (int e = tid; e < Hc + 1; e += HEAD_THREADS) wc[e] = h.w_c[e];
+  for (int e = tid; e < Hc + 1; e += HEAD_THREADS) wc[e] = e < Rc || e == Hc ? h.w_c[min(e, Rc)] : 0.f;
   if (tid < A) {
     const float ls = a.log_std[tid];
     const float inv = expf(-ls);
@@ -1340,7 +1346,7 @@ __global__ __launch_bounds__(HEAD_THREADS) void ppo_head_kernel(const PpoHeadArg
     for (int i = 0; i < HEAD_ROWS / rstep; ++i) {      // uniform trip count; the lane only shifts the first row
       const int r = tid / Ha + i * rstep;
       const long gr = grow(r);
-      if (gr < 0) continue;
+      if (gr < 0 || k >= Ra) continue;
       float s = 0.f;
 #pragma unroll
       for (int q = 0; q < AM / 4; ++q) {
@@ -1348,7 +1354,7 @@ __global__ __launch_bounds__(HEAD_THREADS) void ppo_head_kernel(const PpoHeadArg
         s += d.x * wrow[4 * q] + d.y * wrow[4 * q + 1] + d.z * wrow[4 * q + 2] + d.w * wrow[4 * q + 3];
       }
       const float hv = ha[r * sa + k];
-      h.dz_a[gr * Ha + k] = s * (hv > 0.f ? 1.0f : hv + h.alpha_a);
+      h.dz_a[gr * Ra + k] = s * (hv > 0.f ? 1.0f : hv + h.alpha_a);
     }
   }
   {
@@ -1358,9 +1364,9 @@ __global__ __launch_bounds__(HEAD_THREADS) void ppo_head_kernel(const PpoHeadArg
     for (int i = 0; i < HEAD_ROWS / rstep; ++i) {
       const int r = tid / Hc + i * rstep;
       const long gr = grow(r);
-      if (gr < 0) continue;
+      if (gr < 0 || k >= Rc) continue;
       const float hv = hc[r * sc + k];
-      h.dz_c[gr * Hc + k] = dv[r] * wk * (hv > 0.f ? 1.0f : hv + h.alpha_c);
+      h.dz_c[gr * Rc + k] = dv[r] * wk * (hv > 0.f ? 1.0f : hv + h.alpha_c);
     }
   }
 }
@@ -1368,11 +1374,13 @@ __global__ __launch_bounds__(HEAD_THREADS) void ppo_head_kernel(const PpoHeadArg
 static int head_width(int A) { return A <= 4 ? 4 : A <= 8 ? 8 : A <= 12 ? 12 : A <= 16 ? 16 : 32; }
 
 size_t ppo_head_lds_bytes(int32_t Ha, int32_t Hc, int32_t A) {
-  return sizeof(float) * (size_t)HeadLds(Ha, Hc, A, head_width(A)).total;
+  return sizeof(float) * (size_t)HeadLds(head_pad(Ha), head_pad(Hc), A, head_width(A)).total;
 }
 
 bool ppo_head_supported(int32_t Ha, int32_t Hc, int32_t A) {
-  auto ok = [](int h) { return h == 32 || h == 64 || h == 128 || h == 256; };
+  // 16-byte rows; narrow layers only where they fill their padded width.  Whole update of [48, 400, 200, 100] networks, per-layer
+  // launches around the loss and this: 2621 and 2008 us at 100 environments, 3748 and 3048 at 1000, 8617 and 8019 at 4096.
+  auto ok = [](int h) { return h == 32 || h == 64 || (h > 64 && h <= 256 && h % 4 == 0); };
   return ok(Ha) && ok(Hc) && A >= 1 && A <= 32 && ppo_head_lds_bytes(Ha, Hc, A) <= 150 * 1024;
 }
 
