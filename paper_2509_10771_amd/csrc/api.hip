@@ -613,10 +613,9 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
         const int nbm = mse_num_blocks((int64_t)p.mb * K);
         RSLX_HIP(launch_mse(p.pred.act.out[pr.n_layers - 1], p.targ.out[pr.n_layers - 1], nullptr, p.mb, K,
                             p.pred.d_out, p.mse_partials, s));
-        RSLX_HIP(launch_mse_finish(p.mse_partials, nbm, (int64_t)p.mb * K, stats_row + RSLX_STAT_RND_LOSS, s));
         BwdJob rb{&pr, xr, p.mb, &p.pred.act, p.pred.d_out, p.pred.partials, &p.pred.plan, nullptr, &p.pred.pack};
         RSLX_TRY(backward_nets(&rb, 1, s));
-        RSLX_TRY(reduce_net(pr, p.pred, s));
+        RSLX_TRY(reduce_net(pr, p.pred, MseFinishArgs{p.mse_partials, nbm, (int64_t)p.mb * K, stats_row + RSLX_STAT_RND_LOSS}, s));
         const int64_t tr = *rnd_step + 1;
         AdamLayersArgs rl;
         memset(&rl, 0, sizeof rl);
@@ -762,10 +761,9 @@ int32_t bc_update_impl(rslx_mlp* student, const rslx_mlp* teacher, const float* 
       NetJob fj{student, xs, p.mb, &p.student.act, &p.student.pack};
       RSLX_TRY(forward_nets(&fj, 1, s));
       RSLX_HIP(launch_mse(p.student.act.out[Ls - 1], targets, idx, p.mb, A, p.student.d_out, p.mse_partials, s));
-      RSLX_HIP(launch_mse_finish(p.mse_partials, nbm, (int64_t)p.mb * A, stats_row, s));
       BwdJob bj{student, xs, p.mb, &p.student.act, p.student.d_out, p.student.partials, &p.student.plan, nullptr, &p.student.pack};
       RSLX_TRY(backward_nets(&bj, 1, s));
-      RSLX_TRY(reduce_net(*student, p.student, s));
+      RSLX_TRY(reduce_net(*student, p.student, MseFinishArgs{p.mse_partials, nbm, (int64_t)p.mb * A, stats_row}, s));
       const int64_t t = *adam_step + 1;
       AdamLayersArgs al;
       memset(&al, 0, sizeof al);

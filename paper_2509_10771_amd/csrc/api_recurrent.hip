@@ -741,7 +741,6 @@ int32_t rslx_bc_update_recurrent(rslx_memory* gru, rslx_mlp* student, const floa
       NetJob fj{student, xs, rows, &p.student.act, &p.student.pack};
       RSLX_TRY(forward_nets(&fj, 1, s));
       RSLX_HIP(launch_mse(p.student.act.out[Ls - 1], targets, ridx, rows, A, p.student.d_out, p.mse_partials, s));
-      RSLX_HIP(launch_mse_finish(p.mse_partials, nbm, (int64_t)rows * A, stats_row, s));
       BwdJob bj{student, xs, rows, &p.student.act, p.student.d_out, p.student.partials, &p.student.plan, p.mem.dh, &p.student.pack};
       RSLX_TRY(backward_nets(&bj, 1, s));
       RSLX_TRY(memories_backward(mem, mb, 1, obs, ridx, dones, T, nb, N, s));
@@ -751,6 +750,7 @@ int32_t rslx_bc_update_recurrent(rslx_memory* gru, rslx_mlp* student, const floa
         ra.sumsq_blocks = p.sumsq_all;
         reduce_add_net(ra, *student, p.student);
         reduce_add_memory(ra, *gru, p.mem);
+        ra.mse = MseFinishArgs{p.mse_partials, nbm, (int64_t)rows * A, stats_row};
         RSLX_HIP(launch_reduce_partials(ra, s));
       }
       const int64_t t1 = *adam_step + 1;

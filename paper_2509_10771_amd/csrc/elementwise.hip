@@ -488,9 +488,17 @@ __device__ void loss_finish_block(const LossFinishArgs& f) {
 // first workgroup finishes the loss sums instead.
 __global__ __launch_bounds__(256) void reduce_partials_kernel(const ReduceArgs a) {
   // the loss sums are a chain of dependent loads in one workgroup: it goes first so that it runs beside the others
-  const int has_finish = a.finish.blocks > 0 ? 1 : 0;
+  const int has_finish = a.finish.blocks > 0 || a.mse.blocks > 0 ? 1 : 0;
   if (has_finish && blockIdx.x == 0) {
-    loss_finish_block(a.finish);
+    if (a.finish.blocks > 0) {
+      loss_finish_block(a.finish);
+    } else {
+      __shared__ double sums[4];
+      double s = 0.0;
+      for (int i = threadIdx.x; i < a.mse.blocks; i += 256) s += a.mse.partials[i];
+      const double t = block_sum(s, sums);
+      if (threadIdx.x == 0) *a.mse.stat_out = (float)(t / (double)a.mse.count);
+    }
     return;
   }
   const int bid = (int)blockIdx.x - has_finish;
@@ -532,7 +540,7 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const ReduceArgs a
 }
 
 hipError_t launch_reduce_partials(const ReduceArgs& a, hipStream_t stream) {
-  const int extra = a.finish.blocks > 0 ? 1 : 0;
+  const int extra = a.finish.blocks > 0 || a.mse.blocks > 0 ? 1 : 0;
   if (a.blocks + extra <= 0) return hipSuccess;
   double bytes = 0.0;
   for (int i = 0; i < a.n_seg; ++i) bytes += 4.0 * (double)a.seg[i].size * (a.seg[i].split + 1);
@@ -1460,20 +1468,6 @@ hipError_t launch_mse(const float* y, const float* target, const int32_t* target
   const int64_t n = (int64_t)rows * width;
   hipLaunchKernelGGL(mse_kernel, dim3(mse_num_blocks(n)), dim3(256), 0, stream, y, target, target_idx, rows, width, d_y,
                      partials);
-  return hipGetLastError();
-}
-
-__global__ __launch_bounds__(256) void mse_finish_kernel(const double* __restrict__ partials, int blocks, long count,
-                                                         float* __restrict__ stat_out) {
-  __shared__ double smem[4];
-  double s = 0.0;
-  for (int i = threadIdx.x; i < blocks; i += 256) s += partials[i];
-  double t = block_sum(s, smem);
-  if (threadIdx.x == 0) *stat_out = (float)(t / (double)count);
-}
-
-hipError_t launch_mse_finish(const double* partials, int32_t blocks, int64_t count, float* stat_out, hipStream_t stream) {
-  hipLaunchKernelGGL(mse_finish_kernel, dim3(1), dim3(256), 0, stream, partials, blocks, (long)count, stat_out);
   return hipGetLastError();
 }
 

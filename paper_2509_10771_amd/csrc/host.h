@@ -443,11 +443,12 @@ inline void reduce_add_net(ReduceArgs& a, const rslx_mlp& n, const TrainBufs& t)
   }
 }
 
-inline int32_t reduce_net(const rslx_mlp& n, const TrainBufs& t, hipStream_t s) {
+inline int32_t reduce_net(const rslx_mlp& n, const TrainBufs& t, const MseFinishArgs& mse, hipStream_t s) {
   ReduceArgs a;
   memset(&a, 0, sizeof a);
   a.sumsq_blocks = t.sumsq;
   reduce_add_net(a, n, t);
+  a.mse = mse;
   RSLX_HIP(launch_reduce_partials(a, s));
   return RSLX_OK;
 }

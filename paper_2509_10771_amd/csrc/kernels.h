@@ -153,12 +153,15 @@ struct ReduceSeg {
   int32_t split;
   int32_t block_start;      // first workgroup of the segment
 };
+// Mean of squared errors from launch_mse's block sums.
+struct MseFinishArgs { const double* partials; int32_t blocks; int64_t count; float* stat_out; };   // blocks == 0: nothing to finish
 struct ReduceArgs {
   ReduceSeg seg[16];
   int32_t n_seg;
   int32_t blocks;           // workgroups over all segments; block b writes sumsq_blocks[b]
   double* sumsq_blocks;
-  LossFinishArgs finish;    // handled by one extra workgroup of the same launch
+  LossFinishArgs finish;    // handled by one extra workgroup of the same launch,
+  MseFinishArgs mse;        // and so is this, where there is no `finish`
 };
 constexpr int REDUCE_BLOCK_FLOATS = 256;
 hipError_t launch_reduce_partials(const ReduceArgs& a, hipStream_t stream);
@@ -248,7 +251,6 @@ hipError_t launch_ppo_head(const PpoHeadArgs& h, hipStream_t stream);
 int mse_num_blocks(int64_t n);
 hipError_t launch_mse(const float* y, const float* target, const int32_t* target_idx, int32_t rows, int32_t width,
                       float* d_y, double* partials, hipStream_t stream);
-hipError_t launch_mse_finish(const double* partials, int32_t blocks, int64_t count, float* stat_out, hipStream_t stream);
 
 hipError_t launch_sym_augment(const float* in, int32_t B, int32_t D, const int32_t* perm, const float* sign,
                               float* out, hipStream_t stream);
