@@ -238,8 +238,8 @@ struct SplitPlan {
   int32_t blocks = 0;      // workgroups of the reduction = entries of the squared-norm list
 };
 
-// Enough workgroups to fill the 256 CUs once, but at least 128 rows per split: four 64-row-tile workgroups per CU
-// (the first layer's launch of the 4096-environment update takes 40 us with 1024 of them, 47 with 1152), three of the
+// Enough workgroups to fill the 256 CUs once, but 128 rows per split (fewer in small launches, plan_layer): four
+// 64-row-tile workgroups per CU (the first layer's launch of the 4096-environment update takes 40 us with 1024 of them, 47 with 1152), three of the
 // 128x128 ones.  A weight gradient that shares its launch with the layer's input gradient (every layer but the first)
 // needs fewer - the input gradient's workgroups take the other slots - which also shrinks its partial sums: two per CU for
 // 128x128 tiles (whole update at 4096 environments, [512, 256, 128]: 8.65 ms with 512, 8.72 with 768, 8.85 with 1024), one
