@@ -252,7 +252,7 @@ void carve_memory(Carver& c, const rslx_memory& g, int32_t rows, int32_t nb, Rnn
   plan_layer(b.plan, 1, g.hidden, (int)GH, rows, group, false);
   b.partials = c.take<float>((size_t)b.plan.total);
   b.pack_ih = c.take<uint16_t>((size_t)3 * WeightPack::padded(g.in_dim) * GH);
-  if (seq_supported(g.cell, g.hidden)) {
+  if (seq_supported(g.cell, g.hidden, rows / nb)) {
     b.pack_hh = c.take<uint16_t>(3 * H * GH);
     b.pack_hh_t = c.take<uint16_t>(3 * H * GH);
   }
@@ -278,9 +278,9 @@ void adam_add_memory(AdamLayersArgs& a, const rslx_memory& g, const RnnBufs& m) 
 }
 
 // The roll-out of all memories of a call goes through one launch each way where their common width has that kernel.
-bool memories_seq(const rslx_memory* const* mem, int count) {
+bool memories_seq(const rslx_memory* const* mem, int count, int T) {
   for (int k = 0; k < count; ++k)
-    if (!seq_supported(mem[k]->cell, mem[k]->hidden) || mem[k]->hidden != mem[0]->hidden) return false;
+    if (!seq_supported(mem[k]->cell, mem[k]->hidden, T) || mem[k]->hidden != mem[0]->hidden) return false;
   return true;
 }
 
@@ -380,7 +380,7 @@ int32_t memories_forward(const rslx_memory* const* mem, RnnBufs* const* mb, int 
     bi.p[k].Bp = mb[k]->pack_ih;
   }
   RSLX_HIP(launch_gemm(GEMM_FWD, bi, s));
-  const bool seq = memories_seq(mem, count);
+  const bool seq = memories_seq(mem, count, T);
   if (seq) RSLX_HIP(launch_seq_fwd(seq_args(mem, mb, count, ridx, dones, T, nb), s));
   for (int t = 0; t < (seq ? 0 : T); ++t) {
     StepFwdArgs sa;
@@ -404,7 +404,7 @@ int32_t memories_forward(const rslx_memory* const* mem, RnnBufs* const* mb, int 
 int32_t memories_backward(const rslx_memory* const* mem, RnnBufs* const* mb, int count, const float* const* obs,
                           const int32_t* ridx, const uint8_t* dones, int T, int nb, int N, hipStream_t s) {
   const int rows = T * nb;
-  const bool seq = memories_seq(mem, count);
+  const bool seq = memories_seq(mem, count, T);
   if (seq) RSLX_HIP(launch_seq_bwd(seq_args(mem, mb, count, ridx, dones, T, nb), s));
   for (int t = seq ? -1 : T - 1; t >= 0; --t) {
     StepBwdArgs sb;

@@ -345,7 +345,7 @@ struct SeqArgs {
   const uint8_t* done;        // episode-end flags (null = none); row r reads done[ridx ? ridx[r] : i]
   const int32_t* ridx;        // [T nb]
 };
-bool seq_supported(int32_t cell, int32_t H);
+bool seq_supported(int32_t cell, int32_t H, int32_t T);
 hipError_t launch_seq_fwd(const SeqArgs& a, hipStream_t stream);
 hipError_t launch_seq_bwd(const SeqArgs& a, hipStream_t stream);
 

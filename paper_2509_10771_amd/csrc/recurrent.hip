@@ -1083,7 +1083,11 @@ hipError_t launch_step_bwd(const StepBwdArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-bool seq_supported(int32_t cell, int32_t H) { return (cell == CELL_GRU || cell == CELL_LSTM) && H == 128; }
+// One step has no recurrence to keep the weights for: an update of T = 1 (two memories of 128 and [64, 12], us a call) takes
+// 97 with these kernels and 85 with a launch per step at one minibatch of 16 rows (LSTM; GRU 92 and 84), 428 and 378 at two of 8192 (GRU 382
+// and 353).
+// T = 2: GRU 103 and 102, 568 and 660; LSTM 108 and 104, 623 and 675.
+bool seq_supported(int32_t cell, int32_t H, int32_t T) { return (cell == CELL_GRU || cell == CELL_LSTM) && H == 128 && T >= 2; }
 
 hipError_t launch_seq_fwd(const SeqArgs& a, hipStream_t stream) {
   const double G = a.cell == CELL_LSTM ? 4 : 3;

@@ -27,6 +27,23 @@ def test_whole_rollout_launch(rx, N, T, cell):
 
 
 @pytest.mark.parametrize("cell", ["gru", "lstm"])
+@pytest.mark.parametrize("T", [1, 2])
+def test_one_step_takes_the_launch_per_step(rx, cell, T):
+    """Which kernels an update of memories of 128 runs: the whole roll-out's from two steps on."""
+    case = RCase(_workload(34, T, cell), 1)
+    tr = case.ref["trace"][0]
+    b = tr["before"]
+    nets = _nets(rx, case.w, b["actor"], b["critic"], b["opt"])
+    rx.rslx_trace_begin(256)
+    _call(rx, nets, case.gpu_rollout(rx, tr["envs"]), case.gpu_cfg(rx, 1, 1), 1, b["opt"]["step"])
+    torch.cuda.synchronize()
+    names = [r[0] for r in rx.rslx_trace_end()]
+    per_step = ["%s_step_%s" % (cell, d) for d in ("fwd", "bwd")]
+    whole = ["%s_seq_%s" % (cell, d) for d in ("fwd", "bwd")]
+    assert [names.count(n) for n in per_step + whole] == ([1, 1, 0, 0] if T == 1 else [0, 0, 1, 1]), names
+
+
+@pytest.mark.parametrize("cell", ["gru", "lstm"])
 def test_weights_without_a_split_reach_only_their_own_unit(rx, cell):
     """A recurrent weight of 2^120 saturates the gates of one unit: the update stays finite wherever fp32 arithmetic does."""
     case = RCase(_workload(34, 2, cell, done_p=0.0), 1)
