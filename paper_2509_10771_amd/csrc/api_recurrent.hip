@@ -241,7 +241,14 @@ struct RnnPlan {
   size_t bytes = 0;
 };
 
-void carve_memory(Carver& c, const rslx_memory& g, int32_t rows, int32_t nb, RnnBufs& b, int group = 2) {
+// The roll-out of all memories of a call goes through one launch each way where their common width has that kernel.
+bool memories_seq(const rslx_memory* const* mem, int count, int T) {
+  for (int k = 0; k < count; ++k)
+    if (!seq_supported(mem[k]->cell, mem[k]->hidden, T) || mem[k]->hidden != mem[0]->hidden) return false;
+  return true;
+}
+
+void carve_memory(Carver& c, const rslx_memory& g, int32_t rows, int32_t nb, bool seq, RnnBufs& b, int group = 2) {
   const size_t H = g.hidden, GH = gate_width(g), S = state_width(g);
   b.gi = c.take<float>(rows * GH); b.gh = c.take<float>(rows * GH);
   b.dgi = g.cell == RSLX_CELL_GRU ? c.take<float>(rows * GH) : nullptr;
@@ -252,7 +259,7 @@ void carve_memory(Carver& c, const rslx_memory& g, int32_t rows, int32_t nb, Rnn
   plan_layer(b.plan, 1, g.hidden, (int)GH, rows, group, false);
   b.partials = c.take<float>((size_t)b.plan.total);
   b.pack_ih = c.take<uint16_t>((size_t)3 * WeightPack::padded(g.in_dim) * GH);
-  if (seq_supported(g.cell, g.hidden, rows / nb)) {
+  if (seq) {
     b.pack_hh = c.take<uint16_t>(3 * H * GH);
     b.pack_hh_t = c.take<uint16_t>(3 * H * GH);
   }
@@ -277,13 +284,6 @@ void adam_add_memory(AdamLayersArgs& a, const rslx_memory& g, const RnnBufs& m) 
   a.layer[a.n_layers++] = AdamLayer{g.params + o, g.grads + o, g.adam_m + o, g.adam_v + o, m.pack_hh, m.pack_hh_t, H, GH, m.pack_hh ? H : 0};
 }
 
-// The roll-out of all memories of a call goes through one launch each way where their common width has that kernel.
-bool memories_seq(const rslx_memory* const* mem, int count, int T) {
-  for (int k = 0; k < count; ++k)
-    if (!seq_supported(mem[k]->cell, mem[k]->hidden, T) || mem[k]->hidden != mem[0]->hidden) return false;
-  return true;
-}
-
 SeqArgs seq_args(const rslx_memory* const* mem, RnnBufs* const* mb, int count, const int32_t* ridx, const uint8_t* dones, int T, int nb) {
   SeqArgs a;
   memset(&a, 0, sizeof a);
@@ -306,8 +306,10 @@ void rnn_plan(Carver& c, const rslx_memory* ga, const rslx_mlp* actor, const rsl
   p.rows_all = c.take<int32_t>((size_t)cfg->epochs * p.T * p.N);
   carve_train(c, *actor, p.rows, 2, p.actor, true);
   carve_train(c, *critic, p.rows, 2, p.critic, true);
-  carve_memory(c, *ga, p.rows, p.nb, p.ma);
-  carve_memory(c, *gc, p.rows, p.nb, p.mc);
+  const rslx_memory* mem[2] = {ga, gc};
+  const bool seq = memories_seq(mem, 2, p.T);
+  carve_memory(c, *ga, p.rows, p.nb, seq, p.ma);
+  carve_memory(c, *gc, p.rows, p.nb, seq, p.mc);
   p.n_sumsq = p.actor.n_sumsq + p.critic.n_sumsq + p.ma.plan.blocks + p.mc.plan.blocks + 1;
   p.sumsq_all = c.take<double>((size_t)p.n_sumsq + 1);
   p.fused_head = actor->n_layers >= 2 && critic->n_layers >= 2 &&
@@ -631,7 +633,7 @@ void rnn_bc_plan(Carver& c, const rslx_memory* g, const rslx_mlp* student, int32
   p.perm_ws = c.take<char>(perm_workspace_bytes(N));
   p.rows_all = c.take<int32_t>((size_t)cfg->epochs * T * N);
   carve_train(c, *student, p.rows, 1, p.student, true);
-  carve_memory(c, *g, p.rows, p.nb, p.mem, 1);
+  carve_memory(c, *g, p.rows, p.nb, memories_seq(&g, 1, T), p.mem, 1);
   p.n_sumsq = p.student.n_sumsq + p.mem.plan.blocks;
   p.sumsq_all = c.take<double>((size_t)p.n_sumsq + 1);
   p.mse_partials = c.take<double>(mse_num_blocks((int64_t)p.rows * student->dims[student->n_layers]));

@@ -1,0 +1,27 @@
+"""Workspace queries of the recurrent updates: what a path does not read is not asked for.  Host arithmetic only, no GPU."""
+import pytest
+import torch
+
+import paper_2509_10771_amd as rx
+
+
+def _mlp(dims, log_std=False):
+    n = sum(i * o + o for i, o in zip(dims[:-1], dims[1:])) + (dims[-1] if log_std else 0)
+    return rx.Mlp(dims, torch.zeros(n), trainable=True, has_log_std=log_std)
+
+
+def _bytes(cell, Ha, Hc, T, N):
+    G, D, A, B = (4 if cell == "lstm" else 3), 8, 2, T * N
+    memory = lambda H: rx.Memory(int(cell == "lstm"), D, H, torch.zeros(G * H * (D + H + 2)), trainable=True)  # noqa: E731
+    z = torch.zeros
+    ro = rx.Rollout(T, N, z(B, D), z(B, D), z(B, A), z(B), z(B), z(B, A), z(B, A), z(B), z(B))
+    return rx.rslx_ppo_update_recurrent_workspace_bytes(memory(Ha), _mlp((Ha, 8, A), True), memory(Hc), _mlp((Hc, 8, 1)), ro,
+                                                        rx.PpoCfg(minibatches=1))
+
+
+@pytest.mark.parametrize("cell", ["gru", "lstm"])
+@pytest.mark.parametrize("T,other", [(3, 64), (3, 124), (1, 128)])
+def test_no_split_copies_where_nothing_reads_them(cell, T, other):
+    """A memory of 128 beside one of another width, or for a single step, runs a launch per step, which reads fp32 weights: it asks
+    for no more than the next wider memory."""
+    assert _bytes(cell, 124, other, T, 2) < _bytes(cell, 128, other, T, 2) < _bytes(cell, 132, other, T, 2)
