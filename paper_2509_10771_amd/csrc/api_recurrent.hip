@@ -210,15 +210,17 @@ int32_t rslx_act_recurrent_dc(const rslx_memory* mem_actor, const rslx_mlp* acto
 
 namespace {
 
-struct RnnBufs {          // per memory, one column-wise minibatch (rows = T * nb)
-  float* gi = nullptr;    // [rows, G H] input-side gate terms
-  float* gh = nullptr;    // [rows, G H] what the forward steps store for the backward pass (GRU: gh, LSTM: a)
+// Per memory, one column-wise minibatch (rows = T * nb).  A launch per step and the whole-roll-out kernels (`seq`) leave
+// different things for the backward pass.
+struct RnnBufs {
+  float* gi = nullptr;    // [rows, G H] input-side gate terms; seq: replaced by the activated gates
+  float* gh = nullptr;    // [rows, G H] hidden-side terms (GRU) or pre-activations (LSTM); seq: [rows, H] the candidate's (GRU), none (LSTM)
   float* dgi = nullptr;   // [rows, G H] GRU only: gradient w.r.t. gi
   float* dgh = nullptr;   // [rows, G H] gradient w.r.t. the hidden-side terms (LSTM: w.r.t. a, serves both sides)
   float* hin = nullptr;   // [rows, S] packed state every step starts from
   float* hs = nullptr;    // [rows, H] new hidden states = input of the MLP
   float* dh = nullptr;    // [rows, H] gradient from the MLP
-  float* direct = nullptr;  // [nb, H] carried between backward steps (GRU: dh z, LSTM: gradient w.r.t. c)
+  float* direct = nullptr;  // [nb, H] carried between backward steps (GRU: dh z, LSTM: gradient w.r.t. c); seq: none
   SplitPlan plan;           // layer 0: W_ih / b_ih, layer 1: W_hh / b_hh
   float* partials = nullptr;
   uint16_t* pack_ih = nullptr;    // split weights (launch_pack_weights): W_ih, W_hh and its transpose
@@ -250,11 +252,13 @@ bool memories_seq(const rslx_memory* const* mem, int count, int T) {
 
 void carve_memory(Carver& c, const rslx_memory& g, int32_t rows, int32_t nb, bool seq, RnnBufs& b, int group = 2) {
   const size_t H = g.hidden, GH = gate_width(g), S = state_width(g);
-  b.gi = c.take<float>(rows * GH); b.gh = c.take<float>(rows * GH);
-  b.dgi = g.cell == RSLX_CELL_GRU ? c.take<float>(rows * GH) : nullptr;
+  const bool gru = g.cell == RSLX_CELL_GRU;
+  b.gi = c.take<float>(rows * GH);
+  b.gh = !seq ? c.take<float>(rows * GH) : gru ? c.take<float>(rows * H) : nullptr;
+  b.dgi = gru ? c.take<float>(rows * GH) : nullptr;
   b.dgh = c.take<float>(rows * GH);
   b.hin = c.take<float>(rows * S); b.hs = c.take<float>(rows * H); b.dh = c.take<float>(rows * H);
-  b.direct = c.take<float>(nb * H);
+  b.direct = seq ? nullptr : c.take<float>(nb * H);
   plan_layer(b.plan, 0, g.in_dim, (int)GH, rows, group, false);
   plan_layer(b.plan, 1, g.hidden, (int)GH, rows, group, false);
   b.partials = c.take<float>((size_t)b.plan.total);

@@ -25,3 +25,14 @@ def test_no_split_copies_where_nothing_reads_them(cell, T, other):
     """A memory of 128 beside one of another width, or for a single step, runs a launch per step, which reads fp32 weights: it asks
     for no more than the next wider memory."""
     assert _bytes(cell, 124, other, T, 2) < _bytes(cell, 128, other, T, 2) < _bytes(cell, 132, other, T, 2)
+
+
+@pytest.mark.parametrize("cell", ["gru", "lstm"])
+def test_no_buffers_of_the_path_not_taken(cell):
+    """A launch per step stores 3 H (GRU) or 4 H (LSTM) hidden-side terms per row for the backward pass, the whole-roll-out kernels
+    H or none: what a further row costs lies that much below the widths around."""
+    T, rows = 24, 24 * 512
+    per_row = lambda H: (_bytes(cell, H, H, T, 1024) - _bytes(cell, H, H, T, 512)) / rows  # noqa: E731
+    per_step = 0.5 * (per_row(124) + per_row(132))
+    saved = 2 * 4 * 128 * (2 if cell == "gru" else 4)          # two memories, bytes
+    assert per_row(128) <= per_step - 0.95 * saved             # 5 %: the reduction's partial sums, which step with the width
