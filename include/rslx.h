@@ -200,7 +200,9 @@ int32_t rslx_act(const rslx_mlp* actor, const rslx_mlp* critic, const float* obs
  *   R_t = A_t + V_t.   If timeouts != NULL, r_t is first replaced by r_t + gamma V_t timeout_t.
  * If normalize_adv != 0, advantages are then replaced by (A - mean) / (std + 1e-8) with the
  * mean and the unbiased (n-1) std taken over all T*N entries; returns use the raw A.
- * rewards, values [T,N]; last_values [N]; dones, timeouts uint8 [T,N]; outputs [T,N]. All device. */
+ * rewards, values [T,N]; last_values [N]; dones, timeouts uint8 [T,N]; outputs [T,N]. All device.
+ * advantages and returns may be the buffers rewards and values themselves (one each, in either order),
+ * which are then overwritten; they must not overlap an input in any other way, nor each other. */
 size_t rslx_gae_workspace_bytes(int32_t T, int32_t N);
 int32_t rslx_gae(const float* rewards, const float* values, const float* last_values,
                  const uint8_t* dones, const uint8_t* timeouts_or_null, int32_t T, int32_t N,

@@ -44,13 +44,14 @@ hipError_t launch_fill(float* p, int64_t n, float value, hipStream_t stream) {
 }
 
 // ---- GAE ----------------------------------------------------------------------------------------------
-// One lane per environment column: loads are coalesced across n, the T-step recurrence runs in registers.
-constexpr int GAE_COLS = 64;           // environments per workgroup of the kernel below, and of this one's partial sums
-__global__ __launch_bounds__(256) void gae_scan_kernel(const float* __restrict__ rewards, const float* __restrict__ values,
+// One lane per environment column: loads are coalesced across n, the T-step recurrence runs in registers.  adv and ret may be the
+// buffers of rewards and values: every batch of steps is loaded before its results are stored, and nothing is read again.
+constexpr int GAE_BATCH = 8;
+__global__ __launch_bounds__(256) void gae_scan_kernel(const float* rewards, const float* values,
                                                          const float* __restrict__ last_values,
                                                          const uint8_t* __restrict__ dones,
                                                          const uint8_t* __restrict__ timeouts, int T, int N, float gamma,
-                                                         float lam, float* __restrict__ adv, float* __restrict__ ret,
+                                                         float lam, float* adv, float* ret,
                                                          double* __restrict__ partials) {
   __shared__ double smem[4];
   const int n = blockIdx.x * 256 + threadIdx.x;
@@ -59,20 +60,31 @@ __global__ __launch_bounds__(256) void gae_scan_kernel(const float* __restrict__
     float a_next = 0.f;
     float v_next = last_values[n];
     const float gl = gamma * lam;
-#pragma unroll 8
-    for (int t = T - 1; t >= 0; --t) {
-      const long o = (long)t * N + n;
-      float r = rewards[o];
-      const float v = values[o];
-      const float nd = dones[o] ? 0.f : 1.f;
-      if (timeouts != nullptr && timeouts[o]) r += gamma * v;
-      const float delta = r + gamma * nd * v_next - v;
-      a_next = delta + gl * nd * a_next;
-      adv[o] = a_next;
-      ret[o] = a_next + v;
-      s += (double)a_next;
-      q += (double)a_next * (double)a_next;
-      v_next = v;
+    for (int t1 = T - 1; t1 >= 0; t1 -= GAE_BATCH) {
+      float r[GAE_BATCH], v[GAE_BATCH];
+      uint8_t done[GAE_BATCH], late[GAE_BATCH];
+#pragma unroll
+      for (int i = 0; i < GAE_BATCH; ++i) {
+        const long o = (long)max(t1 - i, 0) * N + n;                 // below the first step: the first again, not used
+        r[i] = rewards[o];
+        v[i] = values[o];
+        done[i] = dones[o];
+        late[i] = timeouts != nullptr ? timeouts[o] : 0;
+      }
+#pragma unroll
+      for (int i = 0; i < GAE_BATCH; ++i) {
+        if (t1 - i < 0) break;
+        const long o = (long)(t1 - i) * N + n;
+        const float nd = done[i] ? 0.f : 1.f;
+        const float rw = late[i] ? r[i] + gamma * v[i] : r[i];
+        const float delta = rw + gamma * nd * v_next - v[i];
+        a_next = delta + gl * nd * a_next;
+        adv[o] = a_next;
+        ret[o] = a_next + v[i];
+        s += (double)a_next;
+        q += (double)a_next * (double)a_next;
+        v_next = v[i];
+      }
     }
   }
   if (partials != nullptr) {
@@ -90,12 +102,15 @@ __global__ __launch_bounds__(256) void gae_scan_kernel(const float* __restrict__
 // GAE_CHUNK steps are requested at once, the first wavefront runs the recurrence from LDS, and all write the results.  Whole
 // calls of 24 steps, one lane per column and this: 10.3 and 8.5 us at 4096 columns, 11.0 and 9.2 at 16 384, 20.3 and 17.9 at
 // 65 535; of 8 steps the same below 40 000, 11.3 and 13.0 at 65 535; of 48 steps 15.2 and 11.5, 16.5 and 12.9, 31.7 and 27.9.
+// Results may lie over the inputs here too: the value of step t0, which the chunk of earlier steps needs, is fetched with this
+// chunk's own loads, before anything of it is overwritten.
+constexpr int GAE_COLS = 64;           // environments per workgroup, and per partial sum
 constexpr int GAE_WAVES = 8, GAE_CHUNK = 32, GAE_STEPS = GAE_CHUNK / GAE_WAVES;
-__global__ __launch_bounds__(64 * GAE_WAVES) void gae_scan_narrow_kernel(const float* __restrict__ rewards, const float* __restrict__ values,
+__global__ __launch_bounds__(64 * GAE_WAVES) void gae_scan_narrow_kernel(const float* rewards, const float* values,
                                                                          const float* __restrict__ last_values,
                                                                          const uint8_t* __restrict__ dones,
                                                                          const uint8_t* __restrict__ timeouts, int T, int N, float gamma,
-                                                                         float lam, float* __restrict__ adv, float* __restrict__ ret,
+                                                                         float lam, float* adv, float* ret,
                                                                          double* __restrict__ partials) {
   __shared__ float delta[GAE_CHUNK][GAE_COLS], decay[GAE_CHUNK][GAE_COLS];   // decay: gamma lambda (1 - done); then the advantage
   __shared__ double smem[GAE_WAVES];
@@ -104,18 +119,19 @@ __global__ __launch_bounds__(64 * GAE_WAVES) void gae_scan_narrow_kernel(const f
   const float gl = gamma * lam;
   double s = 0.0, q = 0.0;
   float a_next = 0.f;
-  const float v_last = last_values[nc];
+  float v_after = last_values[nc];       // value of step t_end
   for (int t_end = T; t_end > 0; t_end -= GAE_CHUNK) {
     const int t0 = max(t_end - GAE_CHUNK, 0);
     float r[GAE_STEPS], v[GAE_STEPS], v_next[GAE_STEPS];
     uint8_t done[GAE_STEPS], late[GAE_STEPS];
+    const float v_first = values[(long)t0 * N + nc];
 #pragma unroll
     for (int i = 0; i < GAE_STEPS; ++i) {
       const int t = min(t0 + wave + GAE_WAVES * i, t_end - 1);       // past the end: the last step again, not used
       const long o = (long)t * N + nc;
       r[i] = rewards[o];
       v[i] = values[o];
-      v_next[i] = values[t + 1 < T ? o + N : o];
+      v_next[i] = values[t + 1 < t_end ? o + N : o];
       done[i] = dones[o];
       late[i] = timeouts != nullptr ? timeouts[o] : 0;
     }
@@ -125,9 +141,10 @@ __global__ __launch_bounds__(64 * GAE_WAVES) void gae_scan_narrow_kernel(const f
       if (t0 + c >= t_end) break;
       const float nd = done[i] ? 0.f : 1.f;
       const float rw = late[i] ? r[i] + gamma * v[i] : r[i];
-      delta[c][lane] = rw + gamma * nd * (t0 + c + 1 < T ? v_next[i] : v_last) - v[i];
+      delta[c][lane] = rw + gamma * nd * (t0 + c + 1 < t_end ? v_next[i] : v_after) - v[i];
       decay[c][lane] = gl * nd;
     }
+    v_after = v_first;
     __syncthreads();
     if (wave == 0) {
       for (int c = t_end - t0 - 1; c >= 0; c -= 8) {
