@@ -22,7 +22,7 @@ def _inputs(T, N, seed):
                 last=g.normal(size=N).astype(np.float32), dones=(g.random((T, N)) < 0.05).astype(np.uint8) | timeouts, timeouts=timeouts)
 
 
-@pytest.mark.parametrize("T,N", [(1, 3), (24, 65), (32, 64), (33, 130), (48, 4097), (100, 63), (7, 65537), (41, 66000)])
+@pytest.mark.parametrize("T,N", [(1, 3), (24, 65), (32, 64), (33, 130), (48, 4097), (100, 63), (7, 65537), (41, 66000), (5, 196609)])
 def test_gae_in_place(rx, T, N):
     """Advantages over the rewards and returns over the values, and the other way round: the bits of separate buffers."""
     d = {k: dev(v) for k, v in _inputs(T, N, T + N).items()}
