@@ -255,7 +255,8 @@ int32_t rslx_act_dc(const rslx_mlp* actor, const rslx_mlp* critic, const float* 
 size_t rslx_gae_workspace_bytes(int32_t T, int32_t N) {
   (void)T;
   if (N <= 0) return 256;
-  return (size_t)gae_num_blocks(N) * 16 + 16 + 512;
+  // as if 64 columns shared a partial sum up to 65 535, so that a workspace for one of these counts serves the smaller ones
+  return (size_t)(N < 65536 ? (N + 63) / 64 : gae_num_blocks(N)) * 16 + 16 + 512;
 }
 
 int32_t rslx_gae(const float* rewards, const float* values, const float* last_values, const uint8_t* dones,

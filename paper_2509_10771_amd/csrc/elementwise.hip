@@ -46,9 +46,10 @@ hipError_t launch_fill(float* p, int64_t n, float value, hipStream_t stream) {
 // ---- GAE ----------------------------------------------------------------------------------------------
 // One lane per environment column: loads are coalesced across n, the T-step recurrence runs in registers.  adv and ret may be the
 // buffers of rewards and values: every batch of steps is loaded before its results are stored, and nothing is read again.
-// Batches of 8 hide the latency where the lanes are few, 2 keep fewer rows of memory open where they are many.  24 steps without
-// normalisation, us: 9.0 and 10.2 at 131 072 columns, 14.3 and 13.7 at 200 000, 17.8 and 16.8 at 262 144, 87.9 and 85.1 at 1 048 576.
-constexpr int GAE_BATCH = 8, GAE_BATCH_MANY = 2, GAE_MANY = 196608;
+// Batches of 8 hide the latency where the lanes are few, shorter ones keep fewer rows of memory open where they are many.  24 steps
+// without normalisation in batches of 8, 2 and 1, us: 9.0, 10.2 and - at 131 072 columns, 14.3, 13.7 and 14.7 at 200 000, 17.8, 16.8
+// and 17.2 at 262 144, 25.5, 25.7 and 24.9 at 400 000, 87.9, 84.8 and 80.4 at 1 048 576.
+constexpr int GAE_MANY = 196608, GAE_MOST = 393216;
 template <int BATCH>
 __global__ __launch_bounds__(256) void gae_scan_kernel(const float* rewards, const float* values,
                                                          const float* __restrict__ last_values,
@@ -102,9 +103,7 @@ __global__ __launch_bounds__(256) void gae_scan_kernel(const float* rewards, con
 
 // The same for fewer columns than fill the chip with one lane each: what a column costs there is the latency of its loads, one
 // batch of steps after the other.  Here 8 wavefronts share 64 columns: each takes every eighth step, so all of up to
-// GAE_CHUNK steps are requested at once, the first wavefront runs the recurrence from LDS, and all write the results.  Whole
-// calls of 24 steps, one lane per column and this: 10.3 and 8.5 us at 4096 columns, 11.0 and 9.2 at 16 384, 20.3 and 17.9 at
-// 65 535; of 8 steps the same below 40 000, 11.3 and 13.0 at 65 535; of 48 steps 15.2 and 11.5, 16.5 and 12.9, 31.7 and 27.9.
+// GAE_CHUNK steps are requested at once, the first wavefront runs the recurrence from LDS, and all write the results.
 // Results may lie over the inputs here too: the value of step t0, which the chunk of earlier steps needs, is fetched with this
 // chunk's own loads, before anything of it is overwritten.
 constexpr int GAE_COLS = 64;           // environments per workgroup, and per partial sum
@@ -248,7 +247,10 @@ __global__ __launch_bounds__(256) void adv_normalize_kernel(float* __restrict__ 
   }
 }
 
-static int gae_block(int32_t N) { return N >= 65536 ? 256 : GAE_COLS; }
+// That kernel as long as every CU has one workgroup of it.  Whole normalised calls, it and one lane per column (us): 24 steps 8.8 and
+// 9.1 at 16 384 columns, 9.8 and 9.3 at 20 000, 16.7 and 12.3 at 65 535; 100 steps 18.7 and 20.1, 21.1 and 20.6, 42.2 and 35.4; 8
+// steps 8.3 both up to 32 768, 13.3 and 8.3 at 65 535.
+static int gae_block(int32_t N) { return N > 256 * GAE_COLS ? 256 : GAE_COLS; }
 int gae_num_blocks(int32_t N) { int b = gae_block(N); return (N + b - 1) / b; }
 
 hipError_t launch_gae(const float* rewards, const float* values, const float* last_values, const uint8_t* dones,
@@ -256,11 +258,12 @@ hipError_t launch_gae(const float* rewards, const float* values, const float* la
                       float* adv, float* ret, double* partials, hipStream_t stream) {
   const int nb = gae_num_blocks(N);
   double* part = normalize ? partials : nullptr;
-  TraceScope ts(stream, normalize ? "gae_scan+normalize" : "gae_scan", 0.0,
+  const bool narrow = gae_block(N) == GAE_COLS;
+  TraceScope ts(stream, narrow ? (normalize ? "gae_scan+normalize" : "gae_scan") : normalize ? "gae_columns+normalize" : "gae_columns", 0.0,
                 (double)T * N * (normalize ? 25.0 : 17.0) + 4.0 * N);
-  if (gae_block(N) == 256)
-    hipLaunchKernelGGL(N >= GAE_MANY ? gae_scan_kernel<GAE_BATCH_MANY> : gae_scan_kernel<GAE_BATCH>, dim3(nb), dim3(256), 0, stream,
-                       rewards, values, last_values, dones, timeouts, T, N, gamma, lam, adv, ret, part);
+  if (!narrow)
+    hipLaunchKernelGGL(N < GAE_MANY ? gae_scan_kernel<8> : N < GAE_MOST ? gae_scan_kernel<2> : gae_scan_kernel<1>, dim3(nb), dim3(256), 0,
+                       stream, rewards, values, last_values, dones, timeouts, T, N, gamma, lam, adv, ret, part);
   else
     hipLaunchKernelGGL(gae_scan_narrow_kernel, dim3(nb), dim3(64 * GAE_WAVES), 0, stream, rewards, values, last_values, dones,
                        timeouts, T, N, gamma, lam, adv, ret, part);

@@ -1,4 +1,4 @@
-"""Workspace queries of the recurrent updates: what a path does not read is not asked for.  Host arithmetic only, no GPU."""
+"""Workspace queries: what a path does not read is not asked for, and a workspace serves smaller calls.  Host arithmetic only."""
 import pytest
 import torch
 
@@ -36,3 +36,8 @@ def test_no_buffers_of_the_path_not_taken(cell):
     per_step = 0.5 * (per_row(124) + per_row(132))
     saved = 2 * 4 * 128 * (2 if cell == "gru" else 4)          # two memories, bytes
     assert per_row(128) <= per_step - 0.95 * saved             # 5 %: the reduction's partial sums, which step with the width
+
+
+def test_gae_workspace_serves_fewer_environments():
+    need = [rx.rslx_gae_workspace_bytes(24, n) for n in (1, 64, 65, 4096, 16384, 16385, 20000, 32768, 65535)]
+    assert need == sorted(need)
