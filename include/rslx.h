@@ -446,7 +446,7 @@ int32_t rslx_sym_augment(const rslx_sym* sym, const float* obs_in, const float* 
 /* x = obs[:, subset]; r_raw_n = sum_k (predictor(x_n) - target(x_n))_k^2.  If update_stats,
  * running = {mean, var, count} (device float[3], population variance) is merged with the N new
  * values (Chan et al. pairwise update) before use.  r_int = r_raw / sqrt(var + 1e-8) is written
- * to r_int_out [N]; if rewards_inout != NULL, rewards_inout[n] += weight * r_int[n]. */
+ * to r_int_out [N]; if rewards_inout != NULL, rewards_inout[n] += weight * r_int[n] (its own buffer). */
 size_t rslx_rnd_workspace_bytes(const rslx_mlp* target, int32_t N);
 int32_t rslx_rnd(const rslx_mlp* target, const rslx_mlp* predictor, const float* obs, int32_t N,
                  int32_t D, const int32_t* subset_idx_or_null, int32_t n_subset, float* running,

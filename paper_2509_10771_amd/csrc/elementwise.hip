@@ -1551,6 +1551,10 @@ hipError_t launch_stage_input(const float* in, int32_t ld, int32_t B, int32_t D,
 // 16 lanes share a row, 64 rows a workgroup: a row is read 256 bytes at a time.  16 384 rows of 64: 4.9 us; one lane per row,
 // which walks its own row 4 bytes at a time, takes 18.5.
 constexpr int RND_ROWS = 64, RND_LANES = 16;
+// Block sums that every workgroup of the second launch adds up itself; longer lists are folded first, as their reads grow with N^2.
+// Whole calls, networks [8, 32, 1], without and with the fold (us): 38.7 and 40.1 at 131 072 rows, 61.3 both at 262 144, 107.7 and 104.6
+// at 524 288, 1358 and 928 at 4 194 304.
+constexpr int RND_MAX_INLINE = 4096;
 int rnd_num_blocks(int32_t N) { return (N + RND_ROWS - 1) / RND_ROWS; }
 
 // `running` is copied to running_old for the launch that follows, whose workgroups all read the statistics from before the
@@ -1649,11 +1653,36 @@ __global__ __launch_bounds__(256) void rnd_apply_kernel(const double* __restrict
   if (rewards != nullptr) rewards[n] = reward + weight * r;
 }
 
+// One workgroup adds a long list of block sums up into its first entry.
+__global__ __launch_bounds__(1024) void rnd_fold_kernel(double* __restrict__ partials, int blocks) {
+  __shared__ double smem[16];
+  double s = 0.0, q = 0.0;
+  for (int i = threadIdx.x; i < blocks; i += 1024) {
+    s += partials[2 * i];
+    q += partials[2 * i + 1];
+  }
+  const double ts = block_sum(s, smem);
+  const double tq = block_sum(q, smem);
+  if (threadIdx.x == 0) {
+    partials[0] = ts;
+    partials[1] = tq;
+  }
+}
+
 hipError_t launch_rnd_reward(const float* yp, const float* yt, int32_t N, int32_t K, float* running, float weight,
                              int32_t update_stats, float* r_int, float* rewards, double* partials, hipStream_t stream) {
-  const int nb = rnd_num_blocks(N);
+  int nb = rnd_num_blocks(N);
   float* running_old = reinterpret_cast<float*>(partials + 2 * (size_t)nb);
-  hipLaunchKernelGGL(rnd_raw_kernel, dim3(nb), dim3(256), 0, stream, yp, yt, N, K, r_int, partials, running, running_old);
+  {
+    TraceScope ts(stream, "rnd_raw", 0.0, 8.0 * N * K + 4.0 * N);
+    hipLaunchKernelGGL(rnd_raw_kernel, dim3(nb), dim3(256), 0, stream, yp, yt, N, K, r_int, partials, running, running_old);
+  }
+  if (update_stats && nb > RND_MAX_INLINE) {
+    TraceScope ts(stream, "rnd_fold", 0.0, 16.0 * nb);
+    hipLaunchKernelGGL(rnd_fold_kernel, dim3(1), dim3(1024), 0, stream, partials, nb);
+    nb = 1;
+  }
+  TraceScope ts(stream, "rnd_apply", 0.0, rewards ? 16.0 * N : 8.0 * N);
   hipLaunchKernelGGL(rnd_apply_kernel, dim3((N + 255) / 256), dim3(256), 0, stream, partials, nb, N, running_old, running, update_stats,
                      weight, r_int, rewards);
   return hipGetLastError();
