@@ -1550,37 +1550,42 @@ hipError_t launch_stage_input(const float* in, int32_t ld, int32_t B, int32_t D,
 // ---- RND reward ---------------------------------------------------------------------------------------
 // 16 lanes share a row, 64 rows a workgroup: a row is read 256 bytes at a time.  16 384 rows of 64: 4.9 us; one lane per row,
 // which walks its own row 4 bytes at a time, takes 18.5.
-constexpr int RND_ROWS = 64, RND_LANES = 16;
+// Narrow rows take as many lanes as they have 16-byte pieces, so that no lane is without work (whole calls, networks [8, 32, K], 16
+// lanes and these, us): K = 1 24.2 and 21.4 at 65 536 rows, 268 and 221 at 1 048 576; K = 8 39.8 and 35.6 at 131 072, K = 16 18.2 and
+// 17.6 at 16 384.
+constexpr int rnd_lanes(int K) { return K <= 4 ? 1 : K <= 16 ? 4 : 16; }
+constexpr int rnd_rows(int lanes) { return lanes == 16 ? 64 : 256; }        // rows per workgroup
 // Block sums that every workgroup of the second launch adds up itself; longer lists are folded first, as their reads grow with N^2.
-// Whole calls, networks [8, 32, 1], without and with the fold (us): 38.7 and 40.1 at 131 072 rows, 61.3 both at 262 144, 107.7 and 104.6
+// Whole calls, networks [8, 32, 1] in 64 rows a workgroup, without and with the fold (us): 38.7 and 40.1 at 131 072 rows, 61.3 both at 262 144, 107.7 and 104.6
 // at 524 288, 1358 and 928 at 4 194 304.
 constexpr int RND_MAX_INLINE = 4096;
-int rnd_num_blocks(int32_t N) { return (N + RND_ROWS - 1) / RND_ROWS; }
+int rnd_num_blocks(int32_t N) { return (N + 63) / 64; }       // at most, for any width
 
 // `running` is copied to running_old for the launch that follows, whose workgroups all read the statistics from before the
 // update that one of them writes.
+template <int LANES>
 __global__ __launch_bounds__(256) void rnd_raw_kernel(const float* __restrict__ yp, const float* __restrict__ yt, int N,
                                                       int K, float* __restrict__ raw, double* __restrict__ partials,
                                                       const float* __restrict__ running, float* __restrict__ running_old) {
   __shared__ double smem[4];
-  constexpr int PER = RND_ROWS * RND_LANES / 256;         // rows per lane
-  const int sub = threadIdx.x & (RND_LANES - 1);
+  constexpr int ROWS = rnd_rows(LANES), PER = ROWS * LANES / 256;       // rows per workgroup and per lane
+  const int sub = threadIdx.x & (LANES - 1);
   if (blockIdx.x == 0 && threadIdx.x < 3) running_old[threadIdx.x] = running[threadIdx.x];
   double s = 0.0, q = 0.0;
   float acc[PER];
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
-    const int n = blockIdx.x * RND_ROWS + (int)(threadIdx.x / RND_LANES) + i * (256 / RND_LANES);
+    const int n = blockIdx.x * ROWS + (int)(threadIdx.x / LANES) + i * (256 / LANES);
     const long o = (long)min(n, N - 1) * K;
     acc[i] = 0.f;
     if ((K & 3) == 0) {                                   // both matrices start 16-byte aligned
-      for (int k = 4 * sub; k < K; k += 4 * RND_LANES) {
+      for (int k = 4 * sub; k < K; k += 4 * LANES) {
         const float4 a = *reinterpret_cast<const float4*>(yp + o + k), b = *reinterpret_cast<const float4*>(yt + o + k);
         const float d0 = a.x - b.x, d1 = a.y - b.y, d2 = a.z - b.z, d3 = a.w - b.w;
         acc[i] += (d0 * d0 + d1 * d1) + (d2 * d2 + d3 * d3);
       }
     } else {
-      for (int k = sub; k < K; k += RND_LANES) {
+      for (int k = sub; k < K; k += LANES) {
         const float d = yp[o + k] - yt[o + k];
         acc[i] += d * d;
       }
@@ -1589,8 +1594,8 @@ __global__ __launch_bounds__(256) void rnd_raw_kernel(const float* __restrict__ 
 #pragma unroll
   for (int i = 0; i < PER; ++i) {
 #pragma unroll
-    for (int off = 1; off < RND_LANES; off <<= 1) acc[i] += __shfl_xor(acc[i], off, WAVE);
-    const int n = blockIdx.x * RND_ROWS + (int)(threadIdx.x / RND_LANES) + i * (256 / RND_LANES);
+    for (int off = 1; off < LANES; off <<= 1) acc[i] += __shfl_xor(acc[i], off, WAVE);
+    const int n = blockIdx.x * ROWS + (int)(threadIdx.x / LANES) + i * (256 / LANES);
     if (sub == 0 && n < N) {
       raw[n] = acc[i];
       s += (double)acc[i];
@@ -1671,11 +1676,12 @@ __global__ __launch_bounds__(1024) void rnd_fold_kernel(double* __restrict__ par
 
 hipError_t launch_rnd_reward(const float* yp, const float* yt, int32_t N, int32_t K, float* running, float weight,
                              int32_t update_stats, float* r_int, float* rewards, double* partials, hipStream_t stream) {
-  int nb = rnd_num_blocks(N);
+  const int lanes = rnd_lanes(K);
+  int nb = (N + rnd_rows(lanes) - 1) / rnd_rows(lanes);
   float* running_old = reinterpret_cast<float*>(partials + 2 * (size_t)nb);
   {
     TraceScope ts(stream, "rnd_raw", 0.0, 8.0 * N * K + 4.0 * N);
-    hipLaunchKernelGGL(rnd_raw_kernel, dim3(nb), dim3(256), 0, stream, yp, yt, N, K, r_int, partials, running, running_old);
+    hipLaunchKernelGGL(lanes == 1 ? rnd_raw_kernel<1> : lanes == 4 ? rnd_raw_kernel<4> : rnd_raw_kernel<16>, dim3(nb), dim3(256), 0, stream, yp, yt, N, K, r_int, partials, running, running_old);
   }
   if (update_stats && nb > RND_MAX_INLINE) {
     TraceScope ts(stream, "rnd_fold", 0.0, 16.0 * nb);

@@ -44,3 +44,9 @@ def test_long_lists_of_block_sums_are_folded_once(rx, K, N):
     """Above 4096 block sums of 64 rows one workgroup adds them up before all others read the result."""
     fold = ["rnd_fold"] if N > 4096 * 64 else []
     assert [n for n in _check(rx, K, N) if n.startswith("rnd")] == ["rnd_raw"] + fold + ["rnd_apply"]
+
+
+@pytest.mark.parametrize("K,N", [(1, 1), (1, 257), (3, 255), (4, 256), (5, 65), (7, 300), (8, 257), (16, 63), (17, 65), (30, 65), (64, 64), (100, 130), (130, 129)])
+def test_rnd_widths(rx, K, N):
+    """Rows of one lane, of four and of sixteen, in 16-byte pieces or single columns, in one pass over the row or several."""
+    _check(rx, K, N)
