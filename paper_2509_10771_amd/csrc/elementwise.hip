@@ -290,7 +290,7 @@ __device__ __forceinline__ uint64_t mix64(uint64_t x) {
 }
 
 // Keys are uniform 64-bit hashes, so their top bits spread the B items evenly over nb buckets
-// (about 8 per bucket).  Bucket membership is order independent; the order inside a bucket is then
+// (8 to 32 per bucket).  Bucket membership is order independent; the order inside a bucket is then
 // fixed by ranking on (key, index), which makes the result independent of atomic scheduling.  One atomic per item, where the
 // buckets are counted, gives its place as well.  Five permutations of 98 304: 63 us; with a second atomic per item in the
 // scatter and 32 items a bucket 112.
@@ -299,10 +299,14 @@ struct PermPlan {
   int32_t nb;      // buckets (power of two)
   int32_t shift;   // key >> shift = bucket
 };
+// Items per bucket, about: few of them are ranked faster, many buckets cost more to count and scan.  One permutation with 8, 16 and 32
+// a bucket, us: 31.0, 30.5 and 38.4 for 98 304 (five of them in an update of one small layer 289, 294 and 316), 60.4, 48.3 and 44.0 for
+// 262 144, 210, 157 and 138 for 2^20 (five 1703, 1677 and 1712), 3436, 2528 and 2240 for 2^24, 15 900, 12 000 and 9900 for 2^26.
 static PermPlan perm_plan(int32_t B) {
   PermPlan p;
+  const int per = B < 1 << 18 ? 8 : B < 1 << 25 ? 16 : 32;
   int lg = 0;
-  while ((1 << (lg + 1)) * 8 <= B && lg < 24) ++lg;
+  while (((int64_t)per << (lg + 1)) <= B && lg < 24) ++lg;
   p.nb = 1 << lg;
   p.shift = 64 - lg;
   return p;
@@ -1556,8 +1560,8 @@ hipError_t launch_stage_input(const float* in, int32_t ld, int32_t B, int32_t D,
 constexpr int rnd_lanes(int K) { return K <= 4 ? 1 : K <= 16 ? 4 : 16; }
 constexpr int rnd_rows(int lanes) { return lanes == 16 ? 64 : 256; }        // rows per workgroup
 // Block sums that every workgroup of the second launch adds up itself; longer lists are folded first, as their reads grow with N^2.
-// Whole calls, networks [8, 32, 1] in 64 rows a workgroup, without and with the fold (us): 38.7 and 40.1 at 131 072 rows, 61.3 both at 262 144, 107.7 and 104.6
-// at 524 288, 1358 and 928 at 4 194 304.
+// Whole calls, networks [8, 32, 1] in 64 rows a workgroup, without and with the fold (us): 38.7 and 40.1 at 131 072 rows, 61.3 both at
+// 262 144, 107.7 and 104.6 at 524 288, 1358 and 928 at 4 194 304.
 constexpr int RND_MAX_INLINE = 4096;
 int rnd_num_blocks(int32_t N) { return (N + 63) / 64; }       // at most, for any width
 

@@ -41,3 +41,10 @@ def test_no_buffers_of_the_path_not_taken(cell):
 def test_gae_workspace_serves_fewer_environments():
     need = [rx.rslx_gae_workspace_bytes(24, n) for n in (1, 64, 65, 4096, 16384, 16385, 20000, 32768, 65535)]
     assert need == sorted(need)
+
+
+@pytest.mark.parametrize("B,per_bucket", [(98304, 8), (262144, 16), (1 << 20, 16), (1 << 24, 16), (1 << 25, 32), (1 << 26, 32)])
+def test_permutation_buckets(B, per_bucket):
+    """Keys and indices of eight permutations, and two words per bucket: large ones have fewer, fuller buckets."""
+    slack = 8 * 5 * 256
+    assert rx.rslx_permutation_workspace_bytes(B) <= 8 * (12 * B + 8 * (B // per_bucket)) + slack
