@@ -4,6 +4,8 @@
 #include "kernels.h"
 #include "split_bf16.h"
 
+#include <algorithm>
+
 namespace rslx {
 namespace {
 
@@ -240,9 +242,9 @@ struct StepTileKK {
 // with an L2 of its own: all hidden-unit blocks of a row block go to one XCD, so a row block's operand rows are
 // fetched into one L2 only (the weights, shared by every row block, fit in each L2).
 constexpr int GS_XCDS = 8;
-__device__ __forceinline__ void step_block(int H, int& rb, int& jb) {
+__device__ __forceinline__ void step_block(int id, int H, int& rb, int& jb) {
   const int jblocks = (H + GS_JB - 1) / GS_JB;
-  const int xcd = (int)blockIdx.x % GS_XCDS, i = (int)blockIdx.x / GS_XCDS;
+  const int xcd = id % GS_XCDS, i = id / GS_XCDS;
   rb = (i / jblocks) * GS_XCDS + xcd;
   jb = i % jblocks;
 }
@@ -251,16 +253,16 @@ template <int CELL> struct CellShape;
 template <> struct CellShape<CELL_GRU> { static constexpr int G = 3, KC = 128; };
 template <> struct CellShape<CELL_LSTM> { static constexpr int G = 4, KC = 64; };   // shorter chunks: 8 tiles of weights in LDS
 
+template <int CELL> using StepFwdTile = StepTile<CellShape<CELL>::G, CellShape<CELL>::KC>;
+
+// Workgroup `id` of a network's share of the launch; smem: StepFwdTile<CELL>::LDS_FLOATS floats.
 template <int CELL>
-__global__ __launch_bounds__(GS_THREADS) void step_fwd_kernel(const StepFwdArgs a) {
+__device__ __forceinline__ void step_fwd(const StepFwdArgs& a, const StepFwdNet& n, int id, float* smem) {
   constexpr int G = CellShape<CELL>::G;
-  using Tile = StepTile<G, CellShape<CELL>::KC>;
-  __shared__ __attribute__((aligned(16))) float smem[Tile::LDS_FLOATS];
-  const int z = blockIdx.y;
-  const StepFwdNet& n = a.net[z];
+  using Tile = StepFwdTile<CELL>;
   const int H = n.H, nb = a.nb, S = CELL == CELL_LSTM ? 2 * H : H;
   int rb, jb;
-  step_block(H, rb, jb);
+  step_block(id, H, rb, jb);
   const int row0 = rb * GS_ROWS, j0 = jb * GS_JB;
   if (row0 >= nb) return;
   int col0[2 * G], col_end[2 * G];      // tile wj * G + g: gate g of hidden units j0 + 16 wj ...
@@ -324,6 +326,12 @@ __global__ __launch_bounds__(GS_THREADS) void step_fwd_kernel(const StepFwdArgs 
 }
 
 template <int CELL>
+__global__ __launch_bounds__(GS_THREADS) void step_fwd_kernel(const StepFwdArgs a) {
+  __shared__ __attribute__((aligned(16))) float smem[StepFwdTile<CELL>::LDS_FLOATS];
+  step_fwd<CELL>(a, a.net[blockIdx.y], blockIdx.x, smem);
+}
+
+template <int CELL>
 __global__ __launch_bounds__(GS_THREADS) void step_bwd_kernel(const StepBwdArgs a) {
   constexpr int G = CellShape<CELL>::G;
   using Tile = StepTileKK<1, 128>;
@@ -332,7 +340,7 @@ __global__ __launch_bounds__(GS_THREADS) void step_bwd_kernel(const StepBwdArgs 
   const StepBwdNet& n = a.net[z];
   const int H = n.H, nb = a.nb, S = CELL == CELL_LSTM ? 2 * H : H;
   int rb, jb;
-  step_block(H, rb, jb);
+  step_block(blockIdx.x, H, rb, jb);
   const int row0 = rb * GS_ROWS, j0 = jb * GS_JB;
   if (row0 >= nb) return;
   const bool has_next = n.dg_next != nullptr;
@@ -814,17 +822,11 @@ template <int CELL> struct StepSplit {
   static constexpr int SIDE = ST_THREADS / (4 * KC), PER = G / SIDE;       // gates side by side in the lanes' loads, gates per lane
 };
 
+// Unit block ub, rows from row0 of a network; lds: 2 CHUNK bytes.
 template <int CELL>
-__global__ __launch_bounds__(ST_THREADS, 2) void step_split_kernel(const StepFwdArgs a) {
+__device__ __forceinline__ void step_split(const StepFwdNet& n, int nb, int ub, int row0, char* lds) {
   using S = StepSplit<CELL>;
   constexpr int G = S::G, NT = S::NT, KC = S::KC, CHUNK = S::CHUNK, PER = S::PER;
-  extern __shared__ __align__(16) char lds[];
-  const int nb = a.nb;
-  const StepGrid grid(a.n_nets, nb, a.n_nets == 2 ? max(a.net[0].H, a.net[1].H) : a.net[0].H);
-  const int xcd = blockIdx.x & 7, id = blockIdx.x >> 3;
-  const int z = a.n_nets == 2 ? xcd >> 2 : 0, rg = a.n_nets == 2 ? xcd & 1 : xcd & 3, ug = a.n_nets == 2 ? (xcd >> 1) & 1 : xcd >> 2;
-  const int ub = ug * grid.per_group + id % grid.per_group, row0 = ((id / grid.per_group) * grid.row_groups + rg) * ST_ROWS;
-  const StepFwdNet& n = a.net[z];
   const int H = n.H, GH = G * H, SW = CELL == CELL_LSTM ? 2 * H : H;
   if (ub >= H / ST_UNITS || row0 >= nb) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -951,13 +953,51 @@ __global__ __launch_bounds__(ST_THREADS, 2) void step_split_kernel(const StepFwd
   }
 }
 
+// One network, or two of one width.
+template <int CELL>
+__global__ __launch_bounds__(ST_THREADS, 2) void step_split_kernel(const StepFwdArgs a) {
+  extern __shared__ __align__(16) char lds[];
+  const StepGrid grid(a.n_nets, a.nb, a.net[0].H);
+  const int xcd = blockIdx.x & 7, id = blockIdx.x >> 3;
+  const int z = a.n_nets == 2 ? xcd >> 2 : 0, rg = a.n_nets == 2 ? xcd & 1 : xcd & 3, ug = a.n_nets == 2 ? (xcd >> 1) & 1 : xcd >> 2;
+  step_split<CELL>(a.net[z], a.nb, ug * grid.per_group + id % grid.per_group, ((id / grid.per_group) * grid.row_groups + rg) * ST_ROWS, lds);
+}
+
+// Two networks of different widths, the wider one first (blockIdx.y): each over the whole chip and through the kernel that its own
+// sizes call for (bit z of split), in one launch.
+template <int CELL>
+__global__ __launch_bounds__(ST_THREADS, 2) void step_uneven_kernel(const StepFwdArgs a, int split) {
+  extern __shared__ __align__(16) char lds[];
+  const StepFwdNet& n = a.net[blockIdx.y];
+  if ((split >> blockIdx.y) & 1) {
+    const StepGrid grid(1, a.nb, n.H);
+    const int xcd = blockIdx.x & 7, id = blockIdx.x >> 3;
+    step_split<CELL>(n, a.nb, (xcd >> 2) * grid.per_group + id % grid.per_group, ((id / grid.per_group) * grid.row_groups + (xcd & 3)) * ST_ROWS, lds);
+  } else {
+    step_fwd<CELL>(a, n, blockIdx.x, reinterpret_cast<float*>(lds));
+  }
+}
+
 template <int CELL>
 hipError_t step_split_launch(const StepFwdArgs& a, hipStream_t stream) {
   constexpr int bytes = 2 * StepSplit<CELL>::CHUNK;
-  const int H = a.n_nets == 2 && a.net[1].H > a.net[0].H ? a.net[1].H : a.net[0].H;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(step_split_kernel<CELL>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((step_split_kernel<CELL>), dim3(StepGrid(a.n_nets, a.nb, H).blocks), dim3(ST_THREADS), bytes, stream, a);
+  hipLaunchKernelGGL((step_split_kernel<CELL>), dim3(StepGrid(a.n_nets, a.nb, a.net[0].H).blocks), dim3(ST_THREADS), bytes, stream, a);
+  return hipGetLastError();
+}
+
+template <int CELL>
+hipError_t step_uneven_launch(const StepFwdArgs& a, int split, int rest_blocks, hipStream_t stream) {
+  static_assert(GS_THREADS == ST_THREADS, "one launch");
+  constexpr int bytes_split = 2 * StepSplit<CELL>::CHUNK, bytes_rest = StepFwdTile<CELL>::LDS_FLOATS * 4;
+  const int bytes = split == 3 || bytes_split > bytes_rest ? bytes_split : bytes_rest;
+  int blocks = rest_blocks;
+  for (int z = 0; z < 2; ++z)
+    if (split >> z & 1) blocks = std::max(blocks, StepGrid(1, a.nb, a.net[z].H).blocks);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(step_uneven_kernel<CELL>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((step_uneven_kernel<CELL>), dim3(blocks, 2), dim3(ST_THREADS), bytes, stream, a, split);
   return hipGetLastError();
 }
 
@@ -1053,21 +1093,25 @@ static hipError_t launch_step_rest(const StepFwdArgs& a, hipStream_t stream) {
 
 hipError_t launch_step_fwd(const StepFwdArgs& a, hipStream_t stream) {
   if (a.nb <= 0 || a.n_nets <= 0) return hipSuccess;
-  StepFwdArgs split = a, rest = a;                 // the networks by the kernel that takes them
-  split.n_nets = rest.n_nets = 0;
+  const bool lstm = a.cell == CELL_LSTM;
+  StepFwdArgs b = a;
+  if (b.n_nets == 2 && b.net[1].H > b.net[0].H) std::swap(b.net[0], b.net[1]);
+  int split = 0;
   double flops = 0.0;
-  for (int k = 0; k < a.n_nets; ++k) {
-    const bool fits = step_split_fits(a.net[k], a);
-    StepFwdArgs& to = fits ? split : rest;
-    to.net[to.n_nets++] = a.net[k];
-    if (fits) flops += 2.0 * a.nb * a.net[k].H * (a.cell == CELL_LSTM ? 4.0 : 3.0) * a.net[k].H;
+  for (int k = 0; k < b.n_nets; ++k) {
+    split |= step_split_fits(b.net[k], b) << k;
+    flops += 2.0 * b.nb * b.net[k].H * (lstm ? 4.0 : 3.0) * b.net[k].H;
   }
-  if (split.n_nets > 0) {
-    TraceScope ts(stream, a.cell == CELL_LSTM ? "lstm_split" : "gru_split", flops, 0.0);
-    const hipError_t e = a.cell == CELL_LSTM ? step_split_launch<CELL_LSTM>(split, stream) : step_split_launch<CELL_GRU>(split, stream);
-    if (e != hipSuccess) return e;
+  if (split == 0) return launch_step_rest(a, stream);
+  if (b.n_nets == 2 && (split != 3 || b.net[0].H != b.net[1].H)) {
+    int rest_blocks = 0;
+    for (int k = 0; k < 2; ++k)
+      if (!(split >> k & 1)) rest_blocks = step_grid(b.nb, &b.net[k].H, 1).x;
+    TraceScope ts(stream, lstm ? "lstm_uneven" : "gru_uneven", flops, 0.0);
+    return lstm ? step_uneven_launch<CELL_LSTM>(b, split, rest_blocks, stream) : step_uneven_launch<CELL_GRU>(b, split, rest_blocks, stream);
   }
-  return launch_step_rest(rest, stream);
+  TraceScope ts(stream, lstm ? "lstm_split" : "gru_split", flops, 0.0);
+  return lstm ? step_split_launch<CELL_LSTM>(b, stream) : step_split_launch<CELL_GRU>(b, stream);
 }
 
 hipError_t launch_step_bwd(const StepBwdArgs& a, hipStream_t stream) {

@@ -102,3 +102,39 @@ def test_large_act_step(rx, cell, H, N):
     got = step(big, h0[1].clone())
     assert torch.isfinite(got["h_a"][:, :H]).all()
     assert torch.equal(got["h_a"][:N - 1], out["h_a"][:N - 1]) and torch.equal(got["h_c"], out["h_c"])
+
+
+@pytest.mark.parametrize("cell,Ha,Hc,N,site", [("gru", 256, 64, 1100, "gru_uneven"), ("gru", 36, 256, 1100, "gru_uneven"), ("gru", 256, 128, 2050, "gru_uneven"),
+                                               ("gru", 64, 64, 4099, "gru_split"), ("lstm", 128, 128, 4099, "lstm_split"),
+                                               ("lstm", 512, 64, 1101, "lstm_uneven"), ("gru", 64, 36, 1100, "gru_step_fwd")])
+def test_act_step_of_memories_of_different_widths(rx, cell, Ha, Hc, N, site):
+    """Each memory takes the kernel of its own sizes, both in one launch: the oracle's values for either network, and the bits of a
+    values-only call."""
+    nets, refs = {}, {}
+    for which, H in (("actor", Ha), ("critic", Hc)):
+        w = replace(WORKLOADS["recurrent"].scaled(N), T=1, hidden=(64, 32), memory_hidden=H, memory_cell=cell)
+        inp = make_inputs(w)
+        inp["reset0"] = (np.random.default_rng(N).random(N) < 0.1).astype(np.uint8)
+        got = _nets(rx, w, _flat(inp, "actor"), _flat(inp, "critic"))
+        nets[which], refs[which] = got[:2] if which == "actor" else got[2:], (inp, oracle_collect(w, inp))
+    (ga, ma), (gc, mc) = nets["actor"], nets["critic"]
+    (ia, ra), (ic, rc) = refs["actor"], refs["critic"]
+    A = w.A
+    ws = rx.workspace(rx.rslx_act_recurrent_workspace_bytes(ga, ma, gc, mc, N))
+    eps = dev(orng.act_noise(SEED, 0, N, A), torch.float32)
+    obs_a, obs_c, reset = dev(ia["obs"][0]), dev(ic["obs"][0]), dev(ia["reset0"])
+    h_a, h_c = dev(ia["h_actor"]), dev(ic["h_critic"])
+    last = torch.empty(N, device="cuda")
+    rx.rslx_act_recurrent(None, None, gc, mc, None, obs_c, N, None, h_c, reset, None, None, 0, 0, None, None, None, last, None, None,
+                          rx.ACT_VALUES_ONLY, ws)
+    out = {k: torch.empty(N, A, device="cuda") for k in ("actions", "mu", "sigma")}
+    out.update(logp=torch.empty(N, device="cuda"), values=torch.empty(N, device="cuda"), h_a=h_a, h_c=h_c)
+    rx.rslx_trace_begin(32)
+    rx.rslx_act_recurrent(ga, ma, gc, mc, obs_a, obs_c, N, h_a, h_c, reset, None, None, SEED, 0, eps, out["actions"], out["logp"], out["values"],
+                          out["mu"], out["sigma"], 0, ws)
+    torch.cuda.synchronize()
+    assert [r[0] for r in rx.rslx_trace_end() if r[0].startswith(cell)] == [site]
+    for k, ref in (("actions", ra), ("mu", ra), ("logp", ra), ("h_a", ra), ("values", rc), ("h_c", rc)):
+        assert rel_l2(host(out[k]), ref[k][0]) <= 2e-5, k
+        assert_elementwise(k, host(out[k]), ref[k][0])
+    assert torch.equal(last, out["values"])
