@@ -74,12 +74,12 @@ size_t act_recurrent_carve(Carver& c, const rslx_memory* ga, const rslx_memory* 
 
 // hin -> gi -> new state (hidden-side contraction fused with the gates), for the memories listed (1 or 2), each with its own input matrix.
 int32_t gru_step(const rslx_memory* const* g, const float* const* obs, const StepBufs* b, float* const* h_out, int count,
-                 int32_t N, hipStream_t s) {
+                 bool alone, int32_t N, hipStream_t s) {
   GemmBatch bi;
   bi.count = count;
   StepFwdArgs sa;
   memset(&sa, 0, sizeof sa);
-  sa.n_nets = count; sa.nb = N; sa.cell = g[0]->cell;
+  sa.n_nets = count; sa.nb = N; sa.cell = g[0]->cell; sa.alone = alone ? 1 : 0;
   for (int k = 0; k < count; ++k) {
     const rslx_memory& m = *g[k];
     bi.p[k] = gate_problem(plain_view(obs[k], m.in_dim), m.in_dim, m.params, m.params + gru_off_bih(m), b[k].gi, N, gate_width(m));
@@ -167,13 +167,13 @@ int32_t act_recurrent_impl(const rslx_memory* gru_actor, const rslx_mlp* actor, 
     const float* obs[2] = {obs_actor, obs_critic};
     const StepBufs b[2] = {ba, bc};
     float* out[2] = {h_actor, h_critic};
-    RSLX_TRY(gru_step(g, obs, b, out, 2, N, s));
+    RSLX_TRY(gru_step(g, obs, b, out, 2, false, N, s));
   } else {
     const rslx_memory* g[1] = {gru_critic};
     const float* obs[1] = {obs_critic};
     const StepBufs b[1] = {bc};
     float* out[1] = {bc.hnew};
-    RSLX_TRY(gru_step(g, obs, b, out, 1, N, s));
+    RSLX_TRY(gru_step(g, obs, b, out, 1, false, N, s));
   }
   return act_impl(a, critic, h_in_actor_mlp, h_in_critic_mlp, N, seed, step, counters, eps_or_null, actions, logp, values,
                   mu, sigma, flags, static_cast<char*>(ws) + used, ws_bytes - used, stream, ga ? state_width(*ga) : 0,
@@ -689,7 +689,7 @@ int32_t rslx_memory_step(const rslx_memory* mem, const float* obs, int32_t N, fl
   const float* o[1] = {obs};
   const StepBufs bb[1] = {b};
   float* out[1] = {state};
-  RSLX_TRY(gru_step(g, o, bb, out, 1, N, s));
+  RSLX_TRY(gru_step(g, o, bb, out, 1, true, N, s));
   if (h_dense_out) RSLX_HIP(launch_copy_matrix(state, state_width(*mem), N, mem->hidden, h_dense_out, s));
   return RSLX_OK;
 }

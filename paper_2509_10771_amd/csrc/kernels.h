@@ -291,6 +291,7 @@ struct StepFwdNet {
 struct StepFwdArgs {
   StepFwdNet net[2];
   int32_t n_nets, nb, cell;
+  int32_t alone;            // 1: rslx_memory_step (see step_split_fits)
   const uint8_t* done;      // episode-end flags (null = none); row i reads done[done_idx ? done_idx[i] : i]
   const int32_t* done_idx;
 };

@@ -1002,12 +1002,16 @@ hipError_t step_uneven_launch(const StepFwdArgs& a, int split, int rest_blocks, 
 }
 
 // Which steps take that kernel: those of act() (nothing kept for a backward pass, no flags) from about the size on where it is the
-// faster one.  Whole calls, a network of [256, 128] behind the memory, the kernel above against this, us: GRU of 256 49.3 and
-// 47.4 at 1024 rows, 87.8 and 70.7 at 4096; GRU of 128 36.3 and 37.9 at 1024, 41.3 and 40.7 at 2048; LSTM of 256 52.3 and 54.3 at
-// 1024, 69.5 and 60.9 at 2048; LSTM of 128 51.6 and 52.4 at 3000, 56.1 and 53.9 at 4096.  A memory's own sizes decide, so that
-// a call for the values alone returns the bits of a full one.
+// faster one for a memory by itself.  The fp32 step and this in rslx_memory_step and in act() with two such memories in front of
+// [64, 12], us: GRU of 256 18.3, 21.0 and 37.0, 35.8 at 1024 rows, 22.8, 21.7 and 44.0, 39.5 at 1055; GRU of 128 15.9, 17.9 and 31.6,
+// 31.3 at 2048, 18.6, 18.1 and 36.2, 33.5 at 2110; LSTM of 256 29.8, 29.6 and 58.1, 52.1 at 2048; LSTM of 128 24.9, 25.3 and 47.6, 47.0
+// at 4096, 31.6, 32.3 and 59.7, 57.0 at 5121, 36.8, 33.8 and 68.1, 65.1 at 6554; LSTM of 64 33.4, 34.3 and 73.8, 72.2 at 16 385.  A
+// memory's own sizes decide, so that a call for the values alone returns the bits of a full one; only rslx_memory_step, which has no
+// such counterpart, may draw its line later.
 bool step_split_fits(const StepFwdNet& n, const StepFwdArgs& a) {
-  if (n.H % 64 != 0 || n.H > 8192 || a.nb < 1024 || (int64_t)a.nb * n.H < (a.cell == CELL_LSTM ? 1 << 19 : 1 << 18)) return false;
+  if (n.H % 64 != 0 || n.H > 8192 || a.nb < 1024) return false;
+  const int64_t size = (int64_t)a.nb * n.H;
+  if (a.cell == CELL_LSTM ? size < (n.H < 128 ? 1 << 21 : a.alone && n.H < 256 ? 3 << 18 : 1 << 19) : size <= 1 << 18) return false;
   if (a.done != nullptr || n.sin_next != nullptr || n.pre_out != nullptr || (a.cell == CELL_LSTM && n.c_out == nullptr)) return false;
   return ((reinterpret_cast<uintptr_t>(n.h_out) | reinterpret_cast<uintptr_t>(n.c_out) | reinterpret_cast<uintptr_t>(n.sin)) & 15) == 0;
 }

@@ -138,3 +138,26 @@ def test_act_step_of_memories_of_different_widths(rx, cell, Ha, Hc, N, site):
         assert rel_l2(host(out[k]), ref[k][0]) <= 2e-5, k
         assert_elementwise(k, host(out[k]), ref[k][0])
     assert torch.equal(last, out["values"])
+
+
+@pytest.mark.parametrize("cell,H,N,site", [("gru", 256, 1024, "gru_step_fwd"), ("gru", 256, 1025, "gru_split"), ("gru", 128, 2048, "gru_step_fwd"),
+                                           ("gru", 128, 2049, "gru_split"), ("lstm", 64, 16385, "lstm_step_fwd"), ("lstm", 128, 4096, "lstm_step_fwd"),
+                                           ("lstm", 128, 6143, "lstm_step_fwd"), ("lstm", 128, 6144, "lstm_split"), ("lstm", 256, 2048, "lstm_split")])
+def test_memory_step_sizes(rx, cell, H, N, site):
+    """Which kernel a memory's own step takes, on both sides of the line; its states are those of calls with fewer rows, which run the
+    fp32 kernel."""
+    g = torch.Generator().manual_seed(N)
+    G, S, D = (4 if cell == "lstm" else 3), (2 if cell == "lstm" else 1) * H, 20
+    m = rx.Memory(rx.CELL_LSTM if cell == "lstm" else rx.CELL_GRU, D, H, ((torch.rand(G * H * (D + H + 2), generator=g) * 2 - 1) / H ** 0.5).cuda())
+    obs, s0 = torch.randn(N, D, generator=g).cuda(), (0.5 * torch.randn(N, S, generator=g)).cuda()
+    ws = rx.workspace(rx.rslx_memory_step_workspace_bytes(m, N))
+    whole, parts = s0.clone(), s0.clone()
+    rx.rslx_trace_begin(16)
+    rx.rslx_memory_step(m, obs, N, whole, None, None, None, ws)
+    torch.cuda.synchronize()
+    assert [r[0] for r in rx.rslx_trace_end() if r[0].startswith(cell)] == [site]
+    for i in range(0, N, 1000):
+        rx.rslx_memory_step(m, obs[i:i + 1000], min(1000, N - i), parts[i:i + 1000], None, None, None, ws)
+    torch.cuda.synchronize()
+    assert rel_l2(host(whole), host(parts)) <= 2e-6
+    assert_elementwise("state", host(whole), host(parts).astype(np.float64))
