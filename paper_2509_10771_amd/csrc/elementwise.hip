@@ -1020,6 +1020,8 @@ __global__ __launch_bounds__(256) void ppo_loss_kernel(const PpoLossArgs a) {
 constexpr int HEAD_ROWS = 32;
 // A block is a chain of phases, and small updates wait for one block: 13.9 us at 384 rows with 512 lanes, 18.6 with 256; updates of
 // [48, 128, 128, 12] 7 % faster up to 1024 environments, of 4096 environments and [512, 256, 128] 0.5 % (1024 lanes: 4 and -2 %).
+// Whole updates of [48, 256, 256, 20] with 256 lanes, with 512 that read the weights 8 bytes at a time, and as it is (us): 387, 403 and
+// 321 at 64 environments, 1333, 1436 and 1186 at 4096, 4791, 5282 and 4298 at 16 384; of [48, 256, 128, 20] 2723, 3055 and 2588 there.
 constexpr int HEAD_THREADS = 512, HEAD_WAVES = HEAD_THREADS / 64;
 constexpr int HEAD_KPARTS = 8;      // lanes that share one of a row's output-layer dot products
 constexpr int HEAD_JGROUPS = HEAD_THREADS / HEAD_ROWS;     // lanes per row
@@ -1224,11 +1226,19 @@ __global__ __launch_bounds__(HEAD_THREADS) void ppo_head_kernel(const PpoHeadArg
     for (int i = 0; i < Ha / HEAD_KPARTS; ++i) {
       const int k = HEAD_KPARTS * i + p8;
       const float hv = ha[row * sa + k];
-      const float2* wr = reinterpret_cast<const float2*>(wa + k * AM + half * AH);
+      const float* wr = wa + k * AM + half * AH;
+      if constexpr (AH % 4 == 0) {         // 16 bytes a read: with 8 the rows' bank conflicts double where A > 16 (see above)
 #pragma unroll
-      for (int q = 0; q < AH / 2; ++q) {
-        const float2 w2 = wr[q];
-        acc[2 * q] += hv * w2.x; acc[2 * q + 1] += hv * w2.y;
+        for (int q = 0; q < AH; q += 4) {
+          const float4 w4 = *reinterpret_cast<const float4*>(wr + q);
+          acc[q] += hv * w4.x; acc[q + 1] += hv * w4.y; acc[q + 2] += hv * w4.z; acc[q + 3] += hv * w4.w;
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < AH; q += 2) {
+          const float2 w2 = *reinterpret_cast<const float2*>(wr + q);
+          acc[q] += hv * w2.x; acc[q + 1] += hv * w2.y;
+        }
       }
     }
 #pragma unroll 4
