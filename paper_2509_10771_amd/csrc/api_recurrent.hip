@@ -317,7 +317,7 @@ void rnn_plan(Carver& c, const rslx_memory* ga, const rslx_mlp* actor, const rsl
   p.n_sumsq = p.actor.n_sumsq + p.critic.n_sumsq + p.ma.plan.blocks + p.mc.plan.blocks + 1;
   p.sumsq_all = c.take<double>((size_t)p.n_sumsq + 1);
   p.fused_head = actor->n_layers >= 2 && critic->n_layers >= 2 &&
-                 ppo_head_supported(actor->dims[actor->n_layers - 1], critic->dims[critic->n_layers - 1], ro->A);
+                 ppo_head_supported(actor->dims[actor->n_layers - 1], critic->dims[critic->n_layers - 1], ro->A, p.rows);
   p.loss_blocks = p.fused_head ? ppo_head_num_blocks(p.rows, false) : ppo_loss_num_blocks(p.rows);
   p.loss_partials = c.take<double>((size_t)p.loss_blocks * (PPO_NPART_FIXED + ro->A));
   p.bytes = c.off + 256;

@@ -1428,11 +1428,19 @@ size_t ppo_head_lds_bytes(int32_t Ha, int32_t Hc, int32_t A) {
   return sizeof(float) * (size_t)HeadLds(head_pad(Ha), head_pad(Hc), A, head_width(A)).total;
 }
 
-bool ppo_head_supported(int32_t Ha, int32_t Hc, int32_t A) {
+bool ppo_head_supported(int32_t Ha, int32_t Hc, int32_t A, int64_t rows) {
   // 16-byte rows; narrow layers only where they fill their padded width.  Whole update of [48, 400, 200, 100] networks, per-layer
   // launches around the loss and this: 2621 and 2008 us at 100 environments, 3748 and 3048 at 1000, 8617 and 8019 at 4096.
   auto ok = [](int h) { return h == 32 || h == 64 || (h > 64 && h <= 256 && h % 4 == 0); };
-  return ok(Ha) && ok(Hc) && A >= 1 && A <= 32 && ppo_head_lds_bytes(Ha, Hc, A) <= 150 * 1024;
+  if (!ok(Ha) || !ok(Hc) || A < 1 || A > 32 || ppo_head_lds_bytes(Ha, Hc, A) > 150 * 1024) return false;
+  if (Ha == head_pad(Ha) && Hc == head_pad(Hc)) return true;
+  // Padding costs LDS, and with it workgroups per CU: padded layers only up to so many rows.  Updates of four steps, [48, 256, H, A], the
+  // same two, us: H = 132: A = 3 3052 and 2911 at 98 304 rows; A = 8 1735 and 1722 at 49 152, 3180 and 3244 at 98 304; A = 12 1268 and
+  // 1236 at 32 766, 1768 and 1804 at 49 152; A = 20 801 and 779 at 16 380, 1042 and 1082 at 24 576, 3363 and 3917 at 98 304.  H = 68:
+  // A = 12 2298 and 2104 at 98 304; A = 20 1336 and 1312 at 49 152, 2395 and 2440 at 98 304.
+  const int width = head_width(A);
+  if (head_pad(Ha > Hc ? Ha : Hc) < 256) return width <= 16 || rows <= 49152;
+  return width <= 4 || rows <= (width <= 8 ? 49152 : width <= 16 ? 32768 : 16384);
 }
 
 int ppo_head_num_blocks(int32_t mb, bool sym) { const int r = sym ? HEAD_ROWS / 2 : HEAD_ROWS; return (mb + r - 1) / r; }

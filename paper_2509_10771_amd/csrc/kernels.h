@@ -243,7 +243,7 @@ struct PpoHeadArgs {
   int32_t Ha, Hc;
   float alpha_a, alpha_c;
 };
-bool ppo_head_supported(int32_t Ha, int32_t Hc, int32_t A);
+bool ppo_head_supported(int32_t Ha, int32_t Hc, int32_t A, int64_t rows);
 int ppo_head_num_blocks(int32_t mb, bool sym);
 hipError_t launch_ppo_head(const PpoHeadArgs& h, hipStream_t stream);
 
