@@ -520,6 +520,7 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
     for (int m = 0; m < cfg->minibatches; ++m) {
       const int32_t* idx = p.perms + (size_t)e * p.B + (size_t)m * p.mb;
       float* stats_row = stats + ((size_t)e * cfg->minibatches + m) * RSLX_NSTATS;
+      const bool last = e + 1 == cfg->epochs && m + 1 == cfg->minibatches;
 
       const XView xa = obs_view(ro->obs_actor, ro->Da, p.stage_a, p.dp_a, sym ? sym->perm_obs_a : nullptr,
                                 sym ? sym->sign_obs_a : nullptr, idx);
@@ -584,8 +585,8 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
       const int64_t t = *adam_step + 1;
       AdamLayersArgs al;
       memset(&al, 0, sizeof al);
-      adam_add_net(al, *actor, p.actor.pack, 1, true);
-      adam_add_net(al, *critic, p.critic.pack, 1, true);
+      adam_add_net(al, *actor, p.actor.pack, 1, true, last);
+      adam_add_net(al, *critic, p.critic.pack, 1, true, last);
       AdamArgs& aa = al.a;
       aa.sumsq_blocks = p.sumsq_all; aa.n_sumsq = p.actor.n_sumsq + p.critic.n_sumsq + 1;
       aa.max_grad_norm = cfg->max_grad_norm;
@@ -620,7 +621,7 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
         const int64_t tr = *rnd_step + 1;
         AdamLayersArgs rl;
         memset(&rl, 0, sizeof rl);
-        adam_add_net(rl, pr, p.pred.pack, 1, true);
+        adam_add_net(rl, pr, p.pred.pack, 1, true, last);
         AdamArgs& ar = rl.a;
         ar.sumsq_blocks = p.pred.sumsq; ar.n_sumsq = 0;
         ar.max_grad_norm = 0.f;
@@ -752,6 +753,7 @@ int32_t bc_update_impl(rslx_mlp* student, const rslx_mlp* teacher, const float* 
     for (int m = 0; m < cfg->minibatches; ++m) {
       const int32_t* idx = p.perms + (size_t)e * B + (size_t)m * p.mb;
       float* stats_row = stats + ((size_t)e * cfg->minibatches + m) * RSLX_NSTATS;
+      const bool last = e + 1 == cfg->epochs && m + 1 == cfg->minibatches;
       XView xs; xs.base = obs_student; xs.ld = student->dims[0]; xs.row_idx = idx; xs.src_rows = B;
       if (e == 0 && m == 0) {                // from then on the optimiser keeps the split weights current
         PackBatch pb;
@@ -768,7 +770,7 @@ int32_t bc_update_impl(rslx_mlp* student, const rslx_mlp* teacher, const float* 
       const int64_t t = *adam_step + 1;
       AdamLayersArgs al;
       memset(&al, 0, sizeof al);
-      adam_add_net(al, *student, p.student.pack, 1, false);
+      adam_add_net(al, *student, p.student.pack, 1, false, last);
       AdamArgs& aa = al.a;
       aa.sumsq_blocks = p.student.sumsq; aa.n_sumsq = p.student.n_sumsq;
       aa.max_grad_norm = cfg->max_grad_norm;

@@ -280,10 +280,15 @@ void pack_add_memory(PackBatch& b, const rslx_memory& g, const RnnBufs& m) {
   }
 }
 
-// Adds a memory to an optimiser step that keeps its split weights current.
-void adam_add_memory(AdamLayersArgs& a, const rslx_memory& g, const RnnBufs& m) {
+// Adds a memory to an optimiser step that keeps its split weights current, except in a call's last one.
+void adam_add_memory(AdamLayersArgs& a, const rslx_memory& g, const RnnBufs& m, bool last) {
   const int H = g.hidden, GH = gate_width(g);
   const int64_t o = gru_off_whh(g);
+  if (last) {
+    a.layer[a.n_layers++] = AdamLayer{g.params, g.grads, g.adam_m, g.adam_v, nullptr, nullptr, g.in_dim, GH, 0};
+    a.layer[a.n_layers++] = AdamLayer{g.params + o, g.grads + o, g.adam_m + o, g.adam_v + o, nullptr, nullptr, H, GH, 0};
+    return;
+  }
   a.layer[a.n_layers++] = AdamLayer{g.params, g.grads, g.adam_m, g.adam_v, m.pack_ih, nullptr, g.in_dim, GH, 0};
   a.layer[a.n_layers++] = AdamLayer{g.params + o, g.grads + o, g.adam_m + o, g.adam_v + o, m.pack_hh, m.pack_hh_t, H, GH, m.pack_hh ? H : 0};
 }
@@ -507,6 +512,7 @@ int32_t ppo_update_recurrent_impl(rslx_memory* gru_actor, rslx_mlp* actor, rslx_
       const int32_t* envs = p.perms + (size_t)e * p.N + (size_t)m * nb;
       const int32_t* ridx = p.rows_all + ((size_t)e * cfg->minibatches + m) * rows;
       float* stats_row = stats + ((size_t)e * cfg->minibatches + m) * RSLX_NSTATS;
+      const bool last = e + 1 == cfg->epochs && m + 1 == cfg->minibatches;
 
       if (e == 0 && m == 0) {          // from then on the optimiser keeps the split weights current
         PackBatch pb;                  // at most 12 layers (rnn_validate) and six copies of the memories
@@ -572,10 +578,10 @@ int32_t ppo_update_recurrent_impl(rslx_memory* gru_actor, rslx_mlp* actor, rslx_
       const int64_t t1 = *adam_step + 1;
       AdamLayersArgs al;
       memset(&al, 0, sizeof al);
-      adam_add_net(al, *actor, p.actor.pack, 0, true);
-      adam_add_net(al, *critic, p.critic.pack, 0, true);
-      adam_add_memory(al, *gru_actor, p.ma);
-      adam_add_memory(al, *gru_critic, p.mc);
+      adam_add_net(al, *actor, p.actor.pack, 0, true, last);
+      adam_add_net(al, *critic, p.critic.pack, 0, true, last);
+      adam_add_memory(al, *gru_actor, p.ma, last);
+      adam_add_memory(al, *gru_critic, p.mc, last);
       AdamArgs& aa = al.a;
       aa.sumsq_blocks = p.sumsq_all; aa.n_sumsq = p.n_sumsq;
       aa.max_grad_norm = cfg->max_grad_norm;
@@ -734,6 +740,7 @@ int32_t rslx_bc_update_recurrent(rslx_memory* gru, rslx_mlp* student, const floa
       const int32_t* envs = p.perms + (size_t)e * N + (size_t)m * nb;
       const int32_t* ridx = p.rows_all + ((size_t)e * cfg->minibatches + m) * rows;
       float* stats_row = stats + ((size_t)e * cfg->minibatches + m) * RSLX_NSTATS;
+      const bool last = e + 1 == cfg->epochs && m + 1 == cfg->minibatches;
       RSLX_HIP(launch_fill(stats_row, RSLX_NSTATS, 0.f, s));
       if (e == 0 && m == 0) {
         PackBatch pb;
@@ -762,8 +769,8 @@ int32_t rslx_bc_update_recurrent(rslx_memory* gru, rslx_mlp* student, const floa
       const int64_t t1 = *adam_step + 1;
       AdamLayersArgs al;
       memset(&al, 0, sizeof al);
-      adam_add_net(al, *student, p.student.pack, 0, false);
-      adam_add_memory(al, *gru, p.mem);
+      adam_add_net(al, *student, p.student.pack, 0, false, last);
+      adam_add_memory(al, *gru, p.mem, last);
       AdamArgs& aa = al.a;
       aa.sumsq_blocks = p.sumsq_all; aa.n_sumsq = p.n_sumsq;
       aa.max_grad_norm = cfg->max_grad_norm;

@@ -169,14 +169,14 @@ inline void pack_add_net(PackBatch& b, const rslx_mlp& n, const WeightPack& w, i
 }
 
 // Adds a network to an optimiser step that keeps its split copies current (dx_from as above; without log_std where the call
-// does not train it).
-inline void adam_add_net(AdamLayersArgs& a, const rslx_mlp& n, const WeightPack& w, int dx_from, bool log_std) {
+// does not train it).  A call's last step leaves the copies: nothing reads them any more.
+inline void adam_add_net(AdamLayersArgs& a, const rslx_mlp& n, const WeightPack& w, int dx_from, bool log_std, bool last) {
   for (int l = 0; l <= n.n_layers; ++l) {
     if (l == n.n_layers && !(log_std && n.has_log_std)) break;
     const int64_t o = layer_offset(n, l);
     const bool vec = l == n.n_layers;
-    a.layer[a.n_layers++] = AdamLayer{n.params + o, n.grads + o, n.adam_m + o, n.adam_v + o, vec ? nullptr : const_cast<uint16_t*>(w.fwd(n, l)),
-                                      vec || l < dx_from ? nullptr : const_cast<uint16_t*>(w.dx(n, l)), vec ? 0 : n.dims[l],
+    a.layer[a.n_layers++] = AdamLayer{n.params + o, n.grads + o, n.adam_m + o, n.adam_v + o, vec || last ? nullptr : const_cast<uint16_t*>(w.fwd(n, l)),
+                                      vec || last || l < dx_from ? nullptr : const_cast<uint16_t*>(w.dx(n, l)), vec ? 0 : n.dims[l],
                                       vec ? n.dims[l] : n.dims[l + 1], 0};
   }
 }

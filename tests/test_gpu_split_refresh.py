@@ -63,3 +63,43 @@ def test_two_epochs_in_one_call_or_two(rx, D, hidden, memory, cell):
         out.append([t for n in nets for t in (n.params, n.grads, n.adam_m, n.adam_v)] + [stats[-M:]])
     for a, b in zip(*out):
         assert torch.isfinite(a).all() and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("kind", ["ppo", "rnd", "bc", "recurrent", "bc_recurrent"])
+def test_last_step_leaves_the_split_copies(rx, kind):
+    """Nothing of a call reads the copies after its last step, so that step does not write them: the workspace behind a call of one
+    step does not depend on the learning rate."""
+    T, N, A, D, H = 3, 20, 4, 20, 128                  # 60 rows: the permutation counts its buckets with one wavefront, in lane order
+    gen = torch.Generator().manual_seed(11)
+    r = lambda *s: torch.randn(*s, generator=gen).cuda()  # noqa: E731
+    obs, act, mu, tg = r(T, N, D), r(T, N, A), r(T, N, A), r(T, N, A)
+    ro = rx.Rollout(T, N, obs, obs, act, r(T, N), r(T, N), mu, torch.full((T, N, A), 0.7).cuda(), r(T, N), r(T, N))
+    dones, h0 = torch.zeros(T, N, dtype=torch.uint8, device="cuda"), (r(N, H), r(N, H))
+    seen = []
+    for lr in (0.0, 0.1):
+        g = torch.Generator().manual_seed(5)
+        rec = kind.endswith("recurrent")
+        d = H if rec else D
+        actor, critic = _net(rx, (d, 64, 32, A), g, True), _net(rx, (d, 64, 32, 1), g)
+        ma, mc = _memory(rx, 0, D, H, g), _memory(rx, 0, D, H, g)
+        rnd = rx.RndTrain(_net(rx, (D, 16, 8), g), _net(rx, (D, 16, 8), g), lr=lr) if kind == "rnd" else None
+        step, stats = C.c_int64(0), torch.zeros(1, rx.NSTATS, device="cuda")
+        cfg = (rx.BcCfg if kind.startswith("bc") else rx.PpoCfg)(epochs=1, minibatches=1, lr=lr)
+        student = _net(rx, (d, 64, 32, A), g)
+        size = dict(ppo=lambda: rx.rslx_ppo_update_workspace_bytes(actor, critic, ro, cfg), rnd=lambda: rx.rslx_ppo_update_workspace_bytes(actor, critic, ro, cfg, None, rnd),
+                    bc=lambda: rx.rslx_bc_update_workspace_bytes(student, None, T * N, cfg),
+                    recurrent=lambda: rx.rslx_ppo_update_recurrent_workspace_bytes(ma, actor, mc, critic, ro, cfg),
+                    bc_recurrent=lambda: rx.rslx_bc_update_recurrent_workspace_bytes(ma, student, T, N, cfg))[kind]()
+        ws = rx.workspace(size).zero_()
+        if kind in ("ppo", "rnd"):
+            rx.rslx_ppo_update(actor, critic, ro, cfg, None, rnd, step, stats, ws)
+        elif kind == "bc":
+            rx.rslx_bc_update(student, None, obs, None, tg, T * N, cfg, step, stats, ws)
+        elif kind == "recurrent":
+            rx.rslx_ppo_update_recurrent(ma, actor, mc, critic, ro, dones, h0[0], h0[1], cfg, step, stats, ws)
+        else:
+            rx.rslx_bc_update_recurrent(ma, student, obs, tg, dones, h0[0], T, N, cfg, step, stats, ws)
+        torch.cuda.synchronize()
+        trained = student if kind.startswith("bc") else actor
+        seen.append((ws, trained.params.clone()))
+    assert torch.equal(seen[0][0], seen[1][0]) and not torch.equal(seen[0][1], seen[1][1])
