@@ -161,3 +161,31 @@ def test_memory_step_sizes(rx, cell, H, N, site):
     torch.cuda.synchronize()
     assert rel_l2(host(whole), host(parts)) <= 2e-6
     assert_elementwise("state", host(whole), host(parts).astype(np.float64))
+
+
+@pytest.mark.parametrize("cell", ["gru", "lstm"])
+@pytest.mark.parametrize("Ha,Hc", [(128, 64), (44, 128)])
+def test_update_of_memories_of_different_widths(rx, cell, Ha, Hc):
+    """A memory of 128 beside one of another width runs a launch per step.  Without a norm clip the two networks' updates do not meet,
+    so the oracle's runs of equal widths give the actor's and the critic's half."""
+    cases = {}
+    for H in (Ha, Hc):
+        w = replace(WORKLOADS["recurrent"].scaled(34), T=4, minibatches=2, hidden=(64, 32), memory_hidden=H, memory_cell=cell, done_p=0.2, max_grad_norm=1e9)
+        cases[H] = RCase(w, 2)
+    ca, cc = cases[Ha], cases[Hc]
+    assert np.array_equal(ca.oro["obs_a"], cc.oro["obs_a"]) and np.array_equal(ca.oro["dones"], cc.oro["dones"])
+    na, nc = _nets(rx, ca.w, ca.actor0, ca.critic0), _nets(rx, cc.w, cc.actor0, cc.critic0)
+    nets = na[:2] + nc[2:]
+    ro_a, dones, h0_a, _ = ca.gpu_rollout(rx)
+    ro_c, _, _, h0_c = cc.gpu_rollout(rx)
+    ro_a.t.update({k: ro_c.t[k] for k in ("values", "returns")})
+    rx.rslx_trace_begin(1024)
+    stats, step = _call(rx, nets, (ro_a, dones, h0_a, h0_c), ca.gpu_cfg(rx, 2, 2), 4, 0)
+    names = [r[0] for r in rx.rslx_trace_end()]
+    assert names.count("%s_step_fwd" % cell) == names.count("%s_step_bwd" % cell) == 4 * 4 and not any("seq" in n for n in names)
+    assert step == 4
+    # the free-running bounds of test_recurrent_update_two_epochs
+    np.testing.assert_allclose(stats[:, 0], ca.ref["stats"][:, 0], rtol=5e-2, atol=1e-2 * 5e-2)
+    np.testing.assert_allclose(stats[:, 1], cc.ref["stats"][:, 1], rtol=5e-2)
+    assert rel_l2(np.concatenate([host(n.params) for n in nets[:2]]), ca.ref["actor"]) <= 2e-4
+    assert rel_l2(np.concatenate([host(n.params) for n in nets[2:]]), cc.ref["critic"]) <= 2e-4
