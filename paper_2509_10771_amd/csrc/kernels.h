@@ -232,9 +232,9 @@ struct PpoLossArgs {
 constexpr int PPO_NPART_FIXED = 5;  // surrogate, value, kl, clip count, mirror ; then A entries of dlog_std
 int ppo_loss_num_blocks(int32_t mb);
 hipError_t launch_ppo_loss(const PpoLossArgs& a, hipStream_t stream);
-// Fused output layers + loss head + input gradient of the output layers (needs the last hidden widths to be
-// 32, 64 or a multiple of 4 from 68 to 256; ppo_head_supported tells).  loss.mu / loss.v are not read; loss.partials needs
-// ppo_head_num_blocks entries.
+// Fused output layers + loss head + input gradient of the output layers (needs the last hidden widths to be 32, 64 or a multiple
+// of 4 from 68 to 256, padded ones only up to so many rows; ppo_head_supported tells).  loss.mu / loss.v are not read;
+// loss.partials needs ppo_head_num_blocks entries.
 struct PpoHeadArgs {
   PpoLossArgs loss;
   const float* h_a; const float* h_c;   // last hidden activations [rows, Ha], [rows, Hc]
