@@ -208,7 +208,9 @@ struct Packed {
   }
   __device__ __forceinline__ void fetch(const GemmProblem&, int k0, int, float (&reg)[NREG], int p) {
     const char* b = base + (long)(k0 / BK) * step;          // uniform
-    const float4 v = *reinterpret_cast<const float4*>(b + off[p]);
+    uint32_t o = off[p];
+    asm volatile("" : "+v"(o));                             // a 32-bit offset beside the uniform base, not a 64-bit sum kept over the loop
+    const float4 v = *reinterpret_cast<const float4*>(b + o);
     reg[4 * p + 0] = v.x; reg[4 * p + 1] = v.y; reg[4 * p + 2] = v.z; reg[4 * p + 3] = v.w;
   }
   __device__ __forceinline__ void put_raw(char* tile, const float* v, int p) const {
@@ -338,18 +340,24 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
   // SIMD tend to be in the same phase.  Body t runs the last three products of step t - 1 and the first three of step
   // t, so the operands of step t replace those of step t - 1 in their registers as these are used up, and the parts
   // of step t + 1 have the whole body to be formed and written; one barrier per body.
+  // Two bodies to a round of the loop, so that the two places of the values on their way, and of the LDS buffers, are known at
+  // compile time: with one body the compiler moved the later values over at its end and waited there for loads of the same
+  // body, and 22 more vector instructions a step were moves and addresses.  Whole updates, us: 4096 environments, [512, 256, 128]
+  // 8634 -> 8465, [256, 256, 128] by regression 1582 -> 1535; 16 384 environments with the curiosity networks 46 060 -> 45 083.
   // Steps past the end: the last body forms the parts of one step too many (nobody reads them), and where the range is
   // no whole number of steps, the indices past its end meet a zero in one operand: the zero padding of packed weights, else
   // zeros put in place of operand B's (weight gradient) or A's values.
   constexpr int NA = decltype(la)::NP, NB = decltype(lb)::NP, NQ = NA + NB, TT = TM * TN;
   {
+    using EVEN = std::integral_constant<int, 0>;
+    using ODD = std::integral_constant<int, 1>;
     bf16x8 a[3][TM], b[3][TN];
     Quad quad;
     // piece p of step kt: a pass of operand A (p < NA) or B; `par` = kt mod 2, known at compile time
-    auto fetch_piece = [&](int p, int kt) {
+    auto fetch_piece = [&](int p, int kt, int slot) {
       const int k0 = k_begin + min(kt, nk - 1) * BK;
       if (p < NA) {
-        la.fetch(P, k0, k_end, ra[DA - 1], p < NA ? p : 0);
+        la.fetch(P, k0, k_end, ra[slot], p < NA ? p : 0);
         if constexpr (MODE == GEMM_DW) {
           if (p == NA - 1) la.look_up(k_begin + min(kt + 1, nk - 1) * BK, k_end);
         }
@@ -357,9 +365,9 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
         lb.fetch(P, k0, k_end, rb, p < NA ? 0 : p - NA);
       }
     };
-    auto split_piece = [&](int p, int kt, int half) {
+    auto split_piece = [&](int p, int kt, int half, int slot) {
       if (PACK && p >= NA) return;
-      float* v = p < NA ? ra[0] + 4 * (p < NA ? p : 0) : rb + 4 * (p < NA ? 0 : p - NA);
+      float* v = p < NA ? ra[slot] + 4 * (p < NA ? p : 0) : rb + 4 * (p < NA ? 0 : p - NA);
       if constexpr (!PACK) {
         if ((MODE == GEMM_DW) == (p >= NA)) {
           const int k0 = k_begin + kt * BK;
@@ -382,9 +390,9 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
         if constexpr (MODE == GEMM_DW) bsum[p < NA ? 0 : p - NA] += (v[0] + v[1]) + (v[2] + v[3]);
       }
     };
-    auto body = [&](int t, auto g2_tag) {
+    auto body = [&](int t, auto par_tag, auto g2_tag) {
       constexpr bool G2 = decltype(g2_tag)::value;
-      const int par = t & 1;
+      constexpr int par = decltype(par_tag)::value, next = DA == 2 ? par ^ 1 : 0;
       constexpr int S = (G2 ? 6 : 3) * TT;
       constexpr int PA[6] = {0, 1, 0, 1, 0, 2}, PB[6] = {1, 0, 0, 1, 2, 0};   // the parts that meet: step t - 1, then step t
       const char* ab = As + par * ABYTES + g * plane_pitch<BM>() + (wm * (TM * 32) + j) * 16;
@@ -407,15 +415,11 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
         acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[q]][x], b[PB[q]][y], acc[x][y], 0, 0, 0);
 #pragma unroll
         for (int p = 0; p < NQ; ++p) {
-          if (i == 3 * p * S / (3 * NQ)) split_piece(p, t + 1, 0);
-          if (i == (3 * p + 1) * S / (3 * NQ)) split_piece(p, t + 1, 1);
+          if (i == 3 * p * S / (3 * NQ)) split_piece(p, t + 1, 0, next);
+          if (i == (3 * p + 1) * S / (3 * NQ)) split_piece(p, t + 1, 1, next);
           if (i == (3 * p + 2) * S / (3 * NQ)) {
             put_piece(p, par ^ 1);
-            if (DA == 2 && p < NA) {
-#pragma unroll
-              for (int c = 0; c < 4; ++c) ra[0][4 * p + c] = ra[DA - 1][4 * p + c];
-            }
-            fetch_piece(p, t + 1 + (p < NA ? DA : 1));
+            fetch_piece(p, t + 1 + (p < NA ? DA : 1), next);
           }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -424,26 +428,25 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
     };
     if constexpr (MODE == GEMM_DW) la.look_up(k_begin, k_end);
 #pragma unroll
-    for (int p = 0; p < NQ; ++p) fetch_piece(p, 0);
+    for (int p = 0; p < NQ; ++p) fetch_piece(p, 0, 0);
     if (DA == 2) {
 #pragma unroll
-      for (int c = 0; c < 4 * NA; ++c) ra[0][c] = ra[DA - 1][c];
-#pragma unroll
-      for (int p = 0; p < NA; ++p) fetch_piece(p, 1);
+      for (int p = 0; p < NA; ++p) fetch_piece(p, 1, DA - 1);
     }
 #pragma unroll
     for (int p = 0; p < NQ; ++p) {
-      split_piece(p, 0, 0); split_piece(p, 0, 1);
+      split_piece(p, 0, 0, 0); split_piece(p, 0, 1, 0);
       put_piece(p, 0);
-      if (DA == 2 && p < NA) {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) ra[0][4 * p + c] = ra[DA - 1][4 * p + c];
-      }
-      fetch_piece(p, p < NA ? DA : 1);
+      fetch_piece(p, p < NA ? DA : 1, 0);
     }
     __syncthreads();
-    body(0, std::false_type{});
-    for (int t = 1; t < nk; ++t) body(t, std::true_type{});
+    body(0, EVEN{}, std::false_type{});
+    int t = 1;
+    for (; t + 1 < nk; t += 2) {
+      body(t, ODD{}, std::true_type{});
+      body(t + 1, EVEN{}, std::true_type{});
+    }
+    if (t < nk) body(t, ODD{}, std::true_type{});
 #pragma unroll
     for (int i = 0; i < 3 * TT; ++i) {
       constexpr int PA[3] = {0, 1, 0}, PB[3] = {1, 0, 0};
