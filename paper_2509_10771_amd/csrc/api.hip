@@ -341,6 +341,7 @@ namespace {
 
 struct PpoPlan {
   int32_t B, mb, rows;
+  bool small = false;                // forward, loss and backward pass in one launch
   bool fused_head = false;           // output layers + loss + their input gradient in one launch
   int32_t loss_blocks = 0;
   int32_t* perms = nullptr;          // [E, B]
@@ -366,12 +367,21 @@ void ppo_plan(Carver& c, const rslx_mlp* actor, const rslx_mlp* critic, const rs
   p.rows = sym ? 2 * p.mb : p.mb;
   p.perms = c.take<int32_t>((size_t)cfg->epochs * p.B);
   p.perm_ws = c.take<char>(perm_workspace_bytes(p.B));
-  p.dp_a = staged_width(*actor, ro->Da, sym != nullptr);
-  p.dp_c = staged_width(*critic, ro->Dc, sym != nullptr);
-  if (p.dp_a) p.stage_a = c.take<float>((size_t)(sym ? 2 : 1) * p.B * p.dp_a);
-  if (p.dp_c) p.stage_c = c.take<float>((size_t)(sym ? 2 : 1) * p.B * p.dp_c);
-  carve_train(c, *actor, p.rows, 2, p.actor);
-  carve_train(c, *critic, p.rows, 2, p.critic);
+  const rslx_mlp* const nets[2] = {actor, critic};
+  const size_t at = c.off;
+  p.small = !sym && p.mb <= small_step_rows(nets, 2);
+  if (p.small) {
+    carve_small(c, *actor, p.mb, p.actor);
+    carve_small(c, *critic, p.mb, p.critic);
+  } else {
+    p.dp_a = staged_width(*actor, ro->Da, sym != nullptr);
+    p.dp_c = staged_width(*critic, ro->Dc, sym != nullptr);
+    if (p.dp_a) p.stage_a = c.take<float>((size_t)(sym ? 2 : 1) * p.B * p.dp_a);
+    if (p.dp_c) p.stage_c = c.take<float>((size_t)(sym ? 2 : 1) * p.B * p.dp_c);
+    carve_train(c, *actor, p.rows, 2, p.actor);
+    carve_train(c, *critic, p.rows, 2, p.critic);
+    if (!sym) reserve_small(c, at, nets, 2, PPO_NPART_FIXED + ro->A);
+  }
   if (sym) {
     p.sym_perm = c.take<int32_t>((size_t)ro->Da + ro->Dc + ro->A);
     p.sym_sign = c.take<float>((size_t)ro->Da + ro->Dc + ro->A);
@@ -381,7 +391,7 @@ void ppo_plan(Carver& c, const rslx_mlp* actor, const rslx_mlp* critic, const rs
   p.critic.sumsq = p.sumsq_all ? p.sumsq_all + p.actor.n_sumsq : nullptr;      // null while only sizing the workspace
   p.fused_head = actor->n_layers >= 2 && critic->n_layers >= 2 &&
                  ppo_head_supported(actor->dims[actor->n_layers - 1], critic->dims[critic->n_layers - 1], ro->A, (int64_t)p.mb * (sym ? 2 : 1));
-  p.loss_blocks = p.fused_head ? ppo_head_num_blocks(p.mb, sym != nullptr) : ppo_loss_num_blocks(p.mb);
+  p.loss_blocks = p.small ? small_step_blocks(p.mb) : p.fused_head ? ppo_head_num_blocks(p.mb, sym != nullptr) : ppo_loss_num_blocks(p.mb);
   p.loss_partials = c.take<double>((size_t)p.loss_blocks * (PPO_NPART_FIXED + ro->A));
   if (rnd) {
     carve_train(c, *rnd->predictor, p.mb, 1, p.pred);
@@ -533,8 +543,10 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
         pack_add_net(pb, *critic, p.critic.pack, 1);
         RSLX_HIP(launch_pack_weights(pb, s));
       }
-      NetJob fj[2] = {NetJob{actor, xa, p.rows, &p.actor.act, &p.actor.pack}, NetJob{critic, xc, p.rows, &p.critic.act, &p.critic.pack}};
-      RSLX_TRY(forward_nets(fj, 2, s, p.fused_head));
+      if (!p.small) {
+        NetJob fj[2] = {NetJob{actor, xa, p.rows, &p.actor.act, &p.actor.pack}, NetJob{critic, xc, p.rows, &p.critic.act, &p.critic.pack}};
+        RSLX_TRY(forward_nets(fj, 2, s, p.fused_head));
+      }
 
       PpoLossArgs la;
       memset(&la, 0, sizeof la);
@@ -552,7 +564,18 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
       la.clipped_value = cfg->use_clipped_value_loss;
       la.d_mu = p.actor.d_out; la.d_v = p.critic.d_out;
       la.partials = p.loss_partials;
-      if (p.fused_head) {
+      if (p.small) {
+        SmallStepArgs sa;
+        memset(&sa, 0, sizeof sa);
+        sa.net[0] = small_net(*actor, p.actor, ro->obs_actor, ro->Da, SMALL_ACTOR);
+        sa.net[1] = small_net(*critic, p.critic, ro->obs_critic, ro->Dc, SMALL_CRITIC);
+        sa.n_nets = 2; sa.rows = p.mb; sa.idx = idx;
+        sa.actions = ro->actions; sa.logp_old = ro->logp; sa.adv = ro->advantages; sa.returns = ro->returns;
+        sa.v_old = ro->values; sa.mu_old = ro->mu; sa.sigma_old = ro->sigma; sa.log_std = la.log_std;
+        sa.terms = la;
+        sa.loss_partials = p.loss_partials;
+        RSLX_HIP(launch_small_step(sa, s));
+      } else if (p.fused_head) {
         PpoHeadArgs ha;
         ha.loss = la;
         ha.h_a = p.actor.act.out[L_a - 2]; ha.h_c = p.critic.act.out[L_c - 2];
@@ -564,9 +587,11 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
       } else {
         RSLX_HIP(launch_ppo_loss(la, s));
       }
-      BwdJob bj[2] = {BwdJob{actor, xa, p.rows, &p.actor.act, p.actor.d_out, p.actor.partials, &p.actor.plan, nullptr, &p.actor.pack},
-                      BwdJob{critic, xc, p.rows, &p.critic.act, p.critic.d_out, p.critic.partials, &p.critic.plan, nullptr, &p.critic.pack}};
-      RSLX_TRY(backward_nets(bj, 2, s, p.fused_head));
+      if (!p.small) {
+        BwdJob bj[2] = {BwdJob{actor, xa, p.rows, &p.actor.act, p.actor.d_out, p.actor.partials, &p.actor.plan, nullptr, &p.actor.pack},
+                        BwdJob{critic, xc, p.rows, &p.critic.act, p.critic.d_out, p.critic.partials, &p.critic.plan, nullptr, &p.critic.pack}};
+        RSLX_TRY(backward_nets(bj, 2, s, p.fused_head));
+      }
       {   // one launch: both networks' split sums and the loss head's sums
         ReduceArgs ra;
         memset(&ra, 0, sizeof ra);
@@ -657,7 +682,8 @@ int32_t rslx_ppo_update_dc(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout
 // ---- behaviour cloning ---------------------------------------------------------------------------------------------
 namespace {
 struct BcPlan {
-  int32_t mb;
+  int32_t mb, mse_blocks;
+  bool small = false;                // forward, loss and backward pass in one launch
   int32_t* perms = nullptr;
   void* perm_ws = nullptr;
   TrainBufs student;
@@ -671,14 +697,22 @@ void bc_plan(Carver& c, const rslx_mlp* student, const rslx_mlp* teacher, int32_
   p.mb = B / cfg->minibatches;
   p.perms = c.take<int32_t>((size_t)cfg->epochs * B);
   p.perm_ws = c.take<char>(perm_workspace_bytes(B));
-  carve_train(c, *student, p.mb, 1, p.student);
+  const size_t at = c.off;
+  p.small = p.mb <= small_step_rows(&student, 1);
+  if (p.small) {
+    carve_small(c, *student, p.mb, p.student);
+  } else {
+    carve_train(c, *student, p.mb, 1, p.student);
+    reserve_small(c, at, &student, 1, 1);
+  }
   p.student.sumsq = c.take<double>((size_t)p.student.n_sumsq + 1);
   const int A = student->dims[student->n_layers];
   if (teacher) {
     carve_net(c, *teacher, p.mb, false, p.teacher);
     p.targets = c.take<float>((size_t)B * A);
   }
-  p.mse_partials = c.take<double>(mse_num_blocks((int64_t)p.mb * A));
+  p.mse_blocks = p.small ? small_step_blocks(p.mb) : mse_num_blocks((int64_t)p.mb * A);
+  p.mse_partials = c.take<double>(p.mse_blocks);
   p.bytes = c.off + 256;
 }
 
@@ -744,7 +778,6 @@ int32_t bc_update_impl(rslx_mlp* student, const rslx_mlp* teacher, const float* 
     RSLX_HIP(launch_permutations(bases.data(), cfg->epochs, B, p.perms, p.perm_ws, s, mix64_host(cfg->seed),
                                  counters ? &counters->call_index : nullptr, cfg->epoch_offset));
   }
-  const int nbm = mse_num_blocks((int64_t)p.mb * A);
   if (cfg->epochs > 0) {
     // once per call: the statistics rows start at zero (each step then writes its loss and gradient norm)
     RSLX_HIP(launch_fill(stats, (int64_t)cfg->epochs * cfg->minibatches * RSLX_NSTATS, 0.f, s));
@@ -761,12 +794,22 @@ int32_t bc_update_impl(rslx_mlp* student, const rslx_mlp* teacher, const float* 
         pack_add_net(pb, *student, p.student.pack, 1);
         RSLX_HIP(launch_pack_weights(pb, s));
       }
-      NetJob fj{student, xs, p.mb, &p.student.act, &p.student.pack};
-      RSLX_TRY(forward_nets(&fj, 1, s));
-      RSLX_HIP(launch_mse(p.student.act.out[Ls - 1], targets, idx, p.mb, A, p.student.d_out, p.mse_partials, s));
-      BwdJob bj{student, xs, p.mb, &p.student.act, p.student.d_out, p.student.partials, &p.student.plan, nullptr, &p.student.pack};
-      RSLX_TRY(backward_nets(&bj, 1, s));
-      RSLX_TRY(reduce_net(*student, p.student, MseFinishArgs{p.mse_partials, nbm, (int64_t)p.mb * A, stats_row}, s));
+      if (p.small) {
+        SmallStepArgs sa;
+        memset(&sa, 0, sizeof sa);
+        sa.net[0] = small_net(*student, p.student, obs_student, student->dims[0], SMALL_REGRESSION);
+        sa.n_nets = 1; sa.rows = p.mb; sa.idx = idx;
+        sa.actions = targets;
+        sa.loss_partials = p.mse_partials;
+        RSLX_HIP(launch_small_step(sa, s));
+      } else {
+        NetJob fj{student, xs, p.mb, &p.student.act, &p.student.pack};
+        RSLX_TRY(forward_nets(&fj, 1, s));
+        RSLX_HIP(launch_mse(p.student.act.out[Ls - 1], targets, idx, p.mb, A, p.student.d_out, p.mse_partials, s));
+        BwdJob bj{student, xs, p.mb, &p.student.act, p.student.d_out, p.student.partials, &p.student.plan, nullptr, &p.student.pack};
+        RSLX_TRY(backward_nets(&bj, 1, s));
+      }
+      RSLX_TRY(reduce_net(*student, p.student, MseFinishArgs{p.mse_partials, p.mse_blocks, (int64_t)p.mb * A, stats_row}, s));
       const int64_t t = *adam_step + 1;
       AdamLayersArgs al;
       memset(&al, 0, sizeof al);

@@ -564,3 +564,5 @@ hipError_t launch_fused_forward(const FusedForwardArgs& a, hipStream_t stream) {
 }
 
 }  // namespace rslx
+
+#include "small_step.h"      // the layer-fused optimiser step, compiled with the layer-fused inference

@@ -286,6 +286,21 @@ inline SplitPlan plan_splits(const rslx_mlp& n, int32_t rows, int group, bool fi
   return p;
 }
 
+// Split plan of a network trained by launch_small_step: every block of rows is a split.
+inline SplitPlan plan_small(const rslx_mlp& n, int32_t rows) {
+  SplitPlan p;
+  for (int l = 0; l < n.n_layers; ++l) {
+    p.split[l] = small_step_blocks(rows);
+    p.chunk[l] = p.big[l] = 0;
+    p.size[l] = (int64_t)n.dims[l] * n.dims[l + 1] + n.dims[l + 1];
+    p.pitch[l] = (p.size[l] + 3) / 4 * 4;
+    p.part_off[l] = p.total;
+    p.total += p.pitch[l] * p.split[l];
+    p.blocks += (int32_t)((p.size[l] + REDUCE_BLOCK_FLOATS - 1) / REDUCE_BLOCK_FLOATS);
+  }
+  return p;
+}
+
 struct BwdJob {
   const rslx_mlp* net;
   XView x;
@@ -426,6 +441,65 @@ inline void carve_train(Carver& c, const rslx_mlp& n, int32_t rows, int group, T
   t.plan = plan_splits(n, rows, group, first_has_dx);
   t.partials = c.take<float>((size_t)t.plan.total);
   t.n_sumsq = t.plan.blocks;
+}
+
+// The same for a network trained by launch_small_step, which keeps its activations to itself.
+inline void carve_small(Carver& c, const rslx_mlp& n, int32_t rows, TrainBufs& t) {
+  t.pack.base = c.take<uint16_t>(WeightPack::offset(n, n.n_layers));
+  t.plan = plan_small(n, rows);
+  t.partials = c.take<float>((size_t)t.plan.total);
+  t.n_sumsq = t.plan.blocks;
+}
+
+// Where one launch for forward, loss and backward pass (small_step.h) replaces those of the layers.  It holds one workgroup of 16
+// rows per CU: while all of them run at once it is the faster one at every size it takes, a second round of them pays only where
+// the layers are narrow.  Whole updates of 5 x 4 steps, launches per layer and this, us: [48, 128, 128, 12] 1112 and 561 at 96 rows,
+// 1045 and 585 at 384, 1275 and 737 at 2046, 1173 and 1021 at 3072, 1335 and 1322 at 4098; [235, 128, 128, 12] 1482 and 920 at 2046,
+// 1343 and 1316 at 2052, 1344 and 1395 at 3072; [48, 256, 128, 12] 1450 and 1003 at 2046, 1405 and 1400 at 2052, 1322 and 1485 at
+// 3072; [48, 256, 256, 128, 12] 1618 and 1356 at 384, 2013 and 1727 at 2046, 1902 and 2705 at 3072; [256, 256, 256, 256, 32] 2249 and
+// 1892 at 96, 2627 and 2561 at 2046.
+inline int32_t small_step_most_rows(int widest, int n_nets) { return (widest <= 128 ? 384 : 256) / n_nets * 16; }
+
+// Rows up to which the networks of a call (equal depth) take it; 0 = never.
+inline int32_t small_step_rows(const rslx_mlp* const* nets, int count) {
+  int widest = 0;
+  for (int i = 0; i < count; ++i) {
+    const rslx_mlp& n = *nets[i];
+    if (n.n_layers != nets[0]->n_layers || !small_step_supported(n.dims, n.n_layers)) return 0;
+    for (int l = 0; l < n.n_layers; ++l) widest = n.dims[l] > widest ? n.dims[l] : widest;
+  }
+  return small_step_most_rows(widest, count);
+}
+
+// Moves the carver to where the buffers of the largest call of these networks that takes the small step end (`at`: where they
+// begin), so that a workspace for more rows serves fewer.
+inline void reserve_small(Carver& c, size_t at, const rslx_mlp* const* nets, int count, size_t loss_doubles_per_block) {
+  const int32_t rows = small_step_rows(nets, count);
+  if (rows == 0) return;
+  Carver t(nullptr);
+  t.off = at;
+  for (int i = 0; i < count; ++i) {
+    TrainBufs unused;
+    carve_small(t, *nets[i], rows, unused);
+  }
+  t.take<double>(loss_doubles_per_block * small_step_blocks(rows));
+  c.off = t.off > c.off ? t.off : c.off;
+}
+
+inline SmallNet small_net(const rslx_mlp& n, const TrainBufs& t, const float* x, int ldx, int role) {
+  SmallNet s;
+  memset(&s, 0, sizeof s);
+  s.params = n.params; s.pack = t.pack.base; s.x = x; s.ldx = ldx; s.partials = t.partials;
+  s.n_layers = n.n_layers; s.role = role; s.alpha = n.elu_alpha;
+  for (int l = 0; l <= n.n_layers; ++l) s.dims[l] = n.dims[l];
+  for (int l = 0; l < n.n_layers; ++l) {
+    s.weights[l] = layer_offset(n, l);
+    s.fwd[l] = t.pack.fwd(n, l) - t.pack.base;
+    s.dx[l] = t.pack.dx(n, l) - t.pack.base;
+    s.part_off[l] = t.plan.part_off[l];
+    s.pitch[l] = t.plan.pitch[l];
+  }
+  return s;
 }
 
 // Appends one network's layers to a reduce launch; the network's sumsq blocks must start at entry a.blocks of

@@ -247,6 +247,36 @@ bool ppo_head_supported(int32_t Ha, int32_t Hc, int32_t A, int64_t rows);
 int ppo_head_num_blocks(int32_t mb, bool sym);
 hipError_t launch_ppo_head(const PpoHeadArgs& h, hipStream_t stream);
 
+// Forward pass, loss and backward pass of an optimiser step in one launch, for small networks and few rows (small_step.h).  Block b
+// of the launch takes rows 16 b onwards and leaves split b of every layer's partial gradient ([W; b], pitch[l] floats apart) and
+// its loss sums: [5 + A] doubles for an actor and a critic (each writes its own entries), one for a regression.
+constexpr int SMALL_MAX_LAYERS = 4, SMALL_MAX_LDS = 160 * 1024;
+enum SmallRole : int { SMALL_ACTOR = 0, SMALL_CRITIC = 1, SMALL_REGRESSION = 2 };
+struct SmallNet {
+  const float* params;
+  const uint16_t* pack;             // split copies of the weights (launch_pack_weights)
+  const float* x;                   // input rows, gathered through idx
+  float* partials;
+  int64_t weights[SMALL_MAX_LAYERS], fwd[SMALL_MAX_LAYERS], dx[SMALL_MAX_LAYERS];      // a layer's place in params and in pack
+  int64_t part_off[SMALL_MAX_LAYERS], pitch[SMALL_MAX_LAYERS];
+  int32_t ldx, n_layers, role;
+  int32_t dims[SMALL_MAX_LAYERS + 1];
+  float alpha;
+};
+struct SmallStepArgs {
+  SmallNet net[2];
+  int32_t n_nets, rows;
+  const int32_t* idx;               // [rows] roll-out rows
+  const float* actions;             // [*, A]; a regression's targets
+  const float* logp_old; const float* adv; const float* returns; const float* v_old; const float* mu_old; const float* sigma_old;
+  const float* log_std;
+  PpoLossArgs terms;                // the loss's scalars, A
+  double* loss_partials;
+};
+int small_step_blocks(int32_t rows);
+bool small_step_supported(const int32_t* dims, int32_t n_layers);
+hipError_t launch_small_step(const SmallStepArgs& a, hipStream_t stream);
+
 // Mean-squared-error head: d = 2 (y - target) / (rows * width), block partial sums of squared error.
 int mse_num_blocks(int64_t n);
 hipError_t launch_mse(const float* y, const float* target, const int32_t* target_idx, int32_t rows, int32_t width,
