@@ -534,8 +534,14 @@ bool fused_forward_supported(const FusedForwardArgs& a) {
   return true;
 }
 
-hipError_t launch_fused_forward(const FusedForwardArgs& a, hipStream_t stream) {
-  if (a.n_rows <= 0) return hipSuccess;
+static double forward_flops(const FusedForwardArgs& a) {
+  double flops = 0.0;
+  for (int i = 0; i < a.n_nets; ++i)
+    for (int l = 0; l < a.net[i].n_layers; ++l) flops += 2.0 * a.n_rows * a.net[i].dims[l] * (double)a.net[i].dims[l + 1];
+  return flops;
+}
+
+static hipError_t launch_wide_forward(const FusedForwardArgs& a, hipStream_t stream) {
   static bool attr_set = false;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_forward_kernel),
@@ -543,10 +549,7 @@ hipError_t launch_fused_forward(const FusedForwardArgs& a, hipStream_t stream) {
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  double flops = 0.0;
-  for (int i = 0; i < a.n_nets; ++i)
-    for (int l = 0; l < a.net[i].n_layers; ++l) flops += 2.0 * a.n_rows * a.net[i].dims[l] * (double)a.net[i].dims[l + 1];
-  TraceScope ts(stream, "fused_forward", flops, 0.0);
+  TraceScope ts(stream, "fused_forward", forward_flops(a), 0.0);
   FusedForwardArgs b = a;
   for (int i = 0; i < b.n_nets; ++i)
     for (int l = 0; l < b.net[i].n_layers; ++l) {
@@ -566,3 +569,26 @@ hipError_t launch_fused_forward(const FusedForwardArgs& a, hipStream_t stream) {
 }  // namespace rslx
 
 #include "small_step.h"      // the layer-fused optimiser step, compiled with the layer-fused inference
+#include "small_forward.h"
+
+namespace rslx {
+
+hipError_t launch_fused_forward(const FusedForwardArgs& a, hipStream_t stream) {
+  if (a.n_rows <= 0) return hipSuccess;
+  const bool small = small_forward_takes(a.net[0], a.n_rows);
+  if (a.n_nets == 2 && (small != small_forward_takes(a.net[1], a.n_rows) || (small && a.net[0].n_layers != a.net[1].n_layers))) {
+    for (int i = 0; i < 2; ++i) {              // networks that take different kernels
+      FusedForwardArgs b = a;
+      b.net[0] = a.net[i];
+      b.n_nets = 1;
+      hipError_t e = launch_fused_forward(b, stream);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  if (!small) return launch_wide_forward(a, stream);
+  TraceScope ts(stream, "small_forward", forward_flops(a), 0.0);
+  return launch_small_forward(a, stream);
+}
+
+}  // namespace rslx

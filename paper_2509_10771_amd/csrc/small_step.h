@@ -133,39 +133,55 @@ __device__ __forceinline__ void ss_load_weights(const uint16_t* pack, int K, int
   }
 }
 
-// Sums over K of weights x C for the tile's 16 columns and the 16 rows.  Four accumulators by turns: an instruction that adds to
-// the result of the one before waits for it.
+// Sums over K of weights x C for the tile's 16 columns and the 16 rows.  Every step's products start from zero, the smallest first, and
+// the steps are added up in pairs: the matrix instructions cut low bits of what they add to a larger sum (error of act() on
+// [48, 128, 128, 12], geometric mean over 60 seeds: 1.04e-7; sums that run on over all steps 1.33e-7, two sums per step 1.13e-7).
 template <int STEPS>
 __device__ __forceinline__ f32x4 ss_product(const SsWeights<STEPS>& w, int K, const char* C, int cols, int m, int kq) {
   constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
-  f32x4 acc[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 sum = {0.f, 0.f, 0.f, 0.f};
   const char* u = C + (kq * SS_ROWS + m) * 16;
-#pragma unroll
-  for (int s = 0; s < STEPS; ++s) {
-    if (32 * s >= K) break;
+  auto step = [&](int s) {
     bf16x8 b[3];
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int p = 0; p < 3; ++p) b[p] = ss_unit(u + p * SS_PLANE * cols + s * 4 * SS_ROWS * 16);
 #pragma unroll
-    for (int q = 0; q < 6; ++q)
-      acc[2 * (s & 1) + (q & 1)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w.u[s][PA[q]]), b[PB[q]], acc[2 * (s & 1) + (q & 1)], 0, 0, 0);
+    for (int q = 0; q < 6; ++q) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w.u[s][PA[q]]), b[PB[q]], acc, 0, 0, 0);
+    return acc;
+  };
+#pragma unroll
+  for (int s = 0; s < STEPS; s += 2) {
+    if (32 * s >= K) break;
+    f32x4 acc = step(s);
+    if (32 * (s + 1) < K) acc += step(s + 1);
+    sum += acc;
   }
-  return ((acc[0] + acc[2]) + (acc[1] + acc[3])) * split_unscale(m);
+  return sum * split_unscale(m);
 }
 
-// Puts sums of fp32 products in place of the non-finite ones (see gemm.hip): W[k * sk + c * sc] for columns c0 .. c0 + 3.
-__device__ __forceinline__ void ss_repeat(const float* W, long sk, long sc, int K, int c0, int N, const char* C, int cols, int m, f32x4& acc) {
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    if (__builtin_isfinite(acc[r])) continue;
-    const float* w = W + min(c0 + r, N - 1) * sc;
-    float s = 0.f;
+// Puts sums of fp32 products (v_mfma_f32_16x16x4_f32) in place of the non-finite ones (see gemm.hip): weights W[k * sk + c * sc] of
+// the tile's columns c0 .. c0 + 15.
+__device__ __forceinline__ void ss_repeat(const float* W, long sk, long sc, int K, int c0, int N, const char* C, int cols, int m, int kq, f32x4& acc) {
+  constexpr int AHEAD = 4;           // products whose operands are requested together
+  const float* w0 = W + min(c0 + m, N - 1) * sc;
+  f32x4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
-    for (int k = 0; k < K; ++k) s = fmaf(w[k * sk], ss_value(C + ((k >> 3) * SS_ROWS + m) * 16 + (k & 7) * 2, SS_PLANE * cols, m & 1), s);
-    acc[r] = s;
+  for (int k0 = 0; k0 < K; k0 += 4 * AHEAD) {
+    float w[AHEAD], x[AHEAD];
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) {
+      const int k = k0 + 4 * i + kq, at = min(k, K - 1);
+      w[i] = w0[at * sk];
+      x[i] = ss_value(C + ((at >> 3) * SS_ROWS + m) * 16 + (at & 7) * 2, SS_PLANE * cols, m & 1);
+      if (k >= K) w[i] = x[i] = 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) s = __builtin_amdgcn_mfma_f32_16x16x4f32(w[i], x[i], s, 0, 0, 0);
   }
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (!__builtin_isfinite(acc[r])) acc[r] = s[r];
 }
 
 // Sums over the 16 lanes of a group, in all of them.
@@ -303,7 +319,7 @@ __global__ __launch_bounds__(SS_THREADS, 2) void small_step_kernel(const SmallSt
         for (int r = 0; r < 4; ++r) bv[i][r] = bias[min(16 * t + 4 * kq + r, N - 1)];
         if (i > 0) ss_load_weights<STEPS>(net.pack + net.fwd[l], K, N, 16 * t + m, kq, w[l % AHEAD]);
         acc[i] = ss_product<STEPS>(w[l % AHEAD], K, C, at.c_cols, m, kq);
-        if (ss_any_nonfinite(acc[i])) ss_repeat(W, N, 1, K, 16 * t + 4 * kq, N, C, at.c_cols, m, acc[i]);
+        if (ss_any_nonfinite(acc[i])) ss_repeat(W, N, 1, K, 16 * t, N, C, at.c_cols, m, kq, acc[i]);
       }
     }
     request(l + AHEAD);
@@ -431,7 +447,7 @@ __global__ __launch_bounds__(SS_THREADS, 2) void small_step_kernel(const SmallSt
         if (t < tk) {
           if (i > 0) ss_load_weights<STEPS>(net.pack + net.dx[l], N, K, 16 * t + m, kq, w[(2 * L - 1 - l) % AHEAD]);
           acc[i] = ss_product<STEPS>(w[(2 * L - 1 - l) % AHEAD], N, C, at.c_cols, m, kq);
-          if (ss_any_nonfinite(acc[i])) ss_repeat(W, 1, N, N, 16 * t + 4 * kq, K, C, at.c_cols, m, acc[i]);
+          if (ss_any_nonfinite(acc[i])) ss_repeat(W, 1, N, N, 16 * t, K, C, at.c_cols, m, kq, acc[i]);
         }
       }
       request(2 * L - 1 - l + AHEAD);
