@@ -72,22 +72,26 @@ size_t act_recurrent_carve(Carver& c, const rslx_memory* ga, const rslx_memory* 
   return c.off;
 }
 
-// hin -> gi -> new state (hidden-side contraction fused with the gates), for the memories listed (1 or 2), each with its own input matrix.
+// hin -> new state (contractions fused with the gates; the input side in a product of its own where step_forms_gi says no), for
+// the memories listed (1 or 2), each with its own input matrix.
 int32_t gru_step(const rslx_memory* const* g, const float* const* obs, const StepBufs* b, float* const* h_out, int count,
                  bool alone, int32_t N, hipStream_t s) {
   GemmBatch bi;
-  bi.count = count;
+  bi.count = 0;
   StepFwdArgs sa;
   memset(&sa, 0, sizeof sa);
   sa.n_nets = count; sa.nb = N; sa.cell = g[0]->cell; sa.alone = alone ? 1 : 0;
   for (int k = 0; k < count; ++k) {
     const rslx_memory& m = *g[k];
-    bi.p[k] = gate_problem(plain_view(obs[k], m.in_dim), m.in_dim, m.params, m.params + gru_off_bih(m), b[k].gi, N, gate_width(m));
     // the new packed state goes to h_out[k] ([N, S]): h in its first H columns, an LSTM's c behind it
     sa.net[k] = StepFwdNet{b[k].gi, b[k].hin, h_out[k], m.cell == RSLX_CELL_LSTM ? h_out[k] + m.hidden : nullptr, nullptr,
-                           m.params + gru_off_whh(m), m.params + gru_off_bhh(m), nullptr, m.hidden, state_width(m)};
+                           m.params + gru_off_whh(m), m.params + gru_off_bhh(m), nullptr, m.hidden, state_width(m),
+                           obs[k], m.params, m.params + gru_off_bih(m), m.in_dim};
+    if (step_forms_gi(sa.net[k], sa)) continue;
+    sa.net[k].x = nullptr;
+    bi.p[bi.count++] = gate_problem(plain_view(obs[k], m.in_dim), m.in_dim, m.params, m.params + gru_off_bih(m), b[k].gi, N, gate_width(m));
   }
-  RSLX_HIP(launch_gemm(GEMM_FWD, bi, s));
+  if (bi.count > 0) RSLX_HIP(launch_gemm(GEMM_FWD, bi, s));
   RSLX_HIP(launch_step_fwd(sa, s));
   return RSLX_OK;
 }

@@ -308,7 +308,7 @@ hipError_t launch_fill(float* p, int64_t n, float value, hipStream_t stream);
 // ---------------------------------------------------------------------------------------------
 enum CellKind : int { CELL_GRU = 0, CELL_LSTM = 1 };
 struct StepFwdNet {
-  const float* gi;        // [nb, G H] this step's rows
+  const float* gi;        // [nb, G H] this step's rows; not read where x is given
   const float* sin;       // [nb, S] packed state the step starts from
   float* h_out;           // new hidden state, row stride ld_out
   float* c_out;           // LSTM: new cell state, row stride ld_out; null = not stored
@@ -317,6 +317,10 @@ struct StepFwdNet {
   const float* b_hh;      // [G H]
   float* pre_out;         // [nb, G H] or null
   int32_t H, ld_out;
+  const float* x;         // [nb, D] or null: the step forms the input-side gate terms itself (step_forms_gi only)
+  const float* w_ih;      // [D, G H]
+  const float* b_ih;      // [G H]
+  int32_t D;
 };
 struct StepFwdArgs {
   StepFwdNet net[2];
@@ -325,6 +329,7 @@ struct StepFwdArgs {
   const uint8_t* done;      // episode-end flags (null = none); row i reads done[done_idx ? done_idx[i] : i]
   const int32_t* done_idx;
 };
+bool step_forms_gi(const StepFwdNet& n, const StepFwdArgs& a);    // of a network with x; false: clear x and provide gi
 hipError_t launch_step_fwd(const StepFwdArgs& a, hipStream_t stream);
 
 // One step of back-propagation through time.  back = dg_next W_hh^T (what step t + 1 sends to its input hidden

@@ -550,7 +550,9 @@ struct SeqContract {
 };
 
 // Sums of fp32 products in place of the non-finite ones of a tile (such inputs have no split, see gemm.hip).  w: element
-// (k, column) at w[k * wk + column * wc], `col` the tile's first column; x: the lane's row, contiguous along k.
+// (k, column) at w[k * wk + column * wc], `col` the tile's first column; x: the lane's row, contiguous along k.  RAGGED: K need
+// not be a multiple of 16.
+template <bool RAGGED = false>
 __device__ __forceinline__ void sq_repeat_fp32(const float* w, long wk, long wc, const float* x, int K, int lane, f4& acc) {
   const int kq = lane >> 4, m = lane & 15;
   f4 c = {0.f, 0.f, 0.f, 0.f};
@@ -559,8 +561,10 @@ __device__ __forceinline__ void sq_repeat_fp32(const float* w, long wk, long wc,
     float a[4], b[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      a[i] = w[(long)(k0 + 4 * i + kq) * wk + m * wc];
-      b[i] = x[k0 + 4 * i + kq];
+      const int k = k0 + 4 * i + kq, kr = RAGGED ? min(k, K - 1) : k;
+      a[i] = w[(long)kr * wk + m * wc];
+      b[i] = x[kr];
+      if (RAGGED && k >= K) a[i] = b[i] = 0.f;
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[i], c, 0, 0, 0);
@@ -801,6 +805,9 @@ __global__ __launch_bounds__(SQ_THREADS, 2) void seq_bwd_kernel(const SeqArgs a)
 // rows), so the gate stage works on the lane's own accumulators.  Weights are split by the workgroup on their way into LDS, 64
 // contraction indices at a time, rows in registers by the only wavefront that uses them.  Two memories of 256 at 4096
 // rows: 36 us, 55 on the fp32 matrix cores (20 at their peak).
+// The input side's contraction follows the hidden side's in the same loop, into sums of its own (which GRU's candidate needs, and
+// chains stay short): no product by itself, no [rows, G H] matrix written and read.  A chunk more costs what a chunk of the hidden
+// side does, about 4 us of those memories; the product took 14 with 48 inputs, launch included.
 constexpr int ST_ROWS = 64, ST_UNITS = 32, ST_THREADS = 256;
 
 // Workgroup -> (network, row block, unit block).  Workgroup ids go round-robin to the 8 XCDs; each XCD takes one network, half
@@ -814,6 +821,8 @@ struct StepGrid {
     blocks = 8 * per_group * (((nb + ST_ROWS - 1) / ST_ROWS + row_groups - 1) / row_groups);
   }
 };
+
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 // Contraction indices of a chunk: two workgroups are to fit a CU (72 KB of LDS for three gates, 48 for four).
 template <int CELL> struct StepSplit {
@@ -834,17 +843,29 @@ __device__ __forceinline__ void step_split(const StepFwdNet& n, int nb, int ub, 
   const int row = min(row0 + 16 * wave + b, nb - 1);
   const bool ok = row0 + 16 * wave + b < nb;             // rows past the end repeat the last one and store nothing
   const float scale = split_scale(b), unscale = split_unscale(b);
-  const int NC = H / KC;
+  // chunks of the hidden side, then those of the input side (n.x; without it gi holds that side's sums)
+  const int NC = H / KC, D = n.D, total = NC + (n.x ? (D + KC - 1) / KC : 0);
 
   // weights: this lane's column of 32 and eight contraction indices of a chunk, for its gates
   const int wc = tid & 31, wk = (tid >> 5) % (KC / 8), wg = tid / (4 * KC);
   float wf[PER][8];
+  const uint32_t col = (uint32_t)(wg * H + j0 + wc);
   auto load_w = [&](int c) {
-    const int k0 = min(c, NC - 1) * KC + 8 * wk;
+    if (c < NC) {
+      const int k0 = c * KC + 8 * wk;
 #pragma unroll
-    for (int g = 0; g < PER; ++g)
+      for (int g = 0; g < PER; ++g)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) wf[g][i] = n.w_hh[(uint32_t)(k0 + i) * (uint32_t)GH + (uint32_t)((g * S::SIDE + wg) * H + j0 + wc)];
+        for (int i = 0; i < 8; ++i) wf[g][i] = n.w_hh[(uint32_t)(k0 + i) * (uint32_t)GH + (uint32_t)(g * S::SIDE * H) + col];
+    } else if (c < total) {              // rows past the input's width: the last one (their operands are zero)
+      const int k0 = (c - NC) * KC + 8 * wk;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const uint32_t o = min((uint32_t)(k0 + i), (uint32_t)(D - 1)) * (uint32_t)GH + col;
+#pragma unroll
+        for (int g = 0; g < PER; ++g) wf[g][i] = n.w_ih[o + (uint32_t)(g * S::SIDE * H)];
+      }
+    }
   };
   auto put_w = [&](int buf) {            // blocks: [step of 32][unit tile][gate][part]
     char* dst = lds + buf * CHUNK + (((wk >> 2) * NT + (wc >> 4) * G + wg) * 3) * SQ_BLOCK + ((wk & 3) * 16 + (wc & 15)) * 16;
@@ -863,10 +884,34 @@ __device__ __forceinline__ void step_split(const StepFwdNet& n, int nb, int ub, 
   };
   // rows: operand B's eight contraction indices of every step of 32 of a chunk
   const float* xrow = n.sin + (long)row * SW;
+  const float* irow = n.x + (long)row * D;
   auto load_x = [&](int c, f4 (&x)[2 * S::KS]) {
-    const float* p = xrow + min(c, NC - 1) * KC + 8 * kq;
+    if (c < NC) {
+      const float* p = xrow + c * KC + 8 * kq;
 #pragma unroll
-    for (int i = 0; i < 2 * S::KS; ++i) x[i] = ld4(p + 32 * (i >> 1) + 4 * (i & 1));
+      for (int i = 0; i < 2 * S::KS; ++i) x[i] = ld4(p + 32 * (i >> 1) + 4 * (i & 1));
+    } else if (c < total) {
+      const int k0 = (c - NC) * KC + 8 * kq;
+      if ((D & 3) == 0 || (c + 1 - NC) * KC <= D) {       // whole groups of four; rows of an odd width are aligned to 4 bytes only
+#pragma unroll
+        for (int i = 0; i < 2 * S::KS; ++i) x[i] = *reinterpret_cast<const f4_any*>(irow + min(k0 + 32 * (i >> 1) + 4 * (i & 1), D - 4));
+      } else {
+#pragma unroll
+        for (int i = 0; i < 2 * S::KS; ++i)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) x[i][r] = irow[min(k0 + 32 * (i >> 1) + 4 * (i & 1) + r, D - 1)];
+      }
+    }
+  };
+  // zeros in place of operands past the input's width
+  auto clear_x = [&](int c, f4 (&x)[2 * S::KS]) {
+    const int k0 = (c - NC) * KC + 8 * kq;
+    if (c < NC || (c + 1 - NC) * KC <= D) return;
+#pragma unroll
+    for (int i = 0; i < 2 * S::KS; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (k0 + 32 * (i >> 1) + 4 * (i & 1) + r >= D) x[i][r] = 0.f;
   };
 
   f4 acc[NT];
@@ -880,14 +925,15 @@ __device__ __forceinline__ void step_split(const StepFwdNet& n, int nb, int ub, 
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) gi[u][g] = ld4(n.gi + (long)row * GH + g * H + ju + 16 * u);
+    for (int g = 0; g < G; ++g) gi[u][g] = n.x ? f4{0.f, 0.f, 0.f, 0.f} : ld4(n.gi + (long)row * GH + g * H + ju + 16 * u);
     st[u] = ld4(n.sin + (long)row * SW + (CELL == CELL_LSTM ? H : 0) + ju + 16 * u);
   }
   put_w(0);
   load_w(1);
   __syncthreads();
-  auto chunk = [&](int c, const f4 (&x)[2 * S::KS], f4 (&next)[2 * S::KS]) {
+  auto chunk = [&](int c, f4 (&x)[2 * S::KS], f4 (&next)[2 * S::KS], auto sum) {
     load_x(c + 1, next);
+    clear_x(c, x);
     const char* wl = lds + (c & 1) * CHUNK + lane * 16;
 #pragma unroll
     for (int ks = 0; ks < S::KS; ++ks) {
@@ -909,18 +955,27 @@ __device__ __forceinline__ void step_split(const StepFwdNet& n, int nb, int ub, 
         for (int p = 0; p < 6; ++p)
 #pragma unroll
           for (int g = 0; g < G; ++g)
-            acc[u * G + g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[3 * g + PA[p]], __builtin_bit_cast(bf16x8, xb[PB[p]]), acc[u * G + g], 0, 0, 0);
+            sum(u, g) = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[3 * g + PA[p]], __builtin_bit_cast(bf16x8, xb[PB[p]]), sum(u, g), 0, 0, 0);
       }
     }
-    if (c + 1 < NC) {
+    if (c + 1 < total) {
       put_w((c + 1) & 1);
       load_w(c + 2);
     }
     __syncthreads();
   };
+  const auto hidden = [&](int u, int g) -> f4& { return acc[u * G + g]; };
+  const auto input = [&](int u, int g) -> f4& { return gi[u][g]; };
   for (int c = 0; c < NC; c += 2) {
-    chunk(c, x0, x1);
-    if (c + 1 < NC) chunk(c + 1, x1, x0);
+    chunk(c, x0, x1, hidden);
+    if (c + 1 < NC) chunk(c + 1, x1, x0, hidden);
+    else
+#pragma unroll
+      for (int i = 0; i < 2 * S::KS; ++i) x0[i] = x1[i];
+  }
+  for (int c = NC; c < total; c += 2) {
+    chunk(c, x0, x1, input);
+    if (c + 1 < total) chunk(c + 1, x1, x0, input);
   }
   float nf = 0.f;                                         // becomes NaN with any non-finite sum
 #pragma unroll
@@ -932,6 +987,22 @@ __device__ __forceinline__ void step_split(const StepFwdNet& n, int nb, int ub, 
   if (__any(!(nf == 0.f))) {
 #pragma unroll
     for (int i = 0; i < NT; ++i) sq_repeat_fp32(n.w_hh + i % G * H + j0 + 16 * (i / G), GH, 1, xrow, H, lane, acc[i]);
+  }
+  if (n.x) {
+    nf = 0.f;
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      f4& v = gi[i / G][i % G];
+      v *= unscale;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) nf = fmaf(v[r], 0.f, nf);
+    }
+    if (__any(!(nf == 0.f))) {
+#pragma unroll
+      for (int i = 0; i < NT; ++i) sq_repeat_fp32<true>(n.w_ih + i % G * H + j0 + 16 * (i / G), GH, 1, irow, D, lane, gi[i / G][i % G]);
+    }
+#pragma unroll
+    for (int i = 0; i < NT; ++i) gi[i / G][i % G] += ld4(n.b_ih + i % G * H + ju + 16 * (i / G));
   }
   if (!ok) return;
 #pragma unroll
@@ -1095,6 +1166,15 @@ static hipError_t launch_step_rest(const StepFwdArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Its line: act() with the input side in a product of its own and here, memories in front of [256, 128], us: GRU of 256 at 4096 rows 74.9
+// and 70.1 with 48 inputs, 92.9 and 86.1 with 235, 102 and 100 with 400, at 1200 rows 55.1 and 49.9, 62.9 and 58.4, 63.7 and 63.7, with
+// 512 67.8 and 67.4; GRU of 512 at 1024 rows with 1000 117 and 106; LSTM of 256 at 4096 rows 86.4 and 81.1, 111 and 102, 123 and
+// 120, with 512 131 and 130; of 128 at 8192 rows with 48 90.8 and 83.4, with 256 110 and 102.  The gain is nearly gone at twice
+// the memory's width.
+bool step_forms_gi(const StepFwdNet& n, const StepFwdArgs& a) {
+  return n.x != nullptr && n.D <= 2 * n.H && step_split_fits(n, a);
+}
+
 hipError_t launch_step_fwd(const StepFwdArgs& a, hipStream_t stream) {
   if (a.nb <= 0 || a.n_nets <= 0) return hipSuccess;
   const bool lstm = a.cell == CELL_LSTM;
@@ -1104,7 +1184,7 @@ hipError_t launch_step_fwd(const StepFwdArgs& a, hipStream_t stream) {
   double flops = 0.0;
   for (int k = 0; k < b.n_nets; ++k) {
     split |= step_split_fits(b.net[k], b) << k;
-    flops += 2.0 * b.nb * b.net[k].H * (lstm ? 4.0 : 3.0) * b.net[k].H;
+    flops += 2.0 * b.nb * (b.net[k].H + (b.net[k].x ? b.net[k].D : 0)) * (lstm ? 4.0 : 3.0) * b.net[k].H;
   }
   if (split == 0) return launch_step_rest(a, stream);
   if (b.n_nets == 2 && (split != 3 || b.net[0].H != b.net[1].H)) {

@@ -1,0 +1,93 @@
+"""One step of a memory that forms the input-side gate terms in the same launch: against float64 at input widths around its chunks, inputs
+aligned to four bytes only, infinite inputs and weights, and the line to a product of its own."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rx():
+    import paper_2509_10771_amd as m
+    m.rslx_device_check()
+    return m
+
+
+def _memory(rx, cell, D, H, gen):
+    G = 4 if cell == "lstm" else 3
+    return rx.Memory(rx.CELL_LSTM if cell == "lstm" else rx.CELL_GRU, D, H, ((torch.rand(G * H * (D + H + 2), generator=gen) * 2 - 1) / H ** 0.5).cuda())
+
+
+def _reference(m, x, state):
+    """The step in float64; sums of products, so that an infinite operand gives infinities of its column and sign."""
+    D, H, GH = m.in_dim, m.hidden, m.gates * m.hidden
+    p, x, h = m.params.double(), x.double(), state.double()[:, :m.hidden]
+    o = D * GH + GH
+    gi = torch.stack([(r[:, None] * p[:D * GH].view(D, GH)).sum(0) for r in x]) if not torch.isfinite(x).all() else x @ p[:D * GH].view(D, GH)
+    gi, gh = gi + p[D * GH:o], h @ p[o:o + H * GH].view(H, GH) + p[o + H * GH:]
+    if m.gates == 3:
+        r, z = torch.sigmoid(gi[:, :H] + gh[:, :H]), torch.sigmoid(gi[:, H:2 * H] + gh[:, H:2 * H])
+        return (1 - z) * torch.tanh(gi[:, 2 * H:] + r * gh[:, 2 * H:]) + z * h
+    i, f, g, u = (gi + gh).split(H, 1)
+    c = torch.sigmoid(f) * state.double()[:, H:] + torch.sigmoid(i) * torch.tanh(g)
+    return torch.cat([torch.sigmoid(u) * torch.tanh(c), c], 1)
+
+
+def _step(rx, m, x, state):
+    s = state.clone()
+    ws = rx.workspace(rx.rslx_memory_step_workspace_bytes(m, x.shape[0]))
+    rx.rslx_trace_begin(16)
+    rx.rslx_memory_step(m, x, x.shape[0], s, None, None, None, ws)
+    torch.cuda.synchronize()
+    return s, [r[0] for r in rx.rslx_trace_end()]
+
+
+@pytest.mark.parametrize("cell,H,N", [("gru", 64, 4099), ("gru", 192, 1400), ("gru", 256, 1025), ("lstm", 128, 6145), ("lstm", 320, 2048)])
+@pytest.mark.parametrize("D", [1, 3, 4, 31, 32, 33, 64, 65, 101, 128])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_state_against_float64(rx, cell, H, N, D, shift):
+    gen = torch.Generator().manual_seed(N + D)
+    m = _memory(rx, cell, D, H, gen)
+    x = torch.randn(N * D + shift, generator=gen).cuda()[shift:].view(N, D)
+    state = (0.5 * torch.randn(N, m.state_width, generator=gen)).cuda()
+    got, sites = _step(rx, m, x, state)
+    assert sites == [cell + "_split"]
+    # gates of D + H terms below 2^2 each in fp32: 2^-24 of the largest partial sum per 32 terms, far below 1e-5 after the sigmoid and tanh
+    assert float((got.double() - _reference(m, x, state)).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("cell,H,N", [("gru", 128, 2049), ("lstm", 128, 6145)])
+def test_line_of_the_input_width(rx, cell, H, N):
+    """Up to twice the memory's width in the step's launch, beyond it in a product of its own: the same states from one column of zeros more."""
+    gen = torch.Generator().manual_seed(5)
+    D, m = 2 * H, _memory(rx, cell, 2 * H, H, gen)
+    x, state = torch.randn(N, D, generator=gen).cuda(), (0.5 * torch.randn(N, m.state_width, generator=gen)).cuda()
+    wide = rx.Memory(m.cell, D + 1, H, torch.cat([m.params[:D * m.gates * H], torch.ones(m.gates * H, device="cuda"), m.params[D * m.gates * H:]]))
+    a, sa = _step(rx, m, x, state)
+    b, sb = _step(rx, wide, torch.cat([x, torch.zeros(N, 1, device="cuda")], 1), state)
+    assert sa == [cell + "_split"] and len(sb) == 2 and sb[1] == cell + "_split"
+    assert float((a - b).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("cell,H,N", [("gru", 64, 4099), ("lstm", 128, 6145)])
+@pytest.mark.parametrize("D", [5, 48])
+def test_infinite_inputs_and_weights(rx, cell, H, N, D):
+    """Infinities saturate the gates of their rows, NaN stays in its row, the other rows keep their bits; an infinite weight of the last
+    input gives the float64 step's values."""
+    gen = torch.Generator().manual_seed(7)
+    m = _memory(rx, cell, D, H, gen)
+    x, state = torch.randn(N, D, generator=gen).cuda(), (0.5 * torch.randn(N, m.state_width, generator=gen)).cuda()
+    clean, _ = _step(rx, m, x, state)
+    bad = x.clone()
+    bad[7, 3], bad[64, D - 1], bad[N - 1, 0] = float("inf"), -float("inf"), float("nan")
+    got, sites = _step(rx, m, bad, state)
+    assert sites == [cell + "_split"] and bool(torch.isnan(got[N - 1, :H]).all())
+    keep = torch.ones(N, dtype=torch.bool, device="cuda")
+    keep[[7, 64, N - 1]] = False
+    assert torch.equal(got[keep], clean[keep])
+    ref = _reference(m, bad[[7, 64]], state[[7, 64]])
+    assert bool(torch.isfinite(ref).all()) and float((got[[7, 64]].double() - ref).abs().max()) <= 1e-5
+    m.params[(D - 1) * m.gates * H + 5] = float("inf")                   # the first gate of unit 5
+    got, _ = _step(rx, m, x, state)
+    ref = _reference(m, x, state)
+    assert bool(torch.isfinite(ref).all()) and float((got.double() - ref).abs().max()) <= 1e-5
