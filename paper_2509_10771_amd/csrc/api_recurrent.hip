@@ -56,9 +56,19 @@ struct StepBufs {     // one memory's buffers of a single act step
   float* hin = nullptr;     // [N, S] state the step starts from (after reset)
   float* gi = nullptr;      // [N, G H]
   float* hnew = nullptr;    // [N, S] values-only: the state is not written back
+  uint16_t* pack = nullptr; // split weights, of memories whose step runs on split operands
 };
 
-size_t act_recurrent_carve(Carver& c, const rslx_memory* ga, const rslx_memory* gc, int32_t N, StepBufs* ba, StepBufs* bc) {
+// Inputs that a step on split operands contracts itself: all or none.
+int32_t step_input(const rslx_memory& m) { return step_takes_input(m.hidden, m.in_dim) ? m.in_dim : 0; }
+
+// The state that a step starts from, and its weights' split in the same launch.
+void gather_step(RowGatherArgs& rg, const rslx_memory& m, const StepBufs& b, const float* state, float* first_out) {
+  rg.job[rg.n_jobs++] = RowGatherJob{state, b.hin, first_out, state_width(m)};
+  if (b.pack) rg.pack[rg.n_packs++] = StepPackJob{m.params + gru_off_whh(m), m.params, b.pack, m.hidden, step_input(m), m.cell};
+}
+
+size_t act_recurrent_carve(Carver& c, const rslx_memory* ga, const rslx_memory* gc, int32_t N, StepBufs* ba, StepBufs* bc, bool alone = false) {
   const rslx_memory* g[2] = {ga, gc};
   StepBufs* b[2] = {ba, bc};
   for (int k = 0; k < 2; ++k) {
@@ -67,28 +77,28 @@ size_t act_recurrent_carve(Carver& c, const rslx_memory* ga, const rslx_memory* 
     t.hin = c.take<float>((size_t)N * state_width(*g[k]));
     t.gi = c.take<float>((size_t)N * gate_width(*g[k]));
     t.hnew = c.take<float>((size_t)N * state_width(*g[k]));
+    if (step_split_sizes(g[k]->cell, g[k]->hidden, N, alone)) t.pack = c.take<uint16_t>(step_pack_bytes(g[k]->cell, g[k]->hidden, step_input(*g[k])) / 2);
     if (b[k]) *b[k] = t;
   }
   return c.off;
 }
 
-// hin -> new state (contractions fused with the gates; the input side in a product of its own where step_forms_gi says no), for
+// hin -> new state (contractions fused with the gates; the input side in a product of its own where the step does not take it), for
 // the memories listed (1 or 2), each with its own input matrix.
 int32_t gru_step(const rslx_memory* const* g, const float* const* obs, const StepBufs* b, float* const* h_out, int count,
-                 bool alone, int32_t N, hipStream_t s) {
+                 int32_t N, hipStream_t s) {
   GemmBatch bi;
   bi.count = 0;
   StepFwdArgs sa;
   memset(&sa, 0, sizeof sa);
-  sa.n_nets = count; sa.nb = N; sa.cell = g[0]->cell; sa.alone = alone ? 1 : 0;
+  sa.n_nets = count; sa.nb = N; sa.cell = g[0]->cell;
   for (int k = 0; k < count; ++k) {
     const rslx_memory& m = *g[k];
     // the new packed state goes to h_out[k] ([N, S]): h in its first H columns, an LSTM's c behind it
     sa.net[k] = StepFwdNet{b[k].gi, b[k].hin, h_out[k], m.cell == RSLX_CELL_LSTM ? h_out[k] + m.hidden : nullptr, nullptr,
                            m.params + gru_off_whh(m), m.params + gru_off_bhh(m), nullptr, m.hidden, state_width(m),
-                           obs[k], m.params, m.params + gru_off_bih(m), m.in_dim};
-    if (step_forms_gi(sa.net[k], sa)) continue;
-    sa.net[k].x = nullptr;
+                           b[k].pack, b[k].pack && step_input(m) > 0 ? obs[k] : nullptr, m.params, m.params + gru_off_bih(m), m.in_dim};
+    if (sa.net[k].x) continue;
     bi.p[bi.count++] = gate_problem(plain_view(obs[k], m.in_dim), m.in_dim, m.params, m.params + gru_off_bih(m), b[k].gi, N, gate_width(m));
   }
   if (bi.count > 0) RSLX_HIP(launch_gemm(GEMM_FWD, bi, s));
@@ -160,8 +170,8 @@ int32_t act_recurrent_impl(const rslx_memory* gru_actor, const rslx_mlp* actor, 
   RowGatherArgs rg;
   memset(&rg, 0, sizeof rg);
   rg.nb = N; rg.reset = reset_or_null;
-  if (ga) rg.job[rg.n_jobs++] = RowGatherJob{h_actor, ba.hin, values_only ? nullptr : h0_actor_out, state_width(*ga)};
-  rg.job[rg.n_jobs++] = RowGatherJob{h_critic, bc.hin, values_only ? nullptr : h0_critic_out, state_width(*gru_critic)};
+  if (ga) gather_step(rg, *ga, ba, h_actor, values_only ? nullptr : h0_actor_out);
+  gather_step(rg, *gru_critic, bc, h_critic, values_only ? nullptr : h0_critic_out);
   RSLX_HIP(launch_row_gather(rg, s));
 
   const float* h_in_actor_mlp = h_actor;
@@ -171,13 +181,13 @@ int32_t act_recurrent_impl(const rslx_memory* gru_actor, const rslx_mlp* actor, 
     const float* obs[2] = {obs_actor, obs_critic};
     const StepBufs b[2] = {ba, bc};
     float* out[2] = {h_actor, h_critic};
-    RSLX_TRY(gru_step(g, obs, b, out, 2, false, N, s));
+    RSLX_TRY(gru_step(g, obs, b, out, 2, N, s));
   } else {
     const rslx_memory* g[1] = {gru_critic};
     const float* obs[1] = {obs_critic};
     const StepBufs b[1] = {bc};
     float* out[1] = {bc.hnew};
-    RSLX_TRY(gru_step(g, obs, b, out, 1, false, N, s));
+    RSLX_TRY(gru_step(g, obs, b, out, 1, N, s));
   }
   return act_impl(a, critic, h_in_actor_mlp, h_in_critic_mlp, N, seed, step, counters, eps_or_null, actions, logp, values,
                   mu, sigma, flags, static_cast<char*>(ws) + used, ws_bytes - used, stream, ga ? state_width(*ga) : 0,
@@ -673,7 +683,7 @@ extern "C" {
 size_t rslx_memory_step_workspace_bytes(const rslx_memory* mem, int32_t N) {
   if (!mem || N <= 0) return 256;
   Carver c(nullptr);
-  act_recurrent_carve(c, mem, nullptr, N, nullptr, nullptr);
+  act_recurrent_carve(c, mem, nullptr, N, nullptr, nullptr, true);
   return c.off + 256;
 }
 
@@ -689,17 +699,17 @@ int32_t rslx_memory_step(const rslx_memory* mem, const float* obs, int32_t N, fl
   hipStream_t s = (hipStream_t)stream;
   Carver c(ws);
   StepBufs b;
-  act_recurrent_carve(c, mem, nullptr, N, &b, nullptr);
+  act_recurrent_carve(c, mem, nullptr, N, &b, nullptr, true);
   RowGatherArgs rg;
   memset(&rg, 0, sizeof rg);
-  rg.n_jobs = 1; rg.nb = N; rg.reset = reset_or_null;
-  rg.job[0] = RowGatherJob{state, b.hin, s0_out, state_width(*mem)};
+  rg.nb = N; rg.reset = reset_or_null;
+  gather_step(rg, *mem, b, state, s0_out);
   RSLX_HIP(launch_row_gather(rg, s));
   const rslx_memory* g[1] = {mem};
   const float* o[1] = {obs};
   const StepBufs bb[1] = {b};
   float* out[1] = {state};
-  RSLX_TRY(gru_step(g, o, bb, out, 1, true, N, s));
+  RSLX_TRY(gru_step(g, o, bb, out, 1, N, s));
   if (h_dense_out) RSLX_HIP(launch_copy_matrix(state, state_width(*mem), N, mem->hidden, h_dense_out, s));
   return RSLX_OK;
 }

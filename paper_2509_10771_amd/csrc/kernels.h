@@ -317,7 +317,8 @@ struct StepFwdNet {
   const float* b_hh;      // [G H]
   float* pre_out;         // [nb, G H] or null
   int32_t H, ld_out;
-  const float* x;         // [nb, D] or null: the step forms the input-side gate terms itself (step_forms_gi only)
+  const uint16_t* pack;   // split weights (StepPackJob) for the step on split operands, or null: the fp32 step
+  const float* x;         // with pack: [nb, D], the step forms the input-side gate terms itself; or null: gi holds them
   const float* w_ih;      // [D, G H]
   const float* b_ih;      // [G H]
   int32_t D;
@@ -325,11 +326,12 @@ struct StepFwdNet {
 struct StepFwdArgs {
   StepFwdNet net[2];
   int32_t n_nets, nb, cell;
-  int32_t alone;            // 1: rslx_memory_step (see step_split_fits)
   const uint8_t* done;      // episode-end flags (null = none); row i reads done[done_idx ? done_idx[i] : i]
   const int32_t* done_idx;
 };
-bool step_forms_gi(const StepFwdNet& n, const StepFwdArgs& a);    // of a network with x; false: clear x and provide gi
+bool step_split_sizes(int32_t cell, int32_t H, int32_t nb, bool alone);    // the step on split operands; alone: rslx_memory_step
+bool step_takes_input(int32_t H, int32_t D);                               // that step forms the input side's terms too
+size_t step_pack_bytes(int32_t cell, int32_t H, int32_t D);
 hipError_t launch_step_fwd(const StepFwdArgs& a, hipStream_t stream);
 
 // One step of back-propagation through time.  back = dg_next W_hh^T (what step t + 1 sends to its input hidden
@@ -388,9 +390,12 @@ hipError_t launch_seq_bwd(const SeqArgs& a, hipStream_t stream);
 // dst[i, :] = src[idx ? idx[i] : i, :] * (reset && reset[i] ? 0 : 1) for up to two [*, H] matrices; a second
 // copy of the result goes to dst2 when it is not null.
 struct RowGatherJob { const float* src; float* dst; float* dst2; int32_t H; };
+// In the same launch, split weights for a step on split operands (pack of StepFwdNet); D = 0: of the hidden side only.
+struct StepPackJob { const float *w_hh, *w_ih; uint16_t* dst; int32_t H, D, cell; };
 struct RowGatherArgs {
   RowGatherJob job[2];
-  int32_t n_jobs, nb;
+  StepPackJob pack[2];
+  int32_t n_jobs, n_packs, nb;
   const int32_t* idx;
   const uint8_t* reset;
 };

@@ -802,12 +802,13 @@ __global__ __launch_bounds__(SQ_THREADS, 2) void seq_bwd_kernel(const SeqArgs a)
 // ---- act(): one time step on split operands ----------------------------------------------------------------
 // For many rows and widths that are multiples of 64.  A workgroup of 4 wavefronts takes 64 rows and 32 hidden units; wavefront w
 // its rows 16 w .., operands and accumulators as in the roll-out kernels above (operand A 16 weight columns, operand B 16
-// rows), so the gate stage works on the lane's own accumulators.  Weights are split by the workgroup on their way into LDS, 64
-// contraction indices at a time, rows in registers by the only wavefront that uses them.  Two memories of 256 at 4096
-// rows: 36 us, 55 on the fp32 matrix cores (20 at their peak).
+// rows), so the gate stage works on the lane's own accumulators.  The weights come split, in the order in which LDS holds them, a
+// chunk of 64 (LSTM: 32) contraction indices at a time through registers; the launch that copies the states splits them.  Each
+// workgroup splitting them for itself, once per 64 rows, took two thirds of the loop's vector instructions: two GRUs of 256 at
+// 4096 rows with 48 inputs in front of [512, 256, 128] 91.1 us a call that way, 84.4 now; LSTMs with 235 in front of [256, 128]
+// 102 and 90.  Rows are split in registers by the only wavefront that uses them.
 // The input side's contraction follows the hidden side's in the same loop, into sums of its own (which GRU's candidate needs, and
-// chains stay short): no product by itself, no [rows, G H] matrix written and read.  A chunk more costs what a chunk of the hidden
-// side does, about 4 us of those memories; the product took 14 with 48 inputs, launch included.
+// chains stay short): no product by itself, no [rows, G H] matrix written and read, 95.9 us a call with them.
 constexpr int ST_ROWS = 64, ST_UNITS = 32, ST_THREADS = 256;
 
 // Workgroup -> (network, row block, unit block).  Workgroup ids go round-robin to the 8 XCDs; each XCD takes one network, half
@@ -828,14 +829,47 @@ typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
 template <int CELL> struct StepSplit {
   static constexpr int G = CellShape<CELL>::G, KC = CELL == CELL_LSTM ? 32 : 64, KS = KC / 32;
   static constexpr int NT = 2 * G, CHUNK = KS * NT * 3 * SQ_BLOCK;         // tiles of 16 weight columns, bytes of a chunk
-  static constexpr int SIDE = ST_THREADS / (4 * KC), PER = G / SIDE;       // gates side by side in the lanes' loads, gates per lane
+  static constexpr int LOADS = CHUNK / (ST_THREADS * 16);
 };
+
+// Chunks of the hidden side, then those of the input side.
+template <int CELL> __host__ __device__ __forceinline__ int step_chunks(int H, int D) {
+  return H / StepSplit<CELL>::KC + (D + StepSplit<CELL>::KC - 1) / StepSplit<CELL>::KC;
+}
+
+// Unit e of a network's weights, split: [unit block][chunk][step of 32][unit tile][gate][part][lane], zeros past the input's width.
+template <int CELL>
+__device__ __forceinline__ void step_pack(const StepPackJob& J, long e) {
+  using S = StepSplit<CELL>;
+  const int total = step_chunks<CELL>(J.H, J.D), NC = J.H / S::KC, GH = S::G * J.H;
+  const int lane = (int)e & 63;
+  const long blk = e >> 6;
+  const int t = (int)(blk % S::NT), ks = (int)(blk / S::NT % S::KS);
+  const int uc = (int)(blk / (S::NT * S::KS)), c = uc % total, ub = uc / total;
+  if (ub >= J.H / ST_UNITS) return;
+  const bool in = c >= NC;
+  const float* w = (in ? J.w_ih : J.w_hh) + t % S::G * J.H + ub * ST_UNITS + 16 * (t / S::G) + (lane & 15);
+  const int k0 = (in ? c - NC : c) * S::KC + 32 * ks + 8 * (lane >> 4), K = in ? J.D : J.H;
+  float v[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = w[(long)min(k0 + i, K - 1) * GH];
+  u32x4 part[3];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    uint32_t p0, p1, p2;
+    split_pair(k0 + 2 * i < K ? SPLIT_SCALE * v[2 * i] : 0.f, k0 + 2 * i + 1 < K ? SPLIT_SCALE * v[2 * i + 1] : 0.f, p0, p1, p2);
+    part[0][i] = p0; part[1][i] = p1; part[2][i] = p2;
+  }
+  char* dst = reinterpret_cast<char*>(J.dst) + blk * (3 * SQ_BLOCK) + lane * 16;
+#pragma unroll
+  for (int s = 0; s < 3; ++s) *reinterpret_cast<u32x4*>(dst + s * SQ_BLOCK) = part[s];
+}
 
 // Unit block ub, rows from row0 of a network; lds: 2 CHUNK bytes.
 template <int CELL>
 __device__ __forceinline__ void step_split(const StepFwdNet& n, int nb, int ub, int row0, char* lds) {
   using S = StepSplit<CELL>;
-  constexpr int G = S::G, NT = S::NT, KC = S::KC, CHUNK = S::CHUNK, PER = S::PER;
+  constexpr int G = S::G, NT = S::NT, KC = S::KC, CHUNK = S::CHUNK, LOADS = S::LOADS;
   const int H = n.H, GH = G * H, SW = CELL == CELL_LSTM ? 2 * H : H;
   if (ub >= H / ST_UNITS || row0 >= nb) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -843,44 +877,21 @@ __device__ __forceinline__ void step_split(const StepFwdNet& n, int nb, int ub, 
   const int row = min(row0 + 16 * wave + b, nb - 1);
   const bool ok = row0 + 16 * wave + b < nb;             // rows past the end repeat the last one and store nothing
   const float scale = split_scale(b), unscale = split_unscale(b);
-  // chunks of the hidden side, then those of the input side (n.x; without it gi holds that side's sums)
-  const int NC = H / KC, D = n.D, total = NC + (n.x ? (D + KC - 1) / KC : 0);
+  // without x, gi holds the input side's sums
+  const int NC = H / KC, D = n.D, total = step_chunks<CELL>(H, n.x ? D : 0);
 
-  // weights: this lane's column of 32 and eight contraction indices of a chunk, for its gates
-  const int wc = tid & 31, wk = (tid >> 5) % (KC / 8), wg = tid / (4 * KC);
-  float wf[PER][8];
-  const uint32_t col = (uint32_t)(wg * H + j0 + wc);
+  // weights: this lane's 16-byte units of a chunk
+  const char* wsrc = reinterpret_cast<const char*>(n.pack) + (long)ub * total * CHUNK + tid * 16;
+  u32x4 wv[LOADS];
   auto load_w = [&](int c) {
-    if (c < NC) {
-      const int k0 = c * KC + 8 * wk;
+    const char* p = wsrc + (long)min(c, total - 1) * CHUNK;
 #pragma unroll
-      for (int g = 0; g < PER; ++g)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) wf[g][i] = n.w_hh[(uint32_t)(k0 + i) * (uint32_t)GH + (uint32_t)(g * S::SIDE * H) + col];
-    } else if (c < total) {              // rows past the input's width: the last one (their operands are zero)
-      const int k0 = (c - NC) * KC + 8 * wk;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const uint32_t o = min((uint32_t)(k0 + i), (uint32_t)(D - 1)) * (uint32_t)GH + col;
-#pragma unroll
-        for (int g = 0; g < PER; ++g) wf[g][i] = n.w_ih[o + (uint32_t)(g * S::SIDE * H)];
-      }
-    }
+    for (int i = 0; i < LOADS; ++i) wv[i] = *reinterpret_cast<const u32x4*>(p + i * (ST_THREADS * 16));
   };
-  auto put_w = [&](int buf) {            // blocks: [step of 32][unit tile][gate][part]
-    char* dst = lds + buf * CHUNK + (((wk >> 2) * NT + (wc >> 4) * G + wg) * 3) * SQ_BLOCK + ((wk & 3) * 16 + (wc & 15)) * 16;
+  auto put_w = [&](int buf) {
+    char* dst = lds + buf * CHUNK + tid * 16;
 #pragma unroll
-    for (int g = 0; g < PER; ++g) {
-      u32x4 part[3];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        uint32_t p0, p1, p2;
-        split_pair(SPLIT_SCALE * wf[g][2 * i], SPLIT_SCALE * wf[g][2 * i + 1], p0, p1, p2);
-        part[0][i] = p0; part[1][i] = p1; part[2][i] = p2;
-      }
-#pragma unroll
-      for (int s = 0; s < 3; ++s) *reinterpret_cast<u32x4*>(dst + (3 * S::SIDE * g + s) * SQ_BLOCK) = part[s];
-    }
+    for (int i = 0; i < LOADS; ++i) *reinterpret_cast<u32x4*>(dst + i * (ST_THREADS * 16)) = wv[i];
   };
   // rows: operand B's eight contraction indices of every step of 32 of a chunk
   const float* xrow = n.sin + (long)row * SW;
@@ -903,16 +914,6 @@ __device__ __forceinline__ void step_split(const StepFwdNet& n, int nb, int ub, 
       }
     }
   };
-  // zeros in place of operands past the input's width
-  auto clear_x = [&](int c, f4 (&x)[2 * S::KS]) {
-    const int k0 = (c - NC) * KC + 8 * kq;
-    if (c < NC || (c + 1 - NC) * KC <= D) return;
-#pragma unroll
-    for (int i = 0; i < 2 * S::KS; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (k0 + 32 * (i >> 1) + 4 * (i & 1) + r >= D) x[i][r] = 0.f;
-  };
 
   f4 acc[NT];
 #pragma unroll
@@ -931,9 +932,8 @@ __device__ __forceinline__ void step_split(const StepFwdNet& n, int nb, int ub, 
   put_w(0);
   load_w(1);
   __syncthreads();
-  auto chunk = [&](int c, f4 (&x)[2 * S::KS], f4 (&next)[2 * S::KS], auto sum) {
+  auto chunk = [&](int c, const f4 (&x)[2 * S::KS], f4 (&next)[2 * S::KS], auto sum) {
     load_x(c + 1, next);
-    clear_x(c, x);
     const char* wl = lds + (c & 1) * CHUNK + lane * 16;
 #pragma unroll
     for (int ks = 0; ks < S::KS; ++ks) {
@@ -1072,21 +1072,6 @@ hipError_t step_uneven_launch(const StepFwdArgs& a, int split, int rest_blocks, 
   return hipGetLastError();
 }
 
-// Which steps take that kernel: those of act() (nothing kept for a backward pass, no flags) from about the size on where it is the
-// faster one for a memory by itself.  The fp32 step and this in rslx_memory_step and in act() with two such memories in front of
-// [64, 12], us: GRU of 256 18.3, 21.0 and 37.0, 35.8 at 1024 rows, 22.8, 21.7 and 44.0, 39.5 at 1055; GRU of 128 15.9, 17.9 and 31.6,
-// 31.3 at 2048, 18.6, 18.1 and 36.2, 33.5 at 2110; LSTM of 256 29.8, 29.6 and 58.1, 52.1 at 2048; LSTM of 128 24.9, 25.3 and 47.6, 47.0
-// at 4096, 31.6, 32.3 and 59.7, 57.0 at 5121, 36.8, 33.8 and 68.1, 65.1 at 6554; LSTM of 64 33.4, 34.3 and 73.8, 72.2 at 16 385.  A
-// memory's own sizes decide, so that a call for the values alone returns the bits of a full one; only rslx_memory_step, which has no
-// such counterpart, may draw its line later.
-bool step_split_fits(const StepFwdNet& n, const StepFwdArgs& a) {
-  if (n.H % 64 != 0 || n.H > 8192 || a.nb < 1024) return false;
-  const int64_t size = (int64_t)a.nb * n.H;
-  if (a.cell == CELL_LSTM ? size < (n.H < 128 ? 1 << 21 : a.alone && n.H < 256 ? 3 << 18 : 1 << 19) : size <= 1 << 18) return false;
-  if (a.done != nullptr || n.sin_next != nullptr || n.pre_out != nullptr || (a.cell == CELL_LSTM && n.c_out == nullptr)) return false;
-  return ((reinterpret_cast<uintptr_t>(n.h_out) | reinterpret_cast<uintptr_t>(n.c_out) | reinterpret_cast<uintptr_t>(n.sin)) & 15) == 0;
-}
-
 template <int CELL, int H>
 hipError_t seq_launch(const SeqArgs& a, bool backward, hipStream_t stream) {
   const dim3 grid((a.nb + SQ_ROWS - 1) / SQ_ROWS, a.n_nets);
@@ -1106,9 +1091,15 @@ hipError_t seq_dispatch(const SeqArgs& a, bool backward, hipStream_t stream) {
 }
 
 __global__ __launch_bounds__(256) void row_gather_kernel(const RowGatherArgs a) {
+  const long e = (long)blockIdx.x * 256 + threadIdx.x;
+  if ((int)blockIdx.y >= a.n_jobs) {
+    const StepPackJob& P = a.pack[blockIdx.y - a.n_jobs];
+    if (P.cell == CELL_LSTM) step_pack<CELL_LSTM>(P, e);
+    else step_pack<CELL_GRU>(P, e);
+    return;
+  }
   const RowGatherJob& J = a.job[blockIdx.y];
   const int q = J.H >> 2;
-  const long e = (long)blockIdx.x * 256 + threadIdx.x;
   if (e >= (long)a.nb * q) return;
   const int i = (int)(e / q), j = (int)(e - (long)i * q) * 4;
   const int src = a.idx ? a.idx[i] : i;
@@ -1166,13 +1157,28 @@ static hipError_t launch_step_rest(const StepFwdArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Its line: act() with the input side in a product of its own and here, memories in front of [256, 128], us: GRU of 256 at 4096 rows 74.9
-// and 70.1 with 48 inputs, 92.9 and 86.1 with 235, 102 and 100 with 400, at 1200 rows 55.1 and 49.9, 62.9 and 58.4, 63.7 and 63.7, with
-// 512 67.8 and 67.4; GRU of 512 at 1024 rows with 1000 117 and 106; LSTM of 256 at 4096 rows 86.4 and 81.1, 111 and 102, 123 and
-// 120, with 512 131 and 130; of 128 at 8192 rows with 48 90.8 and 83.4, with 256 110 and 102.  The gain is nearly gone at twice
-// the memory's width.
-bool step_forms_gi(const StepFwdNet& n, const StepFwdArgs& a) {
-  return n.x != nullptr && n.D <= 2 * n.H && step_split_fits(n, a);
+// Which steps take that kernel: those of act() (nothing kept for a backward pass, no flags) from about the size on where it is the
+// faster one for a memory by itself.  The fp32 step and this one, while it still split its weights itself and left the input side out, in rslx_memory_step and in act() with two such memories in front of
+// [64, 12], us: GRU of 256 18.3, 21.0 and 37.0, 35.8 at 1024 rows, 22.8, 21.7 and 44.0, 39.5 at 1055; GRU of 128 15.9, 17.9 and 31.6,
+// 31.3 at 2048, 18.6, 18.1 and 36.2, 33.5 at 2110; LSTM of 256 29.8, 29.6 and 58.1, 52.1 at 2048; LSTM of 128 24.9, 25.3 and 47.6, 47.0
+// at 4096, 31.6, 32.3 and 59.7, 57.0 at 5121, 36.8, 33.8 and 68.1, 65.1 at 6554; LSTM of 64 33.4, 34.3 and 73.8, 72.2 at 16 385.  A
+// memory's own sizes decide, so that a call for the values alone returns the bits of a full one; only rslx_memory_step, which has no
+// such counterpart, may draw its line later.
+bool step_split_sizes(int32_t cell, int32_t H, int32_t nb, bool alone) {
+  if (H % 64 != 0 || H > 8192 || nb < 1024) return false;
+  const int64_t size = (int64_t)nb * H;
+  return cell == CELL_LSTM ? size >= (H < 128 ? 1 << 21 : alone && H < 256 ? 3 << 18 : 1 << 19) : size > 1 << 18;
+}
+
+// Its line: act() with the input side in a product of its own and weights split by every workgroup, and here, memories in front of
+// [256, 128], us: GRU of 256 at 4096 rows 73.2 and 65.5 with 48 inputs, 91.8 and 79.1 with 235, 108 and 95.6 with 512, at 1200 rows
+// 54.7 and 47.9, 62.6 and 55.2, 67.9 and 62.7; GRU of 512 at 1024 rows with 1000 116 and 102; LSTM of 256 at 4096 rows 85.0 and
+// 74.5, 109 and 89.9, 130 and 112; of 128 at 8192 rows with 48 88.2 and 78.1, with 256 109 and 93.1.
+bool step_takes_input(int32_t H, int32_t D) { return D <= 2 * H; }
+
+size_t step_pack_bytes(int32_t cell, int32_t H, int32_t D) {
+  const size_t units = H / ST_UNITS;
+  return cell == CELL_LSTM ? units * step_chunks<CELL_LSTM>(H, D) * StepSplit<CELL_LSTM>::CHUNK : units * step_chunks<CELL_GRU>(H, D) * StepSplit<CELL_GRU>::CHUNK;
 }
 
 hipError_t launch_step_fwd(const StepFwdArgs& a, hipStream_t stream) {
@@ -1183,7 +1189,7 @@ hipError_t launch_step_fwd(const StepFwdArgs& a, hipStream_t stream) {
   int split = 0;
   double flops = 0.0;
   for (int k = 0; k < b.n_nets; ++k) {
-    split |= step_split_fits(b.net[k], b) << k;
+    split |= (b.net[k].pack != nullptr) << k;
     flops += 2.0 * b.nb * (b.net[k].H + (b.net[k].x ? b.net[k].D : 0)) * (lstm ? 4.0 : 3.0) * b.net[k].H;
   }
   if (split == 0) return launch_step_rest(a, stream);
@@ -1232,8 +1238,9 @@ hipError_t launch_seq_bwd(const SeqArgs& a, hipStream_t stream) {
 hipError_t launch_row_gather(const RowGatherArgs& a, hipStream_t stream) {
   long work = 0;
   for (int k = 0; k < a.n_jobs; ++k) { const long w = (long)a.nb * (a.job[k].H >> 2); work = w > work ? w : work; }
+  for (int k = 0; k < a.n_packs; ++k) work = std::max(work, (long)(step_pack_bytes(a.pack[k].cell, a.pack[k].H, a.pack[k].D) / (3 * 16)));
   if (work == 0) return hipSuccess;
-  hipLaunchKernelGGL(row_gather_kernel, dim3((unsigned)((work + 255) / 256), a.n_jobs), dim3(256), 0, stream, a);
+  hipLaunchKernelGGL(row_gather_kernel, dim3((unsigned)((work + 255) / 256), a.n_jobs + a.n_packs), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -25,3 +25,15 @@ def test_update_workspace_serves_fewer_rows(hidden, line):
 def test_regression_workspace_serves_fewer_rows(hidden, line):
     need = [rx.rslx_bc_update_workspace_bytes(_mlp((48,) + hidden + (12,)), None, n, rx.BcCfg(minibatches=1)) for n in (16, line - 1, line, line + 1, line + 64, 2 * line)]
     assert need == sorted(need)
+
+
+@pytest.mark.parametrize("cell,H,D", [(0, 128, 48), (0, 256, 513), (1, 64, 20), (1, 256, 235)])
+def test_recurrent_inference_query_grows_with_the_environments(cell, H, D):
+    """Also over the line from which the split weights of the memories are held."""
+    G = 4 if cell == rx.CELL_LSTM else 3
+    mem = rx.Memory(cell, D, H, torch.zeros(G * H * (D + H + 2)))
+    net = rx.Mlp((H, 64, 1), torch.zeros(H * 64 + 64 + 64 + 1))
+    rows = [1, 64, 1000, 1023, 1024, 1025, 2048, 2049, 4096, 8192, 16384, 32767, 32768, 65536]
+    for query in (lambda n: rx.rslx_memory_step_workspace_bytes(mem, n), lambda n: rx.rslx_act_recurrent_workspace_bytes(mem, net, mem, net, n)):
+        sizes = [query(n) for n in rows]
+        assert sizes == sorted(sizes)
