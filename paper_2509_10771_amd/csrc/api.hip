@@ -162,11 +162,22 @@ size_t rslx_act_workspace_bytes(const rslx_mlp* actor, const rslx_mlp* critic, i
 
 namespace rslx {
 namespace host {
+void plan_act_pack(const rslx_mlp* actor, const rslx_mlp* critic, int32_t N, void* room, FusedPackBatch& b) {
+  FusedForwardArgs fa;
+  memset(&fa, 0, sizeof fa);
+  fa.n_rows = N;
+  fa.max_dim = actor ? std::max(max_dim_of(*actor), max_dim_of(*critic)) : max_dim_of(*critic);
+  if (actor) fa.net[fa.n_nets++] = fused_net(*actor, nullptr, 0, nullptr, nullptr, true);
+  fa.net[fa.n_nets++] = fused_net(*critic, nullptr, 0, nullptr, nullptr, false);
+  b.count = 0;
+  if (fused_forward_pays(fa)) plan_fused_pack(fa, room, b);
+}
+
 // Shared body of rslx_act and rslx_act_dc: with `counters` the noise position comes from device memory.
 int32_t act_impl(const rslx_mlp* actor, const rslx_mlp* critic, const float* obs_actor, const float* obs_critic,
                  int32_t N, uint64_t seed, uint64_t step, rslx_dev_counters* counters, const float* eps_or_null,
                  float* actions, float* logp, float* values, float* mu, float* sigma, uint32_t flags, void* ws,
-                 size_t ws_bytes, void* stream, int32_t ld_actor, int32_t ld_critic) {
+                 size_t ws_bytes, void* stream, int32_t ld_actor, int32_t ld_critic, void* split) {
   const bool values_only = (flags & RSLX_ACT_VALUES_ONLY) != 0;
   const int64_t* step_dev = counters ? &counters->act_step : nullptr;
   const uint64_t noise_pre = mix64_host(seed ^ 0xAC7ull);
@@ -201,6 +212,8 @@ int32_t act_impl(const rslx_mlp* actor, const rslx_mlp* critic, const float* obs
     fa.step_dev = step_dev; fa.noise_pre = noise_pre;
     fa.actions = actions; fa.logp = logp; fa.sigma = sigma;
     if (fused_forward_pays(fa)) {
+      FusedPackBatch done;
+      if (split) plan_fused_pack(fa, split, done);
       RSLX_HIP(launch_fused_forward(fa, s));
       if (counters && !values_only) RSLX_HIP(advance_counters(counters, 1, 0, 0, 0, s));
       return RSLX_OK;

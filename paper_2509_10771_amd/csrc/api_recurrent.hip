@@ -63,8 +63,8 @@ struct StepBufs {     // one memory's buffers of a single act step
 int32_t step_input(const rslx_memory& m) { return step_takes_input(m.hidden, m.in_dim) ? m.in_dim : 0; }
 
 // The state that a step starts from, and its weights' split in the same launch.
-void gather_step(RowGatherArgs& rg, const rslx_memory& m, const StepBufs& b, const float* state, float* first_out) {
-  rg.job[rg.n_jobs++] = RowGatherJob{state, b.hin, first_out, state_width(m)};
+void gather_step(RowSplitArgs& rg, const rslx_memory& m, const StepBufs& b, const float* state, float* first_out) {
+  rg.rows.job[rg.rows.n_jobs++] = RowGatherJob{state, b.hin, first_out, state_width(m)};
   if (b.pack) rg.pack[rg.n_packs++] = StepPackJob{m.params + gru_off_whh(m), m.params, b.pack, m.hidden, step_input(m), m.cell};
 }
 
@@ -81,6 +81,20 @@ size_t act_recurrent_carve(Carver& c, const rslx_memory* ga, const rslx_memory* 
     if (b[k]) *b[k] = t;
   }
   return c.off;
+}
+
+// Which calls split the weights of the networks behind the memories in the launch that copies the states, for all workgroups of the
+// layer-fused launch; returns the bytes, 0 = not.  Without and with it, two GRUs of 256 in front of [512, 256, 128], us a call: 84.4
+// and 81 at 4096 rows, 68.3 and 66.4 at 1000, 63.7 and 62.2 at 512, 62.9 and 62.7 at 256, 59.2 and 59.8 at 64.  Where the launch
+// splits nothing for the memories it grows by its other kernel and threads: LSTMs of 128 in front of [256, 128] (67 000 weights) 46.8 and
+// 47.7 at 1000 rows, of [400, 200, 100] (152 000) 66.4 and 63.9; with them, GRUs of 128 at 4400 rows in front of [256, 128], 63.2 and 61.3.
+// act() has no launch ahead of it to do that in: one for the split alone, us: [512, 256, 128] 35.3 and 34.6 at 4096 rows, 68.8 and
+// 66.0 at 8192, but 34.8 and 37.2 at 256, and [256, 128] 19.3 and 21.6 at 4096, 34.4 and 36.2 at 8192; it is left out.
+size_t split_ahead_bytes(const rslx_memory* ga, const rslx_mlp* a, const rslx_memory* gc, const rslx_mlp* c, int32_t N) {
+  if (N < 512) return 0;
+  const size_t na = a ? fused_pack_bytes(a->dims, a->n_layers) : 0, nc = fused_pack_bytes(c->dims, c->n_layers);
+  const bool memories = (ga && step_split_sizes(ga->cell, ga->hidden, N, false)) || step_split_sizes(gc->cell, gc->hidden, N, false);
+  return memories || std::max(na, nc) >= 6u << 17 ? na + nc : 0;
 }
 
 // hin -> new state (contractions fused with the gates; the input side in a product of its own where the step does not take it), for
@@ -129,6 +143,7 @@ size_t rslx_act_recurrent_workspace_bytes(const rslx_memory* gru_actor, const rs
   if (N <= 0 || !gru_critic || !critic) return 256;
   Carver c(nullptr);
   act_recurrent_carve(c, gru_actor, gru_critic, N, nullptr, nullptr);
+  c.take<char>(split_ahead_bytes(gru_actor, actor, gru_critic, critic, N));
   return (c.off + 255) / 256 * 256 + rslx_act_workspace_bytes(actor, critic, N);
 }
 
@@ -165,14 +180,17 @@ int32_t act_recurrent_impl(const rslx_memory* gru_actor, const rslx_mlp* actor, 
   Carver c(ws);
   StepBufs ba, bc;
   act_recurrent_carve(c, ga, gru_critic, N, &ba, &bc);
+  const size_t ahead = split_ahead_bytes(ga, a, gru_critic, critic, N);
+  void* room = ahead ? c.take<char>(ahead) : nullptr;
   const size_t used = (c.off + 255) / 256 * 256;
 
-  RowGatherArgs rg;
+  RowSplitArgs rg;
   memset(&rg, 0, sizeof rg);
-  rg.nb = N; rg.reset = reset_or_null;
+  rg.rows.nb = N; rg.rows.reset = reset_or_null;
   if (ga) gather_step(rg, *ga, ba, h_actor, values_only ? nullptr : h0_actor_out);
   gather_step(rg, *gru_critic, bc, h_critic, values_only ? nullptr : h0_critic_out);
-  RSLX_HIP(launch_row_gather(rg, s));
+  if (room) plan_act_pack(a, critic, N, room, rg.layers);
+  RSLX_HIP(launch_row_split(rg, s));
 
   const float* h_in_actor_mlp = h_actor;
   const float* h_in_critic_mlp = values_only ? bc.hnew : h_critic;
@@ -191,7 +209,7 @@ int32_t act_recurrent_impl(const rslx_memory* gru_actor, const rslx_mlp* actor, 
   }
   return act_impl(a, critic, h_in_actor_mlp, h_in_critic_mlp, N, seed, step, counters, eps_or_null, actions, logp, values,
                   mu, sigma, flags, static_cast<char*>(ws) + used, ws_bytes - used, stream, ga ? state_width(*ga) : 0,
-                  state_width(*gru_critic));
+                  state_width(*gru_critic), room);
 }
 }  // namespace
 
@@ -700,11 +718,11 @@ int32_t rslx_memory_step(const rslx_memory* mem, const float* obs, int32_t N, fl
   Carver c(ws);
   StepBufs b;
   act_recurrent_carve(c, mem, nullptr, N, &b, nullptr, true);
-  RowGatherArgs rg;
+  RowSplitArgs rg;
   memset(&rg, 0, sizeof rg);
-  rg.nb = N; rg.reset = reset_or_null;
+  rg.rows.nb = N; rg.rows.reset = reset_or_null;
   gather_step(rg, *mem, b, state, s0_out);
-  RSLX_HIP(launch_row_gather(rg, s));
+  RSLX_HIP(launch_row_split(rg, s));
   const rslx_memory* g[1] = {mem};
   const float* o[1] = {obs};
   const StepBufs bb[1] = {b};

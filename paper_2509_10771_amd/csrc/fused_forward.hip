@@ -6,7 +6,7 @@
 // gemm.hip): 96 matrix-core cycles per 32 contraction indices of a 16 x 16 block, where fp32 instructions take 256.
 // Activations stay in LDS, split, 16 bytes holding one part of eight consecutive contraction indices of a row; weights
 // are not staged at all but streamed from L2 as fp32 and split in registers (each is used by one wavefront of a
-// workgroup only).  A layer is cut into tasks of 64 output columns; when a layer has fewer than 8 such groups the
+// workgroup only), or streamed as a launch ahead has split them.  A layer is cut into tasks of 64 output columns; when a layer has fewer than 8 such groups the
 // contraction range of a group is split over 2, 4 or 8 wavefronts, so all 8 stay busy down to the narrow output layer.
 // Lane (m, kq) of a task owns columns col0 + 4 m .. + 3 at contraction indices 8 kq .. + 7 of a step of 32: eight
 // 16-byte loads per step, of which the 16 lanes of a row read 256 contiguous bytes.  Partial sums meet in LDS; all 512
@@ -15,6 +15,7 @@
 // log-density) runs in the same launch, one lane per (row, action component).
 #include "kernels.h"
 #include "split_bf16.h"
+#include "fused_pack.h"
 #include <algorithm>
 #include <type_traits>
 
@@ -227,6 +228,49 @@ __device__ __forceinline__ void ff_contract(const FfWeights& wt, const FfTask& t
     for (int h = 0; h < 2; ++h) acc[cb][h] *= split_unscale(wt.m);     // batch rows m and 16 + m
 }
 
+// The same from weights that come split (fused_pack.h), the same bits: no vector instruction beside the matrix instructions but
+// addresses, and the step is bound by the weights' way from L2 (6 bytes a weight, 1.1 MB per workgroup of [48, 512, 256, 128, 12]):
+// two such networks at 4096 rows 31 us instead of 36.  p is the lane's unit of the task's first step, w0 holds that step.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void ff_load_packed(const u32x4* p, u32x4 (&w)[12]) {
+#pragma unroll
+  for (int i = 0; i < 12; ++i) w[i] = p[64 * i];
+}
+
+__device__ __forceinline__ void ff_contract_packed(const u32x4* p, const FfTask& task, const char* acts, int m, int kq, u32x4 (&w0)[12], f32x4 (&acc)[4][2]) {
+  u32x4 w1[12];
+  const char* bp = acts + ff_unit(kq, m);
+  const int last = task.s_end - 1;
+  auto step = [&](int s, u32x4 (&w)[12]) {
+    bf16x8 b[3][2];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        b[q][h] = *reinterpret_cast<const bf16x8*>(bp + q * FF_PART + s * (FF_STEP / 8 * FF_ROWS * 16) + h * 256);
+    constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+#pragma unroll
+      for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          acc[cb][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[3 * cb + PA[q]]), b[PB[q]][h], acc[cb][h], 0, 0, 0);
+    ff_load_packed(p + (long)min(s + 2 - task.s_begin, last - task.s_begin) * FP_STEP, w);
+  };
+  if (last > task.s_begin) ff_load_packed(p + FP_STEP, w1);
+  for (int s = task.s_begin;; s += 2) {
+    step(s, w0);
+    if (s + 1 > last) break;
+    step(s + 1, w1);
+    if (s + 2 > last) break;
+  }
+#pragma unroll
+  for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) acc[cb][h] *= split_unscale(m);
+}
+
 // Puts the sums of fp32 products (v_mfma_f32_16x16x4_f32, from the fp32 weights and the activations' values) in place of
 // the non-finite ones of a task (see gemm.hip): such inputs have no split.  The other rows keep their sums.
 __device__ __forceinline__ void ff_repeat_fp32(const float* W, int K, int N, const FfTask& task, const char* acts, int m, int kq,
@@ -278,6 +322,12 @@ __device__ __forceinline__ void ff_first_chunk(const float* __restrict__ W, int 
   else wt.load<false>(task.s_begin, w);
 }
 
+// The lane's unit of a task's first step; layer: the layer's first unit.
+__device__ __forceinline__ const u32x4* ff_task_units(const u32x4* layer, int K, const FfTask& task, int lane) {
+  return layer + (long)((task.col0 / FF_GROUP) * fused_pack_steps(K) + task.s_begin) * FP_STEP + lane;
+}
+
+template <bool PACK>
 __global__ __launch_bounds__(FF_THREADS) void fused_forward_kernel(const FusedForwardArgs args) {
   extern __shared__ __align__(16) char lds[];
   const FusedNet& net = args.net[blockIdx.y];
@@ -294,8 +344,14 @@ __global__ __launch_bounds__(FF_THREADS) void fused_forward_kernel(const FusedFo
   // The first weight chunk of the first layer and the head's per-component inputs do not depend on any
   // activation: they are requested before the input rows, so their latency passes under the staging.
   float wpre[FF_CHUNK];
+  u32x4 upre[12];
+  const u32x4* layer = reinterpret_cast<const u32x4*>(net.pack);
   FfTask task = ff_task(net, 0, wave);
-  ff_first_chunk(net.params, net.dims[0], net.dims[1], task, m, kq, wpre);
+  if constexpr (PACK) {
+    if (task.active) ff_load_packed(ff_task_units(layer, net.dims[0], task, lane), upre);
+  } else {
+    ff_first_chunk(net.params, net.dims[0], net.dims[1], task, m, kq, wpre);
+  }
   const int A = net.dims[net.n_layers];
   float head_ls = 0.f, head_eps = 0.f;
   if (net.head && tid < FF_ROWS * A) {
@@ -366,10 +422,14 @@ __global__ __launch_bounds__(FF_THREADS) void fused_forward_kernel(const FusedFo
       for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
         for (int h = 0; h < 2; ++h) acc[cb][h] = f32x4{0.f, 0.f, 0.f, 0.f};
-      FfWeights wt;
-      wt.setup(W, K, N, task.col0, m, kq);
-      if (wt.vec) ff_contract<true>(wt, task, acts, wpre, acc);
-      else ff_contract<false>(wt, task, acts, wpre, acc);
+      if constexpr (PACK) {
+        ff_contract_packed(ff_task_units(layer, K, task, lane), task, acts, m, kq, upre, acc);
+      } else {
+        FfWeights wt;
+        wt.setup(W, K, N, task.col0, m, kq);
+        if (wt.vec) ff_contract<true>(wt, task, acts, wpre, acc);
+        else ff_contract<false>(wt, task, acts, wpre, acc);
+      }
       float z = 0.f;                 // becomes NaN with any non-finite sum
 #pragma unroll
       for (int cb = 0; cb < 4; ++cb)
@@ -396,7 +456,12 @@ __global__ __launch_bounds__(FF_THREADS) void fused_forward_kernel(const FusedFo
       for (int c = 0; c < 16; ++c) bfin[c] = bias[min(task.col0 + 16 * kq + c, N - 1)];
     }
     // the next layer's first chunk is requested before this layer's sums are exchanged as well
-    if (!last) ff_first_chunk(bias + N, N, N2, next, m, kq, wpre);
+    if constexpr (PACK) {
+      layer += fused_pack_units(K, N);
+      if (!last && next.active) ff_load_packed(ff_task_units(layer, N, next, lane), upre);
+    } else {
+      if (!last) ff_first_chunk(bias + N, N, N2, next, m, kq, wpre);
+    }
     // accumulator register r of block cb: column col0 + 16 kq + 4 r + cb, batch rows m (half 0) and 16 + m
     if (shared && task.active) {
       float* part = sums + task.kpart * plane;
@@ -541,12 +606,23 @@ static double forward_flops(const FusedForwardArgs& a) {
   return flops;
 }
 
+size_t fused_pack_bytes(const int32_t* dims, int32_t n_layers) {
+  size_t units = 0;
+  if (n_layers < 1 || n_layers > 8) return 0;                // workspace queries come before any check
+  for (int l = 0; l < n_layers; ++l) {
+    if (std::min(dims[l], dims[l + 1]) < 1 || std::max(dims[l], dims[l + 1]) > FF_MAX_DIM) return 0;      // no layer-fused inference
+    units += fused_pack_units(dims[l], dims[l + 1]);
+  }
+  return units * 16;
+}
+
 static hipError_t launch_wide_forward(const FusedForwardArgs& a, hipStream_t stream) {
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_forward_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, FF_LDS);
-    if (e != hipSuccess) return e;
+    for (const void* k : {reinterpret_cast<const void*>(fused_forward_kernel<true>), reinterpret_cast<const void*>(fused_forward_kernel<false>)}) {
+      hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, FF_LDS);
+      if (e != hipSuccess) return e;
+    }
     attr_set = true;
   }
   TraceScope ts(stream, "fused_forward", forward_flops(a), 0.0);
@@ -562,7 +638,10 @@ static hipError_t launch_wide_forward(const FusedForwardArgs& a, hipStream_t str
       b.net[i].split_parts[l] = std::max(1, (steps + per - 1) / per);
     }
   dim3 grid((b.n_rows + FF_ROWS - 1) / FF_ROWS, b.n_nets);
-  hipLaunchKernelGGL(fused_forward_kernel, grid, dim3(FF_THREADS), FF_LDS, stream, b);
+  if (b.net[0].pack != nullptr && (b.n_nets < 2 || b.net[1].pack != nullptr))
+    hipLaunchKernelGGL(fused_forward_kernel<true>, grid, dim3(FF_THREADS), FF_LDS, stream, b);
+  else
+    hipLaunchKernelGGL(fused_forward_kernel<false>, grid, dim3(FF_THREADS), FF_LDS, stream, b);
   return hipGetLastError();
 }
 
@@ -572,6 +651,26 @@ static hipError_t launch_wide_forward(const FusedForwardArgs& a, hipStream_t str
 #include "small_forward.h"
 
 namespace rslx {
+
+void plan_fused_pack(FusedForwardArgs& a, void* ws, FusedPackBatch& b) {
+  b.count = 0;
+  uint4* at = static_cast<uint4*>(ws);
+  for (int i = 0; i < a.n_nets; ++i) {
+    FusedNet& n = a.net[i];
+    if (!small_forward_takes(n, a.n_rows)) {
+      n.pack = reinterpret_cast<const uint16_t*>(at);
+      const float* w = n.params;
+      uint4* dst = at;
+      for (int l = 0; l < n.n_layers; ++l) {
+        const int K = n.dims[l], N = n.dims[l + 1];
+        b.job[b.count++] = FusedPackJob{w, reinterpret_cast<uint16_t*>(dst), K, N};
+        w += (long)K * N + N;
+        dst += fused_pack_units(K, N);
+      }
+    }
+    at += fused_pack_bytes(n.dims, n.n_layers) / 16;
+  }
+}
 
 hipError_t launch_fused_forward(const FusedForwardArgs& a, hipStream_t stream) {
   if (a.n_rows <= 0) return hipSuccess;

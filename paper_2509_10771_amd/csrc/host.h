@@ -541,7 +541,9 @@ inline hipError_t advance_counters(rslx_dev_counters* c, int64_t act, int64_t ca
 int32_t act_impl(const rslx_mlp* actor, const rslx_mlp* critic, const float* obs_actor, const float* obs_critic,
                  int32_t N, uint64_t seed, uint64_t step, rslx_dev_counters* counters, const float* eps_or_null,
                  float* actions, float* logp, float* values, float* mu, float* sigma, uint32_t flags, void* ws,
-                 size_t ws_bytes, void* stream, int32_t ld_actor = 0, int32_t ld_critic = 0);
+                 size_t ws_bytes, void* stream, int32_t ld_actor = 0, int32_t ld_critic = 0, void* split = nullptr);
+// The split of its networks' weights into `room` (fused_pack_bytes of each), for a launch ahead of act_impl, which is then given `split` = room.
+void plan_act_pack(const rslx_mlp* actor, const rslx_mlp* critic, int32_t N, void* room, FusedPackBatch& b);
 
 }  // namespace host
 }  // namespace rslx

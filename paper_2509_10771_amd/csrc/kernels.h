@@ -100,6 +100,7 @@ struct FusedNet {
   // per-layer work split, filled in by launch_fused_forward: a layer's 64-column groups are shared by
   // 1 << split_shift wavefronts each, `split_steps` contraction steps apiece, of which `split_parts` have work
   int32_t split_shift[8], split_steps[8], split_parts[8];
+  const uint16_t* pack;     // all layers' split weights (fused_pack.h), or null: the workgroups split them
 };
 struct FusedForwardArgs {
   FusedNet net[2];
@@ -110,6 +111,12 @@ struct FusedForwardArgs {
   uint64_t noise_pre;
   float* actions; float* logp; float* sigma;
 };
+// The split of one layer's weights, and that of all layers of a call's networks (in the launch of RowSplitArgs).
+struct FusedPackJob { const float* src; uint16_t* dst; int32_t K, N; };
+struct FusedPackBatch { FusedPackJob job[16]; int32_t count; };
+size_t fused_pack_bytes(const int32_t* dims, int32_t n_layers);
+// Gives the networks of `a` that are to have split weights their place in ws (fused_pack_bytes of each network, one after another).
+void plan_fused_pack(FusedForwardArgs& a, void* ws, FusedPackBatch& b);
 bool fused_forward_supported(const FusedForwardArgs& a);
 hipError_t launch_fused_forward(const FusedForwardArgs& a, hipStream_t stream);
 
@@ -390,16 +397,25 @@ hipError_t launch_seq_bwd(const SeqArgs& a, hipStream_t stream);
 // dst[i, :] = src[idx ? idx[i] : i, :] * (reset && reset[i] ? 0 : 1) for up to two [*, H] matrices; a second
 // copy of the result goes to dst2 when it is not null.
 struct RowGatherJob { const float* src; float* dst; float* dst2; int32_t H; };
-// In the same launch, split weights for a step on split operands (pack of StepFwdNet); D = 0: of the hidden side only.
-struct StepPackJob { const float *w_hh, *w_ih; uint16_t* dst; int32_t H, D, cell; };
 struct RowGatherArgs {
   RowGatherJob job[2];
-  StepPackJob pack[2];
-  int32_t n_jobs, n_packs, nb;
+  int32_t n_jobs, nb;
   const int32_t* idx;
   const uint8_t* reset;
 };
 hipError_t launch_row_gather(const RowGatherArgs& a, hipStream_t stream);
+
+// In one launch with such copies, split weights for a step on split operands (pack of StepFwdNet; D = 0: of the hidden side only) and
+// for the networks behind the memories (FusedNet::pack).
+struct StepPackJob { const float *w_hh, *w_ih; uint16_t* dst; int32_t H, D, cell; };
+struct RowSplitArgs {
+  RowGatherArgs rows;
+  StepPackJob pack[2];
+  FusedPackBatch layers;
+  int32_t n_packs;
+  int32_t end[20];             // of the blocks of each layer, memory and copy, filled in by the launch
+};
+hipError_t launch_row_split(const RowSplitArgs& a, hipStream_t stream);
 
 // dst[r, 0 .. cols) = src[r * ld_src + 0 .. cols) for r < rows (cols % 4 == 0): the hidden part of packed states as a
 // dense matrix.
