@@ -806,7 +806,7 @@ __global__ __launch_bounds__(SQ_THREADS, 2) void seq_bwd_kernel(const SeqArgs a)
 // rows), so the gate stage works on the lane's own accumulators.  The weights come split, in the order in which LDS holds them, a
 // chunk of 64 (LSTM: 32) contraction indices at a time through registers; the launch that copies the states splits them.  Each
 // workgroup splitting them for itself, once per 64 rows, took two thirds of the loop's vector instructions: two GRUs of 256 at
-// 4096 rows with 48 inputs in front of [512, 256, 128] 91.1 us a call that way, 84.4 now; LSTMs with 235 in front of [256, 128]
+// 4096 rows with 48 inputs in front of [512, 256, 128] 91.1 us a call that way, 84.4 this way; LSTMs with 235 in front of [256, 128]
 // 102 and 90.  Rows are split in registers by the only wavefront that uses them.
 // The input side's contraction follows the hidden side's in the same loop, into sums of its own (which GRU's candidate needs, and
 // chains stay short): no product by itself, no [rows, G H] matrix written and read, 95.9 us a call with them.
@@ -1172,12 +1172,12 @@ static hipError_t launch_step_rest(const StepFwdArgs& a, hipStream_t stream) {
 }
 
 // Which steps take that kernel: those of act() (nothing kept for a backward pass, no flags) from about the size on where it is the
-// faster one for a memory by itself.  The fp32 step and this one, while it still split its weights itself and left the input side out, in rslx_memory_step and in act() with two such memories in front of
-// [64, 12], us: GRU of 256 18.3, 21.0 and 37.0, 35.8 at 1024 rows, 22.8, 21.7 and 44.0, 39.5 at 1055; GRU of 128 15.9, 17.9 and 31.6,
-// 31.3 at 2048, 18.6, 18.1 and 36.2, 33.5 at 2110; LSTM of 256 29.8, 29.6 and 58.1, 52.1 at 2048; LSTM of 128 24.9, 25.3 and 47.6, 47.0
-// at 4096, 31.6, 32.3 and 59.7, 57.0 at 5121, 36.8, 33.8 and 68.1, 65.1 at 6554; LSTM of 64 33.4, 34.3 and 73.8, 72.2 at 16 385.  A
-// memory's own sizes decide, so that a call for the values alone returns the bits of a full one; only rslx_memory_step, which has no
-// such counterpart, may draw its line later.
+// faster one for a memory by itself.  The fp32 step and this one, while it still split its weights itself and left the input side
+// out, in rslx_memory_step and in act() with two such memories in front of [64, 12], us: GRU of 256 18.3, 21.0 and 37.0, 35.8 at
+// 1024 rows, 22.8, 21.7 and 44.0, 39.5 at 1055; GRU of 128 15.9, 17.9 and 31.6, 31.3 at 2048, 18.6, 18.1 and 36.2, 33.5 at 2110; LSTM
+// of 256 29.8, 29.6 and 58.1, 52.1 at 2048; LSTM of 128 24.9, 25.3 and 47.6, 47.0 at 4096, 31.6, 32.3 and 59.7, 57.0 at 5121, 36.8,
+// 33.8 and 68.1, 65.1 at 6554; LSTM of 64 33.4, 34.3 and 73.8, 72.2 at 16 385.  A memory's own sizes decide, so that a call for the
+// values alone returns the bits of a full one; only rslx_memory_step, which has no such counterpart, may draw its line later.
 bool step_split_sizes(int32_t cell, int32_t H, int32_t nb, bool alone) {
   if (H % 64 != 0 || H > 8192 || nb < 1024) return false;
   const int64_t size = (int64_t)nb * H;
