@@ -57,15 +57,22 @@ struct StepBufs {     // one memory's buffers of a single act step
   float* gi = nullptr;      // [N, G H]
   float* hnew = nullptr;    // [N, S] values-only: the state is not written back
   uint16_t* pack = nullptr; // split weights, of memories whose step runs on split operands
+  bool apart = true;        // the inputs lie apart from the states that the call writes
 };
 
-// Inputs that a step on split operands contracts itself: all or none.
-int32_t step_input(const rslx_memory& m) { return step_takes_input(m.hidden, m.in_dim) ? m.in_dim : 0; }
+bool lie_apart(const float* a, size_t na, const float* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a == nullptr || b == nullptr || x + na * sizeof(float) <= y || y + nb * sizeof(float) <= x;
+}
+
+// Inputs that a step on split operands contracts itself: all or none.  Inputs that overlap a state are read by a product of their own
+// before any state is written.
+int32_t step_input(const rslx_memory& m, bool apart = true) { return apart && step_takes_input(m.hidden, m.in_dim) ? m.in_dim : 0; }
 
 // The state that a step starts from, and its weights' split in the same launch.
 void gather_step(RowSplitArgs& rg, const rslx_memory& m, const StepBufs& b, const float* state, float* first_out) {
   rg.rows.job[rg.rows.n_jobs++] = RowGatherJob{state, b.hin, first_out, state_width(m)};
-  if (b.pack) rg.pack[rg.n_packs++] = StepPackJob{m.params + gru_off_whh(m), m.params, b.pack, m.hidden, step_input(m), m.cell};
+  if (b.pack) rg.pack[rg.n_packs++] = StepPackJob{m.params + gru_off_whh(m), m.params, b.pack, m.hidden, step_input(m, b.apart), m.cell};
 }
 
 size_t act_recurrent_carve(Carver& c, const rslx_memory* ga, const rslx_memory* gc, int32_t N, StepBufs* ba, StepBufs* bc, bool alone = false) {
@@ -111,7 +118,7 @@ int32_t gru_step(const rslx_memory* const* g, const float* const* obs, const Ste
     // the new packed state goes to h_out[k] ([N, S]): h in its first H columns, an LSTM's c behind it
     sa.net[k] = StepFwdNet{b[k].gi, b[k].hin, h_out[k], m.cell == RSLX_CELL_LSTM ? h_out[k] + m.hidden : nullptr, nullptr,
                            m.params + gru_off_whh(m), m.params + gru_off_bhh(m), nullptr, m.hidden, state_width(m),
-                           b[k].pack, b[k].pack && step_input(m) > 0 ? obs[k] : nullptr, m.params, m.params + gru_off_bih(m), m.in_dim};
+                           b[k].pack, b[k].pack && step_input(m, b[k].apart) > 0 ? obs[k] : nullptr, m.params, m.params + gru_off_bih(m), m.in_dim};
     if (sa.net[k].x) continue;
     bi.p[bi.count++] = gate_problem(plain_view(obs[k], m.in_dim), m.in_dim, m.params, m.params + gru_off_bih(m), b[k].gi, N, gate_width(m));
   }
@@ -180,6 +187,14 @@ int32_t act_recurrent_impl(const rslx_memory* gru_actor, const rslx_mlp* actor, 
   Carver c(ws);
   StepBufs ba, bc;
   act_recurrent_carve(c, ga, gru_critic, N, &ba, &bc);
+  for (int k = 0; k < 2; ++k) {
+    const rslx_memory* m = k ? gru_critic : ga;
+    if (!m) continue;
+    const float* x = k ? obs_critic : obs_actor;
+    const size_t n = (size_t)N * m->in_dim;
+    (k ? bc : ba).apart = lie_apart(x, n, h_critic, (size_t)N * state_width(*gru_critic)) &&
+                          (!ga || lie_apart(x, n, h_actor, (size_t)N * state_width(*ga)));
+  }
   const size_t ahead = split_ahead_bytes(ga, a, gru_critic, critic, N);
   void* room = ahead ? c.take<char>(ahead) : nullptr;
   const size_t used = (c.off + 255) / 256 * 256;
@@ -718,6 +733,7 @@ int32_t rslx_memory_step(const rslx_memory* mem, const float* obs, int32_t N, fl
   Carver c(ws);
   StepBufs b;
   act_recurrent_carve(c, mem, nullptr, N, &b, nullptr, true);
+  b.apart = lie_apart(obs, (size_t)N * mem->in_dim, state, (size_t)N * state_width(*mem));
   RowSplitArgs rg;
   memset(&rg, 0, sizeof rg);
   rg.rows.nb = N; rg.rows.reset = reset_or_null;

@@ -91,3 +91,28 @@ def test_infinite_inputs_and_weights(rx, cell, H, N, D):
     got, _ = _step(rx, m, x, state)
     ref = _reference(m, x, state)
     assert bool(torch.isfinite(ref).all()) and float((got.double() - ref).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("cell,H,N", [("gru", 64, 4099), ("lstm", 256, 2048)])
+def test_inputs_that_are_the_states(rx, cell, H, N):
+    """The states as inputs, the other memory's and the own: read before any of them is written."""
+    gen = torch.Generator().manual_seed(9)
+    S = 2 * H if cell == "lstm" else H
+    own, other = (_memory(rx, cell, S, H, gen) for _ in range(2))
+    state, second = ((0.5 * torch.randn(N, S, generator=gen)).cuda() for _ in range(2))
+    want, _ = _step(rx, own, state.clone(), state)
+    got = state.clone()
+    ws = rx.workspace(rx.rslx_memory_step_workspace_bytes(own, N))
+    rx.rslx_trace_begin(16)
+    rx.rslx_memory_step(own, got, N, got, None, None, None, ws)
+    torch.cuda.synchronize()
+    assert len(rx.rslx_trace_end()) == 2                   # a product for the inputs, and the step
+    assert float((got - want).abs().max()) <= 1e-5
+    net = lambda A, ls: rx.Mlp((H, 8, A), torch.randn(H * 8 + 8 + 8 * A + A + ls, generator=gen).cuda(), has_log_std=ls > 0)  # noqa: E731
+    actor, critic, e = net(2, 2), net(1, 0), lambda *s: torch.empty(*s, device="cuda")  # noqa: E731
+    a, c = state.clone(), second.clone()
+    ws = rx.workspace(rx.rslx_act_recurrent_workspace_bytes(own, actor, other, critic, N))
+    rx.rslx_act_recurrent(own, actor, other, critic, c, a, N, a, c, None, None, None, 1, 1, None, e(N, 2), e(N), e(N), e(N, 2), e(N, 2), 0, ws)
+    torch.cuda.synchronize()
+    assert float((a.double() - _reference(own, second, state)).abs().max()) <= 1e-5
+    assert float((c.double() - _reference(other, state, second)).abs().max()) <= 1e-5
