@@ -150,7 +150,8 @@ int32_t rslx_device_check(void);
 
 /* While a trace is open, every kernel launch of the library is bracketed by a pair of HIP events on
  * its stream and tagged with its algorithmic work.  rslx_trace_begin clears any earlier trace and
- * keeps at most max_records launches.  rslx_trace_end stops recording, WAITS on the host for the
+ * keeps at most max_records launches.  A launch that runs two networks in different forms side by side leaves a record for
+ * each of them, both with the launch's time.  rslx_trace_end stops recording, WAITS on the host for the
  * recorded events, and copies up to `cap` records (launch order) to `out` (host); *n_out receives the
  * number recorded.  Calling it with out == NULL only reports the count and keeps the records for a
  * second call.  Launches beyond max_records are counted, not recorded: rslx_trace_end then still

@@ -327,11 +327,10 @@ __device__ __forceinline__ const u32x4* ff_task_units(const u32x4* layer, int K,
   return layer + (long)((task.col0 / FF_GROUP) * fused_pack_steps(K) + task.s_begin) * FP_STEP + lane;
 }
 
+// Rows 32 block .. of a network; lds: FF_LDS bytes.
 template <bool PACK>
-__global__ __launch_bounds__(FF_THREADS) void fused_forward_kernel(const FusedForwardArgs args) {
-  extern __shared__ __align__(16) char lds[];
-  const FusedNet& net = args.net[blockIdx.y];
-  const int row0 = blockIdx.x * FF_ROWS;
+__device__ __forceinline__ void wide_forward(const FusedForwardArgs& args, const FusedNet& net, int block, char* lds) {
+  const int row0 = block * FF_ROWS;
   if (row0 >= args.n_rows) return;
   const int tid = threadIdx.x, lane = tid & 63;
   // the wavefront index decides which columns and contraction range a wavefront works on: held in a scalar
@@ -594,6 +593,12 @@ __global__ __launch_bounds__(FF_THREADS) void fused_forward_kernel(const FusedFo
   }
 }
 
+template <bool PACK>
+__global__ __launch_bounds__(FF_THREADS) void fused_forward_kernel(const FusedForwardArgs args) {
+  extern __shared__ __align__(16) char lds[];
+  wide_forward<PACK>(args, args.net[blockIdx.y], blockIdx.x, lds);
+}
+
 bool fused_forward_supported(const FusedForwardArgs& a) {
   if (a.max_dim > FF_MAX_DIM || a.n_nets < 1 || a.n_nets > 2) return false;
   return true;
@@ -616,6 +621,19 @@ size_t fused_pack_bytes(const int32_t* dims, int32_t n_layers) {
   return units * 16;
 }
 
+// The work split of every layer among the wavefronts of wide_forward (FusedNet::split_*).
+static void plan_wide(FusedNet& n) {
+  for (int l = 0; l < n.n_layers; ++l) {
+    const int steps = (n.dims[l] + FF_STEP - 1) / FF_STEP;
+    const int groups = ff_groups(n.dims[l + 1]);
+    const int shift = groups <= 1 ? 3 : groups <= 2 ? 2 : groups <= 4 ? 1 : 0;
+    const int per = (steps + (1 << shift) - 1) >> shift;
+    n.split_shift[l] = shift;
+    n.split_steps[l] = per;
+    n.split_parts[l] = std::max(1, (steps + per - 1) / per);
+  }
+}
+
 static hipError_t launch_wide_forward(const FusedForwardArgs& a, hipStream_t stream) {
   static bool attr_set = false;
   if (!attr_set) {
@@ -627,16 +645,7 @@ static hipError_t launch_wide_forward(const FusedForwardArgs& a, hipStream_t str
   }
   TraceScope ts(stream, "fused_forward", forward_flops(a), 0.0);
   FusedForwardArgs b = a;
-  for (int i = 0; i < b.n_nets; ++i)
-    for (int l = 0; l < b.net[i].n_layers; ++l) {
-      const int g = ff_groups(b.net[i].dims[l + 1]);
-      const int shift = g > FF_WAVES / 2 ? 0 : g > FF_WAVES / 4 ? 1 : g > FF_WAVES / 8 ? 2 : 3;
-      const int steps = (b.net[i].dims[l] + FF_STEP - 1) / FF_STEP;
-      const int per = (steps + (1 << shift) - 1) >> shift;
-      b.net[i].split_shift[l] = shift;
-      b.net[i].split_steps[l] = per;
-      b.net[i].split_parts[l] = std::max(1, (steps + per - 1) / per);
-    }
+  for (int i = 0; i < b.n_nets; ++i) plan_wide(b.net[i]);
   dim3 grid((b.n_rows + FF_ROWS - 1) / FF_ROWS, b.n_nets);
   if (b.net[0].pack != nullptr && (b.n_nets < 2 || b.net[1].pack != nullptr))
     hipLaunchKernelGGL(fused_forward_kernel<true>, grid, dim3(FF_THREADS), FF_LDS, stream, b);
@@ -672,18 +681,52 @@ void plan_fused_pack(FusedForwardArgs& a, void* ws, FusedPackBatch& b) {
   }
 }
 
+// Two networks of which the second takes the kernel of small_forward.h, side by side in one launch (blockIdx.y): each in the form that
+// its own sizes call for, with the bits that it has by itself.  The launch takes as long as the wider network, whose workgroups are
+// dispatched first; two launches take the sum.  act(), both networks through the wider kernel, two launches and this, us at 1024 rows:
+// [48, 128, 128] beside [48, 256, 128] 16.4, 24.6 and 16.2, [48, 512, 256, 128] beside [48, 128, 128] 34.6, 41.2 and 34.0; two narrow
+// networks of different depths (small_uneven_kernel), [48, 64] beside [48, 64, 32], 11.7, 11.1 and 7.5.
+template <bool PACK>
+__global__ __launch_bounds__(FF_THREADS) void uneven_forward_kernel(const FusedForwardArgs args) {
+  extern __shared__ __align__(16) char lds[];
+  if (blockIdx.y == 0) wide_forward<PACK>(args, args.net[0], blockIdx.x, lds);
+  else small_forward_any(args, args.net[1], blockIdx.x, lds);
+}
+
+template <bool PACK>
+static hipError_t launch_uneven_forward(const FusedForwardArgs& a, hipStream_t stream) {
+  static_assert(FF_THREADS == SS_THREADS && SS_ROWS <= FF_ROWS && SF_MAX_LDS <= FF_LDS, "one launch");
+  static bool attr_set = false;
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(uneven_forward_kernel<PACK>), hipFuncAttributeMaxDynamicSharedMemorySize, FF_LDS);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(uneven_forward_kernel<PACK>, dim3((a.n_rows + SS_ROWS - 1) / SS_ROWS, 2), dim3(FF_THREADS), FF_LDS, stream, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_fused_forward(const FusedForwardArgs& a, hipStream_t stream) {
   if (a.n_rows <= 0) return hipSuccess;
   const bool small = small_forward_takes(a.net[0], a.n_rows);
   if (a.n_nets == 2 && (small != small_forward_takes(a.net[1], a.n_rows) || (small && a.net[0].n_layers != a.net[1].n_layers))) {
-    for (int i = 0; i < 2; ++i) {              // networks that take different kernels
-      FusedForwardArgs b = a;
-      b.net[0] = a.net[i];
-      b.n_nets = 1;
-      hipError_t e = launch_fused_forward(b, stream);
-      if (e != hipSuccess) return e;
+    FusedForwardArgs b = a;
+    bool is_small[2];
+    double flops[2];
+    for (int i = 0; i < 2; ++i) {
+      is_small[i] = small_forward_takes(a.net[i], a.n_rows);
+      FusedForwardArgs one = a;
+      one.net[0] = a.net[i];
+      one.n_nets = 1;
+      flops[i] = forward_flops(one);
     }
-    return hipSuccess;
+    // a record for each network, both over the launch
+    TraceScope t0(stream, is_small[0] ? "small_forward" : "fused_forward", flops[0], 0.0);
+    TraceScope t1(stream, is_small[1] ? "small_forward" : "fused_forward", flops[1], 0.0);
+    if (is_small[0] && is_small[1]) return launch_small_uneven(a, stream);
+    if (is_small[0]) std::swap(b.net[0], b.net[1]);
+    plan_wide(b.net[0]);
+    return b.net[0].pack != nullptr ? launch_uneven_forward<true>(b, stream) : launch_uneven_forward<false>(b, stream);
   }
   if (!small) return launch_wide_forward(a, stream);
   TraceScope ts(stream, "small_forward", forward_flops(a), 0.0);

@@ -42,14 +42,24 @@ __device__ __forceinline__ void sf_split(const float (&w)[STEPS][8], int K, SsWe
   }
 }
 
-// IN: contraction steps of 32 of the first layer, L: layers.
+// LDS: the activations of two layers, then outputs, noise and sigma of the head.  IN: contraction steps of 32 of the first layer.
+template <int IN>
+struct SfLds {
+  static constexpr int COLS = 32 * (IN > SF_STEPS ? IN : SF_STEPS), C = 3 * SS_PLANE * COLS;
+  static constexpr int TOTAL = 2 * C + 4 * (2 * SF_OUT * SS_ROWS + 2 * SF_OUT);
+};
+constexpr int SF_MAX_LDS = SfLds<SF_IN / 32>::TOTAL;
+
+// Rows 16 block .. of a network of L layers; lds: SfLds<IN>::TOTAL bytes.
 template <int IN, int L>
-__global__ __launch_bounds__(SS_THREADS, 2) void small_forward_kernel(const FusedForwardArgs args) {
-  constexpr int COLS = 32 * (IN > SF_STEPS ? IN : SF_STEPS);
-  __shared__ __align__(16) char C[2][3 * SS_PLANE * COLS];
-  __shared__ float out[SF_OUT * SS_ROWS], noise[SF_OUT * SS_ROWS], sig[2 * SF_OUT];
-  const FusedNet& net = args.net[blockIdx.y];
-  const int row0 = (int)blockIdx.x * SS_ROWS;
+__device__ __forceinline__ void small_forward(const FusedForwardArgs& args, const FusedNet& net, int block, char* lds) {
+  constexpr int COLS = SfLds<IN>::COLS;
+  char* const C[2] = {lds, lds + SfLds<IN>::C};
+  float* const out = reinterpret_cast<float*>(lds + 2 * SfLds<IN>::C);
+  float* const noise = out + SF_OUT * SS_ROWS;
+  float* const sig = noise + SF_OUT * SS_ROWS;
+  const int row0 = block * SS_ROWS;
+  if (row0 >= args.n_rows) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = lane & 15, kq = lane >> 4;
@@ -187,6 +197,31 @@ __global__ __launch_bounds__(SS_THREADS, 2) void small_forward_kernel(const Fuse
   }
 }
 
+template <int IN, int L>
+__global__ __launch_bounds__(SS_THREADS, 2) void small_forward_kernel(const FusedForwardArgs args) {
+  __shared__ __align__(16) char lds[SfLds<IN>::TOTAL];
+  small_forward<IN, L>(args, args.net[blockIdx.y], blockIdx.x, lds);
+}
+
+// The same for a network of any sizes that small_forward_takes; lds: SF_MAX_LDS bytes.
+template <int IN>
+__device__ __forceinline__ void small_forward_depth(const FusedForwardArgs& args, const FusedNet& net, int block, char* lds) {
+  if (net.n_layers == 2) small_forward<IN, 2>(args, net, block, lds);
+  else if (net.n_layers == 3) small_forward<IN, 3>(args, net, block, lds);
+  else small_forward<IN, 4>(args, net, block, lds);
+}
+__device__ __forceinline__ void small_forward_any(const FusedForwardArgs& args, const FusedNet& net, int block, char* lds) {
+  if (net.dims[0] <= 64) small_forward_depth<2>(args, net, block, lds);
+  else if (net.dims[0] <= 128) small_forward_depth<4>(args, net, block, lds);
+  else small_forward_depth<8>(args, net, block, lds);
+}
+
+// Two networks of different depths.
+__global__ __launch_bounds__(SS_THREADS, 2) void small_uneven_kernel(const FusedForwardArgs args) {
+  __shared__ __align__(16) char lds[SF_MAX_LDS];
+  small_forward_any(args, args.net[blockIdx.y], blockIdx.x, lds);
+}
+
 template <int IN>
 void launch_small_in(const FusedForwardArgs& a, hipStream_t stream) {
   const dim3 grid((a.n_rows + SS_ROWS - 1) / SS_ROWS, a.n_nets), block(SS_THREADS);
@@ -211,6 +246,11 @@ hipError_t launch_small_forward(const FusedForwardArgs& a, hipStream_t stream) {
   if (widest <= 64) launch_small_in<2>(a, stream);
   else if (widest <= 128) launch_small_in<4>(a, stream);
   else launch_small_in<8>(a, stream);
+  return hipGetLastError();
+}
+
+hipError_t launch_small_uneven(const FusedForwardArgs& a, hipStream_t stream) {
+  hipLaunchKernelGGL(small_uneven_kernel, dim3((a.n_rows + SS_ROWS - 1) / SS_ROWS, 2), dim3(SS_THREADS), 0, stream, a);
   return hipGetLastError();
 }
 

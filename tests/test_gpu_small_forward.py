@@ -1,5 +1,7 @@
 """Inference of narrow networks, 16 rows per workgroup: against float64 at rows and widths around its tiles, the line to the wider kernel,
-networks of one call that take different kernels, and values-only calls bit for bit."""
+networks of one call that differ and share a launch, and values-only calls bit for bit."""
+import ctypes
+
 import pytest
 import torch
 
@@ -89,6 +91,50 @@ def test_which_kernel_a_network_takes(rx, N, actor_hidden, critic_hidden, want):
     alone, ws = torch.empty(N, device="cuda"), rx.workspace(rx.rslx_act_workspace_bytes(None, critic, N))
     rx.rslx_act(None, critic, None, x, N, 0, 0, None, None, None, alone, None, None, rx.ACT_VALUES_ONLY, ws)
     assert torch.equal(alone, out["values"])
+
+
+def _launches(rx, call):
+    """Kernel nodes of a captured call (which has run once before, so that nothing is set up inside the capture)."""
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    n = ctypes.c_size_t()
+    assert rx.lib.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("N", [1, 40, 2048])
+@pytest.mark.parametrize("Da,actor_hidden,Dc,critic_hidden", [(40, (132, 64), 40, (128, 64)), (40, (64,), 40, (132, 64)), (48, (128, 128), 300, (128, 128)), (40, (64,), 40, (64, 32)),
+                                                              (130, (20, 128, 7), 33, (128,)), (7, (5, 6, 7), 200, (9,) * 4)])
+def test_networks_that_differ_run_side_by_side(rx, N, Da, actor_hidden, Dc, critic_hidden):
+    gen = torch.Generator().manual_seed(N + Dc)
+    actor, critic = _net(rx, (Da,) + actor_hidden + (5,), gen, True), _net(rx, (Dc,) + critic_hidden + (1,), gen)
+    x, y = torch.randn(N, Da, generator=gen).cuda(), torch.randn(N, Dc, generator=gen).cuda()
+    e = lambda *s: torch.empty(*s, device="cuda")  # noqa: E731
+    out = dict(actions=e(N, 5), logp=e(N), values=e(N), mu=e(N, 5), sigma=e(N, 5))
+    ws = rx.workspace(rx.rslx_act_workspace_bytes(actor, critic, N))
+    assert _launches(rx, lambda: rx.rslx_act(actor, critic, x, y, N, 7, 3, None, out["actions"], out["logp"], out["values"], out["mu"], out["sigma"], 0, ws)) == 1
+    mu, v = _forward(actor, x.double()), _forward(critic, y.double())[:, 0]
+    assert float((out["mu"].double() - mu).abs().max()) <= 1e-5 * float(mu.abs().max() + 1) and float((out["values"].double() - v).abs().max()) <= 1e-5 * float(v.abs().max() + 1)
+    eps = torch.from_numpy(orng.act_noise(7, 3, N, 5)).cuda()
+    assert float((out["actions"].double() - (out["mu"].double() + torch.exp(actor.params[-5:].double()) * eps)).abs().max()) <= 1e-5
+    alone = e(N)
+    rx.rslx_act(None, critic, None, y, N, 0, 0, None, None, None, alone, None, None, rx.ACT_VALUES_ONLY, ws)
+    assert torch.equal(alone, out["values"])
+
+
+def test_student_beside_a_wider_teacher(rx):
+    gen, N, A = torch.Generator().manual_seed(4), 100, 6
+    student, teacher = _net(rx, (30, 64, A), gen), _net(rx, (50, 512, 256, 128, A), gen)
+    x, y = torch.randn(N, 30, generator=gen).cuda(), torch.randn(N, 50, generator=gen).cuda()
+    s, t = torch.empty(N, A, device="cuda"), torch.empty(N, A, device="cuda")
+    ws = rx.workspace(rx.rslx_bc_collect_workspace_bytes(student, teacher, N))
+    assert _launches(rx, lambda: rx.rslx_bc_collect(student, teacher, x, y, N, s, t, ws)) == 1
+    for net, inp, got in ((student, x, s), (teacher, y, t)):
+        ref = _forward(net, inp.double())
+        assert float((got.double() - ref).abs().max()) <= 1e-5 * float(ref.abs().max() + 1)
 
 
 def test_rows_without_a_split_leave_the_others_alone(rx):
