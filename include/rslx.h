@@ -11,7 +11,11 @@
  *  - "device" pointers are HIP device memory owned by the caller.  The library never
  *    allocates, frees or keeps them.  Scratch memory comes from the caller's workspace
  *    (`ws`, `ws_bytes`), sized by the matching *_workspace_bytes() query; a workspace that is
- *    too small gives RSLX_ERR_WORKSPACE.  Device pointers must be 16-byte aligned.
+ *    too small gives RSLX_ERR_WORKSPACE.  Where a call has a faster form that needs more memory
+ *    (rslx_ppo_update and rslx_bc_update of small networks, rslx_act_recurrent, rslx_memory_step;
+ *    and their _dc forms), the query asks for the larger size and a workspace that holds the
+ *    general form is taken too: the call then runs in that form, whose results differ in their
+ *    last bits.  Device pointers must be 16-byte aligned.
  *  - "host" pointers are ordinary host memory, read (or written) before the call returns.
  *  - All matrices are dense row-major fp32 unless said otherwise.
  *  - All work is enqueued on `stream` (a hipStream_t passed as void*; NULL = default stream).

@@ -373,8 +373,9 @@ struct PpoPlan {
   size_t bytes = 0;
 };
 
+// layered: a launch per layer at every size, in the least memory.
 void ppo_plan(Carver& c, const rslx_mlp* actor, const rslx_mlp* critic, const rslx_rollout* ro, const rslx_ppo_cfg* cfg,
-              const rslx_sym* sym, const rslx_rnd_train* rnd, PpoPlan& p) {
+              const rslx_sym* sym, const rslx_rnd_train* rnd, PpoPlan& p, bool layered = false) {
   p.B = ro->T * ro->N;
   p.mb = p.B / cfg->minibatches;
   p.rows = sym ? 2 * p.mb : p.mb;
@@ -382,7 +383,7 @@ void ppo_plan(Carver& c, const rslx_mlp* actor, const rslx_mlp* critic, const rs
   p.perm_ws = c.take<char>(perm_workspace_bytes(p.B));
   const rslx_mlp* const nets[2] = {actor, critic};
   const size_t at = c.off;
-  p.small = !sym && p.mb <= small_step_rows(nets, 2);
+  p.small = !layered && !sym && p.mb <= small_step_rows(nets, 2);
   if (p.small) {
     carve_small(c, *actor, p.mb, p.actor);
     carve_small(c, *critic, p.mb, p.critic);
@@ -393,7 +394,7 @@ void ppo_plan(Carver& c, const rslx_mlp* actor, const rslx_mlp* critic, const rs
     if (p.dp_c) p.stage_c = c.take<float>((size_t)(sym ? 2 : 1) * p.B * p.dp_c);
     carve_train(c, *actor, p.rows, 2, p.actor);
     carve_train(c, *critic, p.rows, 2, p.critic);
-    if (!sym) reserve_small(c, at, nets, 2, PPO_NPART_FIXED + ro->A);
+    if (!layered && !sym) reserve_small(c, at, nets, 2, PPO_NPART_FIXED + ro->A);
   }
   if (sym) {
     p.sym_perm = c.take<int32_t>((size_t)ro->Da + ro->Dc + ro->A);
@@ -487,6 +488,11 @@ int32_t ppo_update_impl(rslx_mlp* actor, rslx_mlp* critic, const rslx_rollout* r
   Carver c(ws);
   PpoPlan p;
   ppo_plan(c, actor, critic, ro, cfg, sym, rnd, p);
+  if (ws_bytes < p.bytes) {
+    c = Carver(ws);
+    p = PpoPlan();
+    ppo_plan(c, actor, critic, ro, cfg, sym, rnd, p, true);
+  }
   if (!ws || ws_bytes < p.bytes) return fail(RSLX_ERR_WORKSPACE, "rslx_ppo_update: workspace %zu < %zu bytes", ws_bytes, p.bytes);
   const int A = ro->A, L_a = actor->n_layers, L_c = critic->n_layers;
 
@@ -706,17 +712,18 @@ struct BcPlan {
   size_t bytes = 0;
 };
 
-void bc_plan(Carver& c, const rslx_mlp* student, const rslx_mlp* teacher, int32_t B, const rslx_bc_cfg* cfg, BcPlan& p) {
+// layered: as in ppo_plan.
+void bc_plan(Carver& c, const rslx_mlp* student, const rslx_mlp* teacher, int32_t B, const rslx_bc_cfg* cfg, BcPlan& p, bool layered = false) {
   p.mb = B / cfg->minibatches;
   p.perms = c.take<int32_t>((size_t)cfg->epochs * B);
   p.perm_ws = c.take<char>(perm_workspace_bytes(B));
   const size_t at = c.off;
-  p.small = p.mb <= small_step_rows(&student, 1);
+  p.small = !layered && p.mb <= small_step_rows(&student, 1);
   if (p.small) {
     carve_small(c, *student, p.mb, p.student);
   } else {
     carve_train(c, *student, p.mb, 1, p.student);
-    reserve_small(c, at, &student, 1, 1);
+    if (!layered) reserve_small(c, at, &student, 1, 1);
   }
   p.student.sumsq = c.take<double>((size_t)p.student.n_sumsq + 1);
   const int A = student->dims[student->n_layers];
@@ -769,6 +776,11 @@ int32_t bc_update_impl(rslx_mlp* student, const rslx_mlp* teacher, const float* 
   Carver c(ws);
   BcPlan p;
   bc_plan(c, student, tch, B, cfg, p);
+  if (ws_bytes < p.bytes) {
+    c = Carver(ws);
+    p = BcPlan();
+    bc_plan(c, student, tch, B, cfg, p, true);
+  }
   if (!ws || ws_bytes < p.bytes) return fail(RSLX_ERR_WORKSPACE, "rslx_bc_update: workspace %zu < %zu bytes", ws_bytes, p.bytes);
   const int A = student->dims[student->n_layers];
   const int Ls = student->n_layers;

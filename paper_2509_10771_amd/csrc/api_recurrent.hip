@@ -75,7 +75,8 @@ void gather_step(RowSplitArgs& rg, const rslx_memory& m, const StepBufs& b, cons
   if (b.pack) rg.pack[rg.n_packs++] = StepPackJob{m.params + gru_off_whh(m), m.params, b.pack, m.hidden, step_input(m, b.apart), m.cell};
 }
 
-size_t act_recurrent_carve(Carver& c, const rslx_memory* ga, const rslx_memory* gc, int32_t N, StepBufs* ba, StepBufs* bc, bool alone = false) {
+// split: with room for split weights, where the sizes call for them; without it the steps run on fp32 operands.
+size_t act_recurrent_carve(Carver& c, const rslx_memory* ga, const rslx_memory* gc, int32_t N, StepBufs* ba, StepBufs* bc, bool split, bool alone = false) {
   const rslx_memory* g[2] = {ga, gc};
   StepBufs* b[2] = {ba, bc};
   for (int k = 0; k < 2; ++k) {
@@ -84,7 +85,7 @@ size_t act_recurrent_carve(Carver& c, const rslx_memory* ga, const rslx_memory* 
     t.hin = c.take<float>((size_t)N * state_width(*g[k]));
     t.gi = c.take<float>((size_t)N * gate_width(*g[k]));
     t.hnew = c.take<float>((size_t)N * state_width(*g[k]));
-    if (step_split_sizes(g[k]->cell, g[k]->hidden, N, alone)) t.pack = c.take<uint16_t>(step_pack_bytes(g[k]->cell, g[k]->hidden, step_input(*g[k])) / 2);
+    if (split && step_split_sizes(g[k]->cell, g[k]->hidden, N, alone)) t.pack = c.take<uint16_t>(step_pack_bytes(g[k]->cell, g[k]->hidden, step_input(*g[k])) / 2);
     if (b[k]) *b[k] = t;
   }
   return c.off;
@@ -102,6 +103,19 @@ size_t split_ahead_bytes(const rslx_memory* ga, const rslx_mlp* a, const rslx_me
   const size_t na = a ? fused_pack_bytes(a->dims, a->n_layers) : 0, nc = fused_pack_bytes(c->dims, c->n_layers);
   const bool memories = (ga && step_split_sizes(ga->cell, ga->hidden, N, false)) || step_split_sizes(gc->cell, gc->hidden, N, false);
   return memories || std::max(na, nc) >= 6u << 17 ? na + nc : 0;
+}
+
+size_t act_recurrent_bytes(const rslx_memory* ga, const rslx_mlp* a, const rslx_memory* gc, const rslx_mlp* critic, int32_t N, bool split) {
+  Carver c(nullptr);
+  act_recurrent_carve(c, ga, gc, N, nullptr, nullptr, split);
+  if (split) c.take<char>(split_ahead_bytes(ga, a, gc, critic, N));
+  return (c.off + 255) / 256 * 256 + rslx_act_workspace_bytes(a, critic, N);
+}
+
+size_t memory_step_bytes(const rslx_memory* mem, int32_t N, bool split) {
+  Carver c(nullptr);
+  act_recurrent_carve(c, mem, nullptr, N, nullptr, nullptr, split, true);
+  return c.off + 256;
 }
 
 // hin -> new state (contractions fused with the gates; the input side in a product of its own where the step does not take it), for
@@ -148,10 +162,7 @@ extern "C" {
 size_t rslx_act_recurrent_workspace_bytes(const rslx_memory* gru_actor, const rslx_mlp* actor, const rslx_memory* gru_critic,
                                           const rslx_mlp* critic, int32_t N) {
   if (N <= 0 || !gru_critic || !critic) return 256;
-  Carver c(nullptr);
-  act_recurrent_carve(c, gru_actor, gru_critic, N, nullptr, nullptr);
-  c.take<char>(split_ahead_bytes(gru_actor, actor, gru_critic, critic, N));
-  return (c.off + 255) / 256 * 256 + rslx_act_workspace_bytes(actor, critic, N);
+  return act_recurrent_bytes(gru_actor, actor, gru_critic, critic, N, true);
 }
 
 }  // extern "C"
@@ -181,12 +192,13 @@ int32_t act_recurrent_impl(const rslx_memory* gru_actor, const rslx_mlp* actor, 
   if (N == 0) return RSLX_OK;
   const rslx_memory* ga = values_only ? nullptr : gru_actor;
   const rslx_mlp* a = values_only ? nullptr : actor;
-  if (!ws || ws_bytes < rslx_act_recurrent_workspace_bytes(ga, a, gru_critic, critic, N))
+  const bool split = ws_bytes >= act_recurrent_bytes(ga, a, gru_critic, critic, N, true);
+  if (!ws || (!split && ws_bytes < act_recurrent_bytes(ga, a, gru_critic, critic, N, false)))
     return fail(RSLX_ERR_WORKSPACE, "rslx_act_recurrent: workspace too small");
   hipStream_t s = (hipStream_t)stream;
   Carver c(ws);
   StepBufs ba, bc;
-  act_recurrent_carve(c, ga, gru_critic, N, &ba, &bc);
+  act_recurrent_carve(c, ga, gru_critic, N, &ba, &bc, split);
   for (int k = 0; k < 2; ++k) {
     const rslx_memory* m = k ? gru_critic : ga;
     if (!m) continue;
@@ -195,7 +207,7 @@ int32_t act_recurrent_impl(const rslx_memory* gru_actor, const rslx_mlp* actor, 
     (k ? bc : ba).apart = lie_apart(x, n, h_critic, (size_t)N * state_width(*gru_critic)) &&
                           (!ga || lie_apart(x, n, h_actor, (size_t)N * state_width(*ga)));
   }
-  const size_t ahead = split_ahead_bytes(ga, a, gru_critic, critic, N);
+  const size_t ahead = split ? split_ahead_bytes(ga, a, gru_critic, critic, N) : 0;
   void* room = ahead ? c.take<char>(ahead) : nullptr;
   const size_t used = (c.off + 255) / 256 * 256;
 
@@ -714,10 +726,7 @@ int32_t rnn_bc_validate(const rslx_memory* g, const rslx_mlp* student, int32_t T
 extern "C" {
 
 size_t rslx_memory_step_workspace_bytes(const rslx_memory* mem, int32_t N) {
-  if (!mem || N <= 0) return 256;
-  Carver c(nullptr);
-  act_recurrent_carve(c, mem, nullptr, N, nullptr, nullptr, true);
-  return c.off + 256;
+  return mem && N > 0 ? memory_step_bytes(mem, N, true) : 256;
 }
 
 int32_t rslx_memory_step(const rslx_memory* mem, const float* obs, int32_t N, float* state, const uint8_t* reset_or_null,
@@ -728,11 +737,12 @@ int32_t rslx_memory_step(const rslx_memory* mem, const float* obs, int32_t N, fl
   if (!aligned16(state) || (s0_out && !aligned16(s0_out)) || (h_dense_out && !aligned16(h_dense_out)))
     return fail(RSLX_ERR_INVALID_ARG, "rslx_memory_step: state buffers not 16-byte aligned");
   if (N == 0) return RSLX_OK;
-  if (!ws || ws_bytes < rslx_memory_step_workspace_bytes(mem, N)) return fail(RSLX_ERR_WORKSPACE, "rslx_memory_step: workspace too small");
+  const bool split = ws_bytes >= memory_step_bytes(mem, N, true);
+  if (!ws || (!split && ws_bytes < memory_step_bytes(mem, N, false))) return fail(RSLX_ERR_WORKSPACE, "rslx_memory_step: workspace too small");
   hipStream_t s = (hipStream_t)stream;
   Carver c(ws);
   StepBufs b;
-  act_recurrent_carve(c, mem, nullptr, N, &b, nullptr, true);
+  act_recurrent_carve(c, mem, nullptr, N, &b, nullptr, split, true);
   b.apart = lie_apart(obs, (size_t)N * mem->in_dim, state, (size_t)N * state_width(*mem));
   RowSplitArgs rg;
   memset(&rg, 0, sizeof rg);
