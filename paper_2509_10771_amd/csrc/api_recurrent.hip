@@ -54,7 +54,7 @@ XView plain_view(const float* base, int ld) {
 
 struct StepBufs {     // one memory's buffers of a single act step
   float* hin = nullptr;     // [N, S] state the step starts from (after reset)
-  float* gi = nullptr;      // [N, G H]
+  float* gi = nullptr;      // [N, G H]; where the step takes the input itself, room for a copy of it
   float* hnew = nullptr;    // [N, S] values-only: the state is not written back
   uint16_t* pack = nullptr; // split weights, of memories whose step runs on split operands
   bool apart = true;        // the inputs lie apart from the states that the call writes
@@ -65,14 +65,13 @@ bool lie_apart(const float* a, size_t na, const float* b, size_t nb) {
   return a == nullptr || b == nullptr || x + na * sizeof(float) <= y || y + nb * sizeof(float) <= x;
 }
 
-// Inputs that a step on split operands contracts itself: all or none.  Inputs that overlap a state are read by a product of their own
-// before any state is written.
-int32_t step_input(const rslx_memory& m, bool apart = true) { return apart && step_takes_input(m.hidden, m.in_dim) ? m.in_dim : 0; }
+// Inputs that a step on split operands contracts itself: all or none.
+int32_t step_input(const rslx_memory& m) { return step_takes_input(m.hidden, m.in_dim) ? m.in_dim : 0; }
 
 // The state that a step starts from, and its weights' split in the same launch.
 void gather_step(RowSplitArgs& rg, const rslx_memory& m, const StepBufs& b, const float* state, float* first_out) {
   rg.rows.job[rg.rows.n_jobs++] = RowGatherJob{state, b.hin, first_out, state_width(m)};
-  if (b.pack) rg.pack[rg.n_packs++] = StepPackJob{m.params + gru_off_whh(m), m.params, b.pack, m.hidden, step_input(m, b.apart), m.cell};
+  if (b.pack) rg.pack[rg.n_packs++] = StepPackJob{m.params + gru_off_whh(m), m.params, b.pack, m.hidden, step_input(m), m.cell};
 }
 
 // split: with room for split weights, where the sizes call for them; without it the steps run on fp32 operands.
@@ -129,10 +128,18 @@ int32_t gru_step(const rslx_memory* const* g, const float* const* obs, const Ste
   sa.n_nets = count; sa.nb = N; sa.cell = g[0]->cell;
   for (int k = 0; k < count; ++k) {
     const rslx_memory& m = *g[k];
+    // A step that reads its inputs itself does so while other workgroups write new states: inputs that overlap one are copied ahead
+    // (into the room of the product that this step does without, D <= 2 H), so that the step and its bits are those of any input.
+    const bool own = b[k].pack && step_input(m) > 0;
+    const float* x = obs[k];
+    if (own && !b[k].apart) {
+      RSLX_HIP(launch_copy_input(x, (int64_t)N * m.in_dim, b[k].gi, s));
+      x = b[k].gi;
+    }
     // the new packed state goes to h_out[k] ([N, S]): h in its first H columns, an LSTM's c behind it
     sa.net[k] = StepFwdNet{b[k].gi, b[k].hin, h_out[k], m.cell == RSLX_CELL_LSTM ? h_out[k] + m.hidden : nullptr, nullptr,
                            m.params + gru_off_whh(m), m.params + gru_off_bhh(m), nullptr, m.hidden, state_width(m),
-                           b[k].pack, b[k].pack && step_input(m, b[k].apart) > 0 ? obs[k] : nullptr, m.params, m.params + gru_off_bih(m), m.in_dim};
+                           b[k].pack, own ? x : nullptr, m.params, m.params + gru_off_bih(m), m.in_dim};
     if (sa.net[k].x) continue;
     bi.p[bi.count++] = gate_problem(plain_view(obs[k], m.in_dim), m.in_dim, m.params, m.params + gru_off_bih(m), b[k].gi, N, gate_width(m));
   }

@@ -420,6 +420,8 @@ hipError_t launch_row_split(const RowSplitArgs& a, hipStream_t stream);
 // dst[r, 0 .. cols) = src[r * ld_src + 0 .. cols) for r < rows (cols % 4 == 0): the hidden part of packed states as a
 // dense matrix.
 hipError_t launch_copy_matrix(const float* src, int32_t ld_src, int32_t rows, int32_t cols, float* dst, hipStream_t stream);
+// n floats, src aligned to 4 bytes and dst to 16.
+hipError_t launch_copy_input(const float* src, int64_t n, float* dst, hipStream_t stream);
 
 // rows_out[((e * M + m) * T + t) * nb + i] = t * N + perm[e * N + m * nb + i]: the roll-out rows of every
 // column-wise minibatch, step-major.

@@ -1132,6 +1132,15 @@ __global__ __launch_bounds__(256) void copy_matrix_kernel(const float* __restric
   st4(dst + (long)r * cols + c, ld4(src + (long)r * ld_src + c));
 }
 
+__global__ __launch_bounds__(256) void copy_input_kernel(const float* __restrict__ src, long n, float* __restrict__ dst) {
+  const long e = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
+  if (e + 4 <= n) {
+    st4(dst + e, *reinterpret_cast<const f4_any*>(src + e));
+  } else {
+    for (long i = e; i < n; ++i) dst[i] = src[i];
+  }
+}
+
 __global__ __launch_bounds__(256) void column_rows_kernel(const int32_t* __restrict__ perm, int E, int M, int T, int N,
                                                           int32_t* __restrict__ rows_out) {
   const long total = (long)E * T * N;
@@ -1281,6 +1290,15 @@ hipError_t launch_copy_matrix(const float* src, int32_t ld_src, int32_t rows, in
   const long total = (long)rows * (cols >> 2);
   if (total == 0) return hipSuccess;
   hipLaunchKernelGGL(copy_matrix_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, src, ld_src, rows, cols, dst);
+  return hipGetLastError();
+}
+
+hipError_t launch_copy_input(const float* src, int64_t n, float* dst, hipStream_t stream) {
+  if (n <= 0) return hipSuccess;
+  const int64_t blocks = (n + 1023) / 1024;
+  if (blocks > INT32_MAX) return hipErrorInvalidValue;
+  TraceScope ts(stream, "copy_input", 0.0, 8.0 * n);
+  hipLaunchKernelGGL(copy_input_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, src, (long)n, dst);
   return hipGetLastError();
 }
 

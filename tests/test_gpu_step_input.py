@@ -106,8 +106,9 @@ def test_inputs_that_are_the_states(rx, cell, H, N):
     rx.rslx_trace_begin(16)
     rx.rslx_memory_step(own, got, N, got, None, None, None, ws)
     torch.cuda.synchronize()
-    assert len(rx.rslx_trace_end()) == 2                   # a product for the inputs, and the step
+    assert len(rx.rslx_trace_end()) == 2                   # a copy of the inputs, and the step
     assert float((got - want).abs().max()) <= 1e-5
+    assert torch.equal(got, want)
     net = lambda A, ls: rx.Mlp((H, 8, A), torch.randn(H * 8 + 8 + 8 * A + A + ls, generator=gen).cuda(), has_log_std=ls > 0)  # noqa: E731
     actor, critic, e = net(2, 2), net(1, 0), lambda *s: torch.empty(*s, device="cuda")  # noqa: E731
     a, c = state.clone(), second.clone()
@@ -116,3 +117,27 @@ def test_inputs_that_are_the_states(rx, cell, H, N):
     torch.cuda.synchronize()
     assert float((a.double() - _reference(own, second, state)).abs().max()) <= 1e-5
     assert float((c.double() - _reference(other, state, second)).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("cell,H,N", [("gru", 64, 4099), ("gru", 256, 1025), ("lstm", 128, 6145)])
+def test_values_by_themselves_from_inputs_that_are_a_state(rx, cell, H, N):
+    """The bootstrap values keep the bits of a full call also where the critic's inputs lie in the actor's state, which a values-only
+    call does not see, or in its own; with 4-byte alignment and a width that is no multiple of four as well."""
+    gen, S = torch.Generator().manual_seed(11), 2 * H if cell == "lstm" else H
+    net = lambda A, ls: rx.Mlp((H, 8, A), torch.randn(H * 8 + 8 + 8 * A + A + ls, generator=gen).cuda(), has_log_std=ls > 0)  # noqa: E731
+    e = lambda *s: torch.empty(*s, device="cuda")  # noqa: E731
+    actor, critic, ma = net(2, 2), net(1, 0), _memory(rx, cell, 5, H, gen)
+    x = torch.randn(N, 5, generator=gen).cuda()
+    for D, shift in ((S, 0), (S // 2 - 1, 1)):
+        mc = _memory(rx, cell, D, H, gen)
+        ws = rx.workspace(rx.rslx_act_recurrent_workspace_bytes(ma, actor, mc, critic, N))
+        for own in (False, True):
+            a, c = ((0.5 * torch.randn(N, S, generator=gen)).cuda() for _ in range(2))
+            seen = (c if own else a).view(-1)[shift:shift + N * D].view(N, D)
+            alone, full = e(N), e(N)
+            rx.rslx_act_recurrent(None, None, mc, critic, None, seen, N, None, c, None, None, None, 1, 1, None, None, None, alone, None, None, rx.ACT_VALUES_ONLY, ws)
+            want = _reference(mc, seen, c)
+            rx.rslx_act_recurrent(ma, actor, mc, critic, x, seen, N, a, c, None, None, None, 1, 1, None, e(N, 2), e(N), full, e(N, 2), e(N, 2), 0, ws)
+            torch.cuda.synchronize()
+            assert torch.equal(alone, full), (D, own)
+            assert float((c.double() - want).abs().max()) <= 1e-5
