@@ -1180,13 +1180,20 @@ static hipError_t launch_step_rest(const StepFwdArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-// Which steps take that kernel: those of act() (nothing kept for a backward pass, no flags) from about the size on where it is the
-// faster one for a memory by itself.  The fp32 step and this one, while it still split its weights itself and left the input side
-// out, in rslx_memory_step and in act() with two such memories in front of [64, 12], us: GRU of 256 18.3, 21.0 and 37.0, 35.8 at
-// 1024 rows, 22.8, 21.7 and 44.0, 39.5 at 1055; GRU of 128 15.9, 17.9 and 31.6, 31.3 at 2048, 18.6, 18.1 and 36.2, 33.5 at 2110; LSTM
-// of 256 29.8, 29.6 and 58.1, 52.1 at 2048; LSTM of 128 24.9, 25.3 and 47.6, 47.0 at 4096, 31.6, 32.3 and 59.7, 57.0 at 5121, 36.8,
-// 33.8 and 68.1, 65.1 at 6554; LSTM of 64 33.4, 34.3 and 73.8, 72.2 at 16 385.  A memory's own sizes decide, so that a call for the
-// values alone returns the bits of a full one; only rslx_memory_step, which has no such counterpart, may draw its line later.
+// Which steps take that kernel: those of act() and rslx_memory_step (nothing kept for a backward pass, no flags), from the sizes on where
+// an earlier form, which split the weights in every workgroup and left the input side out, was the faster one for a memory by itself.
+// The present form leads on both sides of these lines, so they lie too high, not too low; they stay where their tests have them.
+// The fp32 step's time over this one's, every size run through both, rslx_memory_step / act() with two such memories in front of
+// [256, 128], 48 inputs:
+//   GRU of 256   below the line 1.12 / 1.04 at 512 rows, 1.14 / 1.18 at 1024;  above 1.42 at 1100, 1.45 / 1.31 at 2048
+//   GRU of 128                  1.28 / 1.11 at 1024, 1.28 / 1.21 at 2048;  1.53 at 2887, 1.52 / 1.33 at 4096
+//   GRU of 512                  0.95 / 1.16 at 512;  1.20 / 1.31 at 1024, 1.61 at 1443
+//   LSTM of 256                 0.99 / 1.01 at 512, 1.04 / 1.12 at 1024, 1.32 at 1443;  1.31 / 1.35 at 2048
+//   LSTM of 128                 1.12 / 1.06 at 1024, 1.42 / 1.24 at 4096;  1.49 / 1.26 at 8192
+//   LSTM of 64                  1.24 / 1.18 at 4096, 1.47 / 1.12 at 16 384;  1.38 / 1.15 at 32 768
+// With more inputs than step_takes_input allows, where the product stays apart, the lines are the present form's as well: 600 inputs, GRU
+// of 64 0.98 at 4096 rows and 1.04 at 8192, LSTM of 64 0.96 at 8192 and 1.0 from 16 384 on.  A memory's own sizes decide, so that a
+// call for the values alone returns the bits of a full one; only rslx_memory_step, which has no such counterpart, may draw its line later.
 bool step_split_sizes(int32_t cell, int32_t H, int32_t nb, bool alone) {
   if (H % 64 != 0 || H > 8192 || nb < 1024) return false;
   const int64_t size = (int64_t)nb * H;
