@@ -634,6 +634,8 @@ static void plan_wide(FusedNet& n) {
   }
 }
 
+static const char* wide_site(bool packed) { return packed ? "fused_forward_packed" : "fused_forward"; }
+
 static hipError_t launch_wide_forward(const FusedForwardArgs& a, hipStream_t stream) {
   static bool attr_set = false;
   if (!attr_set) {
@@ -643,11 +645,12 @@ static hipError_t launch_wide_forward(const FusedForwardArgs& a, hipStream_t str
     }
     attr_set = true;
   }
-  TraceScope ts(stream, "fused_forward", forward_flops(a), 0.0);
+  const bool packed = a.net[0].pack != nullptr && (a.n_nets < 2 || a.net[1].pack != nullptr);
+  TraceScope ts(stream, wide_site(packed), forward_flops(a), 0.0);
   FusedForwardArgs b = a;
   for (int i = 0; i < b.n_nets; ++i) plan_wide(b.net[i]);
   dim3 grid((b.n_rows + FF_ROWS - 1) / FF_ROWS, b.n_nets);
-  if (b.net[0].pack != nullptr && (b.n_nets < 2 || b.net[1].pack != nullptr))
+  if (packed)
     hipLaunchKernelGGL(fused_forward_kernel<true>, grid, dim3(FF_THREADS), FF_LDS, stream, b);
   else
     hipLaunchKernelGGL(fused_forward_kernel<false>, grid, dim3(FF_THREADS), FF_LDS, stream, b);
@@ -721,8 +724,8 @@ hipError_t launch_fused_forward(const FusedForwardArgs& a, hipStream_t stream) {
       flops[i] = forward_flops(one);
     }
     // a record for each network, both over the launch
-    TraceScope t0(stream, is_small[0] ? "small_forward" : "fused_forward", flops[0], 0.0);
-    TraceScope t1(stream, is_small[1] ? "small_forward" : "fused_forward", flops[1], 0.0);
+    TraceScope t0(stream, is_small[0] ? "small_forward" : wide_site(a.net[0].pack != nullptr), flops[0], 0.0);
+    TraceScope t1(stream, is_small[1] ? "small_forward" : wide_site(a.net[1].pack != nullptr), flops[1], 0.0);
     if (is_small[0] && is_small[1]) return launch_small_uneven(a, stream);
     if (is_small[0]) std::swap(b.net[0], b.net[1]);
     plan_wide(b.net[0]);

@@ -1,5 +1,6 @@
 """Shared helpers of the GPU parity tests: oracle-built rollouts and device marshalling."""
 import ctypes
+import re
 import numpy as np
 import torch
 
@@ -76,3 +77,12 @@ def oracle_cfg(w, epochs, seed=3, call_index=1):
     return oppo.PPOConfig(clip=f32(w.clip), value_coef=f32(w.value_coef), entropy_coef=f32(w.entropy_coef),
                           max_grad_norm=f32(w.max_grad_norm), lr=f32(w.lr), beta1=f32(0.9), beta2=f32(0.999),
                           adam_eps=f32(1e-8), epochs=epochs, minibatches=w.minibatches, seed=seed, call_index=call_index)
+
+
+def least_workspace(rx, call):
+    """The least workspace that call(workspace) takes, which holds its general form only: named by the refusal of a smaller one."""
+    try:
+        call(rx.workspace(256))
+    except rx.RslxError as e:
+        return rx.workspace(int(re.search(r"< (\d+) bytes", str(e))[1]))
+    raise AssertionError("a workspace of 256 bytes was taken")

@@ -48,27 +48,68 @@ def test_values_beyond_the_split(rx, rows, dims):  # noqa: F811
     test_gpu_split.test_update_with_values_beyond_the_split(rx, rows, dims)
 
 
+@pytest.mark.parametrize("N,hidden", [(3072, (128, 32)), (2048, (132, 32))])
+def test_steps_of_the_most_rows_against_the_oracle(rx, N, hidden):  # noqa: F811
+    """As many workgroups, and splits of the partial gradients, as a step may have: 192 and 128 for each network."""
+    case = Case(replace(WORKLOADS["tiny"], T=1, N=N, minibatches=1, Da=20, Dc=20, A=6, hidden=hidden), 1, perturb=0.2)
+    assert "small_step" in _sites(rx, lambda: check_forced_steps(rx, case))
+
+
+@pytest.mark.parametrize("hidden,rows", [((128,), 6144), ((132, 64), 4096)])
+def test_regression_of_the_most_rows(rx, hidden, rows):  # noqa: F811
+    """384 and 256 splits: loss and gradient of one step against float64."""
+    g = torch.Generator().manual_seed(rows)
+    r = lambda *s: torch.randn(*s, generator=g).cuda()  # noqa: E731
+    dims = (20,) + hidden + (5,)
+    flat = torch.cat([torch.cat([r(a * b) / a ** 0.5, 0.1 * r(b)]) for a, b in zip(dims[:-1], dims[1:])])
+    student, obs, tg = rx.Mlp(dims, flat.clone(), trainable=True), r(rows, 20), r(rows, 5)
+    p, x, o = flat.double().requires_grad_(True), obs.double(), 0
+    for i, (a, b) in enumerate(zip(dims[:-1], dims[1:])):
+        x = x @ p[o:o + a * b].view(a, b) + p[o + a * b:o + a * b + b]
+        o += a * b + b
+        x = x if i == len(dims) - 2 else torch.where(x > 0, x, torch.expm1(torch.clamp(x, max=0.0)))
+    loss = ((x - tg.double()) ** 2).mean()
+    loss.backward()
+    loss = float(loss.detach())
+    cfg, stats = rx.BcCfg(epochs=1, minibatches=1), torch.zeros(1, rx.NSTATS, device="cuda")
+    ws = rx.workspace(rx.rslx_bc_update_workspace_bytes(student, None, rows, cfg))
+    assert "small_step" in _sites(rx, lambda: rx.rslx_bc_update(student, None, obs, None, tg, rows, cfg, ctypes.c_int64(0), stats, ws))
+    # sums of `rows` terms in fp32 that partly cancel: 2^-24 sqrt(rows) of the terms, 1e-5 of the gradient's norm with a factor of two
+    assert abs(float(stats[0, 0]) - loss) <= 1e-6 * loss
+    assert float((student.grads.double() - p.grad).norm()) <= 1e-5 * float(p.grad.norm())
+
+
 def test_a_row_of_nan_leaves_other_minibatches_alone(rx):  # noqa: F811
-    """A NaN observation makes the gradients of its minibatch NaN, as fp32 arithmetic does, and a value of 2^112 with small weights
-    does not make those of another NaN."""
+    """A NaN observation makes the gradients of its minibatch NaN, as fp32 arithmetic does, and leaves those of the minibatch before it
+    alone; a value of 2^112 with small weights does not make any NaN."""
     g = torch.Generator().manual_seed(5)
     r = lambda *s: torch.randn(*s, generator=g).cuda()  # noqa: E731
     D, H, A, N = 20, 48, 3, 40
     for bad, finite in ((float("nan"), False), (6e33, True)):
         params = 0.1 * r(D * H + H + H * A + A + A)
         params[:H] *= 1e-36                               # the weights of input 0
-        actor, critic = rx.Mlp((D, H, A), params, trainable=True, has_log_std=True), rx.Mlp((D, H, 1), 0.1 * r(D * H + H + H + 1), trainable=True)
-        critic.params[:H] *= 1e-36
-        obs = r(1, N, D)
-        obs[0, 7, 0] = bad
-        mu = r(1, N, A)
-        ro = rx.Rollout(1, N, obs, obs, mu + r(1, N, A), r(1, N), r(1, N), mu, torch.ones_like(mu), r(1, N), r(1, N))
-        cfg, stats = rx.PpoCfg(epochs=1, minibatches=1), torch.zeros(1, rx.NSTATS, device="cuda")
-        ws = rx.workspace(rx.rslx_ppo_update_workspace_bytes(actor, critic, ro, cfg))
-        rx.rslx_ppo_update(actor, critic, ro, cfg, None, None, ctypes.c_int64(0), stats, ws)
-        torch.cuda.synchronize()
-        upper = torch.cat([actor.grads[D * H:], critic.grads[D * H:]])
+        value = 0.1 * r(D * H + H + H + 1)
+        value[:H] *= 1e-36
+        obs, mu, rest = r(1, N, D), r(1, N, A), [r(1, N) for _ in range(4)]
+        action = mu + r(1, N, A)
+        cfg = rx.PpoCfg(epochs=1, minibatches=2, lr=0.0)             # the small weights stay
+
+        def update(x):
+            actor, critic = rx.Mlp((D, H, A), params.clone(), trainable=True, has_log_std=True), rx.Mlp((D, H, 1), value.clone(), trainable=True)
+            ro = rx.Rollout(1, N, x, x, action, rest[0], rest[1], mu, torch.ones_like(mu), rest[2], rest[3])
+            stats = torch.zeros(2, rx.NSTATS, device="cuda")
+            ws = rx.workspace(rx.rslx_ppo_update_workspace_bytes(actor, critic, ro, cfg))
+            assert "small_step" in _sites(rx, lambda: rx.rslx_ppo_update(actor, critic, ro, cfg, None, None, ctypes.c_int64(0), stats, ws))
+            return torch.cat([actor.grads[D * H:], critic.grads[D * H:]]), stats
+
+        order = torch.empty(N, dtype=torch.int32, device="cuda")
+        rx.rslx_permutation(cfg.c.seed, cfg.c.call_index, 0, N, order, rx.workspace(rx.rslx_permutation_workspace_bytes(N)))
+        row = int(order[N // 2 + 3])                      # of the second minibatch
+        _, clean = update(obs)
+        obs[0, row, 0] = bad
+        upper, stats = update(obs)
         assert bool(torch.isfinite(upper).all()) == finite, bad
+        assert torch.equal(stats[0], clean[0]) and bool(torch.isfinite(stats[1]).all()) == finite
 
 
 @pytest.mark.parametrize("width,rows,small", [(128, 3072, True), (128, 3073, False), (132, 2048, True), (132, 2049, False)])
