@@ -327,10 +327,29 @@ __device__ __forceinline__ const u32x4* ff_task_units(const u32x4* layer, int K,
   return layer + (long)((task.col0 / FF_GROUP) * fused_pack_steps(K) + task.s_begin) * FP_STEP + lane;
 }
 
-// Rows 32 block .. of a network; lds: FF_LDS bytes.
-template <bool PACK>
-__device__ __forceinline__ void wide_forward(const FusedForwardArgs& args, const FusedNet& net, int block, char* lds) {
-  const int row0 = block * FF_ROWS;
+}  // namespace rslx
+
+#include "small_step.h"      // the layer-fused optimiser step, compiled with the layer-fused inference
+#include "small_forward.h"
+
+namespace rslx {
+
+// UNEVEN: two networks of which the second takes the kernel of small_forward.h, side by side in one launch: each in the form that its
+// own sizes call for, with the bits that it has by itself.  The launch takes as long as the wider network, whose workgroups are
+// dispatched first; two launches take the sum.  act(), both networks through the wider kernel, two launches and this, us at 1024 rows:
+// [48, 128, 128] beside [48, 256, 128] 16.4, 24.6 and 16.2, [48, 512, 256, 128] beside [48, 128, 128] 34.6, 41.2 and 34.0; two narrow
+// networks of different depths (small_uneven_kernel), [48, 64] beside [48, 64, 32], 11.7, 11.1 and 7.5.
+template <bool PACK, bool UNEVEN>
+__global__ __launch_bounds__(FF_THREADS) void fused_forward_kernel(const FusedForwardArgs args) {
+  extern __shared__ __align__(16) char lds[];
+  if constexpr (UNEVEN) {
+    if (blockIdx.y == 1) {
+      small_forward_any(args, args.net[1], blockIdx.x, lds);
+      return;
+    }
+  }
+  const FusedNet& net = args.net[UNEVEN ? 0 : blockIdx.y];
+  const int row0 = blockIdx.x * FF_ROWS;
   if (row0 >= args.n_rows) return;
   const int tid = threadIdx.x, lane = tid & 63;
   // the wavefront index decides which columns and contraction range a wavefront works on: held in a scalar
@@ -593,12 +612,6 @@ __device__ __forceinline__ void wide_forward(const FusedForwardArgs& args, const
   }
 }
 
-template <bool PACK>
-__global__ __launch_bounds__(FF_THREADS) void fused_forward_kernel(const FusedForwardArgs args) {
-  extern __shared__ __align__(16) char lds[];
-  wide_forward<PACK>(args, args.net[blockIdx.y], blockIdx.x, lds);
-}
-
 bool fused_forward_supported(const FusedForwardArgs& a) {
   if (a.max_dim > FF_MAX_DIM || a.n_nets < 1 || a.n_nets > 2) return false;
   return true;
@@ -639,7 +652,7 @@ static const char* wide_site(bool packed) { return packed ? "fused_forward_packe
 static hipError_t launch_wide_forward(const FusedForwardArgs& a, hipStream_t stream) {
   static bool attr_set = false;
   if (!attr_set) {
-    for (const void* k : {reinterpret_cast<const void*>(fused_forward_kernel<true>), reinterpret_cast<const void*>(fused_forward_kernel<false>)}) {
+    for (const void* k : {reinterpret_cast<const void*>(fused_forward_kernel<true, false>), reinterpret_cast<const void*>(fused_forward_kernel<false, false>)}) {
       hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, FF_LDS);
       if (e != hipSuccess) return e;
     }
@@ -651,18 +664,11 @@ static hipError_t launch_wide_forward(const FusedForwardArgs& a, hipStream_t str
   for (int i = 0; i < b.n_nets; ++i) plan_wide(b.net[i]);
   dim3 grid((b.n_rows + FF_ROWS - 1) / FF_ROWS, b.n_nets);
   if (packed)
-    hipLaunchKernelGGL(fused_forward_kernel<true>, grid, dim3(FF_THREADS), FF_LDS, stream, b);
+    hipLaunchKernelGGL((fused_forward_kernel<true, false>), grid, dim3(FF_THREADS), FF_LDS, stream, b);
   else
-    hipLaunchKernelGGL(fused_forward_kernel<false>, grid, dim3(FF_THREADS), FF_LDS, stream, b);
+    hipLaunchKernelGGL((fused_forward_kernel<false, false>), grid, dim3(FF_THREADS), FF_LDS, stream, b);
   return hipGetLastError();
 }
-
-}  // namespace rslx
-
-#include "small_step.h"      // the layer-fused optimiser step, compiled with the layer-fused inference
-#include "small_forward.h"
-
-namespace rslx {
 
 void plan_fused_pack(FusedForwardArgs& a, void* ws, FusedPackBatch& b) {
   b.count = 0;
@@ -684,28 +690,16 @@ void plan_fused_pack(FusedForwardArgs& a, void* ws, FusedPackBatch& b) {
   }
 }
 
-// Two networks of which the second takes the kernel of small_forward.h, side by side in one launch (blockIdx.y): each in the form that
-// its own sizes call for, with the bits that it has by itself.  The launch takes as long as the wider network, whose workgroups are
-// dispatched first; two launches take the sum.  act(), both networks through the wider kernel, two launches and this, us at 1024 rows:
-// [48, 128, 128] beside [48, 256, 128] 16.4, 24.6 and 16.2, [48, 512, 256, 128] beside [48, 128, 128] 34.6, 41.2 and 34.0; two narrow
-// networks of different depths (small_uneven_kernel), [48, 64] beside [48, 64, 32], 11.7, 11.1 and 7.5.
-template <bool PACK>
-__global__ __launch_bounds__(FF_THREADS) void uneven_forward_kernel(const FusedForwardArgs args) {
-  extern __shared__ __align__(16) char lds[];
-  if (blockIdx.y == 0) wide_forward<PACK>(args, args.net[0], blockIdx.x, lds);
-  else small_forward_any(args, args.net[1], blockIdx.x, lds);
-}
-
 template <bool PACK>
 static hipError_t launch_uneven_forward(const FusedForwardArgs& a, hipStream_t stream) {
   static_assert(FF_THREADS == SS_THREADS && SS_ROWS <= FF_ROWS && SF_MAX_LDS <= FF_LDS, "one launch");
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(uneven_forward_kernel<PACK>), hipFuncAttributeMaxDynamicSharedMemorySize, FF_LDS);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_forward_kernel<PACK, true>), hipFuncAttributeMaxDynamicSharedMemorySize, FF_LDS);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipLaunchKernelGGL(uneven_forward_kernel<PACK>, dim3((a.n_rows + SS_ROWS - 1) / SS_ROWS, 2), dim3(FF_THREADS), FF_LDS, stream, a);
+  hipLaunchKernelGGL((fused_forward_kernel<PACK, true>), dim3((a.n_rows + SS_ROWS - 1) / SS_ROWS, 2), dim3(FF_THREADS), FF_LDS, stream, a);
   return hipGetLastError();
 }
 
