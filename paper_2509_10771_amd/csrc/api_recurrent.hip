@@ -56,7 +56,8 @@ struct StepBufs {     // one memory's buffers of a single act step
   float* hin = nullptr;     // [N, S] state the step starts from (after reset)
   float* gi = nullptr;      // [N, G H]; where the step takes the input itself, room for a copy of it
   float* hnew = nullptr;    // [N, S] values-only: the state is not written back
-  uint16_t* pack = nullptr; // split weights, of memories whose step runs on split operands
+  bool split = false;       // the step runs on split operands
+  uint16_t* pack = nullptr; // its split weights, where they come split
   bool apart = true;        // the inputs lie apart from the states that the call writes
 };
 
@@ -84,7 +85,9 @@ size_t act_recurrent_carve(Carver& c, const rslx_memory* ga, const rslx_memory* 
     t.hin = c.take<float>((size_t)N * state_width(*g[k]));
     t.gi = c.take<float>((size_t)N * gate_width(*g[k]));
     t.hnew = c.take<float>((size_t)N * state_width(*g[k]));
-    if (split && step_split_sizes(g[k]->cell, g[k]->hidden, N, alone)) t.pack = c.take<uint16_t>(step_pack_bytes(g[k]->cell, g[k]->hidden, step_input(*g[k])) / 2);
+    t.split = split && step_split_sizes(g[k]->cell, g[k]->hidden, N, alone);
+    const size_t pack = t.split ? step_pack_bytes(g[k]->cell, g[k]->hidden, step_input(*g[k])) : 0;
+    if (pack) t.pack = c.take<uint16_t>(pack / 2);
     if (b[k]) *b[k] = t;
   }
   return c.off;
@@ -100,7 +103,8 @@ size_t act_recurrent_carve(Carver& c, const rslx_memory* ga, const rslx_memory* 
 size_t split_ahead_bytes(const rslx_memory* ga, const rslx_mlp* a, const rslx_memory* gc, const rslx_mlp* c, int32_t N) {
   if (N < 512) return 0;
   const size_t na = a ? fused_pack_bytes(a->dims, a->n_layers) : 0, nc = fused_pack_bytes(c->dims, c->n_layers);
-  const bool memories = (ga && step_split_sizes(ga->cell, ga->hidden, N, false)) || step_split_sizes(gc->cell, gc->hidden, N, false);
+  const auto splits = [&](const rslx_memory* m) { return m && step_split_sizes(m->cell, m->hidden, N, false) && step_pack_bytes(m->cell, m->hidden, step_input(*m)) > 0; };
+  const bool memories = splits(ga) || splits(gc);
   return memories || std::max(na, nc) >= 6u << 17 ? na + nc : 0;
 }
 
@@ -130,7 +134,7 @@ int32_t gru_step(const rslx_memory* const* g, const float* const* obs, const Ste
     const rslx_memory& m = *g[k];
     // A step that reads its inputs itself does so while other workgroups write new states: inputs that overlap one are copied ahead
     // (into the room of the product that this step does without, D <= 2 H), so that the step and its bits are those of any input.
-    const bool own = b[k].pack && step_input(m) > 0;
+    const bool own = b[k].split && step_input(m) > 0;
     const float* x = obs[k];
     if (own && !b[k].apart) {
       RSLX_HIP(launch_copy_input(x, (int64_t)N * m.in_dim, b[k].gi, s));
@@ -139,7 +143,7 @@ int32_t gru_step(const rslx_memory* const* g, const float* const* obs, const Ste
     // the new packed state goes to h_out[k] ([N, S]): h in its first H columns, an LSTM's c behind it
     sa.net[k] = StepFwdNet{b[k].gi, b[k].hin, h_out[k], m.cell == RSLX_CELL_LSTM ? h_out[k] + m.hidden : nullptr, nullptr,
                            m.params + gru_off_whh(m), m.params + gru_off_bhh(m), nullptr, m.hidden, state_width(m),
-                           b[k].pack, own ? x : nullptr, m.params, m.params + gru_off_bih(m), m.in_dim};
+                           b[k].pack, own ? x : nullptr, m.params, m.params + gru_off_bih(m), m.in_dim, b[k].split ? 1 : 0};
     if (sa.net[k].x) continue;
     bi.p[bi.count++] = gate_problem(plain_view(obs[k], m.in_dim), m.in_dim, m.params, m.params + gru_off_bih(m), b[k].gi, N, gate_width(m));
   }

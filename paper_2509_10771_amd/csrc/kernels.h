@@ -324,11 +324,12 @@ struct StepFwdNet {
   const float* b_hh;      // [G H]
   float* pre_out;         // [nb, G H] or null
   int32_t H, ld_out;
-  const uint16_t* pack;   // split weights (StepPackJob) for the step on split operands, or null: the fp32 step
-  const float* x;         // with pack: [nb, D], the step forms the input-side gate terms itself; or null: gi holds them
+  const uint16_t* pack;   // split weights (StepPackJob) for the step on split operands, null where step_pack_bytes is 0
+  const float* x;         // with split: [nb, D], the step forms the input-side gate terms itself; or null: gi holds them
   const float* w_ih;      // [D, G H]
   const float* b_ih;      // [G H]
   int32_t D;
+  int32_t split;          // 1: the step on split operands, 0: the fp32 step
 };
 struct StepFwdArgs {
   StepFwdNet net[2];
@@ -338,7 +339,7 @@ struct StepFwdArgs {
 };
 bool step_split_sizes(int32_t cell, int32_t H, int32_t nb, bool alone);    // the step on split operands; alone: rslx_memory_step
 bool step_takes_input(int32_t H, int32_t D);                               // that step forms the input side's terms too
-size_t step_pack_bytes(int32_t cell, int32_t H, int32_t D);
+size_t step_pack_bytes(int32_t cell, int32_t H, int32_t D);                // of the weights that come split (D = 0: of the hidden side)
 hipError_t launch_step_fwd(const StepFwdArgs& a, hipStream_t stream);
 
 // One step of back-propagation through time.  back = dg_next W_hh^T (what step t + 1 sends to its input hidden

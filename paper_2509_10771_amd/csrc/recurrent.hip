@@ -833,6 +833,12 @@ template <int CELL> struct StepSplit {
   static constexpr int LOADS = CHUNK / (ST_THREADS * 16);
 };
 
+// Whether the weights of a step come split.  A GRU's whose inputs stay apart (step_takes_input) are split by every workgroup: without
+// the input side's chunks the split ahead costs more than it saves.  rslx_memory_step, split ahead and in the workgroups, us: 128 units, 300
+// inputs, 4301 rows 32.2 and 31.5; 64 units, 235 inputs, 8602 rows 35.0 and 34.2; 512 units, 1500 inputs, 1076 rows 86.2 and 83.5.  An
+// LSTM's gains nothing from it (128 units, 300 inputs, 8602 rows 54.9 in the workgroups, 54.5 ahead).
+__host__ __device__ constexpr bool step_comes_split(int cell, bool input) { return cell == CELL_LSTM || input; }
+
 // Chunks of the hidden side, then those of the input side.
 template <int CELL> __host__ __device__ __forceinline__ int step_chunks(int H, int D) {
   return H / StepSplit<CELL>::KC + (D + StepSplit<CELL>::KC - 1) / StepSplit<CELL>::KC;
@@ -866,8 +872,8 @@ __device__ __forceinline__ void step_pack(const StepPackJob& J, long e) {
   for (int s = 0; s < 3; ++s) *reinterpret_cast<u32x4*>(dst + s * SQ_BLOCK) = part[s];
 }
 
-// Unit block ub, rows from row0 of a network; lds: 2 CHUNK bytes.
-template <int CELL>
+// Unit block ub, rows from row0 of a network; lds: 2 CHUNK bytes.  INPUT: with the input side's contraction, else gi holds its sums.
+template <int CELL, bool INPUT>
 __device__ __forceinline__ void step_split(const StepFwdNet& n, int nb, int ub, int row0, char* lds) {
   using S = StepSplit<CELL>;
   constexpr int G = S::G, NT = S::NT, KC = S::KC, CHUNK = S::CHUNK, LOADS = S::LOADS;
@@ -878,28 +884,55 @@ __device__ __forceinline__ void step_split(const StepFwdNet& n, int nb, int ub, 
   const int row = min(row0 + 16 * wave + b, nb - 1);
   const bool ok = row0 + 16 * wave + b < nb;             // rows past the end repeat the last one and store nothing
   const float scale = split_scale(b), unscale = split_unscale(b);
-  // without x, gi holds the input side's sums
-  const int NC = H / KC, D = n.D, total = step_chunks<CELL>(H, n.x ? D : 0);
+  const int NC = H / KC, D = n.D, total = step_chunks<CELL>(H, INPUT ? D : 0);
 
-  // weights: this lane's 16-byte units of a chunk
+  // weights: this lane's 16-byte units of a chunk, or its column of 32 and eight contraction indices for all gates, to be split
+  constexpr bool PACKED = step_comes_split(CELL, INPUT);
   const char* wsrc = reinterpret_cast<const char*>(n.pack) + (long)ub * total * CHUNK + tid * 16;
   u32x4 wv[LOADS];
+  const int wc = tid & 31, wk = tid >> 5;
+  float wf[G][8];
+  static_assert(PACKED || ST_THREADS == 4 * KC, "a lane's share of a chunk");
   auto load_w = [&](int c) {
-    const char* p = wsrc + (long)min(c, total - 1) * CHUNK;
+    if constexpr (PACKED) {
+      const char* p = wsrc + (long)min(c, total - 1) * CHUNK;
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i) wv[i] = *reinterpret_cast<const u32x4*>(p + i * (ST_THREADS * 16));
+      for (int i = 0; i < LOADS; ++i) wv[i] = *reinterpret_cast<const u32x4*>(p + i * (ST_THREADS * 16));
+    } else {
+      const int k0 = min(c, NC - 1) * KC + 8 * wk;
+#pragma unroll
+      for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) wf[g][i] = n.w_hh[(uint32_t)(k0 + i) * (uint32_t)GH + (uint32_t)(g * H + j0 + wc)];
+    }
   };
-  auto put_w = [&](int buf) {
-    char* dst = lds + buf * CHUNK + tid * 16;
+  auto put_w = [&](int buf) {            // blocks: [step of 32][unit tile][gate][part]
+    if constexpr (PACKED) {
+      char* dst = lds + buf * CHUNK + tid * 16;
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i) *reinterpret_cast<u32x4*>(dst + i * (ST_THREADS * 16)) = wv[i];
+      for (int i = 0; i < LOADS; ++i) *reinterpret_cast<u32x4*>(dst + i * (ST_THREADS * 16)) = wv[i];
+    } else {
+      char* dst = lds + buf * CHUNK + (((wk >> 2) * NT + (wc >> 4) * G) * 3) * SQ_BLOCK + ((wk & 3) * 16 + (wc & 15)) * 16;
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        u32x4 part[3];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          uint32_t p0, p1, p2;
+          split_pair(SPLIT_SCALE * wf[g][2 * i], SPLIT_SCALE * wf[g][2 * i + 1], p0, p1, p2);
+          part[0][i] = p0; part[1][i] = p1; part[2][i] = p2;
+        }
+#pragma unroll
+        for (int s = 0; s < 3; ++s) *reinterpret_cast<u32x4*>(dst + (3 * g + s) * SQ_BLOCK) = part[s];
+      }
+    }
   };
   // rows: operand B's eight contraction indices of every step of 32 of a chunk
   const float* xrow = n.sin + (long)row * SW;
-  const float* irow = n.x + (long)row * D;
+  const float* irow = INPUT ? n.x + (long)row * D : nullptr;
   auto load_x = [&](int c, f4 (&x)[2 * S::KS]) {
-    if (c < NC) {
-      const float* p = xrow + c * KC + 8 * kq;
+    if (!INPUT || c < NC) {
+      const float* p = xrow + (INPUT ? c : min(c, NC - 1)) * KC + 8 * kq;
 #pragma unroll
       for (int i = 0; i < 2 * S::KS; ++i) x[i] = ld4(p + 32 * (i >> 1) + 4 * (i & 1));
     } else if (c < total) {
@@ -927,7 +960,7 @@ __device__ __forceinline__ void step_split(const StepFwdNet& n, int nb, int ub, 
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) gi[u][g] = n.x ? f4{0.f, 0.f, 0.f, 0.f} : ld4(n.gi + (long)row * GH + g * H + ju + 16 * u);
+    for (int g = 0; g < G; ++g) gi[u][g] = INPUT ? f4{0.f, 0.f, 0.f, 0.f} : ld4(n.gi + (long)row * GH + g * H + ju + 16 * u);
     st[u] = ld4(n.sin + (long)row * SW + (CELL == CELL_LSTM ? H : 0) + ju + 16 * u);
   }
   put_w(0);
@@ -970,13 +1003,15 @@ __device__ __forceinline__ void step_split(const StepFwdNet& n, int nb, int ub, 
   for (int c = 0; c < NC; c += 2) {
     chunk(c, x0, x1, hidden);
     if (c + 1 < NC) chunk(c + 1, x1, x0, hidden);
-    else
+    else if (INPUT)
 #pragma unroll
       for (int i = 0; i < 2 * S::KS; ++i) x0[i] = x1[i];
   }
-  for (int c = NC; c < total; c += 2) {
-    chunk(c, x0, x1, input);
-    if (c + 1 < total) chunk(c + 1, x1, x0, input);
+  if constexpr (INPUT) {
+    for (int c = NC; c < total; c += 2) {
+      chunk(c, x0, x1, input);
+      if (c + 1 < total) chunk(c + 1, x1, x0, input);
+    }
   }
   float nf = 0.f;                                         // becomes NaN with any non-finite sum
 #pragma unroll
@@ -989,7 +1024,7 @@ __device__ __forceinline__ void step_split(const StepFwdNet& n, int nb, int ub, 
 #pragma unroll
     for (int i = 0; i < NT; ++i) sq_repeat_fp32(n.w_hh + i % G * H + j0 + 16 * (i / G), GH, 1, xrow, H, lane, acc[i]);
   }
-  if (n.x) {
+  if constexpr (INPUT) {
     nf = 0.f;
 #pragma unroll
     for (int i = 0; i < NT; ++i) {
@@ -1025,14 +1060,25 @@ __device__ __forceinline__ void step_split(const StepFwdNet& n, int nb, int ub, 
   }
 }
 
-// One network, or two of one width.
-template <int CELL>
-__global__ __launch_bounds__(ST_THREADS, 2) void step_split_kernel(const StepFwdArgs a) {
+// Which networks of a launch contract their inputs in the step (StepFwdNet::x).
+enum StepInput : int { STEP_IN_NONE = 0, STEP_IN_ALL = 1, STEP_IN_SOME = 2 };
+
+template <int CELL, int IN>
+__device__ __forceinline__ void step_split_in(const StepFwdNet& n, int nb, int ub, int row0, char* lds) {
+  if (IN == STEP_IN_ALL || (IN == STEP_IN_SOME && n.x != nullptr)) step_split<CELL, true>(n, nb, ub, row0, lds);
+  else step_split<CELL, false>(n, nb, ub, row0, lds);
+}
+
+// One network, or two of one width.  Without inputs the LSTM's step fits three workgroups on a CU (164 registers, 48 KB of LDS); in one
+// kernel with the other form it had two: rslx_memory_step of 64 units with 160 inputs at 33 424 rows 62.3 and 59.1 us, of 128 with 300 at
+// 8602 rows 56.5 and 54.5.
+template <int CELL, int IN>
+__global__ __launch_bounds__(ST_THREADS, CELL == CELL_LSTM && IN == STEP_IN_NONE ? 3 : 2) void step_split_kernel(const StepFwdArgs a) {
   extern __shared__ __align__(16) char lds[];
   const StepGrid grid(a.n_nets, a.nb, a.net[0].H);
   const int xcd = blockIdx.x & 7, id = blockIdx.x >> 3;
   const int z = a.n_nets == 2 ? xcd >> 2 : 0, rg = a.n_nets == 2 ? xcd & 1 : xcd & 3, ug = a.n_nets == 2 ? (xcd >> 1) & 1 : xcd >> 2;
-  step_split<CELL>(a.net[z], a.nb, ug * grid.per_group + id % grid.per_group, ((id / grid.per_group) * grid.row_groups + rg) * ST_ROWS, lds);
+  step_split_in<CELL, IN>(a.net[z], a.nb, ug * grid.per_group + id % grid.per_group, ((id / grid.per_group) * grid.row_groups + rg) * ST_ROWS, lds);
 }
 
 // Two networks of different widths, the wider one first (blockIdx.y): each over the whole chip and through the kernel that its own
@@ -1044,19 +1090,27 @@ __global__ __launch_bounds__(ST_THREADS, 2) void step_uneven_kernel(const StepFw
   if ((split >> blockIdx.y) & 1) {
     const StepGrid grid(1, a.nb, n.H);
     const int xcd = blockIdx.x & 7, id = blockIdx.x >> 3;
-    step_split<CELL>(n, a.nb, (xcd >> 2) * grid.per_group + id % grid.per_group, ((id / grid.per_group) * grid.row_groups + (xcd & 3)) * ST_ROWS, lds);
+    step_split_in<CELL, STEP_IN_SOME>(n, a.nb, (xcd >> 2) * grid.per_group + id % grid.per_group, ((id / grid.per_group) * grid.row_groups + (xcd & 3)) * ST_ROWS, lds);
   } else {
     step_fwd<CELL>(a, n, blockIdx.x, reinterpret_cast<float*>(lds));
   }
 }
 
-template <int CELL>
+template <int CELL, int IN>
 hipError_t step_split_launch(const StepFwdArgs& a, hipStream_t stream) {
   constexpr int bytes = 2 * StepSplit<CELL>::CHUNK;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(step_split_kernel<CELL>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(step_split_kernel<CELL, IN>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((step_split_kernel<CELL>), dim3(StepGrid(a.n_nets, a.nb, a.net[0].H).blocks), dim3(ST_THREADS), bytes, stream, a);
+  hipLaunchKernelGGL((step_split_kernel<CELL, IN>), dim3(StepGrid(a.n_nets, a.nb, a.net[0].H).blocks), dim3(ST_THREADS), bytes, stream, a);
   return hipGetLastError();
+}
+
+template <int CELL>
+hipError_t step_split_launch(const StepFwdArgs& a, hipStream_t stream) {
+  int in = 0;
+  for (int k = 0; k < a.n_nets; ++k) in += a.net[k].x != nullptr;
+  if (in == 0) return step_split_launch<CELL, STEP_IN_NONE>(a, stream);
+  return in == a.n_nets ? step_split_launch<CELL, STEP_IN_ALL>(a, stream) : step_split_launch<CELL, STEP_IN_SOME>(a, stream);
 }
 
 template <int CELL>
@@ -1207,6 +1261,7 @@ bool step_split_sizes(int32_t cell, int32_t H, int32_t nb, bool alone) {
 bool step_takes_input(int32_t H, int32_t D) { return D <= 2 * H; }
 
 size_t step_pack_bytes(int32_t cell, int32_t H, int32_t D) {
+  if (!step_comes_split(cell, D > 0)) return 0;
   const size_t units = H / ST_UNITS;
   return cell == CELL_LSTM ? units * step_chunks<CELL_LSTM>(H, D) * StepSplit<CELL_LSTM>::CHUNK : units * step_chunks<CELL_GRU>(H, D) * StepSplit<CELL_GRU>::CHUNK;
 }
@@ -1219,7 +1274,7 @@ hipError_t launch_step_fwd(const StepFwdArgs& a, hipStream_t stream) {
   int split = 0;
   double flops = 0.0;
   for (int k = 0; k < b.n_nets; ++k) {
-    split |= (b.net[k].pack != nullptr) << k;
+    split |= (b.net[k].split != 0) << k;
     flops += 2.0 * b.nb * (b.net[k].H + (b.net[k].x ? b.net[k].D : 0)) * (lstm ? 4.0 : 3.0) * b.net[k].H;
   }
   if (split == 0) return launch_step_rest(a, stream);

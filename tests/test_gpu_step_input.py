@@ -141,3 +141,25 @@ def test_values_by_themselves_from_inputs_that_are_a_state(rx, cell, H, N):
             torch.cuda.synchronize()
             assert torch.equal(alone, full), (D, own)
             assert float((c.double() - want).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("cell,Ha,Hc,Da,Dc,N,site", [("gru", 128, 128, 20, 261, 2049, "gru_split"), ("lstm", 128, 128, 257, 33, 4099, "lstm_split"), ("gru", 64, 64, 129, 600, 4111, "gru_split"),
+                                                    ("lstm", 192, 192, 385, 400, 2732, "lstm_split"), ("gru", 256, 64, 513, 130, 4097, "gru_uneven"), ("lstm", 256, 128, 513, 20, 4097, "lstm_uneven")])
+def test_memories_of_which_one_or_none_takes_its_inputs(rx, cell, Ha, Hc, Da, Dc, N, site):
+    """Beyond twice a memory's width its inputs go through a product of their own and a GRU's weights are split in the step: new states of
+    both memories against float64, and the bits of the step of either by itself through a values-only call."""
+    gen, k = torch.Generator().manual_seed(N + Da), 2 if cell == "lstm" else 1
+    net = lambda H, A, ls: rx.Mlp((H, 8, A), torch.randn(H * 8 + 8 + 8 * A + A + ls, generator=gen).cuda(), has_log_std=ls > 0)  # noqa: E731
+    e = lambda *s: torch.empty(*s, device="cuda")  # noqa: E731
+    ma, mc, actor, critic = _memory(rx, cell, Da, Ha, gen), _memory(rx, cell, Dc, Hc, gen), net(Ha, 2, 2), net(Hc, 1, 0)
+    x, y = torch.randn(N, Da, generator=gen).cuda(), torch.randn(N, Dc, generator=gen).cuda()
+    a, c = (0.5 * torch.randn(N, k * Ha, generator=gen)).cuda(), (0.5 * torch.randn(N, k * Hc, generator=gen)).cuda()
+    want_a, want_c, alone, full = _reference(ma, x, a), _reference(mc, y, c), e(N), e(N)
+    ws = rx.workspace(rx.rslx_act_recurrent_workspace_bytes(ma, actor, mc, critic, N))
+    rx.rslx_act_recurrent(None, None, mc, critic, None, y, N, None, c, None, None, None, 1, 1, None, None, None, alone, None, None, rx.ACT_VALUES_ONLY, ws)
+    rx.rslx_trace_begin(16)
+    rx.rslx_act_recurrent(ma, actor, mc, critic, x, y, N, a, c, None, None, None, 1, 1, None, e(N, 2), e(N), full, e(N, 2), e(N, 2), 0, ws)
+    torch.cuda.synchronize()
+    assert [r[0] for r in rx.rslx_trace_end() if r[0].startswith(cell)] == [site]
+    assert float((a.double() - want_a).abs().max()) <= 1e-5 and float((c.double() - want_c).abs().max()) <= 1e-5
+    assert torch.equal(alone, full)

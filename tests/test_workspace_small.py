@@ -37,3 +37,12 @@ def test_recurrent_inference_query_grows_with_the_environments(cell, H, D):
     for query in (lambda n: rx.rslx_memory_step_workspace_bytes(mem, n), lambda n: rx.rslx_act_recurrent_workspace_bytes(mem, net, mem, net, n)):
         sizes = [query(n) for n in rows]
         assert sizes == sorted(sizes)
+
+
+@pytest.mark.parametrize("H,D", [(64, 129), (128, 300), (256, 600)])
+def test_no_split_weights_for_a_gru_whose_inputs_stay_apart(H, D):
+    """Its step splits its weights itself: a row more costs the same on both sides of the line to the step on split operands."""
+    mem = rx.Memory(rx.CELL_GRU, D, H, torch.zeros(3 * H * (D + H + 2)))
+    line = (1 << 18) // H
+    below, at, above = (rx.rslx_memory_step_workspace_bytes(mem, n) for n in (line - 64, line, line + 64))
+    assert above - at == at - below
