@@ -327,12 +327,9 @@ __device__ __forceinline__ const u32x4* ff_task_units(const u32x4* layer, int K,
   return layer + (long)((task.col0 / FF_GROUP) * fused_pack_steps(K) + task.s_begin) * FP_STEP + lane;
 }
 
-}  // namespace rslx
-
-#include "small_step.h"      // the layer-fused optimiser step, compiled with the layer-fused inference
-#include "small_forward.h"
-
-namespace rslx {
+namespace {
+__device__ void small_forward_any(const FusedForwardArgs& args, const FusedNet& net, int block, char* lds);      // small_forward.h
+}
 
 // UNEVEN: two networks of which the second takes the kernel of small_forward.h, side by side in one launch: each in the form that its
 // own sizes call for, with the bits that it has by itself.  The launch takes as long as the wider network, whose workgroups are
@@ -669,6 +666,13 @@ static hipError_t launch_wide_forward(const FusedForwardArgs& a, hipStream_t str
     hipLaunchKernelGGL((fused_forward_kernel<false, false>), grid, dim3(FF_THREADS), FF_LDS, stream, b);
   return hipGetLastError();
 }
+
+}  // namespace rslx
+
+#include "small_step.h"      // the layer-fused optimiser step, compiled with the layer-fused inference
+#include "small_forward.h"
+
+namespace rslx {
 
 void plan_fused_pack(FusedForwardArgs& a, void* ws, FusedPackBatch& b) {
   b.count = 0;

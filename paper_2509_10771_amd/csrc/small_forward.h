@@ -216,7 +216,8 @@ __device__ __forceinline__ void small_forward_any(const FusedForwardArgs& args, 
   else small_forward_depth<8>(args, net, block, lds);
 }
 
-// Two networks of different depths.
+// Two networks of different depths.  (A template so that its code lies behind the other kernels'.)
+template <int = 0>
 __global__ __launch_bounds__(SS_THREADS, 2) void small_uneven_kernel(const FusedForwardArgs args) {
   __shared__ __align__(16) char lds[SF_MAX_LDS];
   small_forward_any(args, args.net[blockIdx.y], blockIdx.x, lds);
@@ -250,7 +251,7 @@ hipError_t launch_small_forward(const FusedForwardArgs& a, hipStream_t stream) {
 }
 
 hipError_t launch_small_uneven(const FusedForwardArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL(small_uneven_kernel, dim3((a.n_rows + SS_ROWS - 1) / SS_ROWS, 2), dim3(SS_THREADS), 0, stream, a);
+  hipLaunchKernelGGL((small_uneven_kernel<0>), dim3((a.n_rows + SS_ROWS - 1) / SS_ROWS, 2), dim3(SS_THREADS), 0, stream, a);
   return hipGetLastError();
 }
 
