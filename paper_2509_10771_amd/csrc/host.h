@@ -451,24 +451,55 @@ inline void carve_small(Carver& c, const rslx_mlp& n, int32_t rows, TrainBufs& t
   t.n_sumsq = t.plan.blocks;
 }
 
-// Where one launch for forward, loss and backward pass (small_step.h) replaces those of the layers.  It holds one workgroup of 16
-// rows per CU: while all of them run at once it is the faster one at every size it takes, a second round of them pays only where
-// the layers are narrow.  Whole updates of 5 x 4 steps, launches per layer and this, us: [48, 128, 128, 12] 1112 and 561 at 96 rows,
-// 1045 and 585 at 384, 1275 and 737 at 2046, 1173 and 1021 at 3072, 1335 and 1322 at 4098; [235, 128, 128, 12] 1482 and 920 at 2046,
-// 1343 and 1316 at 2052, 1344 and 1395 at 3072; [48, 256, 128, 12] 1450 and 1003 at 2046, 1405 and 1400 at 2052, 1322 and 1485 at
-// 3072; [48, 256, 256, 128, 12] 1618 and 1356 at 384, 2013 and 1727 at 2046, 1902 and 2705 at 3072; [256, 256, 256, 256, 32] 2249 and
-// 1892 at 96, 2627 and 2561 at 2046.
+// Where one launch for forward, loss and backward pass (small_step.h) replaces those of the layers: up to as many rows as one round of
+// its workgroups takes (16 rows of a network each, one per CU), half a round more where no layer is wider than 128.
+// Whole updates of 5 x 4 steps, launches per layer and this, us:
+//   [48, 128, 128, 12]        96 rows 1112,  561    384 rows 1045,  585    2046 rows 1275,  737    3072 rows 1173, 1021    4098 rows 1335, 1322
+//   [235, 128, 128, 12]     2046 rows 1482,  920   2052 rows 1343, 1316    3072 rows 1344, 1395
+//   [48, 256, 128, 12]      2046 rows 1450, 1003   2052 rows 1405, 1400    3072 rows 1322, 1485
+//   [48, 256, 256, 128, 12]  384 rows 1618, 1356   2046 rows 2013, 1727    3072 rows 1902, 2705
 inline int32_t small_step_most_rows(int widest, int n_nets) { return (widest <= 128 ? 384 : 256) / n_nets * 16; }
+
+// Fewer where the partial gradients, a network's weights per 16 rows written and read again, meet layers that fill the tiles of the other
+// form (widths of 128 and 256, none wider than the one before, some square of 256): up to SMALL_STEP_WORK rows x weights, which grow with
+// the squares, the first layer's counting twice (its input gradient is not formed).  0 = no such limit, as for more than 16 actions, whose
+// loss launch is the slower one.  Four steps, launches per layer and this, us:
+//   [256, 256, 256, 256, 12]  512 rows 1.00 of each other   1024 rows 394, 435    2048 rows 428, 521
+//   [235, 256, 256, 256, 12]  768 rows 1.00                 1024 rows 398, 421    2048 rows 441, 501
+//   [48, 256, 256, 256, 12]  1024 rows 361, 358             1536 rows 389, 394    2048 rows 404, 428
+//   [256, 256, 128, 12]      1536 rows 283, 270             1792 rows 287, 293    2048 rows 288, 306
+//   [235, 256, 256, 128, 12] 1792 rows 396, 390             2048 rows 396, 425;   [48, 256, 256, 128, 12]  2048 rows 363, 358
+// Two steps of a regression: [256, 256, 256, 256, 12] 0.96 at 2560 rows, [235, 256, 256, 256, 12] 247, 242 at 3584 and 251, 267 at 4096.
+constexpr int64_t SMALL_STEP_WORK[2] = {1020000000, 480000000};        // of one network, of two together
+inline int64_t small_step_work(const rslx_mlp& n) {
+  int squares = 0;
+  int64_t weights = 0;
+  for (int l = 0; l < n.n_layers; ++l) {
+    const int K = n.dims[l], N = n.dims[l + 1];
+    if (l + 1 < n.n_layers && (N % 128 != 0 || (l > 0 && N > K))) return 0;
+    if (K == SMALL_MAX_DIM && N == SMALL_MAX_DIM) squares += l == 0 ? 2 : 1;
+    weights += (int64_t)K * N;
+  }
+  return squares > 0 && n.dims[n.n_layers] <= 16 ? weights * (squares + 1) / 2 : 0;
+}
 
 // Rows up to which the networks of a call (equal depth) take it; 0 = never.
 inline int32_t small_step_rows(const rslx_mlp* const* nets, int count) {
   int widest = 0;
+  int64_t work = 0;
+  bool whole = true;
   for (int i = 0; i < count; ++i) {
     const rslx_mlp& n = *nets[i];
     if (n.n_layers != nets[0]->n_layers || !small_step_supported(n.dims, n.n_layers)) return 0;
     for (int l = 0; l < n.n_layers; ++l) widest = n.dims[l] > widest ? n.dims[l] : widest;
+    const int64_t w = small_step_work(n);
+    whole = whole && w > 0;
+    work += w;
   }
-  return small_step_most_rows(widest, count);
+  const int32_t most = small_step_most_rows(widest, count);
+  if (!whole) return most;
+  const int64_t rows = SMALL_STEP_WORK[count - 1] / work;
+  return rows < most ? (int32_t)rows : most;
 }
 
 // Moves the carver to where the buffers of the largest call of these networks that takes the small step end (`at`: where they

@@ -257,7 +257,7 @@ hipError_t launch_ppo_head(const PpoHeadArgs& h, hipStream_t stream);
 // Forward pass, loss and backward pass of an optimiser step in one launch, for small networks and few rows (small_step.h).  Block b
 // of the launch takes rows 16 b onwards and leaves split b of every layer's partial gradient ([W; b], pitch[l] floats apart) and
 // its loss sums: [5 + A] doubles for an actor and a critic (each writes its own entries), one for a regression.
-constexpr int SMALL_MAX_LAYERS = 4, SMALL_MAX_LDS = 160 * 1024;
+constexpr int SMALL_MAX_LAYERS = 4, SMALL_MAX_DIM = 256, SMALL_MAX_LDS = 160 * 1024;
 enum SmallRole : int { SMALL_ACTOR = 0, SMALL_CRITIC = 1, SMALL_REGRESSION = 2 };
 struct SmallNet {
   const float* params;

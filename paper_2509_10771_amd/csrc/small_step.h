@@ -29,7 +29,7 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int SS_ROWS = 16, SS_THREADS = 512, SS_WAVES = SS_THREADS / 64;
-constexpr int SS_MAX_DIM = 256, SS_MAX_OUT = 32;
+constexpr int SS_MAX_OUT = 32;
 constexpr int SS_PLANE = 2 * SS_ROWS;                     // LDS bytes of one part of one column, either layout
 constexpr float SS_LOG_2PI = 1.8378770664093453f;
 
@@ -597,7 +597,7 @@ int small_step_blocks(int32_t rows) { return (rows + SS_ROWS - 1) / SS_ROWS; }
 bool small_step_supported(const int32_t* dims, int32_t n_layers) {
   if (n_layers < 2 || n_layers > SMALL_MAX_LAYERS || dims[n_layers] > SS_MAX_OUT) return false;
   for (int l = 0; l < n_layers; ++l)
-    if (dims[l] > SS_MAX_DIM) return false;
+    if (dims[l] > SMALL_MAX_DIM) return false;
   return SsLds(dims, n_layers).total <= SMALL_MAX_LDS;
 }
 

@@ -126,6 +126,16 @@ def test_line_of_the_update(rx, width, rows, small):  # noqa: F811
     assert ("small_step" in sites) == small and torch.isfinite(actor.params).all()
 
 
+@pytest.mark.parametrize("D,hidden,A,rows,small", [(256, (256, 256, 256), 12, 480, True), (256, (256, 256, 256), 12, 512, False), (235, (256, 256, 256), 12, 816, True),
+                                                   (235, (256, 256, 256), 12, 832, False), (256, (256, 128), 12, 1584, True), (256, (256, 128), 12, 1680, False),
+                                                   (48, (256, 256, 128), 12, 2048, True), (256, (256, 256, 256), 17, 2048, True), (256, (256, 200, 128), 12, 2048, True),
+                                                   (256, (128, 256), 12, 2048, True), (64, (256, 256), 12, 2048, True)])
+def test_line_of_layers_that_fill_their_tiles(rx, D, hidden, A, rows, small):  # noqa: F811
+    """Fewer rows where launches per layer are the faster form: both sides, and networks without that limit, against the oracle's step."""
+    case = Case(replace(WORKLOADS["tiny"], T=1, N=rows, minibatches=1, Da=D, Dc=D, A=A, hidden=hidden), 1, perturb=0.2)
+    assert ("small_step" in _sites(rx, lambda: check_forced_steps(rx, case))) == small
+
+
 @pytest.mark.parametrize("width,rows,small", [(128, 6144, True), (128, 6145, False), (132, 4096, True), (132, 4097, False)])
 def test_line_of_the_regression(rx, width, rows, small):  # noqa: F811
     g = torch.Generator().manual_seed(rows)

@@ -21,6 +21,17 @@ def test_update_workspace_serves_fewer_rows(hidden, line):
     assert need == sorted(need)
 
 
+@pytest.mark.parametrize("D,hidden", [(256, (256, 256, 256)), (235, (256, 256, 128)), (256, (256, 128))])
+def test_update_workspace_serves_fewer_rows_of_wide_networks(D, hidden):
+    """Their line lies at fewer rows."""
+    z, A = torch.zeros, 12
+    need = []
+    for n in range(16, 2049, 16):
+        ro = rx.Rollout(1, n, z(n, D), z(n, D), z(n, A), z(n), z(n), z(n, A), z(n, A), z(n), z(n))
+        need.append(rx.rslx_ppo_update_workspace_bytes(_mlp((D,) + hidden + (A,), True), _mlp((D,) + hidden + (1,)), ro, rx.PpoCfg(minibatches=1)))
+    assert need == sorted(need)
+
+
 @pytest.mark.parametrize("hidden,line", [((128, 128), 6144), ((256, 256, 128), 4096)])
 def test_regression_workspace_serves_fewer_rows(hidden, line):
     need = [rx.rslx_bc_update_workspace_bytes(_mlp((48,) + hidden + (12,)), None, n, rx.BcCfg(minibatches=1)) for n in (16, line - 1, line, line + 1, line + 64, 2 * line)]
