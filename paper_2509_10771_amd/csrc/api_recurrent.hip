@@ -203,7 +203,11 @@ int32_t act_recurrent_impl(const rslx_memory* gru_actor, const rslx_mlp* actor, 
   if (N == 0) return RSLX_OK;
   const rslx_memory* ga = values_only ? nullptr : gru_actor;
   const rslx_mlp* a = values_only ? nullptr : actor;
-  const bool split = ws_bytes >= act_recurrent_bytes(ga, a, gru_critic, critic, N, true);
+  // The split form where the workspace holds it.  A call for the values alone needs less than a full one: in a workspace that holds the
+  // full call it runs in that call's form, and so returns its bits.
+  const bool holds_full = gru_actor && actor && ws_bytes >= act_recurrent_bytes(gru_actor, actor, gru_critic, critic, N, false);
+  const bool split = ws_bytes >= act_recurrent_bytes(ga, a, gru_critic, critic, N, true) &&
+                     (!holds_full || ws_bytes >= act_recurrent_bytes(gru_actor, actor, gru_critic, critic, N, true));
   if (!ws || (!split && ws_bytes < act_recurrent_bytes(ga, a, gru_critic, critic, N, false)))
     return fail(RSLX_ERR_WORKSPACE, "rslx_act_recurrent: workspace too small");
   hipStream_t s = (hipStream_t)stream;

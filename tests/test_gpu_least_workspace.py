@@ -106,3 +106,31 @@ def test_inference_behind_memories(rx, cell, H, D, hidden, N, least, fast):
         rx.rslx_act_recurrent(mem[0], actor, mem[1], critic, x, x, N, h[0], h[1], None, None, None, 7, 3, None, *out, 0, ws)
         return h + out
     _both(rx, rx.rslx_act_recurrent_workspace_bytes(mem[0], actor, mem[1], critic, N), least, fast, call)
+
+
+@pytest.mark.parametrize("cell,H,D,N,least", [("gru", 256, 48, 1025, 13698564), ("lstm", 256, 33, 2049, None)])
+def test_values_alone_are_those_of_a_full_call(rx, cell, H, D, N, least):
+    """In one workspace, whichever form it holds: the bits of the full call's values; without the actor, in the room for the critic."""
+    gen, A = torch.Generator().manual_seed(N), 12
+    mem = [_memory(rx, cell, D, H, gen) for _ in range(2)]
+    actor, critic = _net(rx, (H, 256, 128, A), gen, True), _net(rx, (H, 256, 128, 1), gen)
+    x, state = torch.randn(N, D, generator=gen).cuda(), [(0.5 * torch.randn(N, mem[0].state_width, generator=gen)).cuda() for _ in range(2)]
+    e = lambda *s: torch.empty(*s, device="cuda")  # noqa: E731
+    def values(ws, flags, with_actor=True):
+        h, out = [s.clone() for s in state], [e(N, A), e(N), e(N), e(N, A), e(N, A)]
+        rx.rslx_trace_begin(64)
+        rx.rslx_act_recurrent(mem[0] if with_actor else None, actor if with_actor else None, mem[1], critic, x, x, N, h[0], h[1], None, None, None, 7, 3,
+                              None, *out, flags, ws)
+        torch.cuda.synchronize()
+        return out[2], {r[0] for r in rx.rslx_trace_end()}
+    query = rx.rslx_act_recurrent_workspace_bytes(mem[0], actor, mem[1], critic, N)
+    alone = rx.rslx_act_recurrent_workspace_bytes(None, None, mem[1], critic, N)
+    room = torch.empty(query, dtype=torch.uint8, device="cuda")
+    for nbytes in (query, query - 1) + ((least,) if least else ()):
+        full, sites = values(room[:nbytes], 0)
+        assert (cell + "_split" in sites) == (nbytes == query)
+        only, sites = values(room[:nbytes], rx.ACT_VALUES_ONLY)
+        assert (cell + "_split" in sites) == (nbytes == query) and torch.equal(only, full)
+    full, _ = values(room, 0)
+    only, sites = values(room[:alone], rx.ACT_VALUES_ONLY, with_actor=False)
+    assert cell + "_split" in sites and torch.equal(only, full)
