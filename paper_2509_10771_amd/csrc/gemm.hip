@@ -342,8 +342,9 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, int lin, const i
   // of step t + 1 have the whole body to be formed and written; one barrier per body.
   // Two bodies to a round of the loop, so that the two places of the values on their way, and of the LDS buffers, are known at
   // compile time: with one body the compiler moved the later values over at its end and waited there for loads of the same
-  // body, and 22 more vector instructions a step were moves and addresses.  Whole updates, us: 4096 environments, [512, 256, 128]
-  // 8634 -> 8465, [256, 256, 128] by regression 1582 -> 1535; 16 384 environments with the curiosity networks 46 060 -> 45 083.
+  // body, and 22 more vector instructions a step were moves and addresses.  Whole updates, us, in turn on one card: 4096
+  // environments, [512, 256, 128] 8641 -> 8499, [256, 256, 128] by regression 1561 -> 1523 (on another card no gain: 1626 and 1630);
+  // 16 384 environments with the curiosity networks 46 212 -> 45 221.
   // Steps past the end: the last body forms the parts of one step too many (nobody reads them), and where the range is
   // no whole number of steps, the indices past its end meet a zero in one operand: the zero padding of packed weights, else
   // zeros put in place of operand B's (weight gradient) or A's values.

@@ -1329,8 +1329,8 @@ hipError_t launch_row_gather(const RowGatherArgs& a, hipStream_t stream) {
 }
 
 // The parts' blocks follow each other in one dimension, first the splits, whose threads' loads and stores are the longer chain.  Two
-// GRUs of 256 in front of [512, 256, 128] at 4096 rows, us a call: copies first 83.2, splits first 76.8 (another card: 82.4); a grid
-// of parts by the largest one's blocks, most of them without work, 82.8.
+// GRUs of 256 in front of [512, 256, 128] at 4096 rows, us a call, in turn on one card: copies first 85.6, splits first 84.5 (runs of one
+// side differ by 0.1).
 hipError_t launch_row_split(const RowSplitArgs& args, hipStream_t stream) {
   if (args.n_packs == 0 && args.layers.count == 0) return launch_row_gather(args.rows, stream);
   RowSplitArgs a = args;

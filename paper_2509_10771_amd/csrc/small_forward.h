@@ -1,10 +1,12 @@
 // Layer-fused inference of networks with hidden layers of up to 128 units for up to 2048 rows: the chain of one workgroup is what a
 // call takes, so everything is made to shorten it.  One workgroup (8 wavefronts) carries 16 rows of one network; a wavefront owns 16
 // columns of every layer, so no sums are exchanged and a layer costs one barrier.  All weights and biases of its columns, and the
-// noise of the Gaussian head, are requested or formed before the rows arrive.  act() of [48, 128, 128, 12] takes 8.1 us at 64
-// environments and 9.1 at 2048 where the wider kernel (fused_forward.hip, 32 rows) takes 14.4 and 15.3, of [235, 128, 128, 12] 11.9 and
-// 12.6 for 19.1 and 19.8, of [100, 128, 4] 8.4 for 10.6; with two rounds of workgroups the wider one is faster (3000: 15.4 and 17).  Operands, LDS layout and the handling of values
+// noise of the Gaussian head, are requested or formed before the rows arrive.  Operands, LDS layout and the handling of values
 // without a split are those of small_step.h; weights are split in registers.
+// act() in the wider kernel (fused_forward.hip, 32 rows) and here, us; with two rounds of workgroups the wider one is faster:
+//   [48, 128, 128, 12]    64 rows 14.4,  8.1    2048 rows 15.3,  9.1    3000 rows 15.4, 17
+//   [235, 128, 128, 12]   64 rows 19.1, 11.9    2048 rows 19.8, 12.6
+//   [100, 128, 4]         64 rows 10.6,  8.4
 #pragma once
 
 #include "small_step.h"
