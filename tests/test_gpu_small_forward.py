@@ -1,5 +1,5 @@
 """Inference of narrow networks, 16 rows per workgroup: against float64 at rows and widths around its tiles, the line to the wider kernel,
-networks of one call that differ and share a launch, and values-only calls bit for bit."""
+networks of one call that take different kernels, and values-only calls bit for bit."""
 import ctypes
 
 import pytest

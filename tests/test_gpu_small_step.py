@@ -45,7 +45,7 @@ def test_regression(rx, student, N):  # noqa: F811
 
 @pytest.mark.parametrize("rows,dims", [(100, (200, 128, 64, 8)), (61, (37, 100, 30, 5)), (384, (64, 256, 256, 32))])
 def test_values_beyond_the_split(rx, rows, dims):  # noqa: F811
-    test_gpu_split.test_update_with_values_beyond_the_split(rx, rows, dims, layered=False)
+    test_gpu_split.test_update_with_values_beyond_the_split(rx, rows, dims)
 
 
 @pytest.mark.parametrize("N,hidden", [(3072, (128, 32)), (2048, (132, 32))])
@@ -80,6 +80,29 @@ def test_regression_of_the_most_rows(rx, hidden, rows):  # noqa: F811
 
 
 def test_a_row_of_nan_leaves_other_minibatches_alone(rx):  # noqa: F811
+    """A NaN observation makes the gradients of its minibatch NaN, as fp32 arithmetic does, and a value of 2^112 with small weights
+    does not make those of another NaN."""
+    g = torch.Generator().manual_seed(5)
+    r = lambda *s: torch.randn(*s, generator=g).cuda()  # noqa: E731
+    D, H, A, N = 20, 48, 3, 40
+    for bad, finite in ((float("nan"), False), (6e33, True)):
+        params = 0.1 * r(D * H + H + H * A + A + A)
+        params[:H] *= 1e-36                               # the weights of input 0
+        actor, critic = rx.Mlp((D, H, A), params, trainable=True, has_log_std=True), rx.Mlp((D, H, 1), 0.1 * r(D * H + H + H + 1), trainable=True)
+        critic.params[:H] *= 1e-36
+        obs = r(1, N, D)
+        obs[0, 7, 0] = bad
+        mu = r(1, N, A)
+        ro = rx.Rollout(1, N, obs, obs, mu + r(1, N, A), r(1, N), r(1, N), mu, torch.ones_like(mu), r(1, N), r(1, N))
+        cfg, stats = rx.PpoCfg(epochs=1, minibatches=1), torch.zeros(1, rx.NSTATS, device="cuda")
+        ws = rx.workspace(rx.rslx_ppo_update_workspace_bytes(actor, critic, ro, cfg))
+        rx.rslx_ppo_update(actor, critic, ro, cfg, None, None, ctypes.c_int64(0), stats, ws)
+        torch.cuda.synchronize()
+        upper = torch.cat([actor.grads[D * H:], critic.grads[D * H:]])
+        assert bool(torch.isfinite(upper).all()) == finite, bad
+
+
+def test_a_row_of_nan_leaves_the_minibatch_before_it_alone(rx):  # noqa: F811
     """A NaN observation makes the gradients of its minibatch NaN, as fp32 arithmetic does, and leaves those of the minibatch before it
     alone; a value of 2^112 with small weights does not make any NaN."""
     g = torch.Generator().manual_seed(5)

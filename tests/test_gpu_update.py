@@ -24,7 +24,7 @@ import torch
 
 from oracle import ppo as oppo, bc as obc, adam as oadam
 from workloads import WORKLOADS, make_inputs, xavier_mlp
-from gpu_util import dev, host, rel_l2, oracle_rollout, flat_rollout, oracle_cfg, f32, least_workspace
+from gpu_util import dev, host, rel_l2, oracle_rollout, flat_rollout, oracle_cfg, f32
 
 pytestmark = pytest.mark.gpu
 
@@ -64,8 +64,6 @@ def _check_stats(got, want, tol, floor=1e-3):
 
 class Case:
     """One workload: seeded inputs, the oracle's rollout and its recorded update trajectory."""
-
-    sites = None          # a set: the updates run with a launch per layer, also where they take one launch for a step, and add the launches' names
 
     def __init__(self, w, epochs, sym_on=False, rnd_on=False, seed=3, call_index=1, perturb=0.0, rnd_subset=0):
         self.w, self.epochs, self.sym_on, self.rnd_on, self.seed, self.call_index = w, epochs, sym_on, rnd_on, seed, call_index
@@ -145,16 +143,9 @@ def _nets(rx, case, actor, critic, opt=None, rnd_state=None):
 def _call(rx, case, a, c, rnd, rollout, cfg, n_rows, step0):
     stats = torch.zeros(n_rows, rx.NSTATS, device="cuda")
     sym = case.gpu_sym(rx)
+    ws = rx.workspace(rx.rslx_ppo_update_workspace_bytes(a, c, rollout, cfg, sym, rnd))
     step = C.c_int64(step0)
-    call = lambda ws: rx.rslx_ppo_update(a, c, rollout, cfg, sym, rnd, step, stats, ws)  # noqa: E731
-    if case.sites is None:
-        call(rx.workspace(rx.rslx_ppo_update_workspace_bytes(a, c, rollout, cfg, sym, rnd)))
-    else:
-        ws = least_workspace(rx, call)
-        rx.rslx_trace_begin(4096)
-        call(ws)
-        torch.cuda.synchronize()
-        case.sites |= {r[0] for r in rx.rslx_trace_end()}
+    rx.rslx_ppo_update(a, c, rollout, cfg, sym, rnd, step, stats, ws)
     torch.cuda.synchronize()
     return host(stats), step.value
 
@@ -460,15 +451,6 @@ def check_free_running(rx, case, found=None, later_tol=2e-2, param_tol=None, gra
     raise AssertionError(log)
 
 
-def check_launches_per_layer(rx, case, site, free_running=False):
-    """The comparisons again with a launch per layer, among them `site`."""
-    case.sites = set()
-    found = check_forced_steps(rx, case)
-    if free_running:
-        check_free_running(rx, case, found)
-    assert site in case.sites and "small_step" not in case.sites, case.sites
-
-
 def test_ppo_tiny(rx):
     case = Case(WORKLOADS["tiny"], 1)
     check_free_running(rx, case, check_forced_steps(rx, case))
@@ -480,13 +462,10 @@ def test_ppo_tiny_off_policy_start(rx):
     check_free_running(rx, case, check_forced_steps(rx, case))
 
 
-@pytest.mark.parametrize("width,site", [(96, "ppo_head"), (98, "ppo_loss")])
-def test_ppo_odd_hidden_width_takes_the_unfused_loss_path(rx, width, site):
-    """With a launch per layer, a last hidden width that is no multiple of 4 uses the per-layer output GEMMs and the stand-alone loss
-    kernel; one that is, is padded in the fused head.  In one launch for the step as well."""
-    case = Case(replace(WORKLOADS["tiny"], N=50, hidden=(64, width)), 1, perturb=0.2)
+def test_ppo_odd_hidden_width_takes_the_unfused_loss_path(rx):
+    """A last hidden width outside {32, 64, 128, 256} uses the per-layer output GEMMs and the stand-alone loss kernel."""
+    case = Case(replace(WORKLOADS["tiny"], N=50, hidden=(64, 96)), 1, perturb=0.2)
     check_free_running(rx, case, check_forced_steps(rx, case))
-    check_launches_per_layer(rx, case, site, True)
 
 
 @pytest.mark.parametrize("base,N,A,hidden,sym_on", [
@@ -502,8 +481,6 @@ def test_ppo_fused_head_widths(rx, base, N, A, hidden, sym_on):
     w = replace(WORKLOADS[base].scaled(N), A=A, hidden=hidden)
     case = Case(w, 1, sym_on=sym_on, perturb=0.2)
     check_free_running(rx, case, check_forced_steps(rx, case))
-    if not sym_on:          # which runs in one launch for the step, without the head
-        check_launches_per_layer(rx, case, "ppo_head", True)
 
 
 @pytest.mark.parametrize("base,N,A,sym_on", [("tiny", 40, 33, False), ("tiny", 30, 48, False), ("rough", 24, 64, True)])
